@@ -300,6 +300,13 @@ __global__ __launch_bounds__(64 * WAVES) void layernorm_wave8_kernel(const float
 
 static constexpr int kLnWaves = 1;      // rows per workgroup of the kernel above (1, 2, 4, 8 measured inside the step: within 2 %, 1 ahead)
 
+static constexpr int kLnWaveMax = 5120; // longest row of the wavefront-per-row kernels
+// does a row go to the kernel that moves 8 elements at a time?
+static bool layernorm_by8(int dtype, int d, const void* y, const void* w, const void* b, const void* w2, const void* b2) {
+    return zo2_dtype_size(dtype) == 2 && d % 8 == 0 && d <= kLnWaveMax &&
+           (((uintptr_t)y | (uintptr_t)w | (uintptr_t)b | (uintptr_t)w2 | (uintptr_t)b2) % 16) == 0;
+}
+
 zo2_status layernorm(int dtype, const float* x, const void* w, const void* b, const void* w2, const void* b2, void* y,
                      int rows, int rows_first, int d, float eps, hipStream_t st) {
     if (rows == 0) return ZO2_OK;
@@ -314,18 +321,17 @@ zo2_status layernorm(int dtype, const float* x, const void* w, const void* b, co
 #define ZO2_LN8(KP)                                                                                                                       \
     hipLaunchKernelGGL((layernorm_wave8_kernel<C, KP, kLnWaves>), dim3((rows + kLnWaves - 1) / kLnWaves), dim3(64 * kLnWaves), 0, st, x, \
                        (const C*)w, (const C*)b, (const C*)w2, (const C*)b2, (C*)y, rows, rows_first, d, eps)
+    const bool by8 = layernorm_by8(dtype, d, y, w, b, w2, b2);
     ZO2_DISPATCH_COMPUTE(dtype, C, {
-        const bool by8 = sizeof(C) == 2 && d % 8 == 0 && ((uintptr_t)y % 16) == 0 && ((uintptr_t)w % 16) == 0 && ((uintptr_t)b % 16) == 0 &&
-                         ((uintptr_t)w2 % 16) == 0 && ((uintptr_t)b2 % 16) == 0;
         // pieces of 512 elements per row: instances for rows of up to 2048 and 5120 elements; longer rows take too many
         // registers for one wavefront (measured at 8192 rows: 5120 46 us against 55 with the kernels below, 7168 76
         // against 69, 12288 145 against 115) and stay with the workgroup-per-row kernel
         if (by8 && d <= 4 * 512) ZO2_LN8(4);
-        else if (by8 && d <= 10 * 512) ZO2_LN8(10);
+        else if (by8) ZO2_LN8(10);
         else if (d <= 8 * 64 * 4)
             hipLaunchKernelGGL((layernorm_wave_kernel<C, 8>), dim3((rows + 3) / 4), dim3(256), 0, st, x, (const C*)w, (const C*)b,
                                (const C*)w2, (const C*)b2, (C*)y, rows, rows_first, d, eps);
-        else if (d <= 20 * 64 * 4)
+        else if (d <= kLnWaveMax)
             hipLaunchKernelGGL((layernorm_wave_kernel<C, 20>), dim3((rows + 3) / 4), dim3(256), 0, st, x, (const C*)w, (const C*)b,
                                (const C*)w2, (const C*)b2, (C*)y, rows, rows_first, d, eps);
         else if (d <= 12 * 256 * 4)
@@ -344,11 +350,38 @@ zo2_status layernorm(int dtype, const float* x, const void* w, const void* b, co
 // registers.  Steps of few tokens are a chain of launches of 4 - 5 us each, most of it start and end; what is left here is the
 // latency of the pieces' loads, sixteen in flight per thread.  2 x 16 rows, d 2048, 32 slices: 6.6 us instead of 5.3 for the sum
 // and 4.5 for the LayerNorm; 2 x 64 rows, d 768, float32, 6 pieces: 3.9 instead of 4.0 and 4.5.
-template <typename C, int V>      // V: 16-byte pieces per thread
+// Whether a projection is cut along k, and whether a sweep sits between its sum and this LayerNorm, must not show in the results:
+// mean and variance are added up as layernorm() does for the same row.  Every thread leaves the sum of its four columns in LDS, and
+// every wavefront adds those in the order of that kernel's lanes.
+enum { kLnWave = 0, kLnWave8 = 1, kLnBlock = 2 };      // layernorm_wave_kernel, layernorm_wave8_kernel, layernorm_kernel
+template <int ORDER>
+__device__ __forceinline__ float layernorm_total(const float* part, int nv) {
+    constexpr int kGroups = ORDER == kLnBlock ? 4 : 1;
+    float tot = 0.f;
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        float s = 0.f;
+        if (ORDER == kLnWave8) {
+#pragma unroll 4
+            for (int i = 2 * (threadIdx.x & 63); i < nv; i += 128) {
+                s += part[i];
+                s += part[i + 1];
+            }
+        } else {
+#pragma unroll 4
+            for (int i = (threadIdx.x & 63) + 64 * g; i < nv; i += 64 * kGroups) s += part[i];
+        }
+        s = wave_sum(s);
+        tot = g == 0 ? s : tot + s;
+    }
+    return tot;
+}
+
+template <typename C, int V, int ORDER>      // V: 16-byte pieces per thread
 __global__ __launch_bounds__(1024) void reduce_layernorm_kernel(RowSum a, float* __restrict__ h, const C* __restrict__ w, const C* __restrict__ b,
                                                                const C* __restrict__ w2, const C* __restrict__ b2, C* __restrict__ y,
                                                                int rows_first, int d, float eps) {
-    __shared__ float sh[16];
+    __shared__ float sh_s[1024 * V], sh_q[1024 * V];
     const int r = blockIdx.x, nv = d >> 2, nt = blockDim.x;
     const bool second = r >= rows_first;
     const float* src = a.part + (second ? a.stream_stride + (size_t)(r - rows_first) * d : (size_t)r * d);
@@ -357,7 +390,6 @@ __global__ __launch_bounds__(1024) void reduce_layernorm_kernel(RowSum a, float*
     const C* bb = second ? b2 : b;
     float4* hr = reinterpret_cast<float4*>(h + (size_t)r * d);
     float4 v[V];
-    float s = 0.f;
 #pragma unroll
     for (int k = 0; k < V; ++k) {
         const int i = threadIdx.x + nt * k;
@@ -379,18 +411,21 @@ __global__ __launch_bounds__(1024) void reduce_layernorm_kernel(RowSum a, float*
             v[k].z = (v[k].z + Fmt<C>::load(bv.v[2])) + res.z;
             v[k].w = (v[k].w + Fmt<C>::load(bv.v[3])) + res.w;
             hr[i] = v[k];
-            s += (v[k].x + v[k].y) + (v[k].z + v[k].w);
+            sh_s[i] = (v[k].x + v[k].y) + (v[k].z + v[k].w);
         }
     }
-    const float mean = block_sum(s, sh) / (float)d;
-    float q = 0.f;
+    __syncthreads();
+    const float mean = layernorm_total<ORDER>(sh_s, nv) / (float)d;
 #pragma unroll
-    for (int k = 0; k < V; ++k)
-        if (threadIdx.x + nt * k < nv) {
+    for (int k = 0; k < V; ++k) {
+        const int i = threadIdx.x + nt * k;
+        if (i < nv) {
             const float a0 = v[k].x - mean, a1 = v[k].y - mean, a2 = v[k].z - mean, a3 = v[k].w - mean;
-            q += (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
+            sh_q[i] = (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
         }
-    const float rstd = 1.0f / sqrtf(block_sum(q, sh) / (float)d + eps);
+    }
+    __syncthreads();
+    const float rstd = 1.0f / sqrtf(layernorm_total<ORDER>(sh_q, nv) / (float)d + eps);
     C* yr = y + (size_t)r * d;
 #pragma unroll
     for (int k = 0; k < V; ++k) {
@@ -417,12 +452,17 @@ zo2_status reduce_layernorm(int dtype, const RowSum& a, float* h, const void* w,
     ZO2_OP_CHECK(ca != 0 && (((uintptr_t)a.part | (uintptr_t)h) & 15) == 0 && a.piece_stride % 4 == 0 && a.stream_stride % 4 == 0 &&
                  (((uintptr_t)w | (uintptr_t)b | (uintptr_t)w2 | (uintptr_t)b2 | (uintptr_t)y | (uintptr_t)a.bias | (uintptr_t)a.bias2) & (ca - 1)) == 0,
                  ZO2_EINVAL, "reduce_layernorm: unknown dtype, or buffers not aligned to 4 elements");
-#define ZO2_RLN(V)                                                                                                                  \
-    hipLaunchKernelGGL((reduce_layernorm_kernel<C, V>), dim3(rows), dim3(std::min(1024, (d / 4 + 63) / 64 * 64)), 0, st, a, h, (const C*)w, (const C*)b, (const C*)w2, \
+    const bool by8 = layernorm_by8(dtype, d, y, w, b, w2, b2);
+#define ZO2_RLN(V, ORDER)                                                                                                           \
+    hipLaunchKernelGGL((reduce_layernorm_kernel<C, V, ORDER>), dim3(rows), dim3(std::min(1024, (d / 4 + 63) / 64 * 64)), 0, st, a, h, (const C*)w, (const C*)b, (const C*)w2, \
                        (const C*)b2, (C*)y, rows_first, d, eps)
     ZO2_DISPATCH_COMPUTE(dtype, C, {
-        if (d <= 4096) ZO2_RLN(1);
-        else ZO2_RLN(2);
+        constexpr int kBy8 = sizeof(C) == 2 ? kLnWave8 : kLnWave;
+        if (by8 && d <= 4096) ZO2_RLN(1, kBy8);
+        else if (by8) ZO2_RLN(2, kBy8);
+        else if (d <= 4096) ZO2_RLN(1, kLnWave);
+        else if (d <= kLnWaveMax) ZO2_RLN(2, kLnWave);
+        else ZO2_RLN(2, kLnBlock);
     });
 #undef ZO2_RLN
     ZO2_HIP_LAUNCH_CHECK();

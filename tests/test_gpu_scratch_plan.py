@@ -100,6 +100,33 @@ def test_per_group_scratch_streamed_equals_whole_block_resident_bitwise(wire, co
     assert all(np.isfinite(x) for x in runs["whole_resident"][0][-1:])
 
 
+@pytest.mark.parametrize("d,heads,vocab", [(512, 8, 4096), (768, 12, 6148), (5248, 41, 15748)])
+def test_float32_projections_in_pieces_give_the_same_bits_under_every_organisation(d, heads, vocab):
+    """Widths at which the output projection is cut along k (its pieces then end in the LayerNorm's pass where no sweep comes
+    between): losses and parameters of eight steps under 1, 2 and 4 sweeps per block, bit for bit; without pieces they differ."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=1, d_model=d, n_heads=heads, d_ffn=72, vocab=vocab, max_pos=40)
+    P = si.make_weights(cfg, seed=11, std=0.15, ln_jitter=True)      # few rows and large logits: a late digit shows in the losses
+    tok = si.make_tokens(cfg["vocab"], 1, 5, seed=12)
+    lab = si.next_token_labels(tok)
+    runs = {}
+    for name, sweeps in (("1", 1), ("2", 2), ("4", 4), ("uncut", 1)):
+        ctx = b.Zo2Context(cfg, P, arena_bytes=(256 << 20) + 40 * vocab * d)
+        ctx.set_scratch_plan(sweeps)
+        if name == "uncut":
+            ctx.set_split_k(-1)
+        r = [tuple(map(float, ctx.step(tok, lab, 5 + j, 1e-3, 1e-6))) for j in range(8)]
+        assert ctx.plan()["sweeps_per_block"] == sweeps
+        ctx.flush(); ctx.sync_to_host()
+        runs[name] = (r, {n: a for n, a in ctx.parameters().items() if n.startswith("blocks.")})
+        ctx.close()
+    for name in ("2", "4"):
+        assert runs[name][0] == runs["1"][0], name
+        for n in runs["1"][1]:
+            assert np.array_equal(runs[name][1][n], runs["1"][1][n]), (name, n)
+    assert runs["uncut"][0] != runs["1"][0] or any(not np.array_equal(runs["uncut"][1][n], runs["1"][1][n]) for n in runs["1"][1])
+
+
 def test_budget_too_small_for_whole_block_scratch_falls_back_to_per_group():
     """The planner's own choice: a budget that cannot hold 3 slots next to a whole-block scratch set, but can next to
     a per-group set, gives the per-group plan (and the same bits); one notch lower is ZO2_EBUDGET."""
