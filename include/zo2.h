@@ -278,7 +278,11 @@ zo2_status zo2_debug_set_slot_poison(zo2_ctx* ctx, int32_t enabled);
  * same Philox4x32-10 stream as z_prev but with the last counter word set to 1 (call e >> 3, low / high half of
  * output word (e >> 1) & 3 for even / odd e).  Values beyond the largest finite value saturate.  A master copy
  * in bf16 / fp16 / fp8 then follows updates far below its spacing in expectation; with rounding to nearest
- * such updates are lost.  No effect on a float32 wire.  Takes effect at the next update. */
+ * such updates are lost.  No effect on a float32 wire.  Takes effect at the next update.
+ * Every stored parameter is then a draw that turns over with a late digit of eta g, so contexts with stochastic rounding of a
+ * low-bit wire format and 16-bit compute add their products in one order whatever the number of tokens makes faster: projections
+ * on the large tiles (zo2_set_split_k says how they are cut), the loader path of zo2_set_loader_fusion by default up to 64 tokens
+ * per stream, written logits below 256.  The planner lays the memory out anew when the setting changes. */
 zo2_status zo2_set_wire_rounding(zo2_ctx* ctx, int32_t stochastic);
 
 /* Ablation switch for the dynamic scheduler (Sec. 5.2; the paper's reverse ablation, Table 4, "no

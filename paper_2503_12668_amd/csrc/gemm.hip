@@ -538,7 +538,7 @@ GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes) {
     GemmChoice best = {0, gemm_pick_splits(a.M, a.N, a.K, a.nprob, dtype)};
     if (gemm_splitk_workspace_bytes(a.M, a.N, a.nprob, best.splits) > workspace_bytes) best.splits = 1;
     // (matrices of up to 2^19 elements, d 512 and less: both kernels' launches are over before the host has enqueued the next)
-    if (gemm256_is_forced() || !gemm_mid_applicable(a, dtype) || (int64_t)a.N * a.K <= 1 << 19) return best;
+    if (a.large_only || gemm256_is_forced() || !gemm_mid_applicable(a, dtype) || (int64_t)a.N * a.K <= 1 << 19) return best;
     double best_ns = 1e30;                 // where the large kernel cannot run, this one replaces the general one
     if (gemm256_applicable(a, dtype)) best_ns = 0.85 * large_tile_ns(a.M, a.N, a.K, a.nprob, best.splits) + (best.splits > 1 ? 4000.0 : 0.0);
     const double cu = (double)device_cu_count(), tn = (double)((a.N + 127) / 128);

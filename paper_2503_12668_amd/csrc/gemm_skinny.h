@@ -25,6 +25,7 @@ struct SkinnyArgs {
     int32_t M, N, K;        // M <= 256 rows per stream; K % 64 == 0; N % 4 == 0
     int64_t ldx, ldy;
     int32_t relu, out_f32, nprob;
+    int32_t in_order;       // 1: one wavefront adds a slab's k in order, where two would share it (33 - 128 rows)
     int32_t splits, k_per_split;     // filled in by skinny_launch: the k range is cut into `splits` pieces of k_per_split
     float eps;
     PhiloxKeys key;         // of the step seed

@@ -382,9 +382,8 @@ size_t skinny_workspace_bytes(int M, int N, int K, int nprob) {
     return (size_t)nprob * splits * 2 * (size_t)M * N * sizeof(float);
 }
 
-template <typename T, int MT, bool CE>
+template <typename T, int MT, bool CE, int NW = (MT >= 2 && MT <= 4 ? 8 : 4)>
 static zo2_status skinny_launch_mt(const SkinnyArgs& a, hipStream_t st) {
-    constexpr int NW = MT >= 2 && MT <= 4 ? 8 : 4;
     const dim3 grid((a.N + kSkBN - 1) / kSkBN, a.splits, a.nprob), block(64 * NW);
     constexpr int lds = 2 * 2 * 32 * MT * kSkKC * 16;
     static bool reserved_on[kMaxDevices] = {false};
@@ -405,8 +404,9 @@ static zo2_status skinny_launch_mt(const SkinnyArgs& a, hipStream_t st) {
 template <typename T>
 static zo2_status skinny_launch_t(const SkinnyArgs& a, hipStream_t st, bool sum) {
     const dim3 block(256);
-    zo2_status s = a.M <= 32 ? skinny_launch_mt<T, 1, false>(a, st) : a.M <= 64 ? skinny_launch_mt<T, 2, false>(a, st)
-                 : a.M <= 96 ? skinny_launch_mt<T, 3, false>(a, st) : a.M <= 128 ? skinny_launch_mt<T, 4, false>(a, st)
+    zo2_status s = a.M <= 32 ? skinny_launch_mt<T, 1, false>(a, st)
+                 : a.in_order && a.M <= 64 ? skinny_launch_mt<T, 2, false, 4>(a, st) : a.in_order && a.M <= 128 ? skinny_launch_mt<T, 4, false, 4>(a, st)
+                 : a.M <= 64 ? skinny_launch_mt<T, 2, false>(a, st) : a.M <= 96 ? skinny_launch_mt<T, 3, false>(a, st) : a.M <= 128 ? skinny_launch_mt<T, 4, false>(a, st)
                  : a.M <= 192 ? skinny_launch_mt<T, 6, false>(a, st) : skinny_launch_mt<T, 8, false>(a, st);
     if (s != ZO2_OK || !sum) return s;
     const size_t work = 2 * (size_t)a.M * (a.N / 4);

@@ -547,11 +547,13 @@ zo2_status embed_gather(const EmbedArgs& a, int wire_dtype, int compute_dtype, b
 }
 
 // ------------------------------------------------------------------ cross-entropy per row
-// 1024 threads per row (a row of 50272 logits is a dozen 16-byte loads each; with 256 threads a launch of 64 rows took 25 us, now 12.7)
-__global__ __launch_bounds__(1024) void ce_rows_kernel(const float* __restrict__ logits, int64_t ld, const int32_t* __restrict__ labels,
+// NT threads per row: 1024 (a row of 50272 logits is a dozen 16-byte loads each: a launch of 64 rows takes 12.7 us against 25 with 256
+// threads), 256 where the order of the sums is kept
+template <int NT>
+__global__ __launch_bounds__(NT) void ce_rows_kernel(const float* __restrict__ logits, int64_t ld, const int32_t* __restrict__ labels,
                                                       int row0, int label_period, int vocab, float* __restrict__ row_loss) {
-    __shared__ float shf[16];
-    __shared__ double shd[16];
+    __shared__ float shf[NT / 64];
+    __shared__ double shd[NT / 64];
     // logits row blockIdx.x is row (row0 + blockIdx.x) of the stacked [+ rows; - rows] batch
     const int r = row0 + blockIdx.x;
     const int lab = labels[r % label_period];
@@ -564,13 +566,13 @@ __global__ __launch_bounds__(1024) void ce_rows_kernel(const float* __restrict__
     float m = -INFINITY, s = 0.f;
     const bool vec = ((ld & 3) == 0) && (((uintptr_t)logits & 15) == 0);
     const int nv = vec ? (vocab >> 2) : 0;
-    for (int i = threadIdx.x; i < nv; i += 1024) {
+    for (int i = threadIdx.x; i < nv; i += NT) {
         const float4 x = reinterpret_cast<const float4*>(lr)[i];
         const float mx = fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w));
         if (mx > m) { s *= expf(m - mx); m = mx; }
         s += (expf(x.x - m) + expf(x.y - m)) + (expf(x.z - m) + expf(x.w - m));
     }
-    for (int i = nv * 4 + threadIdx.x; i < vocab; i += 1024) {
+    for (int i = nv * 4 + threadIdx.x; i < vocab; i += NT) {
         const float x = lr[i];
         if (x > m) { s *= expf(m - x); m = x; }
         s += expf(x - m);
@@ -581,11 +583,12 @@ __global__ __launch_bounds__(1024) void ce_rows_kernel(const float* __restrict__
 }
 
 zo2_status cross_entropy_rows(const float* logits, int64_t ld, const int32_t* labels, int rows, int row0, int label_period,
-                              int vocab, float* row_loss, hipStream_t st) {
+                              int vocab, float* row_loss, hipStream_t st, bool keep_order) {
     if (rows == 0) return ZO2_OK;
     ZO2_OP_CHECK(logits && labels && row_loss, ZO2_EINVAL, "cross_entropy: NULL buffer");
     ZO2_OP_CHECK(vocab > 0 && ld >= vocab && label_period > 0 && row0 >= 0, ZO2_EINVAL, "cross_entropy: bad shape");
-    hipLaunchKernelGGL(ce_rows_kernel, dim3(rows), dim3(1024), 0, st, logits, ld, labels, row0, label_period, vocab, row_loss);
+    if (keep_order) hipLaunchKernelGGL(ce_rows_kernel<256>, dim3(rows), dim3(256), 0, st, logits, ld, labels, row0, label_period, vocab, row_loss);
+    else hipLaunchKernelGGL(ce_rows_kernel<1024>, dim3(rows), dim3(1024), 0, st, logits, ld, labels, row0, label_period, vocab, row_loss);
     ZO2_HIP_LAUNCH_CHECK();
     return ZO2_OK;
 }
@@ -593,14 +596,16 @@ zo2_status cross_entropy_rows(const float* logits, int64_t ld, const int32_t* la
 // ------------------------------------------------------------------ combine the LM-head kernel's cross-entropy partials
 // Row r has n_parts pairs (m_i, s_i), span-major ([i * part_ld + r]), with s_i = sum over a 64-column span of
 // exp(y - m_i); then logsumexp = M + log(sum_i s_i exp(m_i - M)), M = max_i m_i.
-__global__ __launch_bounds__(1024) void ce_combine_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum,
+template <int kGroups>
+__global__ __launch_bounds__(32 * kGroups) void ce_combine_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum,
                                                          const float* __restrict__ label_logit, const int32_t* __restrict__ labels,
                                                          int rows, int n_parts, int64_t part_ld, int row0, int label_period,
                                                          float* __restrict__ row_loss) {
     // 32 rows per block; 32 groups of lanes split the spans, so every load is 32 consecutive floats and a thread walks 25 of
-    // the 788 spans of a 50272-word vocabulary (a block is bound by the latency of that walk: with 8 groups, 31 us at 8192 rows
-    // and as much at 1026).  Two sweeps (max, then sum) keep the loads independent of each other.
-    constexpr int kRows = 32, kGroups = 32;
+    // the 788 spans of a 50272-word vocabulary (a block is bound by the latency of that walk: with 8 groups, which stay where
+    // the order of the sums is kept, 31 us at 8192 rows and as much at 1026).  Two sweeps (max, then sum) keep the loads
+    // independent of each other.
+    constexpr int kRows = 32;
     __shared__ float sh_m[kGroups][kRows];
     __shared__ double sh_s[kGroups][kRows];
     const int lr = threadIdx.x & (kRows - 1), grp = threadIdx.x / kRows;
@@ -639,12 +644,13 @@ __global__ __launch_bounds__(1024) void ce_combine_kernel(const float* __restric
 }
 
 zo2_status ce_combine(const float* part_max, const float* part_sum, const float* label_logit, const int32_t* labels, int rows,
-                      int n_parts, int64_t part_ld, int row0, int label_period, float* row_loss, hipStream_t st) {
+                      int n_parts, int64_t part_ld, int row0, int label_period, float* row_loss, hipStream_t st, bool keep_order) {
     if (rows == 0) return ZO2_OK;
     ZO2_OP_CHECK(part_max && part_sum && label_logit && labels && row_loss && n_parts > 0 && label_period > 0 && part_ld >= rows,
                  ZO2_EINVAL, "ce_combine: bad argument");
-    hipLaunchKernelGGL(ce_combine_kernel, dim3((rows + 31) / 32), dim3(1024), 0, st, part_max, part_sum, label_logit, labels, rows, n_parts,
-                       part_ld, row0, label_period, row_loss);
+    const dim3 grid((rows + 31) / 32);
+    if (keep_order) hipLaunchKernelGGL(ce_combine_kernel<8>, grid, dim3(256), 0, st, part_max, part_sum, label_logit, labels, rows, n_parts, part_ld, row0, label_period, row_loss);
+    else hipLaunchKernelGGL(ce_combine_kernel<32>, grid, dim3(1024), 0, st, part_max, part_sum, label_logit, labels, rows, n_parts, part_ld, row0, label_period, row_loss);
     ZO2_HIP_LAUNCH_CHECK();
     return ZO2_OK;
 }

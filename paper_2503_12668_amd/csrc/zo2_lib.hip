@@ -77,7 +77,7 @@ static constexpr int kDefaultSweeps = 1;       // update + perturb sweeps per bl
 // steps in us, ordinary path -> loader (blocks of ffn 4 d): d 768 x 12: 1 x 16 914 -> 913, 32 913 -> 1001; d 1024 x 8: 8 733 -> 706,
 // 16 743 -> 751; d 1536 x 6: 32 810 -> 806, 48 839 -> 843; d 2048 x 6: 16 1072 -> 937, 64 1109 -> 1091, 80 1164 -> 1173; d 2560 x 4: 64
 // 1293 -> 990, 128 1403 -> 1201; d 4096 x 2: 128 1573 -> 1262.  (Matrices of up to 2^19 elements: host-bound either way.)
-static constexpr int kFuseAlways = 64;      // beyond this its workspace must fit into what the ordinary path needs
+static constexpr int kFuseAlways = 64;      // beyond this its workspace must fit into what the ordinary path needs; the line of contexts that keep_order()
 static int fuse_max_tokens(int d, int f) { return (int64_t)d * f <= 1 << 19 ? 64 : std::min(128, std::max(16, 12 + (d - 1024) / 16)); }
 
 static bool config_ok(const zo2_config* c, char* why, size_t n) {
@@ -523,6 +523,14 @@ extern "C" zo2_status zo2_sync_to_host(zo2_ctx* c) {
 static const int kSweepBounds[3][5] = {{0, 16, 16, 16, 16}, {0, 10, 10, 16, 16}, {0, 8, 10, 14, 16}};
 static inline const int* sweep_bounds(int sweeps) { return kSweepBounds[sweeps == 1 ? 0 : sweeps == 2 ? 1 : 2]; }
 
+// Under stochastic rounding of a low-bit master every stored parameter is a draw that turns over with a late digit of eta g:
+// another order of the same products' sums moves l+ and l- by 1e-5 .. 2e-4 in 16 bits, g by a percent or two, and with it one in ten
+// thousand stored bytes of an 8-bit master in two steps; parameters of a 16-bit one end two spacings apart.  Such a run is to give
+// the same bits under every version of the kernels, so its 16-bit passes keep the order that sums have always had: one
+// accumulator per wavefront along k, the large tiles' pieces, the loader path up to 64 tokens, logits for fewer than 256 tokens.
+// (d 2048, 12 blocks, bf16: 1 x 16 tokens 1845 us where the order others take gives 1730, 5 x 37 2868 for 2570.)
+static inline bool keep_order(const zo2_ctx* c) { return c->stochastic && c->wsz < 4 && c->cfg.compute_dtype != ZO2_F32; }
+
 static zo2_status plan(zo2_ctx* c, int T, int batch, int seq) {
     const zo2_config& g = c->cfg;
     // a new layout starts from current host copies of the blocks (it may make them resident)
@@ -532,7 +540,7 @@ static zo2_status plan(zo2_ctx* c, int T, int batch, int seq) {
     const size_t rows2 = 2 * (size_t)T;
     // logits chunk (float32 mode and shapes the fused LM-head + cross-entropy kernel does not take): up to 1/8 of the
     // budget, at least 128 rows per sign
-    const bool fused_ce = (g.compute_dtype != ZO2_F32) && V >= 256 && (d % 128 == 0) && (V % 4 == 0);
+    const bool fused_ce = (g.compute_dtype != ZO2_F32) && V >= 256 && (d % 128 == 0) && (V % 4 == 0) && (T >= 256 || !keep_order(c));
     const size_t ce_parts = 4 * ((V + 255) / 256);
     size_t lrows = budget / 8 / (V * 4) / 2;
     lrows = lrows / 128 * 128;
@@ -557,7 +565,8 @@ static zo2_status plan(zo2_ctx* c, int T, int batch, int seq) {
     // above 64 tokens only where the slices' partial sums take no more than the logits that the head's partials replace, so
     // that no budget that holds the ordinary path is too small for this one
     const size_t freed = fused_ce && T < 256 ? 2 * std::min<size_t>(T, 128) * V * 4 - rows2 * (2 * ce_parts + 1) * 4 : 0;
-    const bool few_tokens = T <= fuse_max_tokens((int)d, (int)f) && (T <= kFuseAlways || fuse_bytes <= split_bytes + freed);
+    const bool few_tokens = keep_order(c) ? T <= kFuseAlways
+                                          : T <= fuse_max_tokens((int)d, (int)f) && (T <= kFuseAlways || fuse_bytes <= split_bytes + freed);
     const bool fuse = fuse_shapes && c->loader_fusion >= 0 && (c->loader_fusion == 1 || few_tokens) && !c->sk;
     const size_t sk_ws_bytes = std::max(split_bytes, fuse ? fuse_bytes : 0);
     size_t act = 0;
@@ -768,6 +777,7 @@ extern "C" zo2_status zo2_debug_set_stream_delay(zo2_ctx* c, int32_t which, uint
 extern "C" zo2_status zo2_set_wire_rounding(zo2_ctx* c, int32_t stochastic) {
     if (!c) return ZO2_EINVAL;
     if (c->dead) return ZO2_ESTATE;
+    c->need_plan = c->need_plan || c->stochastic != (stochastic != 0);      // see keep_order
     c->stochastic = stochastic != 0;
     return ZO2_OK;
 }
@@ -903,8 +913,9 @@ static size_t f32_split_workspace(const zo2_ctx* c, int T) { return 2 * (size_t)
 static int f32_pieces(const zo2_ctx* c, const GemmArgs& ga) { return gemm_f32_pick_splits(ga.M, ga.N, ga.K, ga.nprob, f32_split_workspace(c, ga.M)); }
 
 // A block projection: split along k when the launch would leave most compute units idle (few rows per stream)
-static zo2_status block_gemm(zo2_ctx* c, const GemmArgs& ga) {
+static zo2_status block_gemm(zo2_ctx* c, GemmArgs ga) {
     const int dt = c->cfg.compute_dtype;
+    ga.large_only = keep_order(c);
     if (dt == ZO2_F32 && c->split_k >= 0) return gemm_launch_f32_splitk(ga, f32_pieces(c, ga), c->logits, f32_split_workspace(c, ga.M), c->sc);
     if (c->split_k >= 0 && dt != ZO2_F32) {
         const GemmChoice k = gemm_choose(ga, dt, c->split_ws_bytes);
@@ -1049,7 +1060,7 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
     auto common = [&](int N, int K, int ldx, int ldy, int relu, int out_f32, int nprob) {
         memset(&sa, 0, sizeof(sa));
         sa.M = T; sa.N = N; sa.K = K; sa.ldx = ldx; sa.ldy = ldy; sa.relu = relu; sa.out_f32 = out_f32; sa.nprob = nprob; sa.eps = eps;
-        sa.key = philox_keys(seed);
+        sa.key = philox_keys(seed); sa.in_order = keep_order(c);
     };
 
     // ---- attention half: h += O(Attn(LN1(h)))
@@ -1366,7 +1377,7 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
                 p.label_logit = c->ce_lab + (size_t)s * T;
             }
             OPK(c, ZO2_KC_GEMM, gemm_launch(ga, dt, c->sc));
-            OPK(c, ZO2_KC_CE, ce_combine(c->ce_pmax, c->ce_psum, c->ce_lab, c->d_labels, ns * T, c->ce_parts, 2 * (int64_t)T, 0, T, c->row_loss, c->sc));
+            OPK(c, ZO2_KC_CE, ce_combine(c->ce_pmax, c->ce_psum, c->ce_lab, c->d_labels, ns * T, c->ce_parts, 2 * (int64_t)T, 0, T, c->row_loss, c->sc, keep_order(c)));
         } else {
             const int R = c->logit_rows;
             for (int r0 = 0; r0 < T; r0 += R) {
@@ -1374,6 +1385,7 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
                 GemmArgs ga;
                 memset(&ga, 0, sizeof(ga));
                 ga.M = rows; ga.N = g.vocab; ga.K = d; ga.ldx = d; ga.ldw = d; ga.ldy = g.vocab; ga.relu = 0; ga.out_f32 = 1; ga.nprob = ns;
+                ga.large_only = keep_order(c);
                 for (int s = 0; s < ns; ++s) {
                     GemmProblem& p = ga.p[s];
                     p.X = c->x + ((size_t)s * T + r0) * d * c->csz; p.W = s ? c->wm : c->wp; p.bias = nullptr; p.residual = nullptr;
@@ -1381,7 +1393,7 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
                 }
                 OPK(c, ZO2_KC_GEMM, gemm_launch(ga, dt, c->sc));
                 for (int s = 0; s < ns; ++s)
-                    OPK(c, ZO2_KC_CE, cross_entropy_rows(c->logits + (size_t)s * R * g.vocab, g.vocab, c->d_labels, rows, s * T + r0, T, g.vocab, c->row_loss, c->sc));
+                    OPK(c, ZO2_KC_CE, cross_entropy_rows(c->logits + (size_t)s * R * g.vocab, g.vocab, c->d_labels, rows, s * T + r0, T, g.vocab, c->row_loss, c->sc, keep_order(c)));
             }
         }
         // eta g of this pass: deferred update 0 of a new round (every older one has been applied on the way), or one more of
