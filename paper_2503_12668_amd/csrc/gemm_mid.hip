@@ -181,7 +181,6 @@ __global__ __launch_bounds__(512, 2) void gemm_mid_kernel(const GemmArgs a, int 
     OutT* __restrict__ Y = reinterpret_cast<OutT*>(p.Y);
     const size_t ldy = splits > 1 ? (size_t)a.N : (size_t)a.ldy;
     if (splits > 1) Y += (size_t)piece * a.M * a.N;                // this piece's partial sums (no bias, residual or ReLU, scale 1)
-    const float lower = a.relu ? 0.f : -INFINITY;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int m = m0 + wm * (BM / 2) + i * 32 + r;
@@ -198,7 +197,11 @@ __global__ __launch_bounds__(512, 2) void gemm_mid_kernel(const GemmArgs a, int 
             }
             float y[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) y[e] = fmaxf(__builtin_fmaf(acc[i][0][4 * q + e], p.out_scale, b4[e]), lower);
+            for (int e = 0; e < 4; ++e) y[e] = __builtin_fmaf(acc[i][0][4 * q + e], p.out_scale, b4[e]);
+            if (a.relu) {                                          // (no maximum with -inf in its place: that would lose a NaN)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) y[e] = fmaxf(y[e], 0.f);
+            }
             const size_t o = (size_t)m * ldy + n;
             if (p.residual) {
                 const v4f_t rv = *reinterpret_cast<const v4f_t*>(p.residual + o);
