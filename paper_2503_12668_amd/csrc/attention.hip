@@ -435,9 +435,10 @@ __global__ __launch_bounds__(64) void attention_f32_mfma_kernel(const float* __r
             }
             tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
             tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-            const float m_new = fmaxf(m_run[t], tmax);           // finite from the first tile on: key 0 is visible to every query
+            // (-inf as long as every score so far was: their weights are 0, and exp(-inf + inf) must not come in)
+            const float m_new = fmaxf(m_run[t], tmax), base = m_new == -INFINITY ? 0.f : m_new;
             if (__builtin_amdgcn_ballot_w64(m_new > m_run[t]) != 0) {
-                const float resc = expf(m_run[t] - m_new);
+                const float resc = expf(m_run[t] - base);
                 l_run[t] *= resc;
 #pragma unroll
                 for (int d = 0; d < DT; ++d) o[t][d] *= resc;
@@ -445,7 +446,7 @@ __global__ __launch_bounds__(64) void attention_f32_mfma_kernel(const float* __r
             }
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                st[t][e] = expf(st[t][e] - m_run[t]);
+                st[t][e] = expf(st[t][e] - base);
                 l_run[t] += st[t][e];
             }
         }
