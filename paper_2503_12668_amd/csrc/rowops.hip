@@ -562,23 +562,25 @@ __global__ __launch_bounds__(NT) void ce_rows_kernel(const float* __restrict__ l
         return;
     }
     const float* lr = logits + (size_t)blockIdx.x * ld;
-    // one pass: running maximum m and sum s of exp(x - m) per lane, rescaled when m grows
+    // one pass: running maximum m and sum s of exp(x - m) per lane, rescaled when m grows; while m is -inf (logits of -inf, which
+    // add nothing, or NaN, which is to stay) the exponents are taken against 0
     float m = -INFINITY, s = 0.f;
+    auto base = [&]() { return m == -INFINITY ? 0.f : m; };
     const bool vec = ((ld & 3) == 0) && (((uintptr_t)logits & 15) == 0);
     const int nv = vec ? (vocab >> 2) : 0;
     for (int i = threadIdx.x; i < nv; i += NT) {
         const float4 x = reinterpret_cast<const float4*>(lr)[i];
         const float mx = fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w));
         if (mx > m) { s *= expf(m - mx); m = mx; }
-        s += (expf(x.x - m) + expf(x.y - m)) + (expf(x.z - m) + expf(x.w - m));
+        s += (expf(x.x - base()) + expf(x.y - base())) + (expf(x.z - base()) + expf(x.w - base()));
     }
     for (int i = nv * 4 + threadIdx.x; i < vocab; i += NT) {
         const float x = lr[i];
         if (x > m) { s *= expf(m - x); m = x; }
-        s += expf(x - m);
+        s += expf(x - base());
     }
     const float mall = block_max(m, shf);
-    const double tot = block_sum((double)(m == -INFINITY ? 0.f : s * expf(m - mall)), shd);
+    const double tot = block_sum((double)(m == -INFINITY ? s : s * expf(m - mall)), shd);
     if (threadIdx.x == 0) row_loss[r] = (float)(log(tot) + (double)mall - (double)lr[lab]);
 }
 
