@@ -374,8 +374,9 @@ zo2_status zo2_op_gemm_perturbed(int32_t dtype, int32_t M, int32_t N, int32_t K,
                                  void* workspace, size_t workspace_bytes, void* stream);
 size_t zo2_op_gemm_perturbed_workspace_bytes(int32_t M, int32_t N, int32_t K);
 
-/* W+ and W- of rows n0 .. n0 + rows - 1 of a dense [N, K] tensor through the code path of that loader (test hook:
- * the bits must equal those of zo2_op_update_perturb without an update).  theta points at row n0. */
+/* W+ and W- of rows n0 .. n0 + rows - 1 of a dense [N, K] tensor by the loader's arithmetic, one chunk of eight elements at a
+ * time (test hook: the bits must equal those of zo2_op_update_perturb without an update; the loader itself draws two chunks in
+ * step and shows its W+ and W- where X+ and X- are rows of the identity).  theta points at row n0. */
 zo2_status zo2_op_perturbed_rows(int32_t dtype, const void* theta, int64_t K, int64_t n0, int64_t rows, uint32_t tensor_id,
                                  uint64_t seed, float eps, void* w_plus, void* w_minus, void* stream);
 

@@ -253,7 +253,7 @@ def op_gemm_perturbed(Xp, Xm, theta, tensor_id, seed, eps, bias_p=None, bias_m=N
 
 
 def op_perturbed_rows(theta_rows, K, n0, tensor_id, seed, eps, stream=None):
-    """W+ and W- of rows n0 .. of a dense [N, K] tensor (theta_rows: those rows) through the loader's code path."""
+    """W+ and W- of rows n0 .. of a dense [N, K] tensor (theta_rows: those rows) by the loader's arithmetic."""
     wp, wm = torch.empty_like(theta_rows), torch.empty_like(theta_rows)
     _op_check(lib().zo2_op_perturbed_rows(_dt(theta_rows), _ptr(theta_rows), K, n0, theta_rows.numel() // K, tensor_id, seed, eps,
                                           _ptr(wp), _ptr(wm), _stream_ptr(stream)))

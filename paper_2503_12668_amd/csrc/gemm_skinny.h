@@ -48,7 +48,7 @@ zo2_status skinny_launch(SkinnyArgs& a, int dtype, void* workspace, size_t works
 zo2_status skinny_launch_ce(SkinnyArgs& a, int dtype, hipStream_t st);
 size_t skinny_workspace_bytes(int M, int N, int K, int nprob);
 bool skinny_applicable(int M, int N, int K, int dtype);
-// W+ and W- of rows [n0, n0 + rows) of a dense [N, K] tensor, through the loader's own code path (a test hook)
+// W+ and W- of rows [n0, n0 + rows) of a dense [N, K] tensor, chunk by chunk with the loader's arithmetic (a test hook)
 zo2_status skinny_perturbed_rows(int dtype, const void* theta, int64_t K, int64_t n0, int64_t rows, uint32_t tensor_id, uint64_t seed,
                                  float eps, void* w_plus, void* w_minus, hipStream_t st);
 

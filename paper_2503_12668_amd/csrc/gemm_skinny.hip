@@ -30,8 +30,7 @@ template <> struct SkMfma<f16_t> {
     }
 };
 
-// Eight consecutive stored elements (one 16-byte chunk starting at element index e, a multiple of 8) -> the same chunk
-// of W+ and of W-: one Philox call, four Box-Muller pairs, one fused multiply-add and one rounding per element and sign.
+// Eight consecutive stored elements (one 16-byte chunk) and their Philox words -> the same chunk of W+ and of W-: one call, four Box-Muller pairs, one fused multiply-add and one rounding per element and sign.
 template <typename T>
 __device__ __forceinline__ void perturb_words(const uint32_t w[4], float eps, v4u_t th, v4u_t& wp, v4u_t& wm) {
     Vec<T, 8> t8, p8, m8;
@@ -48,13 +47,14 @@ __device__ __forceinline__ void perturb_words(const uint32_t w[4], float eps, v4
     __builtin_memcpy(&wp, &p8, 16);
     __builtin_memcpy(&wm, &m8, 16);
 }
+// one chunk, starting at element index e, a multiple of 8 (the test hook)
 template <typename T>
 __device__ __forceinline__ void perturb_chunk(const PhiloxKeys& key, uint32_t tensor_id, uint64_t e, float eps, v4u_t th, v4u_t& wp, v4u_t& wm) {
     uint32_t w[4];
     philox4x32_10((uint32_t)(e >> 3), (uint32_t)(e >> 35), tensor_id, 0u, key, w);
     perturb_words<T>(w, eps, th, wp, wm);
 }
-// two chunks, 16 elements apart, in step
+// two chunks, 16 elements apart, in step (the loader)
 template <typename T>
 __device__ __forceinline__ void perturb_pair(const PhiloxKeys& key, uint32_t tensor_id, uint64_t e, float eps, const v4u_t th[2], v4u_t wp[2], v4u_t wm[2]) {
     uint32_t w[2][4];

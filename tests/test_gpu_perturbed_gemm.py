@@ -160,3 +160,23 @@ def test_row_tile_edges(M):
     for Y, X, w in ((Yp, Xp, wp), (Ym, Xm, wm)):
         Z = X.double() @ w.reshape(N, K).double().T
         assert (Y - Z).abs().max() <= 2e-5 * max(1.0, float(Z.abs().max()))
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("M", [32, 64, 96, 128, 192, 256])
+def test_loader_kernel_itself_forms_the_bits_of_the_sweep_kernel(dt, M):
+    """Rows of the identity as activations: the kernel's outputs are its W+ and W-, for every row-tile height, slices of the k
+    range of different lengths and a last tile of 72 weight rows."""
+    b = _b()
+    N, K, tid, seed, eps = 200, 1088, 40, 9, 1e-3
+    theta = (torch.randn(N, K, generator=torch.Generator().manual_seed(M)) * 0.02).to(TD[dt]).cuda()
+    t = theta.clone().reshape(-1)
+    want = [torch.empty_like(t), torch.empty_like(t)]
+    b.op_update_perturb(t, want[0], want[1], tid, 0, False, 0, 0.0, seed, eps)
+    eye = torch.eye(K, device="cuda").to(TD[dt])
+    for k0 in range(0, K, M):
+        X = torch.zeros(M, K, device="cuda", dtype=TD[dt])
+        m = min(M, K - k0)
+        X[:m] = eye[k0:k0 + m]
+        for Y, w in zip(b.op_gemm_perturbed(X, X, theta, tid, seed, eps, out_dtype=b.F32), want):
+            assert torch.equal(Y[:m].T, w.reshape(N, K)[:, k0:k0 + m].float()), k0
