@@ -74,11 +74,14 @@ static constexpr int64_t kTensorAlign = 256;   // elements
 static constexpr int kDefaultSweeps = 1;       // update + perturb sweeps per block when the budget leaves the choice
 // Up to this many tokens per stream the projections perturb in their weight loader.  The line lies higher the wider the model
 // is: the slices' partial sums grow with the tokens alone, and what is saved, the perturbed copies, with the weights.  Whole
-// steps in us, ordinary path -> loader (blocks of ffn 4 d): d 768 x 12: 1 x 16 914 -> 913, 32 913 -> 1001; d 1024 x 8: 8 733 -> 706,
-// 16 743 -> 751; d 1536 x 6: 32 810 -> 806, 48 839 -> 843; d 2048 x 6: 16 1072 -> 937, 64 1109 -> 1091, 80 1164 -> 1173; d 2560 x 4: 64
-// 1293 -> 990, 128 1403 -> 1201; d 4096 x 2: 128 1573 -> 1262.  (Matrices of up to 2^19 elements: host-bound either way.)
+// steps at the models' own depths in us, ordinary path -> loader (blocks of ffn 4 d): d 768 x 12: 16 tokens 906 -> 854, 24 918 -> 916,
+// 32 917 -> 946; d 1024 x 24: 8 1841 -> 1724, 16 1856 -> 1819, 20 1865 -> 1895; d 1536 x 24: 24 2507 -> 2523, 44 2639 -> 2694; d 2048 x 24: 16
+// 3377 -> 3014, 48 3507 -> 3394, 60 3523 -> 3521, 64 3535 -> 3550, 72 3676 -> 3789; d 2560 x 32: 64 8005 -> 5923, 128 8725 -> 7240; d 4096 x
+// 32: 128 17236 -> 13609; d 5120 x 40: 128 32840 -> 25461.  (A model of few blocks gains more, by its head: d 2048 x 6: 64 1106 -> 1058.)
+// Where no matrix has more than 2^19 elements, which keeps the ordinary path on its older kernels (gemm_choose), it wins up to
+// 64: d 256 x 8, ffn 2048: 32 603 -> 493, 64 641 -> 585, 100 660 -> 736; d 512 x 12, ffn 1024: 64 1056 -> 884.
 static constexpr int kFuseAlways = 64;      // beyond this its workspace must fit into what the ordinary path needs; the line of contexts that keep_order()
-static int fuse_max_tokens(int d, int f) { return (int64_t)d * f <= 1 << 19 ? 64 : std::min(128, std::max(16, 12 + (d - 1024) / 16)); }
+static int fuse_max_tokens(int d, int f) { return (int64_t)d * std::max(d, f) <= 1 << 19 ? 64 : std::min(128, std::max(16, 16 + (d - 1536) * 11 / 128)); }
 
 static bool config_ok(const zo2_config* c, char* why, size_t n) {
 #define BAD(...) do { snprintf(why, n, __VA_ARGS__); return false; } while (0)

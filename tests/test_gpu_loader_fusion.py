@@ -174,3 +174,20 @@ def test_one_sweep_for_matrices_and_vectors_and_the_sum_with_the_layernorm(dt, d
     for n in P:
         assert np.array_equal(got[1][1][n], got[-1][1][n]), n
     assert any(not np.array_equal(got[1][1][n], codec.round_to(P[n], dt)) for n in P)
+
+
+@pytest.mark.parametrize("d,f,vocab,line", [(256, 2048, 260, 64), (768, 768, 260, 16), (1536, 64, 260, 16), (2048, 64, 260, 60), (2816, 64, 260, 64), (2816, 64, 34820, 126)])
+def test_default_line_of_the_loader_path_by_width(d, f, vocab, line):
+    """16 tokens up to d_model 1536, then 11 more per 128; beyond 64 only where the vocabulary's logits have room for the slices;
+    64 where no matrix has more than 2^19 elements, d x d among them.  Under stochastic rounding 64 for every width."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=1, d_model=d, n_heads=d // 64, d_ffn=f, vocab=vocab, max_pos=130)
+    P = si.make_weights(cfg, seed=1)
+    ctx = b.Zo2Context(cfg, P, wire="bf16", compute="bf16", arena_bytes=1 << 30)
+    for stochastic, at in ((False, line), (True, 64)):
+        ctx.set_wire_rounding(stochastic)
+        for seq in (at, at + 1):
+            t = si.make_tokens(vocab, 1, seq, seed=3)
+            ctx.step(t, si.next_token_labels(t), 9, 1e-3, 0.0)
+            assert ctx.plan()["loader_fusion"] == (seq == at), (stochastic, seq)
+    ctx.close()
