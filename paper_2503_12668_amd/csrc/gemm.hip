@@ -385,9 +385,8 @@ static zo2_status launch_large(const GemmArgs& a, int dtype, hipStream_t st) {
     return ZO2_EINVAL;
 }
 
-zo2_status gemm_launch(const GemmArgs& a, int dtype, hipStream_t st) {
-    ZO2_OP_CHECK(a.M >= 0 && a.N >= 0 && a.K > 0, ZO2_EINVAL, "gemm: bad shape %d x %d x %d", a.M, a.N, a.K);
-    if (a.M == 0 || a.N == 0 || a.nprob == 0) return ZO2_OK;
+// what every kernel takes for granted: 16-byte rows of operands that are there
+static zo2_status check_operands(const GemmArgs& a) {
     ZO2_OP_CHECK(a.K % 8 == 0, ZO2_EINVAL, "gemm: K = %d is not a multiple of 8", a.K);
     ZO2_OP_CHECK(a.ldx >= a.K && a.ldw >= a.K && a.ldy >= a.N, ZO2_EINVAL, "gemm: leading dimension too small");
     ZO2_OP_CHECK(a.ldx % 8 == 0 && a.ldw % 8 == 0, ZO2_EINVAL, "gemm: ldx / ldw must be multiples of 8");
@@ -397,6 +396,13 @@ zo2_status gemm_launch(const GemmArgs& a, int dtype, hipStream_t st) {
         ZO2_OP_CHECK(((uintptr_t)a.p[i].X & 15) == 0 && ((uintptr_t)a.p[i].W & 15) == 0, ZO2_EINVAL,
                      "gemm: operands must be 16-byte aligned");
     }
+    return ZO2_OK;
+}
+
+zo2_status gemm_launch(const GemmArgs& a, int dtype, hipStream_t st) {
+    ZO2_OP_CHECK(a.M >= 0 && a.N >= 0 && a.K > 0, ZO2_EINVAL, "gemm: bad shape %d x %d x %d", a.M, a.N, a.K);
+    if (a.M == 0 || a.N == 0 || a.nprob == 0) return ZO2_OK;
+    { const zo2_status s = check_operands(a); if (s != ZO2_OK) return s; }
     // cross-entropy mode has no output matrix (Y may be NULL): only the 256 x 256 kernel implements it, so every
     // other path must be refused before anything is launched
     ZO2_OP_CHECK(!a.ce_mode || (dtype != ZO2_F32 && gemm256_applicable(a, dtype)), ZO2_EINVAL,
@@ -610,7 +616,8 @@ zo2_status gemm_launch_splitk(const GemmArgs& a, int dtype, int splits, void* wo
             q.Y = part + ((size_t)i * splits + k) * plane;
             q.out_scale = 1.0f;
         }
-    zo2_status s = launch_large(e, dtype, st);
+    zo2_status s = check_operands(e);
+    if (s == ZO2_OK) s = launch_large(e, dtype, st);
     if (s != ZO2_OK) return s;
     if (dtype == ZO2_BF16) launch_splitk_reduce<bf16_t>(a, part, splits, st);
     else launch_splitk_reduce<f16_t>(a, part, splits, st);

@@ -45,3 +45,15 @@ def test_layout_helpers_and_argument_errors():
         binding.block_tensor_offsets(binding.make_config(bad))
     # NULL context
     assert L.zo2_flush(None) == 1 and L.zo2_step(None, None, None, 1, 1, 0, 1e-3, 0.0, None, None, None) == 1
+
+
+def test_split_gemm_refuses_operands_that_its_kernels_cannot_load():
+    """Refused on the host before anything is launched: the addresses are nobody's."""
+    from paper_2503_12668_amd import binding
+    L = binding.lib()
+
+    def call(X=1 << 16, W=1 << 16, ldx=1024, ldw=1024, Y=1 << 16, ldy=64, K=1024, splits=2):
+        return L.zo2_op_gemm_split_k(binding.BF16, 64, 64, K, X, ldx, W, ldw, None, None, Y, binding.F32, ldy, 1.0, 0, splits, 1 << 16, 1 << 30, None)
+
+    for bad in (dict(X=(1 << 16) + 8), dict(W=(1 << 16) + 2), dict(ldx=1028), dict(ldw=1020), dict(ldw=504), dict(ldx=8), dict(K=1032, splits=4), dict(X=None)):
+        assert call(**bad) == 1, (bad, L.zo2_op_last_error())
