@@ -351,13 +351,24 @@ zo2_status zo2_op_gemm(int32_t dtype, int32_t M, int32_t N, int32_t K,
 /* zo2_op_gemm with the k range cut into `splits` (2 or 4) pieces: the pieces run as one launch into float32 partial sums
  * in `workspace` (device, 16-byte aligned, zo2_op_gemm_split_k_workspace_bytes(M, N, splits) bytes, overwritten), a second
  * kernel adds them in piece order and applies bias, scale, ReLU and residual.  16-bit dtypes; N % 4 == 0, ldy % 4 == 0,
- * K % (8 splits) == 0.  zo2_op_gemm_split_k_pieces: the number of pieces (1, 2 or 4) zo2_step would use for a launch of `nprob`
- * problems of this shape.  ZO2_EINVAL on anything else. */
+ * K % (8 splits) == 0.  zo2_op_gemm_split_k_pieces: the number of pieces (1, 2 or 4) in which zo2_step would run `nprob` problems
+ * of this shape on the large tiles (zo2_op_gemm_choice says whether it does).  ZO2_EINVAL on anything else. */
 zo2_status zo2_op_gemm_split_k(int32_t dtype, int32_t M, int32_t N, int32_t K, const void* X, int64_t ldx, const void* W, int64_t ldw,
                                const void* bias, const float* residual, void* Y, int32_t out_dtype, int64_t ldy, float out_scale,
                                int32_t relu, int32_t splits, void* workspace, size_t workspace_bytes, void* stream);
 size_t zo2_op_gemm_split_k_workspace_bytes(int32_t M, int32_t N, int32_t splits);
 int32_t zo2_op_gemm_split_k_pieces(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t nprob);
+/* What zo2_step runs `nprob` problems of this shape on, 16-bit dtypes: *rows = 0: the large tiles (or, for shapes that these do not
+ * take, the general kernel), cut into *pieces along k; 64 or 128: 128-wide tiles of that height, *pieces along k.
+ * workspace_bytes: what is there for partial sums (zo2_op_gemm calls have 0). */
+zo2_status zo2_op_gemm_choice(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t nprob, size_t workspace_bytes, int32_t* rows, int32_t* pieces);
+/* zo2_op_gemm on the 128-wide tiles (for tests and measurements; zo2_op_gemm and zo2_step take them where zo2_op_gemm_choice says):
+ * rows = 64 or 128; the k range in `pieces` >= 1 of a multiple of 64, none empty, their float32 sums in `workspace` (device,
+ * 16-byte aligned, M * N * 4 bytes per piece; unused and may be NULL for one), added in piece order.  16-bit dtypes, K % 64 == 0,
+ * N % 4 == 0, ldy % 4 == 0, bias, residual and Y aligned to 4 elements, a residual only with F32 output; ZO2_EINVAL otherwise. */
+zo2_status zo2_op_gemm_wide128(int32_t dtype, int32_t M, int32_t N, int32_t K, const void* X, int64_t ldx, const void* W, int64_t ldw,
+                               const void* bias, const float* residual, void* Y, int32_t out_dtype, int64_t ldy, float out_scale,
+                               int32_t relu, int32_t rows, int32_t pieces, void* workspace, size_t workspace_bytes, void* stream);
 /* The same projection for both perturbation streams at once, with the perturbation generated in the weight loader
  * (Alg. 2 "perturb" folded into the forward; for steps of few tokens, where the projections are bound by reading the
  * weights): Y+- [M, N] = act( (X+- [M, K] . (theta +- eps z)^T + bias+-) * out_scale ) + residual+-, where theta [N, K]
@@ -383,8 +394,9 @@ zo2_status zo2_op_perturbed_rows(int32_t dtype, const void* theta, int64_t K, in
 
 /* The large-tile GEMM kernel works on 256- or 128-row tiles and picks the height per launch (whichever fills the
  * rounds of tiles over the compute units better).  rows = 128 or 256 forces one height for every later launch of the
- * process, step calls included; 0 restores the choice per launch.  For tests and measurements: results are the same
- * bit for bit either way (the order in which a dot product is accumulated does not depend on the tile height).
+ * process, step calls included, and takes launches of a few hundred rows off the 128-wide tiles; 0 restores the choice per
+ * launch.  For tests and measurements: the heights give the same results bit for bit (the order in which a dot product is
+ * accumulated does not depend on them); the 128-wide tiles add each slab's k in two halves and differ by float32 rounding.
  * Returns ZO2_EINVAL for any other value. */
 zo2_status zo2_op_set_gemm_tile_rows(int32_t rows);
 
@@ -399,8 +411,9 @@ zo2_status zo2_op_gemm_phases(int32_t dtype, int32_t M, int32_t N, int32_t K, co
 
 /* Launches of 256-row tiles run with eight wavefronts per workgroup (two per SIMD, one k-slab of prefetch) or with
  * four (a further slab in flight in registers), chosen per launch by the length of k and the number of rows.  waves = 4 or 8 forces one form
- * for every later launch of the process, step calls included; 0 restores the choice per launch.  For tests and
- * measurements: results are the same bit for bit either way.  Returns ZO2_EINVAL for any other value. */
+ * for every later launch of the process, step calls included, and takes launches off the 128-wide tiles as a forced height
+ * does; 0 restores the choice per launch.  For tests and measurements: both forms give the same results bit for bit.
+ * Returns ZO2_EINVAL for any other value. */
 zo2_status zo2_op_set_gemm_wavefronts(int32_t waves);
 
 /* Causal multi-head self-attention.  q, k, v, out: [n_seq * seq, ld] of `dtype`, head h in

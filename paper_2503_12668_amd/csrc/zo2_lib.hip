@@ -1737,6 +1737,31 @@ extern "C" zo2_status zo2_op_gemm_split_k(int32_t dtype, int32_t M, int32_t N, i
     return gemm_launch_splitk(a, dtype, splits, workspace, workspace_bytes, as_stream(stream));
 }
 
+extern "C" zo2_status zo2_op_gemm_choice(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t nprob, size_t workspace_bytes, int32_t* rows, int32_t* pieces) {
+    ZO2_OP_CHECK((dtype == ZO2_BF16 || dtype == ZO2_F16) && M > 0 && N > 0 && K > 0 && nprob >= 1 && nprob <= GemmArgs::kMaxProblems && rows && pieces, ZO2_EINVAL,
+                 "gemm_choice: 16-bit dtypes and positive sizes");
+    GemmArgs a;
+    memset(&a, 0, sizeof(a));
+    a.M = M; a.N = N; a.K = K; a.ldx = K; a.ldw = K; a.ldy = N; a.nprob = nprob;
+    const GemmChoice k = gemm_choose(a, dtype, workspace_bytes);
+    *rows = k.rows;
+    *pieces = k.splits;
+    return ZO2_OK;
+}
+
+extern "C" zo2_status zo2_op_gemm_wide128(int32_t dtype, int32_t M, int32_t N, int32_t K, const void* X, int64_t ldx, const void* W, int64_t ldw,
+                                          const void* bias, const float* residual, void* Y, int32_t out_dtype, int64_t ldy, float out_scale,
+                                          int32_t relu, int32_t rows, int32_t pieces, void* workspace, size_t workspace_bytes, void* stream) {
+    if (M == 0 || N == 0) return ZO2_OK;
+    ZO2_OP_CHECK(out_dtype == ZO2_F32 || out_dtype == dtype, ZO2_EINVAL, "gemm: output dtype must be F32 or the input dtype");
+    GemmArgs a;
+    memset(&a, 0, sizeof(a));
+    a.M = M; a.N = N; a.K = K; a.ldx = ldx; a.ldw = ldw; a.ldy = ldy; a.relu = relu; a.out_f32 = out_dtype == ZO2_F32; a.nprob = 1;
+    a.p[0].X = X; a.p[0].W = W; a.p[0].bias = bias; a.p[0].residual = residual; a.p[0].Y = Y; a.p[0].out_scale = out_scale;
+    ZO2_OP_CHECK(pieces >= 1, ZO2_EINVAL, "gemm: %d pieces", pieces);
+    return gemm_launch_mid_splitk(a, dtype, rows, pieces, workspace, workspace_bytes, as_stream(stream));
+}
+
 extern "C" size_t zo2_op_gemm_perturbed_workspace_bytes(int32_t M, int32_t N, int32_t K) { return skinny_workspace_bytes(M, N, K, 1); }
 
 extern "C" zo2_status zo2_op_gemm_perturbed(int32_t dtype, int32_t M, int32_t N, int32_t K, const void* X_plus, const void* X_minus, int64_t ldx,
