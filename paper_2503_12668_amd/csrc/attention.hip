@@ -2,7 +2,7 @@
 // keys / values are visited in tiles staged through LDS, the softmax is accumulated online,
 // and the S x S score matrix is never written to memory.
 //
-// Three kernels: the matrix cores for 16-bit inputs (d_head 64, 80, 128) and for float32 (d_head a multiple of 16), and
+// Three kernels: the matrix cores for 16-bit inputs (d_head 64, 80, 128) and for float32 (d_head 16, 32, 64, 80, 128), and
 // a vector-ALU kernel with float32 arithmetic throughout as the general fallback: one wavefront per 64 queries of one
 // (sequence, head); a lane owns one query row.
 #include "attention.h"
@@ -483,19 +483,11 @@ __global__ __launch_bounds__(64) void attention_f32_mfma_kernel(const float* __r
     }
 }
 
-template <int QT>
-static zo2_status launch_f32_att(const float* q, const float* k, const float* v, float* out, int n_seq, int seq, int n_heads, int d_head,
-                                 int64_t ld, hipStream_t st) {
+template <int DH, int QT>
+static void launch_f32_att(const float* q, const float* k, const float* v, float* out, int n_seq, int seq, int n_heads, int64_t ld, hipStream_t st) {
     const int n_pairs = n_heads * n_seq, nqb = (seq + 16 * QT - 1) / (16 * QT);
     const dim3 grid((unsigned)(8 * nqb) * (unsigned)((n_pairs + 7) / 8)), block(64);
-    switch (d_head) {
-#define ZO2_ATT_CASE(D) \
-    case D: hipLaunchKernelGGL((attention_f32_mfma_kernel<D, QT>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs); break;
-        ZO2_ATT_CASE(16) ZO2_ATT_CASE(32) ZO2_ATT_CASE(64) ZO2_ATT_CASE(80) ZO2_ATT_CASE(128)
-#undef ZO2_ATT_CASE
-    }
-    ZO2_HIP_LAUNCH_CHECK();
-    return ZO2_OK;
+    hipLaunchKernelGGL((attention_f32_mfma_kernel<DH, QT>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs);
 }
 
 template <typename T>
@@ -535,10 +527,22 @@ zo2_status attention_launch(int dtype, const void* q, const void* k, const void*
     }
     const bool f32_fits = (int64_t)(n_seq * (int64_t)n_heads + 8) * ((seq + 15) / 16) < (int64_t)1 << 25;      // its grid of 64-thread workgroups
     if (!vector_kernel && dtype == ZO2_F32 && f32_fits && (d_head == 16 || d_head == 32 || d_head == 64 || d_head == 80 || d_head == 128)) {
-        // 32 queries per wavefront read the keys half as often; 16 where that would leave SIMDs without a wavefront
-        const bool wide = d_head <= 64 && (int64_t)n_seq * n_heads * ((seq + 31) / 32) >= 4 * (int64_t)device_cu_count();
-        const auto launch = wide ? launch_f32_att<2> : launch_f32_att<1>;
-        return launch((const float*)q, (const float*)k, (const float*)v, (float*)out, n_seq, seq, n_heads, d_head, ld, st);
+        // 32 queries per wavefront read the keys half as often; 16 where that would leave SIMDs without a wavefront, and beyond
+        // d_head 64, where a wavefront's registers hold no more
+        const bool wide = (int64_t)n_seq * n_heads * ((seq + 31) / 32) >= 4 * (int64_t)device_cu_count();
+        const float *qf = (const float*)q, *kf = (const float*)k, *vf = (const float*)v;
+        float* of = (float*)out;
+#define ZO2_ATT_CASE(D, QT) launch_f32_att<D, QT>(qf, kf, vf, of, n_seq, seq, n_heads, ld, st)
+        switch (d_head) {
+            case 16: wide ? ZO2_ATT_CASE(16, 2) : ZO2_ATT_CASE(16, 1); break;
+            case 32: wide ? ZO2_ATT_CASE(32, 2) : ZO2_ATT_CASE(32, 1); break;
+            case 64: wide ? ZO2_ATT_CASE(64, 2) : ZO2_ATT_CASE(64, 1); break;
+            case 80: ZO2_ATT_CASE(80, 1); break;
+            case 128: ZO2_ATT_CASE(128, 1); break;
+        }
+#undef ZO2_ATT_CASE
+        ZO2_HIP_LAUNCH_CHECK();
+        return ZO2_OK;
     }
     ZO2_DISPATCH_COMPUTE(dtype, T, {
         return launch_valu<T>((const T*)q, (const T*)k, (const T*)v, (T*)out, n_seq, seq, n_heads, d_head, ld, st);
