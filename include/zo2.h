@@ -212,9 +212,10 @@ zo2_status zo2_get_scratch_plan(const zo2_ctx* ctx, int32_t* sweeps_per_block, i
 zo2_status zo2_set_scratch_plan(zo2_ctx* ctx, int32_t sweeps);
 
 /* Where the perturbation of a block's six weight matrices is generated.  By default (mode 0) a step of few
- * tokens per stream - 16 + 11 (d_model - 1536) / 128, at least 16 and at most 128, beyond 64 only where the loader path's
- * workspace fits into the logits of the ordinary path's LM head and its split-k workspace; 64 where no matrix of a block has
- * more than 2^19 elements, and under stochastic rounding (zo2_set_wire_rounding) - where the projections are bound by reading the weights, lets the projections read the stored
+ * tokens per stream - 16 + 11 (d_model - 1536) / 128 but at least 16, 16 more where d_model is no multiple of 128, at most 128,
+ * and beyond 64 only where the loader path's workspace fits into the logits of the ordinary path's LM head and its split-k
+ * workspace; 64 where a matrix of the block has at most 2^19 elements, and under stochastic rounding
+ * (zo2_set_wire_rounding) - where the projections are bound by reading the weights, lets the projections read the stored
  * weights and form W+ / W- in their loader (zo2_op_gemm_perturbed), the sweep kernel then only applies the pending
  * update and perturbs the block's one-dimensional tensors (the LM head does the same with the vocabulary matrix up to 128 tokens); larger steps write the perturbed copies with the sweep kernel,
  * because a weight tile would otherwise be regenerated once per 256-row tile of activations.  mode 1: in the loader

@@ -78,10 +78,15 @@ static constexpr int kDefaultSweeps = 1;       // update + perturb sweeps per bl
 // 32 917 -> 946; d 1024 x 24: 8 1841 -> 1724, 16 1856 -> 1819, 20 1865 -> 1895; d 1536 x 24: 24 2507 -> 2523, 44 2639 -> 2694; d 2048 x 24: 16
 // 3377 -> 3014, 48 3507 -> 3394, 60 3523 -> 3521, 64 3535 -> 3550, 72 3676 -> 3789; d 2560 x 32: 64 8005 -> 5923, 128 8725 -> 7240; d 4096 x
 // 32: 128 17236 -> 13609; d 5120 x 40: 128 32840 -> 25461.  (A model of few blocks gains more, by its head: d 2048 x 6: 64 1106 -> 1058.)
-// Where no matrix has more than 2^19 elements, which keeps the ordinary path on its older kernels (gemm_choose), it wins up to
-// 64: d 256 x 8, ffn 2048: 32 603 -> 493, 64 641 -> 585, 100 660 -> 736; d 512 x 12, ffn 1024: 64 1056 -> 884.
+// Widths that are no multiple of 128 take 16 tokens more: the large kernel refuses them (8 blocks: d 832 32 710 -> 682, 64 733 -> 807; d 960
+// 32 730 -> 701; d 1088 32 844 -> 844; d 1728 48 1270 -> 1153; d 2240 90 1636 -> 1581).  And where a matrix of the block has at most 2^19
+// elements, which keeps its launches on the older kernels (gemm_choose), the line is 64: d 256 x 8, ffn 2048 64 641 -> 585, 100 660 ->
+// 736; d 512, ffn 2048 64 698 -> 674, 80 689 -> 717; d 640 64 747 -> 744; d 704 64 938 -> 762; d 1024, ffn 512 64 790 -> 726.
 static constexpr int kFuseAlways = 64;      // beyond this its workspace must fit into what the ordinary path needs; the line of contexts that keep_order()
-static int fuse_max_tokens(int d, int f) { return (int64_t)d * std::max(d, f) <= 1 << 19 ? 64 : std::min(128, std::max(16, 16 + (d - 1536) * 11 / 128)); }
+static int fuse_max_tokens(int d, int f) {
+    if ((int64_t)d * std::min(d, f) <= 1 << 19) return 64;
+    return std::min(128, std::max(16, 16 + (d - 1536) * 11 / 128) + (d % 128 ? 16 : 0));
+}
 
 static bool config_ok(const zo2_config* c, char* why, size_t n) {
 #define BAD(...) do { snprintf(why, n, __VA_ARGS__); return false; } while (0)

@@ -176,10 +176,11 @@ def test_one_sweep_for_matrices_and_vectors_and_the_sum_with_the_layernorm(dt, d
     assert any(not np.array_equal(got[1][1][n], codec.round_to(P[n], dt)) for n in P)
 
 
-@pytest.mark.parametrize("d,f,vocab,line", [(256, 2048, 260, 64), (768, 768, 260, 16), (1536, 64, 260, 16), (2048, 64, 260, 60), (2816, 64, 260, 64), (2816, 64, 34820, 126)])
+@pytest.mark.parametrize("d,f,vocab,line", [(256, 2048, 260, 64), (704, 2816, 260, 64), (1024, 512, 260, 64), (768, 768, 260, 16), (832, 832, 260, 32), (1536, 512, 260, 16),
+                                              (1600, 384, 260, 37), (2048, 320, 260, 60), (2816, 192, 260, 64), (2816, 192, 34820, 126)])
 def test_default_line_of_the_loader_path_by_width(d, f, vocab, line):
-    """16 tokens up to d_model 1536, then 11 more per 128; beyond 64 only where the vocabulary's logits have room for the slices;
-    64 where no matrix has more than 2^19 elements, d x d among them.  Under stochastic rounding 64 for every width."""
+    """16 tokens up to d_model 1536, then 11 more per 128, 16 more for no multiple of 128; beyond 64 only where the vocabulary's logits
+    have room for the slices; 64 where a matrix has at most 2^19 elements, d x d or d x ffn.  Under stochastic rounding 64."""
     b = _b()
     cfg = si.tiny_config(n_layers=1, d_model=d, n_heads=d // 64, d_ffn=f, vocab=vocab, max_pos=130)
     P = si.make_weights(cfg, seed=1)
