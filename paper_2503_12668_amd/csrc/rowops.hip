@@ -607,7 +607,8 @@ __global__ __launch_bounds__(32 * kGroups) void ce_combine_kernel(const float* _
     // the 788 spans of a 50272-word vocabulary (a block is bound by the latency of that walk: with 8 groups, which stay where
     // the order of the sums is kept, 31 us at 8192 rows and as much at 1026).  Two sweeps (max, then sum) keep the loads
     // independent of each other.
-    constexpr int kRows = 32;
+    // (eight loads under way at 8 groups: 55 us at 4096 rows instead of 32)
+    constexpr int kRows = 32, kUnroll = kGroups == 8 ? 4 : 8;
     __shared__ float sh_m[kGroups][kRows];
     __shared__ double sh_s[kGroups][kRows];
     const int lr = threadIdx.x & (kRows - 1), grp = threadIdx.x / kRows;
@@ -616,11 +617,11 @@ __global__ __launch_bounds__(32 * kGroups) void ce_combine_kernel(const float* _
     const float* pm = part_max + rc;
     const float* ps = part_sum + rc;
     float m = -INFINITY;
-#pragma unroll 8
+#pragma unroll kUnroll
     for (int i = grp; i < n_parts; i += kGroups) m = fmaxf(m, pm[(size_t)i * part_ld]);
     double s = 0.0;
     if (m != -INFINITY) {
-#pragma unroll 8
+#pragma unroll kUnroll
         for (int i = grp; i < n_parts; i += kGroups) {
             const float mi = pm[(size_t)i * part_ld];
             s += (double)(ps[(size_t)i * part_ld] * expf(mi - m));     // a span past the last column has sum 0 and exp(-inf) = 0
