@@ -540,6 +540,16 @@ zo2_status gemm_launch_f32_splitk(const GemmArgs& a, int splits, void* workspace
 // d 2048, 185 rows: QKV 30.7 -> 26.1, output 20.9 -> 14.7 (64-row tiles), FC1 30.9 -> 25.9, FC2 38.6 -> 30.8 (4 pieces); 256 rows: 31.2 ->
 // 25.7, 22.3 -> 14.7, 34.6 -> 27.4, 40.9 -> 33.4; 512 rows: output 27.4 -> 16.2, but QKV 34.4 against 46.8 (two rounds) and FC2 45.8 against
 // 49.7; 1024 rows: output 33.1 -> 26.4; 2048: 36.4 against 51.8.  The model picks the faster one in all of these.
+// Where the large kernel cannot run (K a multiple of 64 but not of 128) the other choice is the general one: two workgroups per compute
+// unit, so twice the tiles per round, and 0.8 PFLOP/s once rounds are full (this kernel 0.7).  Its launch: 5.6 us and 0.9 us a slab with
+// up to one tile per compute unit, beyond that 3 us and per round of 512 tiles 3.8 us and 1.25 a slab; several rounds of this kernel are
+// told apart with 4.5 us a round (3 with 64 rows) and correspondingly less a slab.  General -> this kernel (us): K 832, N 832: 512 rows 16.6 ->
+// 8.1, 4096 21.6 -> 15.2, 8192 25.9 against 27.8; K 704, N 2816: 1024 16.5 -> 11.8, 4096 36.6 against 38.0, 7504 57.9 against 70.7; K 1728, N
+// 6080: 512 29.7 -> 20.5, 2048 66.9 -> 61.7, 8192 225 against 247.  The choice is the faster one or within 4 % of it in 90 launches.
+static double general_ns(double tiles, double slabs) {
+    const double cu = (double)device_cu_count();
+    return tiles <= cu ? 5600.0 + 900.0 * slabs : 3000.0 + ceil(tiles / (2.0 * cu)) * (3800.0 + 1250.0 * slabs);
+}
 GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes) {
     GemmChoice best = {0, gemm_pick_splits(a.M, a.N, a.K, a.nprob, dtype)};
     if (gemm_splitk_workspace_bytes(a.M, a.N, a.nprob, best.splits) > workspace_bytes) best.splits = 1;
@@ -549,9 +559,10 @@ GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes) {
     // costs, large -> this kernel: launches of 100 - 1024 rows 8 - 19 -> 5 - 14 us; steps of d 256, ffn 2048, 8 blocks: 100 tokens 660 -> 530
     // us, 400 695 -> 622; d 512, ffn 1024, 12 blocks: 100 1063 -> 806, 1024 1395 -> 1202.
     if (a.large_only || gemm256_is_forced() || !gemm_mid_applicable(a, dtype) || (int64_t)a.N * a.K <= 1 << 19) return best;
-    double best_ns = 1e30;                 // where the large kernel cannot run, this one replaces the general one
-    if (gemm256_applicable(a, dtype)) best_ns = 0.85 * large_tile_ns(a.M, a.N, a.K, a.nprob, best.splits) + (best.splits > 1 ? 4000.0 : 0.0);
     const double cu = (double)device_cu_count(), tn = (double)((a.N + 127) / 128);
+    const bool large = gemm256_applicable(a, dtype);
+    double best_ns = large ? 0.85 * large_tile_ns(a.M, a.N, a.K, a.nprob, best.splits) + (best.splits > 1 ? 4000.0 : 0.0)
+                           : general_ns(a.nprob * tn * (double)((a.M + 127) / 128), (double)(a.K / 64));
     for (int rows = 128; rows >= 64; rows -= 64)
         for (int s = 1; s <= 8; ++s) {
             const int kp = ((a.K + s - 1) / s + 63) / 64 * 64;
@@ -559,7 +570,9 @@ GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes) {
             if (s > 1 && (kp < 256 || (a.K + kp - 1) / kp != s || bytes > workspace_bytes)) continue;
             const double tiles = (double)a.nprob * s * tn * (double)((a.M + rows - 1) / rows), rounds = ceil(tiles / cu);
             if (tiles >= (double)(1 << 22)) continue;              // the grid's limit
-            double ns = 3000.0 + rounds * (kp / 64) * (rows == 128 ? 500.0 + 250.0 * tiles / (rounds * cu) : 300.0 + 120.0 * tiles / (rounds * cu));
+            const double fill = tiles / (rounds * cu);
+            double ns = 3000.0 + rounds * (kp / 64) * (rows == 128 ? 500.0 + 250.0 * fill : 300.0 + 120.0 * fill);
+            if (!large && rounds > 1.0) ns = 3000.0 + rounds * (rows == 128 ? 4500.0 + (kp / 64) * (400.0 + 250.0 * fill) : 3000.0 + (kp / 64) * (240.0 + 120.0 * fill));
             if (s > 1) ns += 4000.0 + 2.0 * (double)bytes / 4.0e3;
             if (ns < 0.95 * best_ns) { best = {rows, s}; best_ns = ns; }
         }
