@@ -203,17 +203,17 @@ def offload_leg(steps=3, budget_legs=True):
 
 def small_steps_leg(ctx, cfg, steps=10):
     """Steps of few tokens on the benchmark's resident context: the perturbation written by the sweep kernel (as in the
-    benchmark step) against generated in the projections' weight loader (what the library does by default up to 64
-    tokens per stream).  ms per step, wall clock around `steps` steps each."""
+    benchmark step) against generated in the projections' weight loader (what the library does by default up to 60
+    tokens per stream at this width).  ms per step, wall clock around `steps` steps each."""
     import torch
 
     import synth_inputs as si
-    out = {"note": "same resident bf16 context; 'sweep_copies' = zo2_set_loader_fusion(-1), 'loader' = the default", "steps": steps}
+    out = {"note": "same resident bf16 context; 'sweep_copies' = zo2_set_loader_fusion(-1), 'loader' = zo2_set_loader_fusion(1)", "steps": steps}
     for (b, s_) in ((1, 16), (1, 64)):
         tok = si.make_tokens(cfg["vocab"], b, s_, seed=2, dist="zipf")
         lab = si.next_token_labels(tok)
         row = {}
-        for name, mode in (("sweep_copies", -1), ("loader", 0)):
+        for name, mode in (("sweep_copies", -1), ("loader", 1)):
             ctx.set_loader_fusion(mode)
             for j in range(2):
                 ctx.step(tok, lab, SEED0 + 500 + j, EPS, LR)
