@@ -100,7 +100,7 @@ def test_per_group_scratch_streamed_equals_whole_block_resident_bitwise(wire, co
     assert all(np.isfinite(x) for x in runs["whole_resident"][0][-1:])
 
 
-@pytest.mark.parametrize("d,heads,vocab", [(512, 8, 4096), (768, 12, 6148), (5248, 41, 15748)])
+@pytest.mark.parametrize("d,heads,vocab", [(512, 8, 4096), (768, 12, 6148), (4352, 34, 13060), (5248, 41, 15748)])
 def test_float32_projections_in_pieces_give_the_same_bits_under_every_organisation(d, heads, vocab):
     """Widths at which the output projection is cut along k (its pieces then end in the LayerNorm's pass where no sweep comes
     between): losses and parameters of eight steps under 1, 2 and 4 sweeps per block, bit for bit; without pieces they differ."""
