@@ -52,7 +52,9 @@ zo2_status gemm_launch_256(const GemmArgs& a, int dtype, hipStream_t st);
 int gemm_pick_splits(int M, int N, int K, int nprob, int dtype);
 size_t gemm_splitk_workspace_bytes(int M, int N, int nprob, int splits);
 zo2_status gemm_launch_splitk(const GemmArgs& a, int dtype, int splits, void* workspace, size_t workspace_bytes, hipStream_t st);
-// The same for float32: any number of pieces that the workspace holds.
+// float32 (gemm_f32.hip): tiles of `rows` = 32, 64 or 128 rows; splits > 1: a.kpiece k per piece, Y = partial sums, a plane per piece
+zo2_status gemm_launch_f32(const GemmArgs& a, int splits, int rows, hipStream_t st);
+// Split-k for float32: any number of pieces that the workspace holds.
 int gemm_f32_pick_splits(int M, int N, int K, int nprob, size_t workspace_bytes);
 // sum = false: the pieces stay in the workspace ([problem][piece][M][N]), the caller adds them and finishes the values.
 zo2_status gemm_launch_f32_splitk(const GemmArgs& a, int splits, void* workspace, size_t workspace_bytes, hipStream_t st, bool sum = true);

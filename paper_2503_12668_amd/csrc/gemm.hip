@@ -5,7 +5,7 @@
 // 8 consecutive k of row l % 32.  So tiles go global -> LDS -> registers as 16-byte chunks
 // with no transposition; an XOR swizzle of the chunk index keeps the 128-bit LDS accesses
 // conflict free.  bf16 / fp16 inputs use v_mfma_f32_32x32x16 (float32 accumulate); the
-// float32 mode uses v_mfma_f32_32x32x2_f32 (gemm_f32_mfma_kernel).
+// float32 mode is in gemm_f32.hip.
 //
 // The +/- streams (and q, k, v) are independent problems of one shape: they share a launch
 // through grid.z so that even the narrow projections fill 256 compute units.
@@ -156,173 +156,6 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(const GemmArgs a) {
     }
 }
 
-// ---------------------------------------------------------------------------------------
-// float32 kernel on the matrix cores: v_mfma_f32_32x32x2_f32 (true float32 products, float32 accumulate).
-// Block tile BM x 128 x 32, four wavefronts (128 rows: in a 2 x 2 grid, each owning 64 x 64 = 2 x 2 MFMA tiles); two or
-// more workgroups per compute unit.  LDS layout as in the 16-bit kernel: rows of 8 chunks of 16 bytes (4 floats), chunk
-// index XOR-swizzled by (row & 7).
-//
-// The instruction contracts two k per issue: lanes 0..31 supply k = 0, lanes 32..63 k = 1 of a row.  A dot product does
-// not care in which order its k are visited, as long as both operands visit them in the same order; so a lane of half
-// h reads one chunk - the four consecutive k = 8 g + 4 h .. + 3 of its row - with a single 128-bit LDS read, and issue t
-// of group g contracts k = 8 g + t (lower half) with k = 8 g + 4 + t (upper half).  One LDS read per operand tile feeds
-// four MFMAs.  The weight tile is the instruction's first operand, which leaves a lane with one output row m and runs
-// of four consecutive columns n: 16-byte stores.
-// Tile height BM (128, 64 or 32 rows; 2 x 2, 2 x 2 and 1 x 4 wavefronts): the MFMA takes 64 cycles here, so a narrower tile's
-// extra LDS reads (1.5 for 1 at 64 rows) still fit under it, and what a launch loses is rows past M and a badly filled last
-// round: see f32_pick.  blockIdx.y is the piece of the k range (GemmArgs::ksplit).
-// Workgroup ids go round robin over the 8 XCDs; each XCD takes a contiguous run of tiles, rows fastest, so that the row tiles
-// of one column panel of W are read through one L2 (the LM head of 768 rows per stream read its 412 MB once per row tile
-// before).
-// ---------------------------------------------------------------------------------------
-template <int BM, bool KTAIL>      // KTAIL: K is not a multiple of 32, the last slab is zero-filled past the end of the rows
-__global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(const GemmArgs a) {
-    constexpr int BN = 128, BK = 32, KC = BK / 4;                 // 8 chunks of 4 floats per row
-    constexpr int WGM = BM == 32 ? 1 : 2, WGN = 4 / WGM;
-    constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
-    constexpr int CA = BM * KC / 256, CB = BN * KC / 256;         // chunks each thread stages per tile
-    __shared__ v4f_t lds[2][(BM + BN) * KC];
-
-    const GemmProblem p = a.p[blockIdx.z];
-    const int tiles_m = (a.M + BM - 1) / BM;
-    const int nblk = (int)gridDim.x, xcd = (int)(blockIdx.x & 7), in_xcd = (int)(blockIdx.x >> 3);
-    const int tile = xcd * (nblk >> 3) + min(xcd, nblk & 7) + in_xcd;         // XCD x owns nblk / 8 tiles, the first nblk % 8 one more
-    const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
-    const int k_first = (int)blockIdx.y * a.kpiece, K = min(a.K - k_first, a.kpiece);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN, r = lane & 31, kh = lane >> 5;
-    const float* __restrict__ X = reinterpret_cast<const float*>(p.X) + k_first;
-    const float* __restrict__ W = reinterpret_cast<const float*>(p.W) + k_first;
-
-    const float* ga[CA];
-    const float* gb[CB];
-    int la[CA], lb[CB], kca[CA], kcb[CB];
-#pragma unroll
-    for (int i = 0; i < CA; ++i) {
-        const int c = tid + 256 * i, row = c >> 3, kc = c & 7;
-        ga[i] = X + (size_t)min(m0 + row, a.M - 1) * a.ldx + kc * 4;
-        la[i] = row * KC + (kc ^ (row & 7));
-        kca[i] = kc * 4;
-    }
-#pragma unroll
-    for (int i = 0; i < CB; ++i) {
-        const int c = tid + 256 * i, row = c >> 3, kc = c & 7;
-        gb[i] = W + (size_t)min(n0 + row, a.N - 1) * a.ldw + kc * 4;
-        lb[i] = BM * KC + row * KC + (kc ^ (row & 7));
-        kcb[i] = kc * 4;
-    }
-
-    f32x16_t acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    v4f_t ra[CA], rb[CB];
-    const v4f_t zero4 = v4f_t{0.f, 0.f, 0.f, 0.f};
-    auto load_tile = [&](int k0) {        // K is a multiple of 4: a chunk is inside the row or entirely past its end
-#pragma unroll
-        for (int i = 0; i < CA; ++i) ra[i] = (!KTAIL || k0 + kca[i] < K) ? *reinterpret_cast<const v4f_t*>(ga[i] + k0) : zero4;
-#pragma unroll
-        for (int i = 0; i < CB; ++i) rb[i] = (!KTAIL || k0 + kcb[i] < K) ? *reinterpret_cast<const v4f_t*>(gb[i] + k0) : zero4;
-    };
-    auto store_tile = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < CA; ++i) lds[buf][la[i]] = ra[i];
-#pragma unroll
-        for (int i = 0; i < CB; ++i) lds[buf][lb[i]] = rb[i];
-    };
-
-    const int nk = (K + BK - 1) / BK;
-    load_tile(0);
-    store_tile(0);
-    if (nk > 1) load_tile(BK);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-#pragma unroll
-        for (int g = 0; g < BK / 8; ++g) {
-            // the other buffer is free for the whole slab (its last readers passed the barrier that ended the previous
-            // one): the next slab is parked there half-way through, not at the end, where every wavefront would arrive
-            // at the barrier behind a burst of LDS stores; the registers it leaves are reloaded at once with the slab
-            // after it, which then has a whole slab's time (4096 cycles of MFMA) to arrive
-            if (g == BK / 16 && kt + 1 < nk) {
-                store_tile(cur ^ 1);
-                if (kt + 2 < nk) load_tile((kt + 2) * BK);
-            }
-            const int kc = 2 * g + kh;
-            v4f_t fx[TM], fw[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int row = wm * WM + i * 32 + r;
-                fx[i] = lds[cur][row * KC + (kc ^ (row & 7))];
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int row = wn * WN + j * 32 + r;
-                fw[j] = lds[cur][BM * KC + row * KC + (kc ^ (row & 7))];
-            }
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[j][t], fx[i][t], acc[i][j], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-
-    // epilogue: in MFMA tile (i, j) a lane holds output row m = r (the second operand's row) and the columns
-    // n = 8 (v / 4) + 4 kh + v % 4 (the first operand's rows): four runs of four consecutive columns
-    const float* __restrict__ bias = reinterpret_cast<const float*>(p.bias);
-    float* __restrict__ Y = reinterpret_cast<float*>(p.Y);
-    if (gridDim.y > 1) Y += (size_t)blockIdx.y * a.M * a.N;       // this piece's partial sums (no bias, scale 1: see gemm_launch_splitk)
-    const bool vec_ok = (a.N % 4 == 0) && (a.ldy % 4 == 0) && (((uintptr_t)Y & 15) == 0) &&
-                        (!p.residual || ((uintptr_t)p.residual & 15) == 0) && (!bias || ((uintptr_t)bias & 15) == 0);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int m = m0 + wm * WM + i * 32 + r;
-        if (m >= a.M) continue;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = n0 + wn * WN + j * 32 + 8 * q + 4 * kh;
-                if (n >= a.N) continue;
-                const size_t o = (size_t)m * a.ldy + n;
-                float y[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) y[e] = acc[i][j][4 * q + e];
-                if (vec_ok) {                      // N % 4 == 0: the run of four is inside the row or entirely past its end
-                    const v4f_t b4 = bias ? *reinterpret_cast<const v4f_t*>(bias + n) : zero4;
-                    const float bb[4] = {b4.x, b4.y, b4.z, b4.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        y[e] = (y[e] + bb[e]) * p.out_scale;
-                        if (a.relu) y[e] = fmaxf(y[e], 0.f);
-                    }
-                    if (p.residual) {
-                        const v4f_t r4 = *reinterpret_cast<const v4f_t*>(p.residual + o);
-                        y[0] += r4.x; y[1] += r4.y; y[2] += r4.z; y[3] += r4.w;
-                    }
-                    *reinterpret_cast<v4f_t*>(Y + o) = v4f_t{y[0], y[1], y[2], y[3]};
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (n + e >= a.N) continue;
-                        float v = (y[e] + (bias ? bias[n + e] : 0.f)) * p.out_scale;
-                        if (a.relu) v = fmaxf(v, 0.f);
-                        if (p.residual) v += p.residual[o + e];
-                        Y[o + e] = v;
-                    }
-                }
-            }
-        }
-    }
-}
-
 template <typename T>
 static zo2_status launch_mfma(const GemmArgs& a, hipStream_t st) {
     constexpr int BM = 128, BN = 128;
@@ -334,46 +167,31 @@ static zo2_status launch_mfma(const GemmArgs& a, hipStream_t st) {
     return ZO2_OK;
 }
 
-// Tile height and k pieces of a float32 launch, by a small cost model.  A compute unit works through its share of the tiles at
-// about 0.52 TFLOP/s (133 TFLOP/s over 256): 2 x 128 x BM flops per k, a lower tile at a slightly lower rate; a launch costs
-// 2.5 us more for the latency of its first loads and last stores, a tile 16 k; pieces add the write and the re-read of their partial sums and a second launch (4 us).
-// Measured, 128-row tiles without pieces against the choice made here, second launch included: 2 x 64 rows, d 768 / ffn 3072:
-// QKV 60 -> 10 + 4 us (3 pieces of 32-row tiles), FC1 60 -> 15 + 4 (2), attention output 62 -> 7 + 4 (6), FC2 222 -> 13 + 4 (10), LM
-// head 220 -> 117 (64-row tiles); 2 x 768 rows, d 2048 / ffn 8192: QKV 430 -> 342 (64-row tiles), output 153 -> 109 + 16,
-// FC2 589 -> 405 + 16 (4), LM head 2685 -> 2468 (the order of the tiles).
+// Tile height and k pieces of a float32 launch, by a small cost model in ns: what the kernels of gemm_f32.hip were measured at.  All of
+// them run two workgroups per compute unit, so per slab of 32 k a round of two tiles a unit costs 2860 (128 rows), 1800 (64) or 1050 (32),
+// a launch or last round of one tile a unit 1120, 780 - 950 (nearly empty chip - full one) or 520 - 740, the launch itself 5300.  Pieces add
+// the write and the re-read of their partial sums at 4 TB/s and a second launch (4 us).
 struct F32Pick { int rows, splits; };
 static F32Pick f32_pick(int M, int N, int K, int nprob, int max_splits) {
     const double cu = (double)device_cu_count();
     const double tn = (double)((N + 127) / 128);
     F32Pick best = {128, 1};
     double best_ns = 1e30;
-    for (int rows = 128; rows >= 32; rows /= 2) {
-        const double tiles = nprob * tn * (double)((M + rows - 1) / rows);
-        const double ns_per_k = 256.0 * rows / 520.0 * (rows == 128 ? 1.0 : rows == 64 ? 1.05 : 1.2);
+    for (int rows = 128; rows >= (K % 32 ? 128 : 32); rows /= 2) {         // the lower tiles take whole slabs of 32 k
         for (int s = 1; s <= max_splits; ++s) {
             const int kp = ((K + s - 1) / s + 31) / 32 * 32;
             if (s > 1 && (kp < 64 || (K + kp - 1) / kp != s)) continue;
-            double ns = 2500.0 + ceil(tiles * s / cu) * (kp + 16.0) * ns_per_k;
+            const double tiles = nprob * s * tn * (double)((M + rows - 1) / rows);
+            const double full = floor(tiles / (2.0 * cu)), rest = tiles - full * 2.0 * cu, fill = rest / cu;
+            const double two = rows == 128 ? 2860.0 : rows == 64 ? 1800.0 : 1050.0;
+            const double one = rows == 128 ? 1120.0 : rows == 64 ? 780.0 + 170.0 * fill : 520.0 + 220.0 * fill;
+            const double slab = two * full + (fill > 1.0 ? two : fill > 0.0 ? one : 0.0);
+            double ns = 5300.0 + kp / 32.0 * slab;
             if (s > 1) ns += 4000.0 + (double)nprob * s * (double)M * (double)N * 8.0 / 4.0e3;
             if (ns < 0.97 * best_ns) { best = {rows, s}; best_ns = ns; }
         }
     }
     return best;
-}
-
-static zo2_status launch_f32(const GemmArgs& a, int splits, int rows, hipStream_t st) {
-    const unsigned tiles = (unsigned)(((a.M + rows - 1) / rows) * ((a.N + 127) / 128));
-    const dim3 grid(tiles, splits, a.nprob), block(256);
-    const bool tail = a.K % 32 != 0;       // pieces are multiples of 32: only the last one can end inside a slab
-#define ZO2_F32_CASE(R)                                                                     \
-    if (rows == R) {                                                                        \
-        if (tail) hipLaunchKernelGGL((gemm_f32_mfma_kernel<R, true>), grid, block, 0, st, a); \
-        else hipLaunchKernelGGL((gemm_f32_mfma_kernel<R, false>), grid, block, 0, st, a);   \
-    }
-    ZO2_F32_CASE(128) ZO2_F32_CASE(64) ZO2_F32_CASE(32)
-#undef ZO2_F32_CASE
-    ZO2_HIP_LAUNCH_CHECK();
-    return ZO2_OK;
 }
 
 // the large-tile kernel, or the general one for the shapes it does not take
@@ -411,7 +229,7 @@ zo2_status gemm_launch(const GemmArgs& a, int dtype, hipStream_t st) {
         ZO2_OP_CHECK(a.out_f32, ZO2_EINVAL, "gemm: the float32 kernel writes float32 output");
         GemmArgs f = a;
         f.kpiece = a.K;
-        return launch_f32(f, 1, f32_pick(a.M, a.N, a.K, a.nprob, 1).rows, st);
+        return gemm_launch_f32(f, 1, f32_pick(a.M, a.N, a.K, a.nprob, 1).rows, st);
     }
     const GemmChoice k = gemm_choose(a, dtype, 0);
     if (!k.rows) return launch_large(a, dtype, st);
@@ -525,7 +343,7 @@ zo2_status gemm_launch_f32_splitk(const GemmArgs& a, int splits, void* workspace
         e.p[i].bias = nullptr; e.p[i].residual = nullptr; e.p[i].out_scale = 1.0f;
         e.p[i].Y = part + (size_t)i * splits * plane;
     }
-    zo2_status s = launch_f32(e, splits, f32_pick(a.M, a.N, e.kpiece, a.nprob * splits, 1).rows, st);
+    zo2_status s = gemm_launch_f32(e, splits, f32_pick(a.M, a.N, e.kpiece, a.nprob * splits, 1).rows, st);
     if (s != ZO2_OK || !sum) return s;
     launch_splitk_reduce<float>(a, part, splits, st);
     ZO2_HIP_LAUNCH_CHECK();
