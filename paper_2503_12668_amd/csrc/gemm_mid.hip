@@ -1,10 +1,12 @@
 // 16-bit projections with a few hundred rows per stream: 128 x 128 x 64 (or 64 x 128 x 64) block tiles, eight wavefronts,
 // a ring of LDS stages filled by direct-to-LDS loads.
 //
-// With so few rows a launch is a handful of k-slabs per compute unit, bound by the time its loads take to come back and by
-// its first and last microseconds, not by the matrix cores: the large tiles of gemm256.hip have too few tiles (or pieces of
-// k whose partial sums are written and read back) and one or two slabs under way.  Here the tile is small enough that the
-// launch fills the chip with little or no splitting, and a ring of five slabs keeps four of them under way.  A wavefront owns
+// With so few rows a launch is a handful of k-slabs per compute unit, bound by the bytes a compute unit can have under way
+// (about 64 KB, whatever the ring's depth: weights from HBM and activations from L2 alike, 46 - 50 GB/s a unit) and by its
+// first and last microseconds, not by the matrix cores: the large tiles of gemm256.hip have too few tiles (or pieces of
+// k whose partial sums are written and read back).  Here the tile is small enough that the launch fills the chip with little
+// or no splitting, and a ring of four slabs keeps three of them under way (five and six are no faster, three cost 10 % on
+// weights from HBM).  A wavefront owns
 // 64 x 64 of the tile (32 x 64 of the lower one) for one half of each slab's k - two wavefronts per SIMD, no more LDS reads
 // than four would make - and the two halves' sums meet in LDS at the end.
 //
@@ -35,12 +37,18 @@ template <> struct MidMfma<f16_t> {
 static constexpr int kMidBN = 128, kMidBK = 64;
 template <int BM> struct MidTile {
     static constexpr int kStage = (BM + kMidBN) * kMidBK * 2;      // 32 KB / 24 KB
-    static constexpr int kStages = BM == 128 ? 5 : 6;
+    static constexpr int kStages = 4;        
     static constexpr int kLds = kStage * kStages;                  // 160 KB / 144 KB
 };
 
-__device__ __forceinline__ void mid_load_to_lds(const void* gptr, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory");
+// source address = wave-uniform base + per-lane 32-bit byte offset
+__device__ __forceinline__ void mid_load_to_lds(const void* sbase, uint32_t voff, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_base), "v"(voff), "s"(sbase) : "memory");
+}
+__device__ __forceinline__ const char* mid_uniform(const void* p) {      // a wave-uniform pointer into scalar registers
+    const uint64_t v = (uint64_t)(uintptr_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (const char*)(uintptr_t)(((uint64_t)hi << 32) | lo);
 }
 
 // All loads of this wavefront but those of the `ahead` youngest slabs (LPW loads each) have landed.
@@ -79,25 +87,29 @@ __global__ __launch_bounds__(512, 2) void gemm_mid_kernel(const GemmArgs a, int 
 
     // this lane's sources: load t of the wavefront brings 8 rows (lane -> row lane / 8, position lane % 8); rows past the end of
     // a matrix repeat its last one, their products are never stored
-    const T* gx[XL];
-    const T* gw[WL];
+    const char* base_x = mid_uniform(reinterpret_cast<const T*>(p.X) + (size_t)m0 * a.ldx + k_first);
+    const char* base_w = mid_uniform(reinterpret_cast<const T*>(p.W) + (size_t)n0 * a.ldw + k_first);
+    uint32_t gx[XL], gw[WL];
     const int lrow = lane >> 3;
 #pragma unroll
     for (int t = 0; t < XL; ++t) {
         const int row = (wave * XL + t) * 8 + lrow;
-        gx[t] = reinterpret_cast<const T*>(p.X) + (size_t)min(m0 + row, a.M - 1) * a.ldx + k_first + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+        gx[t] = (uint32_t)(min(row, a.M - 1 - m0) * a.ldx + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2u;
     }
 #pragma unroll
     for (int t = 0; t < WL; ++t) {
         const int row = (wave * WL + t) * 8 + lrow;
-        gw[t] = reinterpret_cast<const T*>(p.W) + (size_t)min(n0 + row, a.N - 1) * a.ldw + k_first + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+        gw[t] = (uint32_t)(min(row, a.N - 1 - n0) * a.ldw + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2u;
     }
-    auto issue = [&](int kt, int stage) {
+    auto issue_one = [&](int t, int kt, int stage) {               // load t of slab kt: weights first
         const uint32_t at = lds0 + (uint32_t)stage * STAGE;
+        const size_t k = (size_t)kt * (kMidBK * 2);
+        if (t < WL) mid_load_to_lds(base_w + k, gw[t < WL ? t : 0], at + BM * 128 + (wave * WL + t) * 1024);
+        else mid_load_to_lds(base_x + k, gx[t < WL ? 0 : t - WL], at + (wave * XL + t - WL) * 1024);
+    };
+    auto issue = [&](int kt, int stage) {
 #pragma unroll
-        for (int t = 0; t < WL; ++t) mid_load_to_lds(gw[t] + kt * kMidBK, at + BM * 128 + (wave * WL + t) * 1024);
-#pragma unroll
-        for (int t = 0; t < XL; ++t) mid_load_to_lds(gx[t] + kt * kMidBK, at + (wave * XL + t) * 1024);
+        for (int t = 0; t < LPW; ++t) issue_one(t, kt, stage);
     };
 
     f32x16_t acc[TM][TN];
@@ -128,19 +140,37 @@ __global__ __launch_bounds__(512, 2) void gemm_mid_kernel(const GemmArgs a, int 
         }
     };
     int stage = 0;
+    // The wavefront's loads and LDS reads are dealt out between its MFMAs, which run on while it issues them.  (All loads ahead of the
+    // MFMAs, the wavefronts queued for the one address unit behind the barrier with the matrix cores idle: a slab took the sum
+    // of the time of its loads and of its MFMAs, 0.29 + 0.29 us, not the larger.  185 rows, weights in cache: N 2048, K 8192, two
+    // problems 69.6 -> 49.3 us, N 2048, K 2048, six 25.2 -> 20.2, N 8192, K 2048, two 27.1 -> 22.5; from HBM 70.8 -> 58.4, 27.1 -> 24.9, 30.3 -> 27.9.)
     auto step = [&](int kt, const Frag& cur, Frag& next) {
         mid_wait<LPW, NST - 2>(max(0, min(NST - 2, nk - 2 - kt)));      // slab kt + 1 has landed
         __syncthreads();
-        if (kt + NST < nk) issue(kt + NST, stage);
+        const int refill = stage;
+        const bool more = kt + NST < nk;
         stage = stage == NST - 1 ? 0 : stage + 1;
-        read(next, stage);                 // (past the last slab: bytes nobody uses)
+        const char* xs = smem + stage * STAGE + xrow * 128;             // (past the last slab: bytes nobody uses)
+        const char* ws = smem + stage * STAGE + BM * 128 + wrow * 128;
         // weights first: a lane ends with one row of the output and runs of four consecutive columns
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+        for (int u = 0; u < 2 * TM * TN; ++u) {
+            const int ks = u / (TM * TN), i = u / TN % TM, j = u % TN;
+            acc[i][j] = MidMfma<T>::run(cur.w[ks][j], cur.x[ks][i], acc[i][j]);
+            __builtin_amdgcn_sched_barrier(0);
+            // the next slab's fragments: TM + TN per k-step, under the first half of the MFMAs
+            constexpr int FR = 2 * (TM + TN), RPM = (FR + TM * TN - 1) / (TM * TN);
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = MidMfma<T>::run(cur.w[ks][j], cur.x[ks][i], acc[i][j]);
+            for (int q = u * RPM; q < (u + 1) * RPM; ++q)
+                if (q < FR) {
+                    const int kq = q / (TM + TN), e = q % (TM + TN);
+                    if (e < TN) next.w[kq][e < TN ? e : 0] = *reinterpret_cast<const v4u_t*>(ws + e * 4096 + off[kq]);
+                    else next.x[kq][e < TN ? 0 : e - TN] = *reinterpret_cast<const v4u_t*>(xs + (e - TN) * 4096 + off[kq]);
+                }
+            // the retired stage's refill: load t behind MFMA 2 t (128 rows) or t
+            if (more && u * LPW % (2 * TM * TN) < LPW) issue_one(u * LPW / (2 * TM * TN), kt + NST, refill);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
 #pragma unroll
     for (int s = 0; s < NST; ++s)
@@ -238,6 +268,7 @@ static zo2_status mid_launch_t(const GemmArgs& a, int splits, hipStream_t st) {
 
 bool gemm_mid_applicable(const GemmArgs& a, int dtype) {
     if ((dtype != ZO2_BF16 && dtype != ZO2_F16) || a.ce_mode || a.M < 1 || a.K % kMidBK != 0 || a.N % 4 != 0 || a.ldy % 4 != 0) return false;
+    if (a.ldx >= 1 << 22 || a.ldw >= 1 << 22) return false;        // a lane's offset from its tile's first row is 32 bits
     const size_t osz = a.out_f32 ? 4 : 2;
     for (int i = 0; i < a.nprob; ++i) {
         if (((uintptr_t)a.p[i].Y & (4 * osz - 1)) != 0 || ((uintptr_t)a.p[i].bias & 7) != 0 || ((uintptr_t)a.p[i].residual & 15) != 0) return false;
