@@ -350,14 +350,12 @@ zo2_status gemm_launch_f32_splitk(const GemmArgs& a, int splits, void* workspace
     return ZO2_OK;
 }
 
-// Kernel, tile height and pieces of a block projection.  The 128 x 128 kernel's launch: 3 us, and per round of tiles and slab
-// 0.5 us (128 rows) or 0.3 us (64) when the chip is nearly empty, half as much again when every compute unit has a tile (a
-// 128 x 128 tile moves twice the bytes per product of a 256 x 256 one, and two rounds of it are slower than one of those);
-// pieces add their partial sums at 4 TB/s and 4 us for the second launch.  The large kernel's model above is 0.85 of the
-// truth for single rounds, with the same 4 us.  Measured, cold weights, second launch included, large -> this kernel (us):
-// d 2048, 185 rows: QKV 30.7 -> 26.1, output 20.9 -> 14.7 (64-row tiles), FC1 30.9 -> 25.9, FC2 38.6 -> 30.8 (4 pieces); 256 rows: 31.2 ->
-// 25.7, 22.3 -> 14.7, 34.6 -> 27.4, 40.9 -> 33.4; 512 rows: output 27.4 -> 16.2, but QKV 34.4 against 46.8 (two rounds) and FC2 45.8 against
-// 49.7; 1024 rows: output 33.1 -> 26.4; 2048: 36.4 against 51.8.  The model picks the faster one in all of these.
+// Kernel, tile height and pieces of a block projection.  The 128 x 128 kernel's launch: 3.5 us, and per round of tiles and slab
+// 0.44 us (128 rows) or 0.28 us (64) when the chip is nearly empty, two fifths or a third more when every compute unit has a tile;
+// pieces add their partial sums at 4 TB/s and 4 us for the second launch.  The large kernel's launch: 3 us, and per round 4 us and
+// 25.5 ns a k for 256-row tiles.  Measured inside steps, second launch included, large -> this kernel (us):
+// d 2048, 185 rows: QKV 30.7 -> 20.5, output 20.9 -> 14.1 (64-row tiles), FC1 30.9 -> 22.2, FC2 38.6 -> 26.2 (2 pieces); 512 rows:
+// output 27.4 -> 16.2, but FC1 37.2 against 44.5 (two rounds).
 // Where the large kernel cannot run (K a multiple of 64 but not of 128) the other choice is the general one: two workgroups per compute
 // unit, so twice the tiles per round, and 0.8 PFLOP/s once rounds are full (this kernel 0.7).  Its launch: 5.6 us and 0.9 us a slab with
 // up to one tile per compute unit, beyond that 3 us and per round of 512 tiles 3.8 us and 1.25 a slab; several rounds of this kernel are
@@ -379,8 +377,21 @@ GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes) {
     if (a.large_only || gemm256_is_forced() || !gemm_mid_applicable(a, dtype) || (int64_t)a.N * a.K <= 1 << 19) return best;
     const double cu = (double)device_cu_count(), tn = (double)((a.N + 127) / 128);
     const bool large = gemm256_applicable(a, dtype);
-    double best_ns = large ? 0.85 * large_tile_ns(a.M, a.N, a.K, a.nprob, best.splits) + (best.splits > 1 ? 4000.0 : 0.0)
-                           : general_ns(a.nprob * tn * (double)((a.M + 127) / 128), (double)(a.K / 64));
+    double best_ns = general_ns(a.nprob * tn * (double)((a.M + 127) / 128), (double)(a.K / 64));
+    if (large) {
+        best_ns = 1e30;
+        for (int s = 1; s <= 4; s *= 2) {
+            const size_t bytes = gemm_splitk_workspace_bytes(a.M, a.N, a.nprob, s);
+            if (s > 1 && (a.K % (s * 128) != 0 || a.K / s < 512 || a.nprob * s > GemmArgs::kMaxProblems || bytes > workspace_bytes)) break;
+            double ns = 1e30;
+            for (int rows = 128; rows <= 256; rows += 64) {
+                const double tiles = (double)a.nprob * s * (double)((a.N + 255) / 256) * (double)((a.M + rows - 1) / rows);
+                ns = fmin(ns, 3000.0 + ceil(tiles / cu) * gemm256_tile_cost(rows) * (25.5 * a.K / s + 4000.0));
+            }
+            if (s > 1) ns += 4000.0 + 2.0 * (double)bytes / 4.0e3;
+            if (ns < 0.97 * best_ns) { best = {0, s}; best_ns = ns; }
+        }
+    }
     for (int rows = 128; rows >= 64; rows -= 64)
         for (int s = 1; s <= 8; ++s) {
             const int kp = ((a.K + s - 1) / s + 63) / 64 * 64;
@@ -389,7 +400,7 @@ GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes) {
             const double tiles = (double)a.nprob * s * tn * (double)((a.M + rows - 1) / rows), rounds = ceil(tiles / cu);
             if (tiles >= (double)(1 << 22)) continue;              // the grid's limit
             const double fill = tiles / (rounds * cu);
-            double ns = 3000.0 + rounds * (kp / 64) * (rows == 128 ? 500.0 + 250.0 * fill : 300.0 + 120.0 * fill);
+            double ns = 3500.0 + rounds * (kp / 64) * (rows == 128 ? 440.0 + 180.0 * fill : 280.0 + 90.0 * fill);
             if (!large && rounds > 1.0) ns = 3000.0 + rounds * (rows == 128 ? 4500.0 + (kp / 64) * (400.0 + 250.0 * fill) : 3000.0 + (kp / 64) * (240.0 + 120.0 * fill));
             if (s > 1) ns += 4000.0 + 2.0 * (double)bytes / 4.0e3;
             if (ns < 0.95 * best_ns) { best = {rows, s}; best_ns = ns; }

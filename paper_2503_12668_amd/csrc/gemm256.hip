@@ -1,10 +1,10 @@
 // Large-tile MFMA GEMM for the big projections: 256 x 256 x 64 block tile, one workgroup per compute unit,
-// v_mfma_f32_16x16x32 with float32 accumulators in the accumulation registers.  Three instances:
+// v_mfma_f32_16x16x32 with float32 accumulators in the accumulation registers.  Four instances:
 //   256-row tiles, eight wavefronts (2 x 4, two per SIMD), each owning 128 x 64 = 8 x 4 MFMA tiles.  While one
 //     wavefront of a SIMD issues LDS reads, loads or waits, the other one's MFMAs keep the matrix pipeline busy.
 //   256-row tiles, four wavefronts (2 x 2) of 128 x 128: the deeper prefetch below; taken for long k (pick_waves).
-//   128-row tiles: four wavefronts (2 x 2) of 64 x 128, for launches that 256-row tiles would spread badly over
-//     the compute units.
+//   192- and 128-row tiles: four wavefronts (2 x 2) of 96 x 128 or 64 x 128, for launches that 256-row tiles would spread
+//     badly over the compute units or whose last tile row they would leave mostly empty (pick_tile_rows).
 // (Under this kernel's full load - MFMA, LDS reads, 64 KB per k-slab streaming from L2 - the chip sustains a
 // higher clock with the 16 x 16 x 32 shape than with 32 x 32 x 16, although the latter is faster in an MFMA-only loop.)
 //
@@ -76,14 +76,14 @@ template <> struct Mfma16<f16_t> {
     }
 };
 
-// Tile: (32 MI) x 256 x 64 with MI = 8 (256 rows; the main shape) or MI = 4 (128 rows: twice as many tiles for
-// launches whose 256-row tiles would leave compute units idle or a last round of tiles mostly empty).
+// Tile: (32 MI) x 256 x 64 with MI = 8 (256 rows; the main shape), 6 or 4 (192, 128 rows: more tiles for launches whose
+// 256-row tiles would leave compute units idle, or a last round or row of tiles mostly empty).
 static constexpr int kBN = 256, kBK = 64;
 static constexpr int kEpiRegion = 24576;                       // per-wave output staging above stage 0
 template <int MI> struct Tile256 {
     static constexpr int BM = 32 * MI;
-    static constexpr int kStageBytes = (BM + kBN) * kBK * 2;           // 65536 / 49152
-    static constexpr int kLdsBytes = kStageBytes + 4 * kEpiRegion;     // 163840 (all 160 KB of a compute unit) / 147456
+    static constexpr int kStageBytes = (BM + kBN) * kBK * 2;           // 65536 / 57344 / 49152
+    static constexpr int kLdsBytes = kStageBytes + 4 * kEpiRegion;     // 163840 (all 160 KB of a compute unit) / 155648 / 147456
 };
 
 // direct-to-LDS load of 16 bytes per lane: lane i's data lands at lds_base + 16 i
@@ -161,7 +161,6 @@ template <typename T, typename OutT, int MI, int NW>
 __global__ __launch_bounds__(NW * 64, 1) void gemm_mfma256_kernel(const GemmArgs a, int total_tiles) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     constexpr int kBM = Tile256<MI>::BM, kStageBytes = Tile256<MI>::kStageBytes;
-    constexpr int WPG = 8 / MI;                 // W row-blocks handled per group of eight MFMAs: 1 or 2
     static_assert(NW == 4 || (NW == 8 && MI == 8), "eight wavefronts: 256-row tiles only");
     constexpr int WAVES_N = NW / 2;             // wavefronts side by side along the columns: 2 or 4
     constexpr int NJ = 16 / WAVES_N;            // 16-column MFMA tiles per wavefront: 8 or 4
@@ -302,6 +301,9 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_mfma256_kernel(const GemmArgs
             fa[i] = *reinterpret_cast<const uint4*>(sa + i * 2048);
             __builtin_amdgcn_sched_barrier(0);
           } else {
+            // this group's share of the eight W row-blocks: w0 and, if there are two, w0 + 1 (256 rows: one each, 128: two each, 192: 1 1 2 1 1 2)
+            const int w0 = i * 8 / MI;
+            const bool two = (i + 1) * 8 / MI - w0 == 2;
             Mfma16<T>::run(fb[buf][0], fa[i], acc[i][0]);
             __builtin_amdgcn_sched_barrier(0);
             if (stage_out) *reinterpret_cast<u32x4_t*>(wr_a[st] + i * 1024) = sx[i];
@@ -312,24 +314,24 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_mfma256_kernel(const GemmArgs
             __builtin_amdgcn_sched_barrier(0);
             Mfma16<T>::run(fb[buf][2], fa[i], acc[i][2]);
             __builtin_amdgcn_sched_barrier(0);
-            if (stage_out) *reinterpret_cast<u32x4_t*>(wr_b[st] + (i * WPG) * 1024) = sw[i * WPG];
+            if (stage_out) *reinterpret_cast<u32x4_t*>(wr_b[st] + w0 * 1024) = sw[w0];
             __builtin_amdgcn_sched_barrier(0);
             Mfma16<T>::run(fb[buf][3], fa[i], acc[i][3]);
             __builtin_amdgcn_sched_barrier(0);
-            if (stage_out) sw[i * WPG] = panel_load(rs_w, pb[i * WPG], soff);
+            if (stage_out) sw[w0] = panel_load(rs_w, pb[w0], soff);
             __builtin_amdgcn_sched_barrier(0);
             Mfma16<T>::run(fb[buf][4], fa[i], acc[i][4]);
             __builtin_amdgcn_sched_barrier(0);
-            fb[nbuf][i * WPG] = *reinterpret_cast<const uint4*>(sb + (i * WPG) * 2048);
-            if (WPG == 2 && stage_out) *reinterpret_cast<u32x4_t*>(wr_b[st] + (i * WPG + 1) * 1024) = sw[i * WPG + WPG - 1];
+            fb[nbuf][w0] = *reinterpret_cast<const uint4*>(sb + w0 * 2048);
+            if (two && stage_out) *reinterpret_cast<u32x4_t*>(wr_b[st] + (w0 + 1) * 1024) = sw[(w0 + 1) & 7];
             __builtin_amdgcn_sched_barrier(0);
             Mfma16<T>::run(fb[buf][5], fa[i], acc[i][5]);
             __builtin_amdgcn_sched_barrier(0);
-            if (WPG == 2 && stage_out) sw[i * WPG + WPG - 1] = panel_load(rs_w, pb[i * WPG + WPG - 1], soff);
+            if (two && stage_out) sw[(w0 + 1) & 7] = panel_load(rs_w, pb[(w0 + 1) & 7], soff);
             __builtin_amdgcn_sched_barrier(0);
             Mfma16<T>::run(fb[buf][6], fa[i], acc[i][6]);
             __builtin_amdgcn_sched_barrier(0);
-            if (WPG == 2) fb[nbuf][i * WPG + WPG - 1] = *reinterpret_cast<const uint4*>(sb + (i * WPG + WPG - 1) * 2048);
+            if (two) fb[nbuf][(w0 + 1) & 7] = *reinterpret_cast<const uint4*>(sb + (w0 + 1) * 2048);
             __builtin_amdgcn_sched_barrier(0);
             Mfma16<T>::run(fb[buf][7], fa[i], acc[i][7]);
             __builtin_amdgcn_sched_barrier(0);
@@ -388,6 +390,7 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_mfma256_kernel(const GemmArgs
             for (int i = 0; i < MI; ++i) mgroup(i, 0, 1, frag_x[cur][1], frag_w[cur][1], false, 0, 0u);
             ZO2_TIMED(wait_vm, {
                 if constexpr (XA + WB == 16) asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)" ::: "memory");
+                else if constexpr (XA + WB == 14) asm volatile("s_waitcnt vmcnt(14) lgkmcnt(0)" ::: "memory");
                 else if constexpr (XA + WB == 12) asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
                 else asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
             });
@@ -666,26 +669,6 @@ static zo2_status launch256_t(const GemmArgs& a, hipStream_t st) {
     return ZO2_OK;
 }
 
-// Rows per tile for a launch.  Workgroups are persistent, one per compute unit, and take whole tiles: with 256-row tiles
-// a launch of 128 tiles keeps half of 256 compute units busy, one of 640 tiles leaves the third round half empty.
-// A 128-row tile does half the work at a lower rate (same W panel per slab, half the X panel, half the MFMAs per
-// fragment read): measured 0.78 - 0.9 of the 256-row rate for K <= 4096 and 0.67 - 0.78 beyond on launches that fill the
-// chip either way.  It is chosen when the better filling of the rounds outweighs that.
-static int g_forced_tile_rows = 0;      // 0: per launch; 128 / 256: every launch (tests and measurements, see gemm256_force_tile_rows)
-void gemm256_force_tile_rows(int rows) { g_forced_tile_rows = rows; }
-static int pick_tile_rows(const GemmArgs& a) {
-    if (g_forced_tile_rows == 128 || g_forced_tile_rows == 256) return g_forced_tile_rows;
-    if (a.M <= 128) return 128;
-    const long cu = device_cu_count();
-    const long tn = (a.N + kBN - 1) / kBN;
-    auto filling = [&](long rows) {        // useful tile rows over the tile rows the rounds have room for
-        const long t = ((a.M + rows - 1) / rows) * tn * a.nprob, rounds = (t + cu - 1) / cu;
-        return (double)a.M * tn * a.nprob / (double)(rounds * cu * rows);
-    };
-    const double small_tile_rate = a.K > 4096 ? 0.72 : 0.78;
-    return filling(128) * small_tile_rate > filling(256) ? 128 : 256;
-}
-
 // Wavefronts per workgroup for a launch of 256-row tiles.  Eight wavefronts keep the matrix pipeline busier (two per
 // SIMD) but can only prefetch one k-slab ahead; four wavefronts hold a further slab in registers.  Measured inside the
 // benchmark step, same box: eight are 3 - 4 % faster at K = 2048 (QKV, FC1, LM head), four are 4 % faster at K = 8192
@@ -698,6 +681,28 @@ static constexpr int kLongK = 6144, kFewRows = 2048;
 static int pick_waves(const GemmArgs& a) {
     if (g_forced_waves == 4 || g_forced_waves == 8) return g_forced_waves;
     return (a.K >= kLongK || a.M <= kFewRows) ? 4 : 8;
+}
+
+// Rows per tile for a launch.  Workgroups are persistent, one per compute unit, and take whole tiles: with 256-row tiles
+// a launch of 128 tiles keeps half of 256 compute units busy, one of 640 tiles leaves the third round half empty, one of 513 rows
+// computes 768.  A lower tile does less work at a lower rate (the same W panel per slab, fewer MFMAs per fragment read).  The cost of a
+// launch is its rounds times a tile's time, in 256-row tiles of four wavefronts.  Measured per full round at N 8192, 256 -> 192 and 128
+// rows: K 2048 60.5 us -> 48.6, 37.4; K 2560 67.6 -> 56.1, 42.7; K 8192 204 -> 161, 123; K 20480 503 -> 403, 308.
+double gemm256_tile_cost(int rows) { return rows == 256 ? 1.0 : rows == 192 ? 0.80 : 0.61; }
+static int g_forced_tile_rows = 0;      // 0: per launch; 128 / 256: every launch (tests and measurements, see gemm256_force_tile_rows)
+void gemm256_force_tile_rows(int rows) { g_forced_tile_rows = rows; }
+static int pick_tile_rows(const GemmArgs& a) {
+    if (g_forced_tile_rows == 128 || g_forced_tile_rows == 256) return g_forced_tile_rows;
+    const long cu = device_cu_count();
+    const long tn = (a.N + kBN - 1) / kBN;
+    int best = 256;
+    double best_cost = 0.0;
+    for (int rows = 256; rows >= 128; rows -= 64) {
+        const long t = ((a.M + rows - 1) / rows) * tn * a.nprob, rounds = (t + cu - 1) / cu;
+        const double cost = (double)rounds * gemm256_tile_cost(rows) * (rows == 256 && pick_waves(a) == 8 ? 0.96 : 1.0);
+        if (rows == 256 || cost < best_cost) { best = rows; best_cost = cost; }
+    }
+    return best;
 }
 
 bool gemm256_is_forced() { return g_forced_tile_rows != 0 || g_forced_waves != 0; }
@@ -730,18 +735,18 @@ zo2_status gemm_launch_256(const GemmArgs& a, int dtype, hipStream_t st) {
         set_op_error("gemm256: shape or alignment not supported by the 256 x 256 kernel");
         return ZO2_EINVAL;
     }
-    const bool small = pick_tile_rows(a) == 128;
-    const bool eight = !small && pick_waves(a) == 8;
-    if (dtype == ZO2_BF16) {
-        if (small) return a.out_f32 ? launch256_t<bf16_t, float, 4, 4>(a, st) : launch256_t<bf16_t, bf16_t, 4, 4>(a, st);
-        if (eight) return a.out_f32 ? launch256_t<bf16_t, float, 8, 8>(a, st) : launch256_t<bf16_t, bf16_t, 8, 8>(a, st);
-        return a.out_f32 ? launch256_t<bf16_t, float, 8, 4>(a, st) : launch256_t<bf16_t, bf16_t, 8, 4>(a, st);
-    }
-    if (dtype == ZO2_F16) {
-        if (small) return a.out_f32 ? launch256_t<f16_t, float, 4, 4>(a, st) : launch256_t<f16_t, f16_t, 4, 4>(a, st);
-        if (eight) return a.out_f32 ? launch256_t<f16_t, float, 8, 8>(a, st) : launch256_t<f16_t, f16_t, 8, 8>(a, st);
-        return a.out_f32 ? launch256_t<f16_t, float, 8, 4>(a, st) : launch256_t<f16_t, f16_t, 8, 4>(a, st);
-    }
+    const int rows = pick_tile_rows(a);
+    const bool eight = rows == 256 && pick_waves(a) == 8;
+#define ZO2_G256(T, MI, NW) return a.out_f32 ? launch256_t<T, float, MI, NW>(a, st) : launch256_t<T, T, MI, NW>(a, st)
+#define ZO2_G256_DTYPE(T)               \
+    if (rows == 128) ZO2_G256(T, 4, 4); \
+    if (rows == 192) ZO2_G256(T, 6, 4); \
+    if (eight) ZO2_G256(T, 8, 8);       \
+    ZO2_G256(T, 8, 4)
+    if (dtype == ZO2_BF16) { ZO2_G256_DTYPE(bf16_t); }
+    if (dtype == ZO2_F16) { ZO2_G256_DTYPE(f16_t); }
+#undef ZO2_G256_DTYPE
+#undef ZO2_G256
     set_op_error("gemm256: dtype %d unsupported", dtype);
     return ZO2_EINVAL;
 }
