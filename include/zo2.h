@@ -157,7 +157,8 @@ zo2_status zo2_step_extra(zo2_ctx* ctx, const int32_t* tokens, const int32_t* la
  * results: host array of 3 n_dirs floats, (l+, l-, g) per direction.  Losses, g and the state left behind (deferred
  * updates, parameters) equal those of zo2_step(seeds[0]) followed by zo2_step_extra(seeds[1 ..]) bit for bit.  Needs one
  * more residual stream (2 tokens x d_model floats) of arena per further direction; the plan is redone when n_dirs
- * exceeds what it holds.  1 <= n_dirs <= 16 (ZO2_EINVAL beyond); ZO2_ENONFINITE if any direction's loss is not finite:
+ * exceeds what it holds.  Where blocks are resident and the budget has room for it - two sets of a block's perturbed copies and the
+ * activations of two streams per direction - up to four directions go through a block together (bfloat16 compute), faster.  1 <= n_dirs <= 16 (ZO2_EINVAL beyond); ZO2_ENONFINITE if any direction's loss is not finite:
  * then the whole round is dropped (results still filled in). */
 zo2_status zo2_step_multi(zo2_ctx* ctx, const int32_t* tokens, const int32_t* labels, int32_t batch, int32_t seq,
                           int32_t n_dirs, const uint64_t* seeds, float eps, float lr, float* results);
@@ -193,7 +194,8 @@ zo2_status zo2_add_pending(zo2_ctx* ctx, uint64_t seed, float step);
 zo2_status zo2_sync_to_host(zo2_ctx* ctx);
 
 /* Facts about the plan used by the last step: how many block slots exist, whether blocks are
- * resident, how many arena bytes are in use.  Any pointer may be NULL. */
+ * resident, how many arena bytes are in use (what the plan cannot do without: rounds of several directions on
+ * resident blocks also use what the budget leaves beyond it).  Any pointer may be NULL. */
 zo2_status zo2_get_plan(const zo2_ctx* ctx, int32_t* n_slots, int32_t* resident, size_t* bytes_used);
 
 /* How the W+ / W- scratch of the last plan is organised (Sec. 5.3's reusable block space, applied to the perturbed

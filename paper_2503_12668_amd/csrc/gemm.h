@@ -22,7 +22,8 @@ struct GemmProblem {
 };
 
 struct GemmArgs {
-    static constexpr int kMaxProblems = 12;      // q/k/v x two streams x two k pieces
+    static constexpr int kMaxProblems = 24;      // q/k/v x two streams x four directions, or x two k pieces x two directions
+    static constexpr int kMaxPieces = 12;        // problems x pieces of one direction's launch
     int32_t M, N, K;
     int64_t ldx, ldw, ldy;
     int64_t part_ld;        // cross-entropy mode: elements between consecutive spans of the partial arrays (>= M)
@@ -62,6 +63,9 @@ zo2_status gemm_launch_f32_splitk(const GemmArgs& a, int splits, void* workspace
 // kernel with tiles of that height (gemm_launch_mid_splitk); splits: pieces along k that the workspace holds.
 struct GemmChoice { int rows, splits; };
 GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes);
+// The launch that choice `k`, made for a.nprob / groups problems, stands for: the same sums for `groups` times as many problems at once
+// (tile heights, which do not change a sum's order, are chosen anew).  Workspace: the pieces of all of them.
+zo2_status gemm_launch_groups(const GemmArgs& a, int dtype, GemmChoice k, int groups, void* workspace, size_t workspace_bytes, hipStream_t st);
 bool gemm256_is_forced();                 // a tile height or wavefront count is forced: the large-tile kernel is meant
 zo2_status gemm_launch_mid_splitk(const GemmArgs& a, int dtype, int rows, int splits, void* workspace, size_t workspace_bytes, hipStream_t st);
 // 0 (default): the 256 x 256 kernel picks 256- or 128-row tiles per launch; 128 / 256: every launch uses that height

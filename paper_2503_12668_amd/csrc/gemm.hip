@@ -299,7 +299,7 @@ int gemm_pick_splits(int M, int N, int K, int nprob, int dtype) {
     int best = 1;
     double best_ns = launch_ns(1);
     for (int s = 2; s <= 4; s *= 2) {
-        if (K % (s * 128) != 0 || K / s < 512 || nprob * s > GemmArgs::kMaxProblems) break;
+        if (K % (s * 128) != 0 || K / s < 512 || nprob * s > GemmArgs::kMaxPieces) break;
         const double ns = launch_ns(s);
         if (ns < 0.92 * best_ns) { best = s; best_ns = ns; }
     }
@@ -366,6 +366,11 @@ static double general_ns(double tiles, double slabs) {
     const double cu = (double)device_cu_count();
     return tiles <= cu ? 5600.0 + 900.0 * slabs : 3000.0 + ceil(tiles / (2.0 * cu)) * (3800.0 + 1250.0 * slabs);
 }
+static double mid_ns(int rows, double tiles, int kp, bool large) {
+    const double cu = (double)device_cu_count(), rounds = ceil(tiles / cu), fill = tiles / (rounds * cu);
+    if (!large && rounds > 1.0) return 3000.0 + rounds * (rows == 128 ? 4500.0 + (kp / 64) * (400.0 + 250.0 * fill) : 3000.0 + (kp / 64) * (240.0 + 120.0 * fill));
+    return 3500.0 + rounds * (kp / 64) * (rows == 128 ? 440.0 + 180.0 * fill : 280.0 + 90.0 * fill);
+}
 GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes) {
     GemmChoice best = {0, gemm_pick_splits(a.M, a.N, a.K, a.nprob, dtype)};
     if (gemm_splitk_workspace_bytes(a.M, a.N, a.nprob, best.splits) > workspace_bytes) best.splits = 1;
@@ -382,7 +387,7 @@ GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes) {
         best_ns = 1e30;
         for (int s = 1; s <= 4; s *= 2) {
             const size_t bytes = gemm_splitk_workspace_bytes(a.M, a.N, a.nprob, s);
-            if (s > 1 && (a.K % (s * 128) != 0 || a.K / s < 512 || a.nprob * s > GemmArgs::kMaxProblems || bytes > workspace_bytes)) break;
+            if (s > 1 && (a.K % (s * 128) != 0 || a.K / s < 512 || a.nprob * s > GemmArgs::kMaxPieces || bytes > workspace_bytes)) break;
             double ns = 1e30;
             for (int rows = 128; rows <= 256; rows += 64) {
                 const double tiles = (double)a.nprob * s * (double)((a.N + 255) / 256) * (double)((a.M + rows - 1) / rows);
@@ -397,11 +402,9 @@ GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes) {
             const int kp = ((a.K + s - 1) / s + 63) / 64 * 64;
             const size_t bytes = (size_t)a.nprob * s * a.M * a.N * sizeof(float);
             if (s > 1 && (kp < 256 || (a.K + kp - 1) / kp != s || bytes > workspace_bytes)) continue;
-            const double tiles = (double)a.nprob * s * tn * (double)((a.M + rows - 1) / rows), rounds = ceil(tiles / cu);
+            const double tiles = (double)a.nprob * s * tn * (double)((a.M + rows - 1) / rows);
             if (tiles >= (double)(1 << 22)) continue;              // the grid's limit
-            const double fill = tiles / (rounds * cu);
-            double ns = 3500.0 + rounds * (kp / 64) * (rows == 128 ? 440.0 + 180.0 * fill : 280.0 + 90.0 * fill);
-            if (!large && rounds > 1.0) ns = 3000.0 + rounds * (rows == 128 ? 4500.0 + (kp / 64) * (400.0 + 250.0 * fill) : 3000.0 + (kp / 64) * (240.0 + 120.0 * fill));
+            double ns = mid_ns(rows, tiles, kp, large);
             if (s > 1) ns += 4000.0 + 2.0 * (double)bytes / 4.0e3;
             if (ns < 0.95 * best_ns) { best = {rows, s}; best_ns = ns; }
         }
@@ -470,6 +473,31 @@ zo2_status gemm_launch_splitk(const GemmArgs& a, int dtype, int splits, void* wo
     if (dtype == ZO2_BF16) launch_splitk_reduce<bf16_t>(a, part, splits, st);
     else launch_splitk_reduce<f16_t>(a, part, splits, st);
     ZO2_HIP_LAUNCH_CHECK();
+    return ZO2_OK;
+}
+
+zo2_status gemm_launch_groups(const GemmArgs& a, int dtype, GemmChoice k, int groups, void* workspace, size_t workspace_bytes, hipStream_t st) {
+    ZO2_OP_CHECK(groups >= 1 && a.nprob >= groups && a.nprob % groups == 0 && a.nprob <= GemmArgs::kMaxProblems, ZO2_EINVAL, "gemm: %d problems in %d groups", a.nprob, groups);
+    if (k.rows) {
+        const int kp = k.splits > 1 ? ((a.K + k.splits - 1) / k.splits + 63) / 64 * 64 : a.K;
+        const double n = (double)a.nprob * k.splits * (double)((a.N + 127) / 128);
+        const bool large = gemm256_applicable(a, dtype);
+        const int rows = mid_ns(64, n * ((a.M + 63) / 64), kp, large) < mid_ns(128, n * ((a.M + 127) / 128), kp, large) ? 64 : 128;
+        return gemm_launch_mid_splitk(a, dtype, rows, k.splits, workspace, workspace_bytes, st);
+    }
+    if (k.splits <= 1) {
+        { const zo2_status s = check_operands(a); if (s != ZO2_OK) return s; }
+        return launch_large(a, dtype, st);
+    }
+    // as many groups at a time as the list of problems holds pieces of
+    const int each = a.nprob / groups, at_once = std::max(1, std::min(groups, GemmArgs::kMaxProblems / (each * k.splits)));
+    for (int g0 = 0; g0 < groups; g0 += at_once) {
+        GemmArgs e = a;
+        e.nprob = each * std::min(at_once, groups - g0);
+        for (int i = 0; i < e.nprob; ++i) e.p[i] = a.p[g0 * each + i];
+        const zo2_status s = gemm_launch_splitk(e, dtype, k.splits, workspace, workspace_bytes, st);
+        if (s != ZO2_OK) return s;
+    }
     return ZO2_OK;
 }
 

@@ -34,6 +34,25 @@ struct K1Args {
     K1Seg seg[kMaxSeg];
 };
 
+// The sweep of a round of several directions: any number of deferred updates, each stored before the next is applied, and the
+// perturbed copies of up to kMaxDirs directions, with theta read and written once.
+struct K1RoundArgs {
+    static constexpr int kMaxUpdates = 16, kMaxDirs = 4;
+    void* theta;
+    void* w_plus[kMaxDirs];          // addressed as w_plus[j][off - w_off0 + i]
+    void* w_minus[kMaxDirs];
+    int64_t w_off0;
+    const float* c_ptr;              // coefficients of the updates, in order
+    int32_t n_upd, n_dir, nseg, stochastic;
+    uint32_t total_chunks;
+    float eps;
+    PhiloxKeys k_upd[kMaxUpdates], k_dir[kMaxDirs];
+    uint32_t first_chunk[K1Args::kMaxSeg];
+    K1Seg seg[K1Args::kMaxSeg];      // (woff unused)
+};
+bool k1_round_applicable(int wire_dtype, int compute_dtype);
+zo2_status k1_round_launch(K1RoundArgs& a, int wire_dtype, int compute_dtype, hipStream_t st);
+
 // Enqueue K1 over the segments.  update: apply theta' = theta - c z_prev; perturb: write W+, W-.
 zo2_status k1_launch(K1Args& a, int wire_dtype, int compute_dtype, bool update, bool perturb, hipStream_t st);
 uint32_t k1_chunks(uint64_t n);

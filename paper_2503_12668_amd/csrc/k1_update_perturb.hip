@@ -28,7 +28,7 @@ static constexpr int kChunk = kThreads * kPerLane * kIters;   // 2048 elements p
 // The arithmetic of one group of 8 consecutive elements (one Philox call q per random stream): tv holds
 // theta on entry and theta' on return.
 template <typename W, typename C, bool UPDATE, bool PERTURB, bool SR, bool DRAW>
-__device__ __forceinline__ void k1_group(const K1Args& a, uint32_t tensor_id, uint64_t q, float c, float eps, float scale,
+__device__ __forceinline__ void k1_group(const PhiloxKeys& k_prev, const PhiloxKeys& k_cur, uint32_t tensor_id, uint64_t q, float c, float eps, float scale,
                                          float inv_scale, Vec<W, kPerLane>& tv, Vec<C, kPerLane>& p, Vec<C, kPerLane>& m) {
     constexpr bool kScaled = (Fmt<W>::kBytes == 1);
     float th[kPerLane];
@@ -42,10 +42,10 @@ __device__ __forceinline__ void k1_group(const K1Args& a, uint32_t tensor_id, ui
     }
     if (UPDATE) {
         float zp[kPerLane];
-        gaussian8(a.k_prev, tensor_id, q, zp);
+        gaussian8(k_prev, tensor_id, q, zp);
         uint32_t rw[4] = {0u, 0u, 0u, 0u};
         constexpr bool sr = SR && Fmt<W>::kBytes < 4;
-        if (sr) rounding_words(a.k_prev, tensor_id, q, rw);
+        if (sr) rounding_words(k_prev, tensor_id, q, rw);
         if constexpr (kScaled && !sr) {
             float ts[kPerLane];
 #pragma unroll
@@ -72,7 +72,7 @@ __device__ __forceinline__ void k1_group(const K1Args& a, uint32_t tensor_id, ui
     }
     if constexpr (PERTURB && DRAW) {
         float z[kPerLane];
-        gaussian8(a.k_cur, tensor_id, q, z);
+        gaussian8(k_cur, tensor_id, q, z);
 #pragma unroll
         for (int j = 0; j < kPerLane; ++j) {
             p.v[j] = Fmt<C>::store(__builtin_fmaf(eps, z[j], th[j]));
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kThreads) void k1_kernel(const K1Args a) {
             const uint64_t i = chunk0 + (uint64_t)threadIdx.x * kPerLane;
             Vec<W, kPerLane> tv = load_vec_stream<W, kPerLane>(theta + i);
             Vec<C, kPerLane> p, m;
-            k1_group<W, C, true, false, SR, false>(a, sg.tensor_id, (sg.e0 + i) >> 3, c, eps, scale, inv_scale, tv, p, m);
+            k1_group<W, C, true, false, SR, false>(a.k_prev, a.k_cur, sg.tensor_id, (sg.e0 + i) >> 3, c, eps, scale, inv_scale, tv, p, m);
             store_vec<W, kPerLane>(theta + i, tv);
             return;
         }
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kThreads) void k1_kernel(const K1Args a) {
         for (int it = 0; it < kIters; ++it) {
             const uint64_t i = i0 + (uint64_t)it * kStride;
             Vec<C, kPerLane> p, m;
-            k1_group<W, C, UPDATE, PERTURB, SR, DRAW>(a, sg.tensor_id, (sg.e0 + i) >> 3, c, eps, scale, inv_scale, tv[it], p, m);
+            k1_group<W, C, UPDATE, PERTURB, SR, DRAW>(a.k_prev, a.k_cur, sg.tensor_id, (sg.e0 + i) >> 3, c, eps, scale, inv_scale, tv[it], p, m);
             // (theta' is not read again before the next step when the perturbed copies are written here: streamed past the
             // caches it leaves them to the copies; in an update-only sweep the projections read theta' next, so it stays)
             if (UPDATE && PERTURB) store_vec_stream<W, kPerLane>(theta + i, tv[it]);
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kThreads) void k1_kernel(const K1Args a) {
             for (int j = 0; j < kPerLane; ++j) tv.v[j] = (j < valid) ? theta[i0 + j] : Fmt<W>::store(0.f);
         }
         Vec<C, kPerLane> p, m;
-        k1_group<W, C, UPDATE, PERTURB, SR, DRAW>(a, sg.tensor_id, (sg.e0 + i0) >> 3, c, eps, scale, inv_scale, tv, p, m);
+        k1_group<W, C, UPDATE, PERTURB, SR, DRAW>(a.k_prev, a.k_cur, sg.tensor_id, (sg.e0 + i0) >> 3, c, eps, scale, inv_scale, tv, p, m);
         if (valid == kPerLane) {
             if (UPDATE && PERTURB) store_vec_stream<W, kPerLane>(theta + i0, tv);
             else if (UPDATE) store_vec<W, kPerLane>(theta + i0, tv);
@@ -180,6 +180,75 @@ __global__ __launch_bounds__(kThreads) void k1_kernel(const K1Args a) {
                 }
         }
     }
+}
+
+// A round of directions in one sweep (zo2_step_multi).  Bound by the vector ALU, which draws n_upd + n_dir Gaussians an element;
+// sweep by sweep the same draws each wait for theta and its write: a block of 50 M bf16 elements, four updates and four directions
+// 99 + 59 + 137 us in seven launches.  The group's arithmetic is k1_group's, update by update and direction by direction, so
+// the stored bits are those of the single sweeps.
+template <typename W, typename C, bool SR>
+__global__ __launch_bounds__(kThreads) void k1_round_kernel(const K1RoundArgs a) {
+    const uint32_t chunk = a.total_chunks - 1u - blockIdx.x;      // last to first, as in k1_kernel
+    int s = 0;
+#pragma unroll
+    for (int i = 1; i < K1Args::kMaxSeg; ++i) s += (chunk >= a.first_chunk[i]) ? 1 : 0;
+    const K1Seg sg = a.seg[s];
+    const uint64_t i0 = (uint64_t)(chunk - a.first_chunk[s]) * kChunk + (uint64_t)threadIdx.x * kPerLane;
+    if (i0 >= sg.n) return;
+    W* __restrict__ theta = reinterpret_cast<W*>(a.theta) + sg.off + i0;
+    const int64_t wofs = sg.off - a.w_off0 + (int64_t)i0;
+    const int valid = (sg.n - i0 >= (uint64_t)kPerLane) ? kPerLane : (int)(sg.n - i0);
+    const float scale = sg.scale, inv_scale = 1.0f / sg.scale;
+    const uint64_t q = (sg.e0 + i0) >> 3;
+    Vec<W, kPerLane> tv;
+    Vec<C, kPerLane> p, m;
+    if (valid == kPerLane) {
+        tv = load_vec_stream<W, kPerLane>(theta);
+    } else {
+#pragma unroll
+        for (int j = 0; j < kPerLane; ++j) tv.v[j] = (j < valid) ? theta[j] : Fmt<W>::store(0.f);
+    }
+#pragma unroll 1
+    for (int u = 0; u < a.n_upd; ++u)
+        k1_group<W, C, true, false, SR, false>(a.k_upd[u], a.k_upd[u], sg.tensor_id, q, a.c_ptr[u], 0.f, scale, inv_scale, tv, p, m);
+    if (a.n_upd > 0) {
+        if (valid == kPerLane) {
+            store_vec_stream<W, kPerLane>(theta, tv);
+        } else {
+#pragma unroll
+            for (int j = 0; j < kPerLane; ++j)
+                if (j < valid) theta[j] = tv.v[j];
+        }
+    }
+#pragma unroll 1
+    for (int d = 0; d < a.n_dir; ++d) {
+        k1_group<W, C, false, true, false, true>(a.k_dir[d], a.k_dir[d], sg.tensor_id, q, 0.f, a.eps, scale, inv_scale, tv, p, m);
+        C* __restrict__ wp = reinterpret_cast<C*>(a.w_plus[d]) + wofs;
+        C* __restrict__ wm = reinterpret_cast<C*>(a.w_minus[d]) + wofs;
+        if (valid == kPerLane) {
+            store_vec<C, kPerLane>(wp, p);
+            store_vec<C, kPerLane>(wm, m);
+        } else {
+#pragma unroll
+            for (int j = 0; j < kPerLane; ++j)
+                if (j < valid) { wp[j] = p.v[j]; wm[j] = m.v[j]; }
+        }
+    }
+}
+
+// (bfloat16 copies of anything but float16: where float16 is stored the compiler folds the rounding into the multiply-add in some
+// instances and not in others, 34 of a million elements differ, and a round in one pass is to leave the bits of one in several)
+bool k1_round_applicable(int wire_dtype, int compute_dtype) { return compute_dtype == ZO2_BF16 && wire_dtype != ZO2_F16; }
+template <typename W, typename C>
+static zo2_status launch_round(const K1RoundArgs& a, hipStream_t st) {
+    if constexpr (__is_same(C, bf16_t) && !__is_same(W, f16_t)) {
+        if (a.stochastic && sizeof(W) < 4) hipLaunchKernelGGL((k1_round_kernel<W, C, true>), dim3(a.total_chunks), dim3(kThreads), 0, st, a);
+        else hipLaunchKernelGGL((k1_round_kernel<W, C, false>), dim3(a.total_chunks), dim3(kThreads), 0, st, a);
+        ZO2_HIP_LAUNCH_CHECK();
+        return ZO2_OK;
+    }
+    set_op_error("k1: no round in one sweep for these formats");
+    return ZO2_EINVAL;
 }
 
 template <typename W, typename C>
@@ -208,29 +277,47 @@ static zo2_status launch_wc(const K1Args& a, bool update, bool perturb, hipStrea
 
 uint32_t k1_chunks(uint64_t n) { return (uint32_t)((n + kChunk - 1) / kChunk); }
 
-zo2_status k1_launch(K1Args& a, int wire_dtype, int compute_dtype, bool update, bool perturb, hipStream_t st) {
-    ZO2_OP_CHECK(a.nseg >= 1 && a.nseg <= K1Args::kMaxSeg, ZO2_EINVAL, "k1: %d segments", a.nseg);
+// workgroups of the segments, and the checks that every sweep needs of them
+static zo2_status plan_chunks(const K1Seg* seg, int nseg, uint32_t* first_chunk, uint32_t& total) {
+    ZO2_OP_CHECK(nseg >= 1 && nseg <= K1Args::kMaxSeg, ZO2_EINVAL, "k1: %d segments", nseg);
     uint32_t chunks = 0;
-    for (int i = 0; i < a.nseg; ++i) {
-        ZO2_OP_CHECK((a.seg[i].e0 & 7) == 0 && (a.seg[i].off & 7) == 0, ZO2_EINVAL,
+    for (int i = 0; i < nseg; ++i) {
+        ZO2_OP_CHECK((seg[i].e0 & 7) == 0 && (seg[i].off & 7) == 0, ZO2_EINVAL,
                      "k1: segment %d not aligned to 8 elements", i);
         int ex = 0;
-        ZO2_OP_CHECK(a.seg[i].scale > 0.f && isfinite(a.seg[i].scale) && frexpf(a.seg[i].scale, &ex) == 0.5f, ZO2_EINVAL,
-                     "k1: segment %d has scale %g (must be a power of two)", i, (double)a.seg[i].scale);
-        a.first_chunk[i] = chunks;
-        const uint64_t nc = (a.seg[i].n + kChunk - 1) / kChunk;
+        ZO2_OP_CHECK(seg[i].scale > 0.f && isfinite(seg[i].scale) && frexpf(seg[i].scale, &ex) == 0.5f, ZO2_EINVAL,
+                     "k1: segment %d has scale %g (must be a power of two)", i, (double)seg[i].scale);
+        first_chunk[i] = chunks;
+        const uint64_t nc = (seg[i].n + kChunk - 1) / kChunk;
         ZO2_OP_CHECK(chunks + nc < 0x7fffffffull, ZO2_EINVAL, "k1: too many chunks");
         chunks += (uint32_t)nc;
     }
-    for (int i = a.nseg; i < K1Args::kMaxSeg; ++i) a.first_chunk[i] = 0xffffffffu;
-    a.total_chunks = chunks;
-    if (chunks == 0 || (!update && !perturb)) return ZO2_OK;
+    for (int i = nseg; i < K1Args::kMaxSeg; ++i) first_chunk[i] = 0xffffffffu;
+    total = chunks;
+    return ZO2_OK;
+}
+
+zo2_status k1_launch(K1Args& a, int wire_dtype, int compute_dtype, bool update, bool perturb, hipStream_t st) {
+    { const zo2_status s = plan_chunks(a.seg, a.nseg, a.first_chunk, a.total_chunks); if (s != ZO2_OK) return s; }
+    if (a.total_chunks == 0 || (!update && !perturb)) return ZO2_OK;
     ZO2_OP_CHECK(a.theta != nullptr, ZO2_EINVAL, "k1: theta is NULL");
     ZO2_OP_CHECK(!perturb || a.w_plus, ZO2_EINVAL, "k1: W+ missing");
     ZO2_OP_CHECK(!a.mixed || (update && perturb && a.packed_w && a.w_minus && a.eps != 0.f && wire_dtype == compute_dtype && zo2_dtype_size(wire_dtype) == 2),
                  ZO2_EINVAL, "k1: a mixed sweep updates and perturbs 16-bit tensors into packed copies");
     ZO2_DISPATCH_WIRE(wire_dtype, W, {
         ZO2_DISPATCH_COMPUTE(compute_dtype, C, { return launch_wc<W, C>(a, update, perturb, st); });
+    });
+    return ZO2_OK;
+}
+
+zo2_status k1_round_launch(K1RoundArgs& a, int wire_dtype, int compute_dtype, hipStream_t st) {
+    { const zo2_status s = plan_chunks(a.seg, a.nseg, a.first_chunk, a.total_chunks); if (s != ZO2_OK) return s; }
+    ZO2_OP_CHECK(a.n_upd >= 0 && a.n_upd <= K1RoundArgs::kMaxUpdates && a.n_dir >= 1 && a.n_dir <= K1RoundArgs::kMaxDirs && a.theta && (a.n_upd == 0 || a.c_ptr),
+                 ZO2_EINVAL, "k1: a round of %d updates and %d directions", a.n_upd, a.n_dir);
+    for (int j = 0; j < a.n_dir; ++j) ZO2_OP_CHECK(a.w_plus[j] && a.w_minus[j], ZO2_EINVAL, "k1: W+- of direction %d missing", j);
+    if (a.total_chunks == 0) return ZO2_OK;
+    ZO2_DISPATCH_WIRE(wire_dtype, W, {
+        ZO2_DISPATCH_COMPUTE(compute_dtype, C, { return launch_round<W, C>(a, st); });
     });
     return ZO2_OK;
 }

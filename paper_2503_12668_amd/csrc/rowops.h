@@ -10,6 +10,11 @@ zo2_status gaussian(uint64_t seed, uint32_t tid, uint64_t e0, uint64_t n, float*
 zo2_status convert(const void* src, int sdt, float sscale, void* dst, int ddt, float dscale, uint64_t n, hipStream_t st);
 zo2_status layernorm(int dtype, const float* x, const void* w, const void* b, const void* w2, const void* b2, void* y,
                      int rows, int rows_first, int d, float eps, hipStream_t st);
+// The same for any number of runs of rows_per_set rows, run i with the gain and offset i step_bytes on from w and b; 16-bit formats, rows and
+// step as layernorm_sets_applicable() has them.
+bool layernorm_sets_applicable(int dtype, int d, const void* y, const void* w, const void* b, int64_t step_bytes);
+zo2_status layernorm_sets(int dtype, const float* x, const void* w, const void* b, int64_t step_bytes, void* y, int rows, int rows_per_set, int d, float eps,
+                          hipStream_t st);
 
 // The residual stream's rows from the partial sums of a projection that was cut along k, and the LayerNorm behind it, in one pass:
 // h[r] += sum of its pieces in piece order + bias, y[r] = LayerNorm(h[r]).  Rows 0 .. rows_first - 1 take bias, gain and offset of

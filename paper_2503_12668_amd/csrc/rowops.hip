@@ -241,17 +241,19 @@ __global__ __launch_bounds__(256) void layernorm_wave_kernel(const float* __rest
 }
 
 // The same with 8 consecutive elements per lane and piece (two adjacent 16-byte loads, one 16-byte store of 16-bit
-// results): for rows whose length is a multiple of 8.  WAVES rows per workgroup.
+// results): for rows whose length is a multiple of 8.  WAVES rows per workgroup.  Rows come in runs of rows_first, each with gain
+// and offset of its own (a stream of a direction), w_step and b_step elements on from the run's before; the last run has the rest.
 template <typename C, int KP, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void layernorm_wave8_kernel(const float* __restrict__ x, const C* __restrict__ w, const C* __restrict__ b,
-                                                                     const C* __restrict__ w2, const C* __restrict__ b2, C* __restrict__ y,
+                                                                     int64_t w_step, int64_t b_step, int last_run, C* __restrict__ y,
                                                                      int rows, int rows_first, int d, float eps) {
     const int lane = threadIdx.x & 63;
     const int r = blockIdx.x * WAVES + (threadIdx.x >> 6);
     if (r >= rows) return;
     const float4* xr = reinterpret_cast<const float4*>(x + (size_t)r * d);
-    const C* ww = r < rows_first ? w : w2;
-    const C* bb = r < rows_first ? b : b2;
+    const int run = min(r / rows_first, last_run);
+    const C* ww = w + run * w_step;
+    const C* bb = b + run * b_step;
     const int n8 = d >> 3;
     float4 v[KP][2];
 #pragma unroll
@@ -307,6 +309,28 @@ static bool layernorm_by8(int dtype, int d, const void* y, const void* w, const 
            (((uintptr_t)y | (uintptr_t)w | (uintptr_t)b | (uintptr_t)w2 | (uintptr_t)b2) % 16) == 0;
 }
 
+template <typename C>
+static void launch_ln8(const float* x, const void* w, const void* b, int64_t w_bytes, int64_t b_bytes, int last_run, void* y, int rows, int rows_first, int d, float eps, hipStream_t st) {
+    // pieces of 512 elements per row: instances for rows of up to 2048 and 5120 elements
+    const dim3 grid((rows + kLnWaves - 1) / kLnWaves), block(64 * kLnWaves);
+    const int64_t ws = w_bytes / (int64_t)sizeof(C), bs = b_bytes / (int64_t)sizeof(C);
+    if (d <= 4 * 512) hipLaunchKernelGGL((layernorm_wave8_kernel<C, 4, kLnWaves>), grid, block, 0, st, x, (const C*)w, (const C*)b, ws, bs, last_run, (C*)y, rows, rows_first, d, eps);
+    else hipLaunchKernelGGL((layernorm_wave8_kernel<C, 10, kLnWaves>), grid, block, 0, st, x, (const C*)w, (const C*)b, ws, bs, last_run, (C*)y, rows, rows_first, d, eps);
+}
+
+bool layernorm_sets_applicable(int dtype, int d, const void* y, const void* w, const void* b, int64_t step_bytes) {
+    return layernorm_by8(dtype, d, y, w, b, (const void*)(uintptr_t)step_bytes, nullptr);
+}
+zo2_status layernorm_sets(int dtype, const float* x, const void* w, const void* b, int64_t step_bytes, void* y, int rows, int rows_per_set, int d, float eps,
+                          hipStream_t st) {
+    ZO2_OP_CHECK(rows > 0 && rows_per_set > 0 && x && w && b && y && ((uintptr_t)x % 16) == 0 && layernorm_sets_applicable(dtype, d, y, w, b, step_bytes), ZO2_EINVAL,
+                 "layernorm: rows %d, d %d, or buffers not aligned to 8 elements", rows, d);
+    if (dtype == ZO2_BF16) launch_ln8<bf16_t>(x, w, b, step_bytes, step_bytes, (rows - 1) / rows_per_set, y, rows, rows_per_set, d, eps, st);
+    else launch_ln8<f16_t>(x, w, b, step_bytes, step_bytes, (rows - 1) / rows_per_set, y, rows, rows_per_set, d, eps, st);
+    ZO2_HIP_LAUNCH_CHECK();
+    return ZO2_OK;
+}
+
 zo2_status layernorm(int dtype, const float* x, const void* w, const void* b, const void* w2, const void* b2, void* y,
                      int rows, int rows_first, int d, float eps, hipStream_t st) {
     if (rows == 0) return ZO2_OK;
@@ -318,17 +342,16 @@ zo2_status layernorm(int dtype, const float* x, const void* w, const void* b, co
         ZO2_OP_CHECK(ca != 0 && ((uintptr_t)x % 16) == 0 && ((uintptr_t)y % ca) == 0 && ((uintptr_t)w % ca) == 0 && ((uintptr_t)b % ca) == 0 &&
                      ((uintptr_t)w2 % ca) == 0 && ((uintptr_t)b2 % ca) == 0, ZO2_EINVAL, "layernorm: unknown dtype, or buffers not aligned to 4 elements");
     }
-#define ZO2_LN8(KP)                                                                                                                       \
-    hipLaunchKernelGGL((layernorm_wave8_kernel<C, KP, kLnWaves>), dim3((rows + kLnWaves - 1) / kLnWaves), dim3(64 * kLnWaves), 0, st, x, \
-                       (const C*)w, (const C*)b, (const C*)w2, (const C*)b2, (C*)y, rows, rows_first, d, eps)
     const bool by8 = layernorm_by8(dtype, d, y, w, b, w2, b2);
     ZO2_DISPATCH_COMPUTE(dtype, C, {
-        // pieces of 512 elements per row: instances for rows of up to 2048 and 5120 elements; longer rows take too many
+        // rows of up to 5120 elements by one wavefront each; longer rows take too many
         // registers for one wavefront (measured at 8192 rows: 5120 46 us against 55 with the kernels below, 7168 76
         // against 69, 12288 145 against 115) and stay with the workgroup-per-row kernel
-        if (by8 && d <= 4 * 512) ZO2_LN8(4);
-        else if (by8) ZO2_LN8(10);
-        else if (d <= 8 * 64 * 4)
+        if (by8) {
+            const bool first = rows_first > 0, one = !first || rows_first >= rows;      // (without rows of the first stream all are the second's)
+            const void *w0 = first ? w : w2, *b0 = first ? b : b2;
+            launch_ln8<C>(x, w0, b0, one ? 0 : (intptr_t)w2 - (intptr_t)w0, one ? 0 : (intptr_t)b2 - (intptr_t)b0, one ? 0 : 1, y, rows, one ? rows : rows_first, d, eps, st);
+        } else if (d <= 8 * 64 * 4)
             hipLaunchKernelGGL((layernorm_wave_kernel<C, 8>), dim3((rows + 3) / 4), dim3(256), 0, st, x, (const C*)w, (const C*)b,
                                (const C*)w2, (const C*)b2, (C*)y, rows, rows_first, d, eps);
         else if (d <= kLnWaveMax)
@@ -341,7 +364,6 @@ zo2_status layernorm(int dtype, const float* x, const void* w, const void* b, co
             hipLaunchKernelGGL((layernorm_kernel<C, false>), dim3(rows), dim3(256), 0, st, x, (const C*)w, (const C*)b,
                                (const C*)w2, (const C*)b2, (C*)y, rows_first, d, eps);
     });
-#undef ZO2_LN8
     ZO2_HIP_LAUNCH_CHECK();
     return ZO2_OK;
 }

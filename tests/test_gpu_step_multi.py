@@ -162,3 +162,34 @@ def test_step_multi_rejects_bad_arguments_and_one_direction_is_a_step():
         r = ref.step(tok, lab, 70 + j, 1e-3, 1e-4)
         assert tuple(map(float, a)) == tuple(map(float, r))
     ctx.close(); ref.close()
+
+
+@pytest.mark.parametrize("batch,seq,dirs,wire,sr", [(1, 70, 2, "bf16", False), (3, 97, 3, "fp8_e4m3", False), (4, 128, 4, "bf16", False),
+                                                    (2, 190, 5, "bf16", False), (1, 300, 4, "f32", False), (2, 150, 3, "bf16", True)])
+def test_directions_that_share_their_launches(batch, seq, dirs, wire, sr):
+    """Directions of a round go through a resident block together where the budget has room for their scratch sets (here on sizes whose
+    projections take 64- and 128-wide tiles, large tiles and pieces of k; five directions go as four and one), one after the
+    other where it has none: the same bits, also of single directions one by one."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=2, d_model=1024, n_heads=16, d_ffn=4096, vocab=515, max_pos=320, tied=True)
+    P = si.make_weights(cfg, seed=21, std=0.03, ln_jitter=True)
+    tok = si.make_tokens(cfg["vocab"], batch, seq, seed=22)
+    lab = si.next_token_labels(tok)
+    found = []
+    for how in ("room", "no room", "one by one"):
+        ctx = b.Zo2Context(cfg, P, wire=wire, compute="bf16", arena_bytes=1 << 30)
+        ctx.set_wire_rounding(sr)
+        ctx.set_loader_fusion(-1)
+        rnd = _sequential_round if how == "one by one" else _multi_round
+        out = [rnd(ctx, tok, lab, [7 + j for j in range(dirs)], 1e-3, 1e-4)]
+        if how == "no room":
+            ctx.set_resident_budget(ctx.plan()["bytes_used"])
+        out += [rnd(ctx, tok, lab, [20 * k + j for j in range(dirs)], 1e-3, 1e-4) for k in (1, 2)]
+        assert ctx.plan()["resident"]
+        ctx.flush(); ctx.sync_to_host()
+        found.append((out, ctx.parameters()))
+        ctx.close()
+    for out, params in found[1:]:
+        assert out == found[0][0]
+        for n in params:
+            assert np.array_equal(params[n], found[0][1][n]), n
