@@ -5,6 +5,9 @@
 // Three kernels: the matrix cores for 16-bit inputs (d_head 64, 80, 128) and for float32 (d_head 16, 32, 64, 80, 128), and
 // a vector-ALU kernel with float32 arithmetic throughout as the general fallback: one wavefront per 64 queries of one
 // (sequence, head); a lane owns one query row.
+#include <algorithm>
+#include <type_traits>
+
 #include "attention.h"
 
 namespace zo2 {
@@ -136,22 +139,38 @@ template <> struct AttMfma<f16_t> {
     }
 };
 
-// direct-to-LDS load of 16 bytes per lane (lane i lands at lds_base + 16 i)
-__device__ __forceinline__ void att_load_to_lds(const void* gptr, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory");
+// direct-to-LDS load of 16 bytes per lane (lane i lands at lds_base + 16 i); source: wave-uniform base + 32-bit byte offset per lane
+__device__ __forceinline__ void att_load_to_lds(const void* sbase, uint32_t voff, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_base), "v"(voff), "s"(sbase) : "memory");
+}
+
+// Maximum over a lane and its partner in the other half of the wavefront: the swap hands every lane the lower half's value in one
+// register and the upper half's in the other (a vector instruction; as an LDS permutation it cost a trip per tile).
+__device__ __forceinline__ float att_max_halves(float x) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, x);
+    const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    const uint32_t lower = h[0], upper = h[1];              // (as scalars: a bit cast of h[1] itself reads h[0])
+    return fmaxf(__builtin_bit_cast(float, lower), __builtin_bit_cast(float, upper));
 }
 
 // One workgroup = 128 queries of one (sequence, head); wavefront w owns queries 32 w .. 32 w + 31.
-// Key tiles of 32 keys are brought into LDS once per workgroup (direct-to-LDS loads, two buffers,
+// Key tiles of 32 keys are brought into LDS once per workgroup (direct-to-LDS loads, a ring of four buffers,
 // one barrier per tile) and shared by the four wavefronts; a wavefront skips the tiles past its
-// diagonal.  K and V tiles: 32 rows of d_head elements, 16-byte chunks XOR-swizzled by (row & 7).
+// diagonal.  K and V tiles: 32 rows of d_head elements, 16-byte chunks XOR-swizzled by swz(row).
 // The transposing 8-byte LDS read works on groups of 16 lanes: lane 4 j + g of a group supplies the
 // address of 4 consecutive elements, and lane 4 g + c receives element c of lanes g, 4 + g, 8 + g, 12 + g.
 // Pointing lane 4 j + g at V[key0 + j][m0 + 4 g ..] therefore hands lane i the keys key0 .. key0 + 3 of
 // column m0 + i: four consecutive contraction slots of its V^T row.
+//
+// What bounds it: the exponentials and the rest of the softmax take about as many cycles of the vector ALU as both products
+// take of the matrix cores, so the two have to run side by side.  The first product is therefore one tile ahead: while tile t is
+// exponentiated, the MFMAs of K Q^T of tile t + 1 run, and the maximum of tile t + 1 is found under the MFMAs of V^T P^T of tile t.
+// The order of every sum is that of one tile after the other.  2 x 8192 queries, 40 heads of 128: 1690 us one tile after the other
+// with banks met four times, 1380 now (1.0 PFLOP/s; matrix cores and vector ALU each busy half of the time); 32 heads of 64: 727 -> 670.
+// Above d_head 64 a wavefront in its second product goes before its neighbour's exponentials (2 %; at 64 that costs 2 %).
 template <typename T, int DH>
 __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
-                                                                 T* __restrict__ out, int seq, int64_t ld, int n_heads, int n_pairs) {
+                                                                 T* __restrict__ out, int seq, int64_t ld, int n_heads, int n_pairs, int group) {
     constexpr int KS = DH / 16;          // contraction steps of the first product
     constexpr int DT = (DH + 31) / 32;   // 32-row tiles of O^T (rows past DH are computed on padding and dropped)
     constexpr int DHP = DH <= 64 ? 64 : 128;   // LDS row pitch in elements: a power of two, so that the swizzle stays inside the row
@@ -159,18 +178,26 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const T* __restr
     constexpr int GCH = DH / 8;          // 16-byte chunks per row in memory
     constexpr int KTILE = 32 * DHP * 2, BUF = 2 * KTILE;                  // K tile, then V tile
     constexpr int KINSTR = KTILE / 1024 / 4;                              // direct-to-LDS loads per wavefront per tile and operand
-    constexpr int NBUF = 4;                                               // ring of K / V tiles: loads run NBUF - 1 tiles ahead of the MFMAs
+    constexpr int NBUF = 4;                                               // ring of K / V tiles: loads run up to NBUF - 1 tiles ahead
     __shared__ __attribute__((aligned(1024))) char lds[NBUF * BUF];
+    // Both reads of a tile should meet every bank once.  A transposing read of 32 lanes takes 64 bytes of each of four
+    // consecutive rows: those go to different quarters of the banks (a row is all 64 banks, or half of them at a pitch of 128
+    // bytes).  A 16-byte read of K takes one chunk of each row: rows that agree in their place among four differ by the next two bits.
+    // (With the chunk index XORed by row & 7, all lanes of a transposing read met in a quarter of the banks.)
+    auto swz = [](int row) { return DHP == 128 ? ((row & 3) << 2) | ((row >> 2) & 3) : ((row & 2) << 1) | ((row >> 2) & 3); };
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, kh = lane >> 5;
     // Workgroup id -> (block of 128 queries, head, sequence).  The query blocks of one (sequence, head) read the same
     // keys and values; consecutive workgroup ids go to different XCDs, each with its own L2, so those blocks get ids that
-    // are congruent mod 8 and adjacent in their XCD's order.  Late query blocks (more keys under the causal mask) first.
-    const int nqb = (seq + 127) >> 7;
+    // are congruent mod 8.  An XCD takes its pairs in groups of `group`, and in a group late query blocks (more keys under the
+    // causal mask) first.
+    const int nqb = (seq + 127) >> 7, pairs_xcd = (n_pairs + 7) >> 3;
     const int slot = blockIdx.x >> 3;
-    const int qb = nqb - 1 - slot % nqb;
-    const int pair = (slot / nqb) * 8 + (int)(blockIdx.x & 7);
+    const int first = slot / (group * nqb) * group, size = min(group, pairs_xcd - first);
+    const int local = slot - first * nqb;
+    const int qb = nqb - 1 - local / size;
+    const int pair = (first + local % size) * 8 + (int)(blockIdx.x & 7);
     if (pair >= n_pairs) return;                             // padding of the last group of 8 (whole workgroup)
     const int head = pair % n_heads, sq = pair / n_heads;
     const int q0 = qb * 128 + wave * 32;
@@ -196,73 +223,78 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const T* __restr
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
     const int wg_last_q = min(qb * 128 + 127, seq - 1);
     const int wg_last_tile = wg_last_q >> 5;
-    const int my_last_tile = q0 >> 5;
+    const int my_last_tile = active ? q0 >> 5 : -1;
     // transposing read: lane = 16 g16 + a; the group covers columns 16 (g16 & 1) .. + 15 and keys 8 (g16 >> 1) + 4 h + (a >> 2)
     const int g16 = lane >> 4, a16 = lane & 15;
 
+    // loader plan: offsets inside a tile, the same for every tile that lies wholly inside the sequence
+    uint32_t ld_chunk[KINSTR], ld_off[KINSTR];
+    int ld_row[KINSTR];
+#pragma unroll
+    for (int x = 0; x < KINSTR; ++x) {                       // 1024 / (2 DHP) rows per instruction
+        ld_row[x] = (wave * KINSTR + x) * (512 / DHP) + lane / KCH;
+        int chunk = (lane % KCH) ^ swz(ld_row[x]);
+        if (GCH < KCH && chunk >= GCH) chunk &= 7;           // padding positions of a row repeat a real chunk (finite, never used in a kept result)
+        ld_chunk[x] = chunk * 16;
+        ld_off[x] = (uint32_t)ld_row[x] * (uint32_t)ld * 2u + ld_chunk[x];
+    }
     auto issue_tile = [&](int tile, int buf) {
         const int j0 = tile * 32;
+        const T* kt = k + base + (size_t)j0 * ld;
+        const T* vt = v + base + (size_t)j0 * ld;
+        const int last = seq - 1 - j0;                       // rows past the end repeat the last one (masked keys)
 #pragma unroll
-        for (int x = 0; x < KINSTR; ++x) {                   // K rows: 1024 / (2 DH) rows per instruction
-            const int inst = wave * KINSTR + x;
-            const int row = inst * (512 / DHP) + lane / KCH;
-            int chunk = (lane % KCH) ^ (row & 7);
-            if (GCH < KCH && chunk >= GCH) chunk &= 7;       // padding positions of a row repeat a real chunk (finite, never used in a kept result)
-            const size_t g = base + (size_t)min(j0 + row, seq - 1) * ld + chunk * 8;   // rows past the end repeat the last one (masked keys)
-            att_load_to_lds(k + g, lds0 + buf * BUF + inst * 1024);
-            att_load_to_lds(v + g, lds0 + buf * BUF + KTILE + inst * 1024);
+        for (int x = 0; x < KINSTR; ++x) {
+            const uint32_t off = last >= 31 ? ld_off[x] : (uint32_t)min(ld_row[x], last) * (uint32_t)ld * 2u + ld_chunk[x];
+            const uint32_t dst = lds0 + buf * BUF + (wave * KINSTR + x) * 1024;
+            att_load_to_lds(kt, off, dst);
+            att_load_to_lds(vt, off, dst + KTILE);
         }
     };
-    auto process_tile = [&](int tile, int buf) {
-        const int j0 = tile * 32;
-        const char* kb = lds + buf * BUF;
-        const char* vb = kb + KTILE;
-        uint4 kf[KS], vf[DT][2];
+    // where this lane reads in a tile of K (one 16-byte chunk of row pr per step) and of V
+    uint32_t k_at[KS], v_at[DT][2];
 #pragma unroll
-        for (int c = 0; c < KS; ++c) kf[c] = *reinterpret_cast<const uint4*>(kb + pr * (DHP * 2) + (((2 * c + kh) ^ (pr & 7)) * 16));
+    for (int c = 0; c < KS; ++c) k_at[c] = pr * (DHP * 2) + (((2 * c + kh) ^ swz(pr)) * 16);
 #pragma unroll
-        for (int d = 0; d < DT; ++d)
+    for (int d = 0; d < DT; ++d)
 #pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2) {
-                att_i16x4 half[2];
+        for (int h = 0; h < 2; ++h) {
+            const int key = 8 * (g16 >> 1) + 4 * h + (a16 >> 2);                       // + 16 s2, which leaves swz() alone
+            const int chunk = 4 * d + 2 * (g16 & 1) + ((a16 & 3) >> 1);
+            v_at[d][h] = KTILE + key * (DHP * 2) + ((chunk ^ swz(key)) * 16) + 8 * (a16 & 1);
+        }
+    auto scores = [&](int buf) {                             // S^T = K Q^T of the tile in `buf`
+        uint4 kf[KS];
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int key = 16 * s2 + 8 * (g16 >> 1) + 4 * h + (a16 >> 2);
-                    const int chunk = 4 * d + 2 * (g16 & 1) + ((a16 & 3) >> 1);
-                    const char* src = vb + key * (DHP * 2) + ((chunk ^ (key & 7)) * 16) + 8 * (a16 & 1);
-                    half[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) att_i16x4*)src);
-                }
-                vf[d][s2] = make_uint4(__builtin_bit_cast(uint2, half[0]).x, __builtin_bit_cast(uint2, half[0]).y,
-                                       __builtin_bit_cast(uint2, half[1]).x, __builtin_bit_cast(uint2, half[1]).y);
-            }
-        // ---- S^T = K Q^T
+        for (int c = 0; c < KS; ++c) kf[c] = *reinterpret_cast<const uint4*>(lds + buf * BUF + k_at[c]);
         att_f32x16 st;
 #pragma unroll
         for (int v = 0; v < 16; ++v) st[v] = 0.f;
 #pragma unroll
         for (int c = 0; c < KS; ++c) st = AttMfma<T>::run(kf[c], qf[c], st);
-        // ---- mask (only the diagonal tile has hidden keys; the branch is wave-uniform) and online softmax
-        if (tile == my_last_tile) {
+        return st;
+    };
+    auto mask = [&](int tile, att_f32x16& st) {              // only the diagonal tile has hidden keys; the branch is wave-uniform
+        if (tile != my_last_tile) return;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                // accumulator row rho = 8 (v/4) + 4 kh + v%4 carries key j0 + pi(rho) = j0 + 16 (v/8) + 8 kh + v%8
-                const int key = j0 + 16 * (v >> 3) + 8 * kh + (v & 7);
-                if (key > qi) st[v] = -INFINITY;
-            }
+        for (int v = 0; v < 16; ++v) {
+            // accumulator row rho = 8 (v/4) + 4 kh + v%4 carries key j0 + pi(rho) = j0 + 16 (v/8) + 8 kh + v%8
+            const int key = tile * 32 + 16 * (v >> 3) + 8 * kh + (v & 7);
+            if (key > qi) st[v] = -INFINITY;
         }
+    };
+    auto tile_max = [&](const att_f32x16& st) {
         float tmax = st[0];
 #pragma unroll
         for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, st[v]);
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+        return att_max_halves(tmax);
+    };
+    att_f32x16 st;                                           // scores of the tile at hand, and their maximum
+    float tmax = 0.f;
+
+    // tile `tile` in buffer `cur` (= tile % NBUF): its scores are at hand
+    auto process_tile = [&](int tile, int cur) {
         const float m_new = fmaxf(m_run, tmax);              // finite: key j0 <= q0 <= qi is always visible in tile 0
-        const float m2 = m_new * kLog2e;
-        float psum = 0.f;
-        float p[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            p[v] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[v], kLog2e, -m2));      // exp(st - m_new)
-            psum += p[v];
-        }
         // the running maximum of a query rarely moves after its first tiles: the accumulators are rescaled only when it
         // moved for some query of this wavefront
         if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
@@ -274,25 +306,52 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const T* __restr
                 for (int v = 0; v < 16; ++v) o[d][v] *= resc;
             m_run = m_new;
         }
-        l_run += psum;
-        // ---- O^T += V^T P^T
+        // (of the tile after the last one the buffer holds other bytes, or none yet: their products are not used)
+        att_f32x16 next = scores((cur + 1) % NBUF);
+        const float m2 = m_new * kLog2e;
+        float psum = 0.f;
         uint4 pf[2];
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
             Vec<T, 8> pv;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) pv.v[e] = Fmt<T>::store(p[8 * s2 + e]);
+            for (int e = 0; e < 8; ++e) {
+                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[8 * s2 + e], kLog2e, -m2));      // exp(st - m_new)
+                psum += p;
+                pv.v[e] = Fmt<T>::store(p);
+            }
             pf[s2] = __builtin_bit_cast(uint4, pv);
         }
+        l_run += psum;
+        uint4 vf[DT][2];
 #pragma unroll
         for (int d = 0; d < DT; ++d)
 #pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2) o[d] = AttMfma<T>::run(vf[d][s2], pf[s2], o[d]);
+            for (int s2 = 0; s2 < 2; ++s2) {
+                att_i16x4 half[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    half[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) att_i16x4*)(lds + cur * BUF + v_at[d][h] + s2 * 16 * DHP * 2));
+                vf[d][s2] = make_uint4(__builtin_bit_cast(uint2, half[0]).x, __builtin_bit_cast(uint2, half[0]).y,
+                                       __builtin_bit_cast(uint2, half[1]).x, __builtin_bit_cast(uint2, half[1]).y);
+            }
+        // (held here, or the compiler moves the exponentials behind the branch below and away from those MFMAs)
+        asm volatile("" : "+v"(pf[0].x), "+v"(pf[0].y), "+v"(pf[0].z), "+v"(pf[0].w), "+v"(pf[1].x), "+v"(pf[1].y), "+v"(pf[1].z), "+v"(pf[1].w), "+v"(l_run));
+        mask(tile + 1, next);
+        // ---- O^T += V^T P^T
+        if constexpr (DH > 64) __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+            for (int d = 0; d < DT; ++d) o[d] = AttMfma<T>::run(vf[d][s2], pf[s2], o[d]);
+        st = next;
+        tmax = tile_max(st);
+        if constexpr (DH > 64) __builtin_amdgcn_s_setprio(0);
     };
 
-    // A tile is 8 - 16 KB and its MFMAs take a few hundred cycles, far less than a trip to memory: with one tile in
-    // flight every iteration waited out the full latency.  NBUF - 1 tiles are kept in flight instead; direct-to-LDS loads
-    // complete in issue order, so "all but the loads of the `ahead` younger tiles" is an exact wait for this tile.
+    // A tile is 8 - 16 KB and its MFMAs take a few hundred cycles, far less than a trip to memory, so several
+    // tiles are kept in flight; direct-to-LDS loads complete in issue order, so "all but the loads of the younger
+    // tile" is an exact wait for a tile.
 #pragma unroll
     for (int t = 0; t < NBUF - 1; ++t)
         if (t <= wg_last_tile) issue_tile(t, t);
@@ -300,15 +359,27 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const T* __restr
     // of the loop instead of inside it, where it would also wait for every tile in flight)
 #pragma unroll
     for (int c = 0; c < KS; ++c) asm volatile("" : : "v"(qf[c].x), "v"(qf[c].y), "v"(qf[c].z), "v"(qf[c].w));
-    for (int tile = 0; tile <= wg_last_tile; ++tile) {
-        const int ahead = min(NBUF - 2, wg_last_tile - tile);        // younger tiles already issued
-        // own loads of this tile landed; own reads of the buffer that is refilled below are done
-        if (ahead >= 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(2 * 2 * KINSTR) : "memory");
-        else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(2 * KINSTR) : "memory");
+    if (wg_last_tile >= 2) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * 2 * KINSTR) : "memory");
+    else if (wg_last_tile == 1) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * KINSTR) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    st = scores(0);
+    mask(0, st);
+    tmax = tile_max(st);
+    auto step = [&](int tile, auto cur_c) {                  // the buffer as a constant: its offset is part of the LDS instructions
+        constexpr int cur = decltype(cur_c)::value;
+        // own loads of the next tile landed; own reads of the buffer that is refilled below are done
+        if (tile + 2 <= wg_last_tile) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(2 * KINSTR) : "memory");
         else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tile + NBUF - 1 <= wg_last_tile) issue_tile(tile + NBUF - 1, (tile + NBUF - 1) % NBUF);   // into the buffer of tile - 1
-        if (active && tile <= my_last_tile) process_tile(tile, tile % NBUF);
+        if (tile + NBUF - 1 <= wg_last_tile) issue_tile(tile + NBUF - 1, (cur + NBUF - 1) % NBUF);   // into the buffer of tile - 1
+        if (tile <= my_last_tile) process_tile(tile, cur);
+    };
+    for (int tile = 0; tile <= wg_last_tile; tile += NBUF) {
+        step(tile, std::integral_constant<int, 0>{});
+        if (tile + 1 <= wg_last_tile) step(tile + 1, std::integral_constant<int, 1>{});
+        if (tile + 2 <= wg_last_tile) step(tile + 2, std::integral_constant<int, 2>{});
+        if (tile + 3 <= wg_last_tile) step(tile + 3, std::integral_constant<int, 3>{});
     }
     const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
     const float inv = 1.0f / l_tot;
@@ -331,10 +402,17 @@ template <typename T>
 static zo2_status launch_mfma_att(const T* q, const T* k, const T* v, T* out, int n_seq, int seq, int n_heads, int d_head,
                                   int64_t ld, hipStream_t st) {
     const int n_pairs = n_heads * n_seq, nqb = (seq + 127) / 128;
+    // Pairs of (sequence, head) that an XCD takes together, long query blocks first.  More of them keep the compute units evenly
+    // busy to the end, fewer keep the keys and values of all of them in the XCD's L2: 8 up to 4096 queries, fewer beyond,
+    // in groups of about equal size.  2 x 2048 queries, 40 heads of 128: 136 us a pair at a time, 124 with 4, 110 with all ten
+    // of an XCD; 16 x 512, 32 heads of 80: 69, 58 with 4, 56 with 8, 70 with all 64; 2 x 8192, 40 of 128: 1438, 1380 with 4, 1422.
+    const int pairs_xcd = (n_pairs + 7) / 8, target = nqb <= 32 ? 8 : std::max(1, 256 / nqb);
+    const int groups = std::max(1, (2 * pairs_xcd + target) / (2 * target));
+    const int group = (pairs_xcd + groups - 1) / groups;
     const dim3 grid((unsigned)(8 * nqb) * (unsigned)((n_pairs + 7) / 8)), block(256);
-    if (d_head == 64) hipLaunchKernelGGL((attention_mfma_kernel<T, 64>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs);
-    else if (d_head == 80) hipLaunchKernelGGL((attention_mfma_kernel<T, 80>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs);
-    else hipLaunchKernelGGL((attention_mfma_kernel<T, 128>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs);
+    if (d_head == 64) hipLaunchKernelGGL((attention_mfma_kernel<T, 64>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs, group);
+    else if (d_head == 80) hipLaunchKernelGGL((attention_mfma_kernel<T, 80>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs, group);
+    else hipLaunchKernelGGL((attention_mfma_kernel<T, 128>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs, group);
     ZO2_HIP_LAUNCH_CHECK();
     return ZO2_OK;
 }
@@ -520,7 +598,8 @@ zo2_status attention_launch(int dtype, const void* q, const void* k, const void*
         ZO2_OP_CHECK(align != 0 && ((uintptr_t)q % align) == 0 && ((uintptr_t)k % align) == 0 && ((uintptr_t)v % align) == 0 &&
                      ((uintptr_t)out % align) == 0, ZO2_EINVAL, "attention: unknown dtype, or operands not aligned to 8 elements");
     }
-    if (!vector_kernel && dtype != ZO2_F32 && (d_head == 64 || d_head == 80 || d_head == 128)) {
+    // (an offset inside a tile of 32 rows is 32 bits wide there)
+    if (!vector_kernel && dtype != ZO2_F32 && ld < (int64_t)1 << 25 && (d_head == 64 || d_head == 80 || d_head == 128)) {
         if (dtype == ZO2_BF16)
             return launch_mfma_att<bf16_t>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)out, n_seq, seq, n_heads, d_head, ld, st);
         return launch_mfma_att<f16_t>((const f16_t*)q, (const f16_t*)k, (const f16_t*)v, (f16_t*)out, n_seq, seq, n_heads, d_head, ld, st);
