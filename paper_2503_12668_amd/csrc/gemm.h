@@ -52,7 +52,8 @@ zo2_status gemm_launch_256(const GemmArgs& a, int dtype, hipStream_t st);
 // bias, scale, ReLU and residual.  gemm_pick_splits: 1 (do not split), 2 or 4 for a launch of `nprob` problems.
 int gemm_pick_splits(int M, int N, int K, int nprob, int dtype);
 size_t gemm_splitk_workspace_bytes(int M, int N, int nprob, int splits);
-zo2_status gemm_launch_splitk(const GemmArgs& a, int dtype, int splits, void* workspace, size_t workspace_bytes, hipStream_t st);
+// sum = false: the pieces stay in the workspace, the caller adds them and finishes the values.
+zo2_status gemm_launch_splitk(const GemmArgs& a, int dtype, int splits, void* workspace, size_t workspace_bytes, hipStream_t st, bool sum = true);
 // float32 (gemm_f32.hip): tiles of `rows` = 32, 64 or 128 rows; splits > 1: a.kpiece k per piece, Y = partial sums, a plane per piece
 zo2_status gemm_launch_f32(const GemmArgs& a, int splits, int rows, hipStream_t st);
 // Split-k for float32: any number of pieces that the workspace holds.
@@ -67,7 +68,7 @@ GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes);
 // (tile heights, which do not change a sum's order, are chosen anew).  Workspace: the pieces of all of them.
 zo2_status gemm_launch_groups(const GemmArgs& a, int dtype, GemmChoice k, int groups, void* workspace, size_t workspace_bytes, hipStream_t st);
 bool gemm256_is_forced();                 // a tile height or wavefront count is forced: the large-tile kernel is meant
-zo2_status gemm_launch_mid_splitk(const GemmArgs& a, int dtype, int rows, int splits, void* workspace, size_t workspace_bytes, hipStream_t st);
+zo2_status gemm_launch_mid_splitk(const GemmArgs& a, int dtype, int rows, int splits, void* workspace, size_t workspace_bytes, hipStream_t st, bool sum = true);
 // 0 (default): the 256 x 256 kernel picks 256- or 128-row tiles per launch; 128 / 256: every launch uses that height
 void gemm256_force_tile_rows(int rows);
 void gemm256_force_waves(int waves);      // 0: chosen per launch; 4 or 8: every launch of 256-row tiles

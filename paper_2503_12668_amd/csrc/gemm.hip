@@ -412,7 +412,7 @@ GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes) {
 }
 
 // The 128 x 128 kernel with its k range in pieces
-zo2_status gemm_launch_mid_splitk(const GemmArgs& a, int dtype, int rows, int splits, void* workspace, size_t workspace_bytes, hipStream_t st) {
+zo2_status gemm_launch_mid_splitk(const GemmArgs& a, int dtype, int rows, int splits, void* workspace, size_t workspace_bytes, hipStream_t st, bool sum) {
     ZO2_OP_CHECK(a.M > 0 && a.N > 0 && a.K > 0, ZO2_EINVAL, "gemm: bad shape %d x %d x %d", a.M, a.N, a.K);
     { const zo2_status s = check_operands(a); if (s != ZO2_OK) return s; }
     GemmArgs e = a;
@@ -429,13 +429,14 @@ zo2_status gemm_launch_mid_splitk(const GemmArgs& a, int dtype, int rows, int sp
     }
     zo2_status s = gemm_launch_mid(e, dtype, rows, splits, st);
     if (s != ZO2_OK) return s;
+    if (!sum) return ZO2_OK;
     if (dtype == ZO2_BF16) launch_splitk_reduce<bf16_t>(a, part, splits, st);
     else launch_splitk_reduce<f16_t>(a, part, splits, st);
     ZO2_HIP_LAUNCH_CHECK();
     return ZO2_OK;
 }
 
-zo2_status gemm_launch_splitk(const GemmArgs& a, int dtype, int splits, void* workspace, size_t workspace_bytes, hipStream_t st) {
+zo2_status gemm_launch_splitk(const GemmArgs& a, int dtype, int splits, void* workspace, size_t workspace_bytes, hipStream_t st, bool sum) {
     if (splits <= 1) return gemm_launch(a, dtype, st);
     ZO2_OP_CHECK(dtype == ZO2_BF16 || dtype == ZO2_F16, ZO2_EINVAL, "gemm split-k: 16-bit compute formats only");
     ZO2_OP_CHECK(!a.ce_mode, ZO2_EINVAL, "gemm split-k: not with the cross-entropy epilogue");
@@ -470,6 +471,7 @@ zo2_status gemm_launch_splitk(const GemmArgs& a, int dtype, int splits, void* wo
     zo2_status s = check_operands(e);
     if (s == ZO2_OK) s = launch_large(e, dtype, st);
     if (s != ZO2_OK) return s;
+    if (!sum) return ZO2_OK;
     if (dtype == ZO2_BF16) launch_splitk_reduce<bf16_t>(a, part, splits, st);
     else launch_splitk_reduce<f16_t>(a, part, splits, st);
     ZO2_HIP_LAUNCH_CHECK();

@@ -178,6 +178,8 @@ struct zo2_ctx {
     bool stochastic;                     // theta' is stored with stochastic rounding (low-bit wire formats)
     bool serial_streams;                 // ablation: upload, compute and offload of a block run one after the other
     int ns;                              // perturbation streams of the pass in progress: 2 (step) or 1 (evaluation)
+    bool one_dir;                        // the pass in progress evaluates one direction
+    RowSum left;                         // FC2's pieces that the next LayerNorm adds up (pieces 0: none)
     float *ce_pmax, *ce_psum, *ce_lab;  // [4 ceil(V/256), 2T] x 2 and [2T]
     int ce_parts;
     float* row_loss;
@@ -862,10 +864,12 @@ static zo2_status k1_tensor(zo2_ctx* c, void* theta, int64_t n, uint32_t tid, bo
     return ZO2_OK;
 }
 
-// tensors [t0, t1) of block l whose bucket sits at `bucket`; W+- go to the scratch, tensor t0 at its start
+// tensors [t0, t1) of block l whose bucket sits at `bucket`; W+- go to the scratch, tensor t0 at its start (fc2.b, if it is not
+// negative, at element fc2_bias_at)
 static zo2_status k1_block(zo2_ctx* c, int l, char* bucket, int t0, int t1, bool perturb, uint64_t seed, float eps,
-                           hipStream_t st = nullptr, int pend = -1) {
+                           hipStream_t st = nullptr, int pend = -1, int64_t fc2_bias_at = -1) {
     if (!st) st = c->sc;
+    if (fc2_bias_at < 0) fc2_bias_at = c->offs[15] - c->offs[t0];
     K1Args a;
     k1_common(c, a, seed, eps, pend);
     a.theta = bucket; a.w_plus = c->wp; a.w_minus = c->ns == 2 ? c->wm : nullptr; a.w_off0 = c->offs[t0]; a.nseg = t1 - t0;
@@ -873,7 +877,9 @@ static zo2_status k1_block(zo2_ctx* c, int l, char* bucket, int t0, int t1, bool
     for (int k = t0; k < t1; ++k) {
         K1Seg& s = a.seg[k - t0];
         s.off = c->offs[k]; s.e0 = 0; s.n = (uint64_t)c->tn[k]; s.tensor_id = block_tid(l, k); s.scale = c->scales[s.tensor_id];
+        s.woff = k == 15 && perturb ? fc2_bias_at : c->offs[k] - a.w_off0;
     }
+    a.packed_w = 1;
     OPKS(c, ZO2_KC_K1, st, k1_launch(a, c->cfg.wire_dtype, c->cfg.compute_dtype, pend >= 0 || fused_update(c), perturb, st));
     return ZO2_OK;
 }
@@ -945,17 +951,51 @@ static zo2_status earlier_updates_block(zo2_ctx* c, int l, char* bucket, hipStre
 static size_t f32_split_workspace(const zo2_ctx* c, int T) { return 2 * (size_t)std::min(T, 128) * c->cfg.vocab * sizeof(float); }
 static int f32_pieces(const zo2_ctx* c, const GemmArgs& ga) { return gemm_f32_pick_splits(ga.M, ga.N, ga.K, ga.nprob, f32_split_workspace(c, ga.M)); }
 
-// A block projection: split along k when the launch would leave most compute units idle (few rows per stream)
-static zo2_status block_gemm(zo2_ctx* c, GemmArgs ga) {
+// A block projection: split along k when the launch would leave most compute units idle (few rows per stream).
+// left: a projection onto the residual stream that is split leaves its pieces in the workspace, described here but for the biases, for
+// the pass of the LayerNorm behind it; pieces = 0 where there is nothing left to add.
+static zo2_status block_gemm(zo2_ctx* c, GemmArgs ga, RowSum* left = nullptr) {
     const int dt = c->cfg.compute_dtype;
     ga.large_only = keep_order(c);
-    if (dt == ZO2_F32 && c->split_k >= 0) return gemm_launch_f32_splitk(ga, f32_pieces(c, ga), c->logits, f32_split_workspace(c, ga.M), c->sc);
+    const bool sum = left == nullptr;
+    auto leave = [&](const void* part, int pieces) {
+        if (left && pieces > 1) *left = RowSum{(const float*)part, pieces, (int64_t)ga.M * ga.N, (int64_t)pieces * ga.M * ga.N, nullptr, nullptr};
+    };
+    if (left) left->pieces = 0;
+    if (dt == ZO2_F32 && c->split_k >= 0) {
+        const int pieces = f32_pieces(c, ga);
+        leave(c->logits, pieces);
+        return gemm_launch_f32_splitk(ga, pieces, c->logits, f32_split_workspace(c, ga.M), c->sc, sum);
+    }
     if (c->split_k >= 0 && dt != ZO2_F32) {
         const GemmChoice k = gemm_choose(ga, dt, c->split_ws_bytes);
-        if (k.rows) return gemm_launch_mid_splitk(ga, dt, k.rows, k.splits, c->sk_ws, c->sk_ws_bytes, c->sc);
-        if (k.splits > 1) return gemm_launch_splitk(ga, dt, k.splits, c->sk_ws, c->sk_ws_bytes, c->sc);
+        if (k.rows || k.splits > 1) leave(c->sk_ws, k.splits);
+        if (k.rows) return gemm_launch_mid_splitk(ga, dt, k.rows, k.splits, c->sk_ws, c->sk_ws_bytes, c->sc, sum);
+        if (k.splits > 1) return gemm_launch_splitk(ga, dt, k.splits, c->sk_ws, c->sk_ws_bytes, c->sc, sum);
     }
     return gemm_launch(ga, dt, c->sc);
+}
+
+// Pieces of a projection onto the residual stream can wait for the LayerNorm behind it, whose pass adds them up in the order that the
+// sum's own pass would take.  That saves a launch (370 rows of 2048: 5.8 + 5.0 -> 6.1 us), but a workgroup per row is
+// the slower way where there are rows enough (1026 of 2560: 16.0 + 6.5 -> 23.9); the line is drawn between the two.
+static inline bool may_leave_sum(const zo2_ctx* c, int T) {
+    return c->sweeps == 1 && reduce_layernorm_applicable(c->cfg.d_model) && (int64_t)c->ns * T * c->cfg.d_model <= (int64_t)1 << 20;
+}
+// FC2's pieces wait for the next block's first LayerNorm, or the final one.  Between the two comes the next block's sweep, so the
+// perturbed FC2 biases must outlive it: odd blocks keep them behind the block's other copies (`after`: elements of one block's copies),
+// where the scratch has room for that.
+static inline bool may_leave_fc2(const zo2_ctx* c, int T, int64_t after, int64_t more) {
+    return c->one_dir && !c->overlap_k1 && may_leave_sum(c, T) && after + more <= c->scratch_elems;
+}
+static inline int64_t fc2_bias_room(const zo2_ctx* c) { return (c->tn[15] + kTensorAlign - 1) / kTensorAlign * kTensorAlign; }
+// h += pieces that the block before left, if any; x = LayerNorm(h)
+static zo2_status sum_and_norm(zo2_ctx* c, const void* wp, const void* bp, const void* wm, const void* bm, int T) {
+    const zo2_config& g = c->cfg;
+    if (c->left.pieces > 0) OPK(c, ZO2_KC_LN, reduce_layernorm(g.compute_dtype, c->left, c->h, wp, bp, wm, bm, c->x, c->ns * T, T, g.d_model, g.ln_eps, c->sc));
+    else OPK(c, ZO2_KC_LN, layernorm(g.compute_dtype, c->h, wp, bp, wm, bm, c->x, c->ns * T, T, g.d_model, g.ln_eps, c->sc));
+    c->left.pieces = 0;
+    return ZO2_OK;
 }
 
 struct PhaseView {       // where tensor k's perturbed copies are inside the scratch
@@ -974,9 +1014,11 @@ static zo2_status block_forward(zo2_ctx* c, int l, char* bucket, int batch, int 
     const size_t half_d = (size_t)T * d * cs, half_f = (size_t)T * f * cs;
     const bool f32 = dt == ZO2_F32;
     const int ns = c->ns;                 // 2: both perturbation streams (rows 0..T-1 and T..2T-1); 1: a single forward
+    const bool leave_fc2 = !k1_enqueued && may_leave_fc2(c, T, c->offs[ZO2_BLOCK_TENSORS], fc2_bias_room(c));
+    const int64_t bias2_at = leave_fc2 && (l & 1) ? c->offs[ZO2_BLOCK_TENSORS] : -1;
     auto phase = [&](int p) -> zo2_status {
         if (k1_enqueued || c->pb[p + 1] == c->pb[p]) return ZO2_OK;
-        zo2_status s = k1_block(c, l, bucket, c->pb[p], c->pb[p + 1], true, seed, eps);
+        zo2_status s = k1_block(c, l, bucket, c->pb[p], c->pb[p + 1], true, seed, eps, nullptr, -1, bias2_at);
         // the block's parameters are final after its last sweep: the offload may start (streamed mode)
         if (s == ZO2_OK && c->pb[p + 1] == ZO2_BLOCK_TENSORS && k1_done) HIPCHK(c, hipEventRecord(k1_done, c->sc));
         return s;
@@ -993,7 +1035,7 @@ static zo2_status block_forward(zo2_ctx* c, int l, char* bucket, int batch, int 
     if (!k1_enqueued) { zo2_status s = earlier_updates_block(c, l, bucket); if (s != ZO2_OK) return s; }
     { zo2_status s = phase(0); if (s != ZO2_OK) return s; }
     PhaseView w = view(0);
-    OPK(c, ZO2_KC_LN, layernorm(dt, c->h, w.P(0), w.P(1), w.M(0), w.M(1), c->x, ns * T, T, d, g.ln_eps, c->sc));
+    { zo2_status s = sum_and_norm(c, w.P(0), w.P(1), w.M(0), w.M(1), T); if (s != ZO2_OK) return s; }
     memset(&ga, 0, sizeof(ga));
     ga.M = T; ga.N = d; ga.K = d; ga.ldx = d; ga.ldw = d; ga.ldy = d; ga.relu = 0; ga.out_f32 = f32; ga.nprob = 3 * ns;
     char* outs[3] = {c->qb, c->kb, c->vb};
@@ -1018,20 +1060,15 @@ static zo2_status block_forward(zo2_ctx* c, int l, char* bucket, int batch, int 
         p.X = c->ctxb + s * half_d; p.W = s ? w.M(8) : w.P(8); p.bias = s ? w.M(9) : w.P(9);
         p.residual = c->h + (size_t)s * T * d; p.Y = c->h + (size_t)s * T * d; p.out_scale = 1.0f;
     }
-    // float32 in pieces, one sweep per block (no other one between the two): the pieces are summed by the LayerNorm's pass
-    const int o_pieces = f32 && c->split_k >= 0 && c->sweeps == 1 && reduce_layernorm_applicable(d) ? f32_pieces(c, ga) : 1;
-    if (o_pieces > 1) {
-        OPK(c, ZO2_KC_GEMM, gemm_launch_f32_splitk(ga, o_pieces, c->logits, f32_split_workspace(c, T), c->sc, false));
-        const RowSum rs = {c->logits, o_pieces, (int64_t)T * d, (int64_t)o_pieces * T * d, w.P(9), w.M(9)};
-        OPK(c, ZO2_KC_LN, reduce_layernorm(dt, rs, c->h, w.P(10), w.P(11), w.M(10), w.M(11), c->x, ns * T, T, d, g.ln_eps, c->sc));
-    } else {
-        OPK(c, ZO2_KC_GEMM, block_gemm(c, ga));
-    }
+    // in pieces and with one sweep per block (no other one between the two): the LayerNorm's pass adds them up
+    const bool leave_o = may_leave_sum(c, T) || (f32 && c->sweeps == 1 && reduce_layernorm_applicable(d));
+    OPK(c, ZO2_KC_GEMM, block_gemm(c, ga, leave_o ? &c->left : nullptr));
+    c->left.bias = w.P(9); c->left.bias2 = w.M(9);
 
     // ---- FFN half: h += FC2(ReLU(FC1(LN2(h))))
     { zo2_status s = phase(2); if (s != ZO2_OK) return s; }
     w = view(2);
-    if (o_pieces == 1) OPK(c, ZO2_KC_LN, layernorm(dt, c->h, w.P(10), w.P(11), w.M(10), w.M(11), c->x, ns * T, T, d, g.ln_eps, c->sc));
+    { zo2_status s = sum_and_norm(c, w.P(10), w.P(11), w.M(10), w.M(11), T); if (s != ZO2_OK) return s; }
     memset(&ga, 0, sizeof(ga));
     ga.M = T; ga.N = f; ga.K = d; ga.ldx = d; ga.ldw = d; ga.ldy = f; ga.relu = 1; ga.out_f32 = f32; ga.nprob = ns;
     for (int s = 0; s < ns; ++s) {
@@ -1044,12 +1081,14 @@ static zo2_status block_forward(zo2_ctx* c, int l, char* bucket, int batch, int 
     w = view(3);
     memset(&ga, 0, sizeof(ga));
     ga.M = T; ga.N = d; ga.K = f; ga.ldx = f; ga.ldw = f; ga.ldy = d; ga.relu = 0; ga.out_f32 = 1; ga.nprob = ns;
+    const char *bias2_p = bias2_at < 0 ? w.P(15) : c->wp + (size_t)bias2_at * cs, *bias2_m = bias2_at < 0 ? w.M(15) : c->wm + (size_t)bias2_at * cs;
     for (int s = 0; s < ns; ++s) {
         GemmProblem& p = ga.p[s];
-        p.X = c->mid + s * half_f; p.W = s ? w.M(14) : w.P(14); p.bias = s ? w.M(15) : w.P(15);
+        p.X = c->mid + s * half_f; p.W = s ? w.M(14) : w.P(14); p.bias = s ? bias2_m : bias2_p;
         p.residual = c->h + (size_t)s * T * d; p.Y = c->h + (size_t)s * T * d; p.out_scale = 1.0f;
     }
-    OPK(c, ZO2_KC_GEMM, block_gemm(c, ga));
+    OPK(c, ZO2_KC_GEMM, block_gemm(c, ga, leave_fc2 ? &c->left : nullptr));
+    c->left.bias = bias2_p; c->left.bias2 = bias2_m;
     return ZO2_OK;
 }
 
@@ -1144,9 +1183,11 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
     const size_t cs = c->csz;
     const size_t half_d = (size_t)T * d * cs, half_f = (size_t)T * f * cs;
     { zo2_status s = earlier_updates_block(c, l, bucket); if (s != ZO2_OK) return s; }
-    int64_t voff[ZO2_BLOCK_TENSORS] = {0};
+    int64_t voff[ZO2_BLOCK_TENSORS] = {0}, vec_elems = 0;
+    for (const int k : kVecTensors) vec_elems += (c->tn[k] + kTensorAlign - 1) / kTensorAlign * kTensorAlign;
+    const bool leave_fc2 = may_leave_fc2(c, T, vec_elems, vec_elems);
     {
-        int64_t o = 0;
+        int64_t o = leave_fc2 && (l & 1) ? vec_elems : 0;
         for (const int k : kVecTensors) {
             voff[k] = o;
             o += (c->tn[k] + kTensorAlign - 1) / kTensorAlign * kTensorAlign;
@@ -1176,7 +1217,7 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
     };
 
     // ---- attention half: h += O(Attn(LN1(h)))
-    OPK(c, ZO2_KC_LN, layernorm(dt, c->h, VP(0), VP(1), VM(0), VM(1), c->x, 2 * T, T, d, g.ln_eps, c->sc));
+    { zo2_status s = sum_and_norm(c, VP(0), VP(1), VM(0), VM(1), T); if (s != ZO2_OK) return s; }
     common(d, d, d, d, 0, 0, 3);
     char* outs[3] = {c->qb, c->kb, c->vb};
     for (int t = 0; t < 3; ++t) {
@@ -1214,7 +1255,8 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
         p.Xp = c->mid; p.Xm = c->mid + half_f; p.theta = TH(14); p.bias_p = VP(15); p.bias_m = VM(15);
         p.res_p = c->h; p.res_m = c->h + (size_t)T * d; p.Yp = c->h; p.Ym = c->h + (size_t)T * d; p.out_scale = 1.0f; p.tensor_id = block_tid(l, 14);
     }
-    OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, c->sk_ws, c->sk_ws_bytes, c->sc));
+    OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, c->sk_ws, c->sk_ws_bytes, c->sc, !leave_fc2));
+    if (leave_fc2) c->left = RowSum{sa.partial, sa.splits, 2 * (int64_t)T * d, (int64_t)T * d, VP(15), VM(15)};
     return ZO2_OK;
 }
 
@@ -1305,6 +1347,8 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
     if (batch <= 0 || seq <= 0 || seq > g.max_pos) return fail(c, ZO2_EINVAL, "%s: batch %d, seq %d (max_pos %d)", who, batch, seq, g.max_pos);
     if ((int64_t)batch * seq > (1 << 24)) return fail(c, ZO2_EINVAL, "%s: too many tokens", who);
     c->ns = ns;
+    c->one_dir = ndirs == 1;
+    c->left = RowSum{};
     const int T = batch * seq;
     for (int i = 0; i < T; ++i) {
         if (tokens[i] < 0 || tokens[i] >= g.vocab) return fail(c, ZO2_EINVAL, "%s: token %d at %d outside [0, %d)", who, tokens[i], i, g.vocab);
@@ -1446,7 +1490,7 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
             for (int k = 0; k + 1 < c->n_pend; ++k) { zo2_status s = k1_final_ln(c, false, 0, 0.f, k); if (s != ZO2_OK) return s; }
         { zo2_status s = k1_final_ln(c, true, seed, eps); if (s != ZO2_OK) return s; }
         const size_t boff = (size_t)c->fln_off_b * c->csz;
-        OPK(c, ZO2_KC_LN, layernorm(dt, c->h, c->fln_wp, c->fln_wp + boff, c->fln_wm, c->fln_wm + boff, c->x, ns * T, T, d, g.ln_eps, c->sc));
+        { zo2_status s = sum_and_norm(c, c->fln_wp, c->fln_wp + boff, c->fln_wm, c->fln_wm + boff, T); if (s != ZO2_OK) return s; }
         // few tokens: the sweep only updates the vocabulary matrix, the head perturbs it in its loader (c->fuse rules overlap_k1 out)
         const bool loader_head = c->fuse && ns == 2 && c->fused_ce && T <= 128;
         if (loader_head) {

@@ -127,6 +127,32 @@ def test_float32_projections_in_pieces_give_the_same_bits_under_every_organisati
     assert runs["uncut"][0] != runs["1"][0] or any(not np.array_equal(runs["uncut"][1][n], runs["1"][1][n]) for n in runs["1"][1])
 
 
+# the last two: a scratch without room for a second copy of the biases, and more rows than are worth it
+@pytest.mark.parametrize("wire,compute,d,vocab,batch,seq,layers", [
+    ("bf16", "bf16", 1024, 13060, 5, 37, 3), ("f16", "f16", 1024, 13060, 1, 150, 2), ("bf16", "bf16", 1024, 13060, 1, 13, 3), ("f32", "f32", 768, 9476, 1, 40, 3),
+    ("f32", "f32", 768, 212, 1, 40, 3), ("bf16", "bf16", 1024, 13060, 3, 200, 2)])
+def test_pieces_that_wait_for_the_next_layernorm_give_the_same_bits(wire, compute, d, vocab, batch, seq, layers):
+    """The second FFN projection's pieces are added up by the next block's first LayerNorm, or the final one (odd and even numbers of
+    blocks), on every kernel that leaves pieces; with a sweep per tensor group they never wait.  Steps and an evaluation, bit for bit."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=layers, d_model=d, n_heads=d // 64, d_ffn=4 * d, vocab=vocab, max_pos=256)
+    P = si.make_weights(cfg, seed=11, std=0.05, ln_jitter=True)
+    tok = si.make_tokens(vocab, batch, seq, seed=12)
+    lab = si.next_token_labels(tok)
+    runs = []
+    for sweeps in (1, 4):
+        ctx = b.Zo2Context(cfg, P, wire=wire, compute=compute, arena_bytes=1 << 30)
+        ctx.set_scratch_plan(sweeps)
+        r = [tuple(map(float, ctx.step(tok, lab, 5 + j, 1e-3, 1e-5))) for j in range(3)] + [float(ctx.eval(tok, lab))]
+        assert ctx.plan()["sweeps_per_block"] == sweeps
+        ctx.flush(); ctx.sync_to_host()
+        runs.append((r, ctx.parameters()))
+        ctx.close()
+    assert runs[0][0] == runs[1][0]
+    for n in runs[0][1]:
+        assert np.array_equal(runs[0][1][n], runs[1][1][n]), n
+
+
 def test_budget_too_small_for_whole_block_scratch_falls_back_to_per_group():
     """The planner's own choice: a budget that cannot hold 3 slots next to a whole-block scratch set, but can next to
     a per-group set, gives the per-group plan (and the same bits); one notch lower is ZO2_EBUDGET."""
