@@ -224,7 +224,7 @@ zo2_status zo2_set_scratch_plan(zo2_ctx* ctx, int32_t sweeps);
  * whenever the shapes allow (16-bit storage equal to the compute format, d_model and d_ffn multiples of 64, at most
  * 256 tokens per stream); mode -1: never.  The two paths give the same W+- bit for bit; their projections add the
  * same products in a different order (results agree to float32 rounding, each path is deterministic by itself).
- * Evaluation passes (zo2_eval) always take the sweep-kernel path.  Takes effect at the next step. */
+ * Evaluation passes (zo2_eval) have nothing to perturb: they read the weights in place, or a sweep's converted copies.  Takes effect at the next step. */
 zo2_status zo2_set_loader_fusion(zo2_ctx* ctx, int32_t mode);
 /* *active = 1 if the last plan lets the projections perturb in their loader. */
 zo2_status zo2_get_loader_fusion(const zo2_ctx* ctx, int32_t* active);
