@@ -153,6 +153,18 @@ __device__ __forceinline__ float att_max_halves(float x) {
     return fmaxf(__builtin_bit_cast(float, lower), __builtin_bit_cast(float, upper));
 }
 
+// Workgroup id -> (block of queries, pair of sequence and head).  The query blocks of one pair read the same
+// keys and values; consecutive workgroup ids go to different XCDs, each with its own L2, so those blocks get ids that
+// are congruent mod 8.  An XCD takes its pairs in groups of `group`, and in a group late query blocks (more keys under the
+// causal mask) first.
+__device__ __forceinline__ void att_place(int nqb, int n_pairs, int group, int& qb, int& pair) {
+    const int pairs_xcd = (n_pairs + 7) >> 3, slot = blockIdx.x >> 3;
+    const int first = slot / (group * nqb) * group, size = min(group, pairs_xcd - first);
+    const int local = slot - first * nqb;
+    qb = nqb - 1 - local / size;
+    pair = (first + local % size) * 8 + (int)(blockIdx.x & 7);
+}
+
 // One workgroup = 128 queries of one (sequence, head); wavefront w owns queries 32 w .. 32 w + 31.
 // Key tiles of 32 keys are brought into LDS once per workgroup (direct-to-LDS loads, a ring of four buffers,
 // one barrier per tile) and shared by the four wavefronts; a wavefront skips the tiles past its
@@ -188,16 +200,9 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const T* __restr
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 31, kh = lane >> 5;
-    // Workgroup id -> (block of 128 queries, head, sequence).  The query blocks of one (sequence, head) read the same
-    // keys and values; consecutive workgroup ids go to different XCDs, each with its own L2, so those blocks get ids that
-    // are congruent mod 8.  An XCD takes its pairs in groups of `group`, and in a group late query blocks (more keys under the
-    // causal mask) first.
-    const int nqb = (seq + 127) >> 7, pairs_xcd = (n_pairs + 7) >> 3;
-    const int slot = blockIdx.x >> 3;
-    const int first = slot / (group * nqb) * group, size = min(group, pairs_xcd - first);
-    const int local = slot - first * nqb;
-    const int qb = nqb - 1 - local / size;
-    const int pair = (first + local % size) * 8 + (int)(blockIdx.x & 7);
+    const int nqb = (seq + 127) >> 7;
+    int qb, pair;
+    att_place(nqb, n_pairs, group, qb, pair);
     if (pair >= n_pairs) return;                             // padding of the last group of 8 (whole workgroup)
     const int head = pair % n_heads, sq = pair / n_heads;
     const int q0 = qb * 128 + wave * 32;
@@ -398,17 +403,22 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const T* __restr
     }
 }
 
+// Pairs of (sequence, head) that an XCD takes together, long query blocks first.  More of them keep the compute units evenly
+// busy to the end, fewer keep the keys and values of all of them in the XCD's L2: 8 up to 4096 queries, fewer beyond,
+// in groups of about equal size (nqb: blocks of 128 queries).  2 x 2048 queries, 40 heads of 128: 136 us a pair at a time, 124 with 4, 110 with
+// all ten of an XCD; 16 x 512, 32 heads of 80: 69, 58 with 4, 56 with 8, 70 with all 64; 2 x 8192, 40 of 128: 1438, 1380 with 4, 1422.
+// float32, a pair at a time -> this: 2 x 2048, 12 heads of 64: 308 -> 199; 4 x 512, 32 of 80: 112 -> 88; 4 x 384, 32 of 64: 50 -> 46.
+static int att_group(int n_pairs, int nqb) {
+    const int pairs_xcd = (n_pairs + 7) / 8, target = nqb <= 32 ? 8 : std::max(1, 256 / nqb);
+    const int groups = std::max(1, (2 * pairs_xcd + target) / (2 * target));
+    return (pairs_xcd + groups - 1) / groups;
+}
+
 template <typename T>
 static zo2_status launch_mfma_att(const T* q, const T* k, const T* v, T* out, int n_seq, int seq, int n_heads, int d_head,
                                   int64_t ld, hipStream_t st) {
     const int n_pairs = n_heads * n_seq, nqb = (seq + 127) / 128;
-    // Pairs of (sequence, head) that an XCD takes together, long query blocks first.  More of them keep the compute units evenly
-    // busy to the end, fewer keep the keys and values of all of them in the XCD's L2: 8 up to 4096 queries, fewer beyond,
-    // in groups of about equal size.  2 x 2048 queries, 40 heads of 128: 136 us a pair at a time, 124 with 4, 110 with all ten
-    // of an XCD; 16 x 512, 32 heads of 80: 69, 58 with 4, 56 with 8, 70 with all 64; 2 x 8192, 40 of 128: 1438, 1380 with 4, 1422.
-    const int pairs_xcd = (n_pairs + 7) / 8, target = nqb <= 32 ? 8 : std::max(1, 256 / nqb);
-    const int groups = std::max(1, (2 * pairs_xcd + target) / (2 * target));
-    const int group = (pairs_xcd + groups - 1) / groups;
+    const int group = att_group(n_pairs, nqb);
     const dim3 grid((unsigned)(8 * nqb) * (unsigned)((n_pairs + 7) / 8)), block(256);
     if (d_head == 64) hipLaunchKernelGGL((attention_mfma_kernel<T, 64>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs, group);
     else if (d_head == 80) hipLaunchKernelGGL((attention_mfma_kernel<T, 80>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs, group);
@@ -423,7 +433,7 @@ static zo2_status launch_mfma_att(const T* q, const T* k, const T* v, T* out, in
 // their way meanwhile: 8 KB (d_head 64) per 1024 QT cycles of MFMA, which the caches deliver without a trip through LDS,
 // and without barriers small launches spread over as many compute units as they have groups of 16 queries.  The
 // vector-ALU kernel has one wavefront per 64 queries, which walk their keys one by one: 62 us at 1 x 64 tokens (24 pairs of
-// sequence and head) against 7 here, 365 us at 2 x 384 (128 pairs) against 74.
+// sequence and head) against 7 here, 365 us at 2 x 384 (128 pairs) against 46.
 //   S^T = K Q^T    lane (r, kg) supplies key row r / query row r at the d_head positions 16 c + 4 kg .. + 3 with one 16-byte
 //                  load: element t of it is contraction slot kg of issue t, the same positions for both operands;
 //   O^T += V^T P^T  accumulator element e of S^T is key 4 kg + e of query r: contraction slot kg of issue e, where it is used
@@ -435,15 +445,13 @@ typedef float att_f32x2 __attribute__((ext_vector_type(2)));
 
 template <int DH, int QT>
 __global__ __launch_bounds__(64) void attention_f32_mfma_kernel(const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
-                                                                float* __restrict__ out, int seq, int64_t ld, int n_heads, int n_pairs) {
+                                                                float* __restrict__ out, int seq, int64_t ld, int n_heads, int n_pairs, int group) {
     static_assert(DH % 16 == 0 && DH % 64 != 48, "16-column tiles of the output: groups of four, then one or two");
     constexpr int DT = DH / 16, G4 = DH / 64, REM = DT % 4;      // tiles; groups of four; the rest
     const int lane = threadIdx.x, r = lane & 15, kg = lane >> 4;
-    // workgroup id -> (query block, head, sequence): as in attention_mfma_kernel
     const int nqb = (seq + 16 * QT - 1) / (16 * QT);
-    const int slot = blockIdx.x >> 3;
-    const int qb = nqb - 1 - slot % nqb;
-    const int pair = (slot / nqb) * 8 + (int)(blockIdx.x & 7);
+    int qb, pair;
+    att_place(nqb, n_pairs, group, qb, pair);
     if (pair >= n_pairs) return;
     const int head = pair % n_heads, sq = pair / n_heads;
     const int q0 = qb * 16 * QT;
@@ -565,7 +573,7 @@ template <int DH, int QT>
 static void launch_f32_att(const float* q, const float* k, const float* v, float* out, int n_seq, int seq, int n_heads, int64_t ld, hipStream_t st) {
     const int n_pairs = n_heads * n_seq, nqb = (seq + 16 * QT - 1) / (16 * QT);
     const dim3 grid((unsigned)(8 * nqb) * (unsigned)((n_pairs + 7) / 8)), block(64);
-    hipLaunchKernelGGL((attention_f32_mfma_kernel<DH, QT>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs);
+    hipLaunchKernelGGL((attention_f32_mfma_kernel<DH, QT>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs, att_group(n_pairs, (seq + 127) / 128));
 }
 
 template <typename T>
@@ -606,9 +614,11 @@ zo2_status attention_launch(int dtype, const void* q, const void* k, const void*
     }
     const bool f32_fits = (int64_t)(n_seq * (int64_t)n_heads + 8) * ((seq + 15) / 16) < (int64_t)1 << 25;      // its grid of 64-thread workgroups
     if (!vector_kernel && dtype == ZO2_F32 && f32_fits && (d_head == 16 || d_head == 32 || d_head == 64 || d_head == 80 || d_head == 128)) {
-        // 32 queries per wavefront read the keys half as often; 16 where that would leave SIMDs without a wavefront, and beyond
-        // d_head 64, where a wavefront's registers hold no more
-        const bool wide = (int64_t)n_seq * n_heads * ((seq + 31) / 32) >= 4 * (int64_t)device_cu_count();
+        // 16 queries per wavefront: a tile's loads take longer than its products, and more wavefronts per SIMD cover each other's.  32
+        // read the keys half as often, which counts where there are wavefronts in any case (d_head 64, 32 heads, 32 -> 16 queries, us:
+        // 4 x 384 63 -> 46, 2 x 1024 139 -> 128, 8 x 1024 422 against 428, 4 x 2048 749 against 784; 32 x 256 of 32 91 -> 88).
+        // Beyond d_head 64 a wavefront's registers hold no more than 16.
+        const bool wide = (int64_t)n_seq * n_heads * ((seq + 31) / 32) >= 32 * (int64_t)device_cu_count();
         const float *qf = (const float*)q, *kf = (const float*)k, *vf = (const float*)v;
         float* of = (float*)out;
 #define ZO2_ATT_CASE(D, QT) launch_f32_att<D, QT>(qf, kf, vf, of, n_seq, seq, n_heads, ld, st)
