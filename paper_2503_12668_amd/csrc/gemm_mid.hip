@@ -37,8 +37,8 @@ template <> struct MidMfma<f16_t> {
 static constexpr int kMidBN = 128, kMidBK = 64;
 template <int BM> struct MidTile {
     static constexpr int kStage = (BM + kMidBN) * kMidBK * 2;      // 32 KB / 24 KB
-    static constexpr int kStages = 4;        
-    static constexpr int kLds = kStage * kStages;                  // 160 KB / 144 KB
+    static constexpr int kStages = 4;
+    static constexpr int kLds = kStage * kStages;                  // 128 KB / 96 KB
 };
 
 // source address = wave-uniform base + per-lane 32-bit byte offset
