@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "gemm.h"
+#include "gemm_f32_index.h"
 
 namespace zo2 {
 
@@ -168,15 +169,14 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(const GemmArgs a
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         const int row = tid / 4 + 64 * (c & 1);
-        g[c] = (c < 2 ? W + (size_t)min(n0 + row, a.N - 1) * a.ldw : X + (size_t)min(m0 + row, a.M - 1) * a.ldx) + kc4;
+        g[c] = c < 2 ? W + (size_t)min(n0 + row, a.N - 1) * a.ldw : X + (size_t)min(m0 + row, a.M - 1) * a.ldx;
         l[c] = ((c < 2 ? BM : 0) + row) * ROW + (((tid & 3) >> 1) ^ swz(row)) * 16 + (tid & 1) * 8;
     }
     const int nk = (K + BK - 1) / BK;
     v4f_t rg[2][4];
     auto load_slab = [&](v4f_t (&to)[4], int kt) {         // past the last slab: the last one again, which nobody reads
-        const int k0 = min(kt, nk - 1) * BK;
-        const bool in = !KTAIL || k0 + kc4 < K;            // K is a multiple of 8: a chunk is inside the row or entirely past its end
-        const int at = in ? k0 : 0;
+        const bool in = !KTAIL || f32_chunk_inside(kt, nk, BK, kc4, K);      // K is a multiple of 8: a chunk is inside the row or entirely past its end
+        const int at = KTAIL ? f32_chunk_at(kt, nk, BK, kc4, K) : min(kt, nk - 1) * BK + kc4;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             to[c] = *reinterpret_cast<const v4f_t*>(g[c] + at);
