@@ -43,7 +43,9 @@ struct GemmArgs {
 static constexpr int kStampWorkgroup = 37;      // the workgroup that writes them
 
 // Y = act((X W^T + bias) * out_scale) + residual for every problem; float32 accumulation.
-zo2_status gemm_launch(const GemmArgs& a, int dtype, hipStream_t st);
+// of_rows > M: rows of a matrix of that many, on the kernel that all of them at once would run on (the kernel, not its
+// tiles' height, is what the order of a sum depends on: rows in chunks then have the bits of one launch).
+zo2_status gemm_launch(const GemmArgs& a, int dtype, hipStream_t st, int of_rows = 0);
 // the 256 x 256 x 64 kernel (bf16 / fp16, K % 128 == 0); gemm_launch picks it for large problems
 zo2_status gemm_launch_256(const GemmArgs& a, int dtype, hipStream_t st);
 // Split-k for launches that leave most compute units idle (few rows per stream): each problem is cut into `splits` pieces

@@ -217,9 +217,10 @@ static zo2_status check_operands(const GemmArgs& a) {
     return ZO2_OK;
 }
 
-zo2_status gemm_launch(const GemmArgs& a, int dtype, hipStream_t st) {
+zo2_status gemm_launch(const GemmArgs& a, int dtype, hipStream_t st, int of_rows) {
     ZO2_OP_CHECK(a.M >= 0 && a.N >= 0 && a.K > 0, ZO2_EINVAL, "gemm: bad shape %d x %d x %d", a.M, a.N, a.K);
     if (a.M == 0 || a.N == 0 || a.nprob == 0) return ZO2_OK;
+    const int all_rows = std::max(a.M, of_rows);
     { const zo2_status s = check_operands(a); if (s != ZO2_OK) return s; }
     // cross-entropy mode has no output matrix (Y may be NULL): only the 256 x 256 kernel implements it, so every
     // other path must be refused before anything is launched
@@ -229,11 +230,13 @@ zo2_status gemm_launch(const GemmArgs& a, int dtype, hipStream_t st) {
         ZO2_OP_CHECK(a.out_f32, ZO2_EINVAL, "gemm: the float32 kernel writes float32 output");
         GemmArgs f = a;
         f.kpiece = a.K;
-        return gemm_launch_f32(f, 1, f32_pick(a.M, a.N, a.K, a.nprob, 1).rows, st);
+        return gemm_launch_f32(f, 1, f32_pick(all_rows, a.N, a.K, a.nprob, 1).rows, st);
     }
-    const GemmChoice k = gemm_choose(a, dtype, 0);
-    if (!k.rows) return launch_large(a, dtype, st);
     GemmArgs m = a;
+    m.M = all_rows;
+    const GemmChoice k = gemm_choose(m, dtype, 0);
+    if (!k.rows) return launch_large(a, dtype, st);
+    m.M = a.M;
     m.kpiece = a.K;
     return gemm_launch_mid(m, dtype, k.rows, 1, st);
 }

@@ -1573,7 +1573,8 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
                     p.X = c->x + ((size_t)s * T + r0) * d * c->csz; p.W = s ? head_wm : head_wp; p.bias = nullptr; p.residual = nullptr;
                     p.Y = c->logits + (size_t)s * R * g.vocab; p.out_scale = 1.0f;
                 }
-                OPK(c, ZO2_KC_GEMM, gemm_launch(ga, dt, c->sc));
+                // (the kernel of all T rows: R is the budget's, and the budget is not to show in a loss)
+                OPK(c, ZO2_KC_GEMM, gemm_launch(ga, dt, c->sc, T));
                 for (int s = 0; s < ns; ++s)
                     OPK(c, ZO2_KC_CE, cross_entropy_rows(c->logits + (size_t)s * R * g.vocab, g.vocab, c->d_labels, rows, s * T + r0, T, g.vocab, c->row_loss, c->sc, keep_order(c)));
             }

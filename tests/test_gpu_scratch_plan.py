@@ -269,3 +269,33 @@ def test_fp8_wire_at_30b_width_one_block_matches_oracle():
     print("oracle", a, flush=True)
     assert abs(float(g[0]) - float(a[0])) <= 2e-2 * abs(float(a[0]))
     assert abs(float(g[1]) - float(a[1])) <= 2e-2 * abs(float(a[1]))
+
+
+@pytest.mark.parametrize("wire,compute,d,ffn,seq", [("f32", "f32", 256, 512, 144), ("f32", "f32", 256, 512, 137), ("bf16", "bf16", 192, 768, 144), ("f16", "f16", 320, 640, 129)])
+def test_heads_logits_in_chunks_give_the_bits_of_one_piece(wire, compute, d, ffn, seq):
+    """Where the head writes logits (float32; 16-bit widths that its fused kernel does not take), the budget says how many rows at a time.
+    512 rows and a few left over, on which alone another kernel would run, against all at once: steps, a round, an evaluation, bit for bit."""
+    b = _b()
+    vocab, batch = 12068, 4
+    cfg = si.tiny_config(n_layers=2, d_model=d, n_heads=d // 64, d_ffn=ffn, vocab=vocab, max_pos=160)
+    P = si.make_weights(cfg, seed=11, std=0.2, ln_jitter=True)
+    tok = si.make_tokens(vocab, batch, seq, seed=12)
+    lab = si.next_token_labels(tok)
+    lab[:3] = -100                             # losses of the rows left over alone: a mean over all rows would round their late digits away
+    lab[3, :-4] = -100
+    runs, launches = [], []
+    for rows in (512, 640):                    # a chunk: an eighth of the budget, in 128 rows of both streams
+        ctx = b.Zo2Context(cfg, P, wire=wire, compute=compute, arena_bytes=1 << 30)
+        ctx.set_resident_budget(64 * vocab * rows + 1000)
+        ctx.set_profiling(["ce"])
+        r = [tuple(map(float, ctx.step(tok, lab, 5 + j, 1e-3, 1e-5))) for j in range(2)]
+        launches.append(ctx.kernel_times()["ce"][1])
+        r += [tuple(map(float, x)) for x in ctx.step_multi(tok, lab, [8, 9], 1e-3, 1e-5)] + [float(ctx.eval(tok, lab))]
+        assert ctx.plan()["resident"]
+        ctx.flush(); ctx.sync_to_host()
+        runs.append((r, ctx.parameters()))
+        ctx.close()
+    assert launches[0] == launches[1] + 2      # a cross-entropy pass per stream and chunk
+    assert runs[0][0] == runs[1][0]
+    for n in runs[0][1]:
+        assert np.array_equal(runs[0][1][n], runs[1][1][n]), n
