@@ -365,6 +365,10 @@ int32_t zo2_op_gemm_split_k_pieces(int32_t dtype, int32_t M, int32_t N, int32_t 
  * take, the general kernel), cut into *pieces along k; 64 or 128: 128-wide tiles of that height, *pieces along k.
  * workspace_bytes: what is there for partial sums (zo2_op_gemm calls have 0). */
 zo2_status zo2_op_gemm_choice(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t nprob, size_t workspace_bytes, int32_t* rows, int32_t* pieces);
+/* How a launch of `nprob` problems of this shape, whole along k, is tiled: float32 in tiles of rows[0] rows; 16-bit dtypes, on the large
+ * tiles, in tiles of rows[0] rows and, where rows[1] is not 0, in a second launch of tiles of rows[1] rows, which has the problems from
+ * *problems on, or of every problem the columns from *columns on (the other of the two is 0).  For tests. */
+zo2_status zo2_op_gemm_tiles(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t nprob, int32_t rows[2], int32_t* problems, int32_t* columns);
 /* zo2_op_gemm on the 128-wide tiles (for tests and measurements; zo2_op_gemm and zo2_step take them where zo2_op_gemm_choice says):
  * rows = 64 or 128; the k range in `pieces` >= 1 of a multiple of 64, none empty, their float32 sums in `workspace` (device,
  * 16-byte aligned, M * N * 4 bytes per piece; unused and may be NULL for one), added in piece order.  16-bit dtypes, K % 64 == 0,

@@ -75,6 +75,11 @@ zo2_status gemm_launch_mid_splitk(const GemmArgs& a, int dtype, int rows, int sp
 void gemm256_force_tile_rows(int rows);
 void gemm256_force_waves(int waves);      // 0: chosen per launch; 4 or 8: every launch of 256-row tiles
 bool gemm256_applicable(const GemmArgs& a, int dtype);
+// How the large kernel runs a launch: tiles of rows[0] rows, and where it is two launches rows[1] for the problems from `probs` on, or
+// for the tile columns (of 256) from `cols` on of every problem.
+struct GemmTiles { int rows[2], probs, cols; };
+GemmTiles gemm256_tiles(const GemmArgs& a);
+int gemm_f32_tile_rows(int M, int N, int K, int nprob);      // of an uncut float32 launch
 double gemm256_tile_cost(int rows);       // time of a tile of 256, 192 or 128 rows, in 256-row ones
 // 128 x 128 (or 64 x 128) tiles with a deep ring of slabs, for launches of a few hundred rows
 bool gemm_mid_applicable(const GemmArgs& a, int dtype);

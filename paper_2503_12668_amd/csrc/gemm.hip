@@ -194,6 +194,8 @@ static F32Pick f32_pick(int M, int N, int K, int nprob, int max_splits) {
     return best;
 }
 
+int gemm_f32_tile_rows(int M, int N, int K, int nprob) { return f32_pick(M, N, K, nprob, 1).rows; }
+
 // the large-tile kernel, or the general one for the shapes it does not take
 static zo2_status launch_large(const GemmArgs& a, int dtype, hipStream_t st) {
     if (gemm256_applicable(a, dtype)) return gemm_launch_256(a, dtype, st);

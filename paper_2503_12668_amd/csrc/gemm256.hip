@@ -772,14 +772,9 @@ static zo2_status launch_one_height(const GemmArgs& a, int dtype, hipStream_t st
     return ZO2_EINVAL;
 }
 
-zo2_status gemm_launch_256(const GemmArgs& a, int dtype, hipStream_t st) {
-    if (!gemm256_applicable(a, dtype)) {
-        set_op_error("gemm256: shape or alignment not supported by the 256 x 256 kernel");
-        return ZO2_EINVAL;
-    }
-    const LaunchCut cut = pick_cut(a);
-    if (!cut.probs && !cut.cols) return launch_one_height(a, dtype, st);
-    GemmArgs first = a, rest = a;
+// the two launches that a cut stands for
+static void cut_launch(const GemmArgs& a, LaunchCut cut, GemmArgs& first, GemmArgs& rest) {
+    first = rest = a;
     if (cut.probs) {
         first.nprob = cut.probs;
         rest.nprob = a.nprob - cut.probs;
@@ -796,6 +791,25 @@ zo2_status gemm_launch_256(const GemmArgs& a, int dtype, hipStream_t st) {
             p.Y = reinterpret_cast<char*>(p.Y) + n0 * osz;
         }
     }
+}
+
+GemmTiles gemm256_tiles(const GemmArgs& a) {
+    const LaunchCut cut = pick_cut(a);
+    if (!cut.probs && !cut.cols) return {{pick_tile_rows(a), 0}, 0, 0};
+    GemmArgs first, rest;
+    cut_launch(a, cut, first, rest);
+    return {{pick_tile_rows(first), pick_tile_rows(rest)}, cut.probs, cut.cols};
+}
+
+zo2_status gemm_launch_256(const GemmArgs& a, int dtype, hipStream_t st) {
+    if (!gemm256_applicable(a, dtype)) {
+        set_op_error("gemm256: shape or alignment not supported by the 256 x 256 kernel");
+        return ZO2_EINVAL;
+    }
+    const LaunchCut cut = pick_cut(a);
+    if (!cut.probs && !cut.cols) return launch_one_height(a, dtype, st);
+    GemmArgs first, rest;
+    cut_launch(a, cut, first, rest);
     const zo2_status s = launch_one_height(first, dtype, st);
     return s != ZO2_OK ? s : launch_one_height(rest, dtype, st);
 }

@@ -1929,6 +1929,19 @@ extern "C" zo2_status zo2_op_gemm_choice(int32_t dtype, int32_t M, int32_t N, in
     return ZO2_OK;
 }
 
+extern "C" zo2_status zo2_op_gemm_tiles(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t nprob, int32_t rows[2], int32_t* problems, int32_t* columns) {
+    ZO2_OP_CHECK((dtype == ZO2_F32 || dtype == ZO2_BF16 || dtype == ZO2_F16) && M > 0 && N > 0 && K > 0 && nprob >= 1 && nprob <= GemmArgs::kMaxProblems && rows && problems &&
+                 columns, ZO2_EINVAL, "gemm_tiles: compute dtypes and positive sizes");
+    GemmArgs a;
+    memset(&a, 0, sizeof(a));
+    a.M = M; a.N = N; a.K = K; a.ldx = K; a.ldw = K; a.ldy = N; a.out_f32 = 1; a.nprob = nprob;
+    ZO2_OP_CHECK(dtype == ZO2_F32 || gemm256_applicable(a, dtype), ZO2_EINVAL, "gemm_tiles: not a shape of the large tiles");
+    const GemmTiles t = dtype == ZO2_F32 ? GemmTiles{{gemm_f32_tile_rows(M, N, K, nprob), 0}, 0, 0} : gemm256_tiles(a);
+    rows[0] = t.rows[0]; rows[1] = t.rows[1];
+    *problems = t.probs; *columns = t.cols * 256;
+    return ZO2_OK;
+}
+
 extern "C" zo2_status zo2_op_gemm_wide128(int32_t dtype, int32_t M, int32_t N, int32_t K, const void* X, int64_t ldx, const void* W, int64_t ldw,
                                           const void* bias, const float* residual, void* Y, int32_t out_dtype, int64_t ldy, float out_scale,
                                           int32_t relu, int32_t rows, int32_t pieces, void* workspace, size_t workspace_bytes, void* stream) {
