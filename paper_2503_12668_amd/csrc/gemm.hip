@@ -170,22 +170,26 @@ static zo2_status launch_mfma(const GemmArgs& a, hipStream_t st) {
 // Tile height and k pieces of a float32 launch, by a small cost model in ns: what the kernels of gemm_f32.hip were measured at.  All of
 // them run two workgroups per compute unit, so per slab of 32 k a round of two tiles a unit costs 2860 (128 rows), 1800 (64) or 1050 (32),
 // a launch or last round of one tile a unit 1120, 780 - 950 (nearly empty chip - full one) or 520 - 740, the launch itself 5300.  Pieces add
-// the write and the re-read of their partial sums at 4 TB/s and a second launch (4 us).
+// the write and the re-read of their partial sums at 4 TB/s and a second launch (4 us).  With a k that ends inside a slab of 16, 128-row
+// tiles were measured at 1130 - 1445 and, from one tile a unit to two, 2240 - 2800; the lower ones, whose last slab alone differs, as above
+// (N 8192, K 2056, 128 | 64 | 32 rows, us: 64 rows 79 | 54 | 41, 256 81 | 63 | 75, 512 98 | 121 | 143, 768 155 | 182, 1024 185 | 242).
 struct F32Pick { int rows, splits; };
 static F32Pick f32_pick(int M, int N, int K, int nprob, int max_splits) {
     const double cu = (double)device_cu_count();
     const double tn = (double)((N + 127) / 128);
+    const bool ragged = K % 16 != 0;
     F32Pick best = {128, 1};
     double best_ns = 1e30;
-    for (int rows = 128; rows >= (K % 32 ? 128 : 32); rows /= 2) {         // the lower tiles take whole slabs of 32 k
+    for (int rows = 128; rows >= 32; rows /= 2) {
         for (int s = 1; s <= max_splits; ++s) {
             const int kp = ((K + s - 1) / s + 31) / 32 * 32;
             if (s > 1 && (kp < 64 || (K + kp - 1) / kp != s)) continue;
             const double tiles = nprob * s * tn * (double)((M + rows - 1) / rows);
             const double full = floor(tiles / (2.0 * cu)), rest = tiles - full * 2.0 * cu, fill = rest / cu;
-            const double two = rows == 128 ? 2860.0 : rows == 64 ? 1800.0 : 1050.0;
-            const double one = rows == 128 ? 1120.0 : rows == 64 ? 780.0 + 170.0 * fill : 520.0 + 220.0 * fill;
-            const double slab = two * full + (fill > 1.0 ? two : fill > 0.0 ? one : 0.0);
+            const double two = rows == 128 ? (ragged ? 2800.0 : 2860.0) : rows == 64 ? 1800.0 : 1050.0;
+            const double one = rows == 128 ? (ragged ? 1070.0 + 375.0 * fill : 1120.0) : rows == 64 ? 780.0 + 170.0 * fill : 520.0 + 220.0 * fill;
+            const double last = rows == 128 && ragged ? 2060.0 + 740.0 * (fill - 1.0) : two;
+            const double slab = two * full + (fill > 1.0 ? last : fill > 0.0 ? one : 0.0);
             double ns = 5300.0 + kp / 32.0 * slab;
             if (s > 1) ns += 4000.0 + (double)nprob * s * (double)M * (double)N * 8.0 / 4.0e3;
             if (ns < 0.97 * best_ns) { best = {rows, s}; best_ns = ns; }

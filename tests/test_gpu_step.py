@@ -75,6 +75,24 @@ def test_fp32_steps_match_oracle(tied):
     ctx.close()
 
 
+@pytest.mark.parametrize("d,ffn,split_k", [(296, 1064, 0), (296, 1064, -1), (264, 536, 0)])
+def test_fp32_widths_that_end_inside_a_slab_of_k(d, ffn, split_k):
+    """Projections in pieces along k (the last one ending eight k into a slab) and whole: steps and an evaluation as in the oracle."""
+    cfg = si.tiny_config(n_layers=2, d_model=d, n_heads=d // 8, d_ffn=ffn, vocab=5150, max_pos=40)
+    P = si.make_weights(cfg, seed=11, std=0.05, ln_jitter=True)
+    tok = si.make_tokens(cfg["vocab"], 2, 19, seed=12)
+    lab = si.next_token_labels(tok)
+    oz = zo_step.Zo2Blockwise(opt_model.OptShape(**cfg), copy.deepcopy(P))
+    ctx = _b().Zo2Context(cfg, P, arena_bytes=256 << 20)
+    ctx.set_split_k(split_k)
+    for j in range(3):
+        a, g = oz.step(tok, lab, 42 + j, 1e-3, 1e-5), ctx.step(tok, lab, 42 + j, 1e-3, 1e-5)
+        for k in range(2):
+            assert abs(float(g[k]) - float(a[k])) <= 1e-5 * abs(float(a[k])), (j, k)
+    assert abs(float(ctx.eval(tok, lab)) - float(oz.eval_loss(tok, lab))) <= 1e-5 * float(a[0])
+    ctx.close()
+
+
 def test_streamed_equals_resident_bitwise():
     """Sec. 5 claim: offloading changes nothing.  Same kernels, same order -> identical bits."""
     b = _b()
