@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(const GemmArgs a
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         const int row = tid / 4 + 64 * (c & 1);
-        g[c] = c < 2 ? W + (size_t)min(n0 + row, a.N - 1) * a.ldw : X + (size_t)min(m0 + row, a.M - 1) * a.ldx;
+        g[c] = (c < 2 ? W + (size_t)min(n0 + row, a.N - 1) * a.ldw : X + (size_t)min(m0 + row, a.M - 1) * a.ldx) + (KTAIL ? 0 : kc4);
         l[c] = ((c < 2 ? BM : 0) + row) * ROW + (((tid & 3) >> 1) ^ swz(row)) * 16 + (tid & 1) * 8;
     }
     const int nk = (K + BK - 1) / BK;
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(const GemmArgs a
     const int last_at = f32_chunk_at(nk - 1, nk, BK, kc4, K);
     const bool past = KTAIL && !f32_chunk_inside(nk - 1, nk, BK, kc4, K);
     auto load_slab = [&](v4f_t (&to)[4], int kt) {         // past the last slab: the last one again, which nobody reads
-        const int at = KTAIL && kt >= nk - 1 ? last_at : min(kt, nk - 1) * BK + kc4;
+        const int slab = min(kt, nk - 1) * BK, at = !KTAIL ? slab : kt >= nk - 1 ? last_at : slab + kc4;
 #pragma unroll
         for (int c = 0; c < 4; ++c) to[c] = *reinterpret_cast<const v4f_t*>(g[c] + at);
     };
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_ring_kernel(const GemmArgs a)
     const int nblk = (int)gridDim.x, xcd = (int)(blockIdx.x & 7), in_xcd = (int)(blockIdx.x >> 3);
     const int tile = xcd * (nblk >> 3) + min(xcd, nblk & 7) + in_xcd;
     const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
-    const int k_first = (int)blockIdx.y * a.kpiece, K = min(a.K - k_first, a.kpiece), nk = (K + BK - 1) / BK;
+    const int k_first = (int)blockIdx.y * a.kpiece, K = min(a.K - k_first, a.kpiece), nk = KTAIL ? (K + BK - 1) / BK : K / BK;
     const int lane = threadIdx.x & 63, r = lane & 31, kh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int half = wave >> 2, wm = (wave & 3) / WGN, wn = (wave & 3) % WGN;
@@ -338,21 +338,23 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_ring_kernel(const GemmArgs a)
     const int xr = xrow8 + lrow;
     const char* base_x = ring_uniform(X + (size_t)m0 * a.ldx);
     const char* base_w = ring_uniform(W + (size_t)n0 * a.ldw);
-    uint32_t g[3], g_last[3];          // W, W, X: offsets from the slab's first k, and of the last slab from the rows' (a chunk past
-#pragma unroll                         // the end of a row is then the row's first: fill_tail() puts zeros in its place)
-    for (int t = 0; t < 3; ++t) {
-        const int row = t < 2 ? (wave * 2 + t) * 8 + lrow : xr, kc = ((lane & 7) ^ ((row >> 1) & 7)) * 4;
-        const uint32_t first = (uint32_t)(t < 2 ? min(row, a.N - 1 - n0) * a.ldw : min(row, a.M - 1 - m0) * a.ldx) * 4u;
-        g[t] = first + kc * 4u;
-        if (KTAIL) g_last[t] = first + 4u * (uint32_t)f32_chunk_at(nk - 1, nk, BK, kc, K);
+    // offsets from a slab's first k; of the last slab from the rows' first (a chunk past the end of a row is then the row's first:
+    // fill_tail() puts zeros in its place)
+    const uint32_t gx = (uint32_t)(min(xr, a.M - 1 - m0) * a.ldx + ((lane & 7) ^ ((xr >> 1) & 7)) * 4) * 4u;
+    uint32_t gw[2], last_w[2], last_x = 0;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int row = (wave * 2 + t) * 8 + lrow;
+        gw[t] = (uint32_t)(min(row, a.N - 1 - n0) * a.ldw + ((lane & 7) ^ ((row >> 1) & 7)) * 4) * 4u;
+        if (KTAIL) last_w[t] = (uint32_t)(min(row, a.N - 1 - n0) * a.ldw + f32_chunk_at(nk - 1, nk, BK, ((lane & 7) ^ ((row >> 1) & 7)) * 4, K)) * 4u;
     }
+    if (KTAIL) last_x = (uint32_t)(min(xr, a.M - 1 - m0) * a.ldx + f32_chunk_at(nk - 1, nk, BK, ((lane & 7) ^ ((xr >> 1) & 7)) * 4, K)) * 4u;
     auto issue_one = [&](int t, int kt, int stage) {
         const uint32_t at = lds0 + (uint32_t)stage * STAGE;
         const bool last = KTAIL && kt == nk - 1;
         const size_t k = last ? 0 : (size_t)kt * (BK * 4);
-        const uint32_t off = last ? g_last[t] : g[t];
-        if (t < 2) ring_load_to_lds(base_w + k, off, at + BM * 128 + (wave * 2 + t) * 1024);
-        else ring_load_to_lds(base_x + k, off, at + xrow8 * 128);
+        if (t < 2) ring_load_to_lds(base_w + k, last ? last_w[t & 1] : gw[t & 1], at + BM * 128 + (wave * 2 + t) * 1024);
+        else ring_load_to_lds(base_x + k, last ? last_x : gx, at + xrow8 * 128);
     };
     auto issue = [&](int kt, int stage) {
 #pragma unroll
