@@ -345,7 +345,11 @@ zo2_status zo2_op_convert(const void* src, int32_t src_dtype, float src_scale,
 /* Y[M, N] = act( (X[M, K] . W[N, K]^T + bias[N]) * out_scale ) + residual[M, N].
  * X, W, bias: `dtype` (F32, BF16 or F16), leading dimensions ldx, ldw in elements;
  * residual: float32 [M, ldy] or NULL; Y: out_dtype (F32 or `dtype`) with leading dimension ldy;
- * relu: apply max(.,0) before the residual.  Accumulation is float32.  K must be a multiple of 8. */
+ * relu: apply max(.,0) before the residual.  Accumulation is float32.  K must be a multiple of 8.
+ * F32 operands enter with all their bits, as sums of three bfloat16 numbers, of whose products the smallest are left out: a product is off by up to
+ * 2^-23 of itself (float32: 2^-24), sums of 256 k and more by less than with float32 products.  Infinities and NaN give what float32
+ * products give, and so does an operand below 2^-110 where it matters beside factors of up to 2^20; beside larger ones, and where all
+ * products of a sum are with operands below 2^-134, such an operand counts to the nearest 2^-133. */
 zo2_status zo2_op_gemm(int32_t dtype, int32_t M, int32_t N, int32_t K,
                        const void* X, int64_t ldx, const void* W, int64_t ldw, const void* bias,
                        const float* residual, void* Y, int32_t out_dtype, int64_t ldy,

@@ -1,10 +1,12 @@
-// float32 projections on the bfloat16 matrix cores: every operand as the exact sum of three bfloat16 numbers.
+// float32 projections on the bfloat16 matrix cores: every operand as the sum of three bfloat16 numbers.
 //
 // A float32 significand has 24 bits, a bfloat16 one 8.  x = hi + mid + lo, each part the rest rounded to nearest, holds every
-// bit of x (the rests are exact in float32), so x w is nine products of bfloat16 numbers, each exact in the matrix core's
-// float32.  The six largest are taken: what is left out (mid lo, lo mid, lo lo) is 2^-26 of |x w| at the most and of random
-// sign, less than a float32 product's own rounding.  v_mfma_f32_32x32x16_bf16 does 16 k in 32 cycles where
-// v_mfma_f32_32x32x2_f32 needs 512, so six of them still are 2.7 times as fast.  hi hi goes to one accumulator and the five
+// bit of an x of 2^-110 or more (the rests are exact in float32; for smaller ones see OddSums), so x w is nine products of
+// bfloat16 numbers, each exact in the matrix core's float32.  The six largest are taken.  mid is up to 2^-8 and lo up to 2^-17 of x, just
+// above a power of two, so what is left out (mid lo, lo mid, lo lo) is up to 2^-24 of |x w|, as much as a float32 product's
+// rounding; over random significands it is 2^-27.5 in the root mean square, a fifth of that rounding, and of random sign.  A
+// product by itself is off by up to 2^-23 (2^-25.2 in the root mean square, as in float32), sums are nearer than float32's (below).
+// v_mfma_f32_32x32x16_bf16 does 16 k in 32 cycles where v_mfma_f32_32x32x2_f32 needs 512, so six of them still are 2.7 times as fast.  hi hi goes to one accumulator and the five
 // small products to another, added at the end: the large sums are rounded once per 16 k (every two k with float32 products).
 //
 // Measured, float32 products -> this, in us: 2 x 768 rows, d 2048 / ffn 8192: LM head 2468 -> 1610 (129 -> 197 TFLOP/s), FC1 410 ->
@@ -55,18 +57,30 @@ __device__ __forceinline__ void clear_acc(f32x16_t (&acc)[TM][TN]) {
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 }
 
-// An infinity (or a value that rounds to one in bfloat16) has no such parts: inf - inf is a NaN where float32 has inf.  A
-// wavefront with a sum that is not finite computes its tile again with float32 products, straight from memory.
-template <int TM, int TN>
-__device__ __forceinline__ bool not_finite(const f32x16_t (&acc)[TM][TN]) {
+// Two kinds of operands have no such parts.  An infinity (or a value that rounds to one in bfloat16): inf - inf is a NaN where
+// float32 has inf.  A value below 2^-110: its later parts fall under bfloat16's range, to 2^-134 each in the worst case, which is nothing
+// beside a sum of 2^-74 or more whose other factors are up to 2^20 (2^-40 of it, times K) and shows in one that is smaller.  A wavefront with
+// a sum that is not finite, or below 2^-74 and not zero, computes its tile again with float32 products, straight from memory.  (To look
+// at every operand as it is split takes 1.5 instructions an element more: 64 x 24576 x 1024 35 -> 40 us, 768 x 50272 x 2048 822 -> 868.)
+struct OddSums {
     float odd = 0.f;                       // 0 x finite sums to 0; anything else to a NaN
+    uint32_t least = 0xffffffffu;          // (bits << 1) - 1 has the magnitudes in order, zero last
+    __device__ __forceinline__ void look(float x) {
+        odd = __builtin_fmaf(x, 0.f, odd);
+        least = min(least, (f2u(x) << 1) - 1u);
+    }
+    __device__ __forceinline__ bool any() const { return __any(odd != 0.f || least < ((uint32_t)(127 - 74) << 24) - 1u); }
+};
+template <int TM, int TN>
+__device__ __forceinline__ bool odd_sums(const f32x16_t (&acc)[TM][TN]) {
+    OddSums o;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) odd = __builtin_fmaf(acc[i][j][v], 0.f, odd);
-    return __any(odd != 0.f);
+            for (int v = 0; v < 16; ++v) o.look(acc[i][j][v]);
+    return o.any();
 }
 // v_mfma_f32_32x32x2_f32: lanes 0..31 supply k = 0, lanes 32..63 k = 1 of a row.  A lane of half h reads k = 8 g + 4 h .. + 3 of its
 // row with one load; issue t of group g contracts k = 8 g + t with k = 8 g + 4 + t.  (K is a multiple of 8.)
@@ -264,7 +278,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_split_kernel(const GemmArgs a
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] += low[i][j];
-    if (not_finite<2, 2>(acc)) float32_products<2, 2>(a, X, W, m0 + wm * 64, n0 + wn * 64, K, acc);
+    if (odd_sums<2, 2>(acc)) float32_products<2, 2>(a, X, W, m0 + wm * 64, n0 + wn * 64, K, acc);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -473,17 +487,17 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_ring_kernel(const GemmArgs a)
             for (int e = 0; e < 4; ++e) y[t][e] = half ? hi[e] : lo[e];
         }
         __syncthreads();
-        float odd = 0.f;
+        OddSums odd;
 #pragma unroll
         for (int t = 0; t < QUADS / 2; ++t) {
             const v4f_t o = *reinterpret_cast<const v4f_t*>(recv + t * 256);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 y[t][e] = half ? o[e] + y[t][e] : y[t][e] + o[e];
-                odd = __builtin_fmaf(y[t][e], 0.f, odd);
+                odd.look(y[t][e]);
             }
         }
-        if (__any(odd != 0.f)) {
+        if (odd.any()) {
             float32_products<1, TN>(a, X, W, m0 + wm * 32, n0 + wn * (32 * TN), K, acc);
 #pragma unroll
             for (int t = 0; t < QUADS / 2; ++t)
