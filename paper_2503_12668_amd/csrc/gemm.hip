@@ -231,7 +231,7 @@ zo2_status gemm_launch(const GemmArgs& a, int dtype, hipStream_t st, int of_rows
     // cross-entropy mode has no output matrix (Y may be NULL): only the 256 x 256 kernel implements it, so every
     // other path must be refused before anything is launched
     ZO2_OP_CHECK(!a.ce_mode || (dtype != ZO2_F32 && gemm256_applicable(a, dtype)), ZO2_EINVAL,
-                 "gemm: cross-entropy mode needs the large-tile kernel (16-bit inputs, K %% 128 == 0, N >= 256, N %% 4 == 0)");
+                 "gemm: cross-entropy mode needs the large-tile kernel (16-bit inputs, K %% 128 == 0, N >= 256, N %% 4 == 0, 256 rows within 2 GiB)");
     if (dtype == ZO2_F32) {
         ZO2_OP_CHECK(a.out_f32, ZO2_EINVAL, "gemm: the float32 kernel writes float32 output");
         GemmArgs f = a;

@@ -22,6 +22,7 @@
 //
 // Requires K % 128 == 0 (an even number of k-slabs), N % 4 == 0, ldy % 4 == 0 and 16-byte aligned Y / residual (gemm256_applicable);
 // M and N are otherwise arbitrary (rows are clamped on load, masked on store).
+#include <algorithm>
 #include <type_traits>
 
 #include "gemm.h"
@@ -740,6 +741,9 @@ bool gemm256_applicable(const GemmArgs& a, int dtype) {
     if (a.K % 128 != 0 || a.M < 1 || a.N < 256 || a.N % 4 != 0 || a.ldy % 4 != 0) return false;
     if (!a.out_f32 && (a.N % 8 != 0 || a.ldy % 8 != 0)) return false;
     if (a.ce_mode && !a.out_f32) return false;
+    // a panel of 256 rows is one buffer resource with 32-bit offsets
+    auto panel_fits = [&](int rows, int64_t ld) { return ((int64_t)std::min(rows, 256) - 1) * ld + a.K < (int64_t)1 << 30; };
+    if (!panel_fits(a.M, a.ldx) || !panel_fits(a.N, a.ldw)) return false;
     const size_t tsz = 2;
     for (int i = 0; i < a.nprob; ++i) {
         if (a.ce_mode) {
