@@ -12,6 +12,8 @@
 //
 // Slab layout: rows of 8 chunks of 16 bytes, chunk kc of row m at position kc ^ ((m >> 1) & 7); a direct-to-LDS load lands
 // lane i's 16 bytes at offset 16 i, so the permutation is applied to the address a lane fetches from.
+#include <type_traits>
+
 #include "gemm.h"
 
 namespace zo2 {
@@ -45,6 +47,9 @@ template <int BM> struct MidTile {
 __device__ __forceinline__ void mid_load_to_lds(const void* sbase, uint32_t voff, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_base), "v"(voff), "s"(sbase) : "memory");
 }
+__device__ __forceinline__ void mid_load_to_lds(const void* sbase, int64_t off, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"((const char*)sbase + off) : "memory");
+}
 __device__ __forceinline__ const char* mid_uniform(const void* p) {      // a wave-uniform pointer into scalar registers
     const uint64_t v = (uint64_t)(uintptr_t)p;
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
@@ -62,7 +67,7 @@ __device__ __forceinline__ void mid_wait(int ahead) {
     }
 }
 
-template <typename T, typename OutT, int BM>
+template <typename T, typename OutT, int BM, bool FAR>          // FAR: rows lie too far apart for 32-bit offsets inside a tile
 __global__ __launch_bounds__(512, 2) void gemm_mid_kernel(const GemmArgs a, int splits) {
     constexpr int KC = kMidBK / 8, TM = BM / 64, TN = 2;           // 32 x 32 MFMA tiles per wavefront: TM x 2
     constexpr int NST = MidTile<BM>::kStages, STAGE = MidTile<BM>::kStage;
@@ -89,17 +94,18 @@ __global__ __launch_bounds__(512, 2) void gemm_mid_kernel(const GemmArgs a, int 
     // a matrix repeat its last one, their products are never stored
     const char* base_x = mid_uniform(reinterpret_cast<const T*>(p.X) + (size_t)m0 * a.ldx + k_first);
     const char* base_w = mid_uniform(reinterpret_cast<const T*>(p.W) + (size_t)n0 * a.ldw + k_first);
-    uint32_t gx[XL], gw[WL];
+    using Offset = std::conditional_t<FAR, int64_t, uint32_t>;
+    Offset gx[XL], gw[WL];
     const int lrow = lane >> 3;
 #pragma unroll
     for (int t = 0; t < XL; ++t) {
         const int row = (wave * XL + t) * 8 + lrow;
-        gx[t] = (uint32_t)(min(row, a.M - 1 - m0) * a.ldx + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2u;
+        gx[t] = (Offset)(min(row, a.M - 1 - m0) * a.ldx + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2;
     }
 #pragma unroll
     for (int t = 0; t < WL; ++t) {
         const int row = (wave * WL + t) * 8 + lrow;
-        gw[t] = (uint32_t)(min(row, a.N - 1 - n0) * a.ldw + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2u;
+        gw[t] = (Offset)(min(row, a.N - 1 - n0) * a.ldw + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2;
     }
     auto issue_one = [&](int t, int kt, int stage) {               // load t of slab kt: weights first
         const uint32_t at = lds0 + (uint32_t)stage * STAGE;
@@ -246,9 +252,9 @@ __global__ __launch_bounds__(512, 2) void gemm_mid_kernel(const GemmArgs a, int 
     }
 }
 
-template <typename T, typename OutT, int BM>
+template <typename T, typename OutT, int BM, bool FAR = false>
 static zo2_status mid_launch_t(const GemmArgs& a, int splits, hipStream_t st) {
-    auto kern = gemm_mid_kernel<T, OutT, BM>;
+    auto kern = gemm_mid_kernel<T, OutT, BM, FAR>;
     static bool reserved_on[kMaxDevices] = {false};
     bool& reserved = reserved_on[current_device()];
     if (!reserved) {
@@ -268,7 +274,6 @@ static zo2_status mid_launch_t(const GemmArgs& a, int splits, hipStream_t st) {
 
 bool gemm_mid_applicable(const GemmArgs& a, int dtype) {
     if ((dtype != ZO2_BF16 && dtype != ZO2_F16) || a.ce_mode || a.M < 1 || a.K % kMidBK != 0 || a.N % 4 != 0 || a.ldy % 4 != 0) return false;
-    if (a.ldx >= 1 << 22 || a.ldw >= 1 << 22) return false;        // a lane's offset from its tile's first row is 32 bits
     const size_t osz = a.out_f32 ? 4 : 2;
     for (int i = 0; i < a.nprob; ++i) {
         if (((uintptr_t)a.p[i].Y & (4 * osz - 1)) != 0 || ((uintptr_t)a.p[i].bias & 7) != 0 || ((uintptr_t)a.p[i].residual & 15) != 0) return false;
@@ -282,12 +287,19 @@ zo2_status gemm_launch_mid(const GemmArgs& a, int dtype, int rows, int splits, h
     ZO2_OP_CHECK(gemm_mid_applicable(a, dtype) && (rows == 64 || rows == 128) && splits >= 1 && a.kpiece > 0 && a.kpiece % kMidBK == 0 &&
                  (int64_t)a.kpiece * (splits - 1) < a.K && (int64_t)a.kpiece * splits >= a.K && (splits == 1 || a.out_f32),
                  ZO2_EINVAL, "gemm: shape or alignment not supported by the 128 x 128 kernel");
+    // rows of 8 MB and more: 64-row tiles with 64-bit addresses (the height does not show in a sum)
+    const bool far = a.ldx >= 1 << 22 || a.ldw >= 1 << 22;
+#define ZO2_MID(T, OutT)                                                \
+    if (far) return mid_launch_t<T, OutT, 64, true>(a, splits, st);     \
+    if (rows == 64) return mid_launch_t<T, OutT, 64>(a, splits, st);    \
+    return mid_launch_t<T, OutT, 128>(a, splits, st)
     if (dtype == ZO2_BF16) {
-        if (rows == 64) return a.out_f32 ? mid_launch_t<bf16_t, float, 64>(a, splits, st) : mid_launch_t<bf16_t, bf16_t, 64>(a, splits, st);
-        return a.out_f32 ? mid_launch_t<bf16_t, float, 128>(a, splits, st) : mid_launch_t<bf16_t, bf16_t, 128>(a, splits, st);
+        if (a.out_f32) { ZO2_MID(bf16_t, float); }
+        ZO2_MID(bf16_t, bf16_t);
     }
-    if (rows == 64) return a.out_f32 ? mid_launch_t<f16_t, float, 64>(a, splits, st) : mid_launch_t<f16_t, f16_t, 64>(a, splits, st);
-    return a.out_f32 ? mid_launch_t<f16_t, float, 128>(a, splits, st) : mid_launch_t<f16_t, f16_t, 128>(a, splits, st);
+    if (a.out_f32) { ZO2_MID(f16_t, float); }
+    ZO2_MID(f16_t, f16_t);
+#undef ZO2_MID
 }
 
 }  // namespace zo2
