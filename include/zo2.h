@@ -208,6 +208,10 @@ zo2_status zo2_get_plan(const zo2_ctx* ctx, int32_t* n_slots, int32_t* resident,
  * use.  Any pointer may be NULL.  Results do not depend on the organisation. */
 zo2_status zo2_get_scratch_plan(const zo2_ctx* ctx, int32_t* sweeps_per_block, int64_t* scratch_elems, int32_t* scratch_sets);
 
+/* Facts about the last pass, for tests: how many directions of a round went through a block together (1: one after the other), and how
+ * many projections cut along k left their partial sums to the pass of the LayerNorm behind them.  Any pointer may be NULL. */
+zo2_status zo2_get_pass_facts(const zo2_ctx* ctx, int32_t* directions_together, int32_t* sums_in_layernorm);
+
 /* sweeps = 1, 2 or 4: use exactly that organisation (ZO2_EBUDGET at the next step if 3 block slots do not fit next to
  * it); 0 (default): the planner starts from its preferred organisation and moves to smaller scratch sets until 3
  * block slots fit.  Takes effect at the next step.  ZO2_EINVAL for any other value. */

@@ -179,6 +179,7 @@ struct zo2_ctx {
     bool serial_streams;                 // ablation: upload, compute and offload of a block run one after the other
     int ns;                              // perturbation streams of the pass in progress: 2 (step) or 1 (evaluation)
     bool one_dir;                        // the pass in progress evaluates one direction
+    int together, sums_left;             // facts about the last pass: directions that went through a block at once; sums that a LayerNorm's pass made
     RowSum left;                         // FC2's pieces that the next LayerNorm adds up (pieces 0: none)
     float *ce_pmax, *ce_psum, *ce_lab;  // [4 ceil(V/256), 2T] x 2 and [2T]
     int ce_parts;
@@ -733,6 +734,13 @@ extern "C" zo2_status zo2_get_scratch_plan(const zo2_ctx* c, int32_t* sweeps_per
     return ZO2_OK;
 }
 
+extern "C" zo2_status zo2_get_pass_facts(const zo2_ctx* c, int32_t* directions_together, int32_t* sums_in_layernorm) {
+    if (!c) return ZO2_EINVAL;
+    if (directions_together) *directions_together = c->together;
+    if (sums_in_layernorm) *sums_in_layernorm = c->sums_left;
+    return ZO2_OK;
+}
+
 extern "C" zo2_status zo2_set_scratch_plan(zo2_ctx* c, int32_t mode) {
     if (!c) return ZO2_EINVAL;
     if (c->dead) return ZO2_ESTATE;
@@ -992,6 +1000,7 @@ static inline int64_t fc2_bias_room(const zo2_ctx* c) { return (c->tn[15] + kTen
 // h += pieces that the block before left, if any; x = LayerNorm(h)
 static zo2_status sum_and_norm(zo2_ctx* c, const void* wp, const void* bp, const void* wm, const void* bm, int T) {
     const zo2_config& g = c->cfg;
+    if (c->left.pieces > 0) ++c->sums_left;
     if (c->left.pieces > 0) OPK(c, ZO2_KC_LN, reduce_layernorm(g.compute_dtype, c->left, c->h, wp, bp, wm, bm, c->x, c->ns * T, T, g.d_model, g.ln_eps, c->sc));
     else OPK(c, ZO2_KC_LN, layernorm(g.compute_dtype, c->h, wp, bp, wm, bm, c->x, c->ns * T, T, g.d_model, g.ln_eps, c->sc));
     c->left.pieces = 0;
@@ -1252,6 +1261,7 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
     OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, c->sk_ws, c->sk_ws_bytes, c->sc, !sum_with_ln));
     if (sum_with_ln) {
         const RowSum rs = {sa.partial, sa.splits, 2 * (int64_t)T * d, (int64_t)T * d, VP(9), VM(9)};
+        ++c->sums_left;
         OPK(c, ZO2_KC_LN, reduce_layernorm(dt, rs, c->h, VP(10), VP(11), VM(10), VM(11), c->x, 2 * T, T, d, g.ln_eps, c->sc));
     } else {
         OPK(c, ZO2_KC_LN, layernorm(dt, c->h, VP(10), VP(11), VM(10), VM(11), c->x, 2 * T, T, d, g.ln_eps, c->sc));
@@ -1363,6 +1373,8 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
     c->ns = ns;
     c->one_dir = ndirs == 1;
     c->left = RowSum{};
+    c->together = 1;
+    c->sums_left = 0;
     const int T = batch * seq;
     for (int i = 0; i < T; ++i) {
         if (tokens[i] < 0 || tokens[i] >= g.vocab) return fail(c, ZO2_EINVAL, "%s: token %d at %d outside [0, %d)", who, tokens[i], i, g.vocab);
@@ -1462,6 +1474,7 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
             { zo2_status ds = debug_delay(c, 0, c->sc); if (ds != ZO2_OK) return ds; }
             const bool fused_block = c->fuse && ns == 2, reads_slot = fused_block || reads_in_place(c);
             const bool together = ndirs > 1 && c->wide > 1;
+            if (together) c->together = std::min(c->wide, ndirs);
             for (int j = 0; together && j < ndirs; j += c->wide) {
                 zo2_status s = block_forward_round(c, l, bucket, batch, seq, seeds, j, std::min(c->wide, ndirs - j), upd && j == 0, eps);
                 if (s != ZO2_OK) return s;

@@ -127,11 +127,12 @@ def test_float32_projections_in_pieces_give_the_same_bits_under_every_organisati
     assert runs["uncut"][0] != runs["1"][0] or any(not np.array_equal(runs["uncut"][1][n], runs["1"][1][n]) for n in runs["1"][1])
 
 
-# the last two: a scratch without room for a second copy of the biases, and more rows than are worth it
-@pytest.mark.parametrize("wire,compute,d,vocab,batch,seq,layers", [
-    ("bf16", "bf16", 1024, 13060, 5, 37, 3), ("f16", "f16", 1024, 13060, 1, 150, 2), ("bf16", "bf16", 1024, 13060, 1, 13, 3), ("f32", "f32", 768, 9476, 1, 40, 3),
-    ("f32", "f32", 768, 212, 1, 40, 3), ("bf16", "bf16", 1024, 13060, 3, 200, 2)])
-def test_pieces_that_wait_for_the_next_layernorm_give_the_same_bits(wire, compute, d, vocab, batch, seq, layers):
+# the last three: no pieces at all, a scratch without room for a second copy of the biases, and more rows than are worth it.  step, evaluation:
+# sums left to a LayerNorm's pass (the loader path's output projections, 1 x 13, are among them under every organisation)
+@pytest.mark.parametrize("wire,compute,d,vocab,batch,seq,layers,step,evaluation", [
+    ("bf16", "bf16", 1024, 13060, 5, 37, 3, 3, 3), ("f16", "f16", 1024, 13060, 1, 150, 2, 2, 2), ("bf16", "bf16", 1024, 13060, 1, 13, 3, 6, 3), ("f32", "f32", 768, 9476, 1, 40, 3, 6, 6),
+    ("f32", "f32", 768, 212, 1, 40, 3, 0, 0), ("bf16", "bf16", 1024, 212, 5, 37, 3, 0, 3), ("bf16", "bf16", 1024, 13060, 3, 200, 2, 0, 2)])
+def test_pieces_that_wait_for_the_next_layernorm_give_the_same_bits(wire, compute, d, vocab, batch, seq, layers, step, evaluation):
     """The second FFN projection's pieces are added up by the next block's first LayerNorm, or the final one (odd and even numbers of
     blocks), on every kernel that leaves pieces; with a sweep per tensor group they never wait.  Steps and an evaluation, bit for bit."""
     b = _b()
@@ -143,7 +144,10 @@ def test_pieces_that_wait_for_the_next_layernorm_give_the_same_bits(wire, comput
     for sweeps in (1, 4):
         ctx = b.Zo2Context(cfg, P, wire=wire, compute=compute, arena_bytes=1 << 30)
         ctx.set_scratch_plan(sweeps)
-        r = [tuple(map(float, ctx.step(tok, lab, 5 + j, 1e-3, 1e-5))) for j in range(3)] + [float(ctx.eval(tok, lab))]
+        r = [tuple(map(float, ctx.step(tok, lab, 5 + j, 1e-3, 1e-5))) for j in range(3)]
+        assert ctx.pass_facts()[1] == (step if sweeps == 1 else layers if ctx.plan()["loader_fusion"] else 0)
+        r += [float(ctx.eval(tok, lab))]
+        assert ctx.pass_facts()[1] == (evaluation if sweeps == 1 else 0)
         assert ctx.plan()["sweeps_per_block"] == sweeps
         ctx.flush(); ctx.sync_to_host()
         runs.append((r, ctx.parameters()))

@@ -186,6 +186,7 @@ def test_directions_that_share_their_launches(batch, seq, dirs, wire, sr):
             ctx.set_resident_budget(ctx.plan()["bytes_used"])
         out += [rnd(ctx, tok, lab, [20 * k + j for j in range(dirs)], 1e-3, 1e-4) for k in (1, 2)]
         assert ctx.plan()["resident"]
+        assert ctx.pass_facts()[0] == (min(dirs, 4) if how == "room" else 1)
         ctx.flush(); ctx.sync_to_host()
         found.append((out, ctx.parameters()))
         ctx.close()
