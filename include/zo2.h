@@ -407,11 +407,12 @@ size_t zo2_op_gemm_perturbed_workspace_bytes(int32_t M, int32_t N, int32_t K);
 zo2_status zo2_op_perturbed_rows(int32_t dtype, const void* theta, int64_t K, int64_t n0, int64_t rows, uint32_t tensor_id,
                                  uint64_t seed, float eps, void* w_plus, void* w_minus, void* stream);
 
-/* The large-tile GEMM kernel works on 256- or 128-row tiles and picks the height per launch (whichever fills the
- * rounds of tiles over the compute units better).  rows = 128 or 256 forces one height for every later launch of the
- * process, step calls included, and takes launches of a few hundred rows off the 128-wide tiles; 0 restores the choice per
- * launch.  For tests and measurements: the heights give the same results bit for bit (the order in which a dot product is
- * accumulated does not depend on them); the 128-wide tiles add each slab's k in two halves and differ by float32 rounding.
+/* The large-tile GEMM kernel works on 256-, 192- or 128-row tiles and picks the height per launch (whichever fills the
+ * rounds of tiles over the compute units better), or runs the launch as two of different heights (zo2_op_gemm_tiles says
+ * which).  rows = 128 or 256 forces one height, and one launch, for every later call of the process, steps included, and takes
+ * projections of a few hundred rows off the 128-wide tiles; 0 restores the choice per launch.  For tests and measurements: the
+ * heights give the same results bit for bit (the order in which a dot product is accumulated does not depend on them); the
+ * 128-wide tiles add each slab's k in two halves and differ by float32 rounding.
  * Returns ZO2_EINVAL for any other value. */
 zo2_status zo2_op_set_gemm_tile_rows(int32_t rows);
 

@@ -273,8 +273,8 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_mfma256_kernel(const GemmArgs
         // the traffic that brings a later k-slab in, dealt out between them.  Every instruction takes an issue slot
         // of its wavefront and only about three fit under one 16-cycle MFMA: scheduling barriers pin one piece of
         // memory work behind each MFMA.
-        // stage_out, four wavefronts: the group moves its share of the register-staged slab on: row-block i of X and WPG
-        // row-blocks of W are stored to stage `st` (retired by the barrier just passed) and their registers are reloaded
+        // stage_out, four wavefronts: the group moves its share of the register-staged slab on: row-block i of X and its
+        // one or two row-blocks of W are stored to stage `st` (retired by the barrier just passed) and their registers are reloaded
         // with the same pieces of the slab at byte offset `soff` of the panels.
         // stage_out, eight wavefronts: the group issues one of the wavefront's eight direct-to-LDS loads of the slab at k
         // offset `soff` (elements) into stage `st`; `lanes` is all ones, or zero where that slab does not exist.

@@ -9,8 +9,8 @@
 // v_mfma_f32_32x32x16_bf16 does 16 k in 32 cycles where v_mfma_f32_32x32x2_f32 needs 512, so six of them still are 2.7 times as fast.  hi hi goes to one accumulator and the five
 // small products to another, added at the end: the large sums are rounded once per 16 k (every two k with float32 products).
 //
-// Measured, float32 products -> this, in us: 2 x 768 rows, d 2048 / ffn 8192: LM head 2468 -> 1610 (129 -> 197 TFLOP/s), FC1 410 ->
-// 270, FC2 405 + 16 -> 313, QKV 342 -> 241, output 109 + 16 -> 90; 64 rows, N 24576, K 1024: 46 -> 34; 16 rows, N 8192, K 2048: 55 -> 42.
+// Measured, float32 products -> this, in us: 2 x 768 rows, d 2048 / ffn 8192: LM head 2468 -> 1633 (128 -> 194 TFLOP/s), FC1 410 ->
+// 274, FC2 405 + 16 -> 321, QKV 342 -> 247, output 109 + 16 -> 92; 64 rows, N 24576, K 1024: 46 -> 34; 16 rows, N 8192, K 2048: 55 -> 42.
 // Distance from the sums in 64 bits, of the result's norm: K 2048, normal operands 8.1e-7 -> 2.7e-7 (128-row tiles) and 1.9e-7; K 8192, X
 // behind a ReLU 1.15e-6 -> 4.9e-7 and 3.3e-7; K 256 2.9e-7 -> 0.9e-7 and 0.7e-7.  (One accumulator for all six products: 7.0e-7, 1.35e-6.)
 //

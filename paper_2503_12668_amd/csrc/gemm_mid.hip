@@ -173,7 +173,7 @@ __global__ __launch_bounds__(512, 2) void gemm_mid_kernel(const GemmArgs a, int 
                     if (e < TN) next.w[kq][e < TN ? e : 0] = *reinterpret_cast<const v4u_t*>(ws + e * 4096 + off[kq]);
                     else next.x[kq][e < TN ? 0 : e - TN] = *reinterpret_cast<const v4u_t*>(xs + (e - TN) * 4096 + off[kq]);
                 }
-            // the retired stage's refill: load t behind MFMA 2 t (128 rows) or t
+            // the retired stage's refill: load t behind MFMA 2 t (128 rows: four loads, eight MFMAs); 64 rows: behind 0, 2 and 3 of four
             if (more && u * LPW % (2 * TM * TN) < LPW) issue_one(u * LPW / (2 * TM * TN), kt + NST, refill);
             __builtin_amdgcn_sched_barrier(0);
         }

@@ -182,9 +182,10 @@ __global__ __launch_bounds__(kThreads) void k1_kernel(const K1Args a) {
     }
 }
 
-// A round of directions in one sweep (zo2_step_multi).  Bound by the vector ALU, which draws n_upd + n_dir Gaussians an element;
+// A round of directions in one sweep (zo2_step_multi).  Bound by the vector ALU, which draws n_upd + n_dir Gaussians an element
+// (busy 99 % of the cycles; at four and four the bytes alone would take about as long);
 // sweep by sweep the same draws each wait for theta and its write: a block of 50 M bf16 elements, four updates and four directions
-// 99 + 59 + 137 us in seven launches.  The group's arithmetic is k1_group's, update by update and direction by direction, so
+// 99 + 59 + 137 us in seven launches, 194 in one.  The group's arithmetic is k1_group's, update by update and direction by direction, so
 // the stored bits are those of the single sweeps.
 template <typename W, typename C, bool SR>
 __global__ __launch_bounds__(kThreads) void k1_round_kernel(const K1RoundArgs a) {

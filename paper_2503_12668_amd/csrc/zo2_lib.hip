@@ -1009,7 +1009,8 @@ static zo2_status sum_and_norm(zo2_ctx* c, const void* wp, const void* bp, const
 
 // A single forward whose parameters are stored in the compute format has nothing to perturb and nothing to convert: it reads
 // them where they lie, and a sweep only comes before it where an update is pending.  (Copies cost 33 us a block and 63 for the
-// vocabulary matrix at d 2048: an evaluation of 8 blocks, 16 x 256 tokens, 4384 -> 4112 us.)
+// vocabulary matrix at d 2048: an evaluation of 8 blocks, 16 x 256 tokens, nothing pending, 4473 -> 4077 us; right behind a step, whose
+// update the sweeps still apply, 4606 -> 4451.)
 static inline bool reads_in_place(const zo2_ctx* c) { return c->ns == 1 && c->cfg.wire_dtype == c->cfg.compute_dtype && !c->overlap_k1; }
 
 struct PhaseView {       // where tensor k's perturbed copies are inside the scratch, or the tensor itself
