@@ -309,7 +309,11 @@ def op_gemm_phases(X, W, Y, stamps, residual=None, stream=None):
 
 
 def op_attention(q, k, v, n_seq, seq, n_heads, d_head, vector_kernel=False, stream=None):
-    out = torch.empty_like(q)
+    """q, k and v: [tokens, ...], one token's values side by side and all three with the same distance between tokens (dense, or columns
+    of one packed tensor, say); the result has that distance too."""
+    if any(t.shape[0] > 1 and (t.stride(0) != q.stride(0) or not t[0].is_contiguous()) for t in (q, k, v)):
+        raise ValueError("op_attention: q, k and v need the same distance between tokens, and each token's values side by side")
+    out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
     _op_check(lib().zo2_op_attention(_dt(q), _ptr(q), _ptr(k), _ptr(v), _ptr(out), n_seq, seq, n_heads, d_head,
                                      q.stride(0), 1 if vector_kernel else 0, _stream_ptr(stream)))
     return out

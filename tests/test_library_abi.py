@@ -57,3 +57,31 @@ def test_split_gemm_refuses_operands_that_its_kernels_cannot_load():
 
     for bad in (dict(X=(1 << 16) + 8), dict(W=(1 << 16) + 2), dict(ldx=1028), dict(ldw=1020), dict(ldw=504), dict(ldx=8), dict(K=1032, splits=4), dict(X=None)):
         assert call(**bad) == 1, (bad, L.zo2_op_last_error())
+
+
+def test_attention_of_columns_of_a_packed_tensor_gets_a_result_with_the_same_rows(monkeypatch):
+    """The kernels write the result at q's distance between rows: the memory handed to them reaches as far.  (Nothing is launched.)"""
+    import torch
+    from paper_2503_12668_amd import binding
+    calls = []
+
+    class Recorder:
+        def zo2_op_attention(self, *args):
+            calls.append(args)
+            return 0
+
+    monkeypatch.setattr(binding, "lib", lambda: Recorder())
+    monkeypatch.setattr(binding, "_stream_ptr", lambda stream=None: None)
+    rows, d = 6, 128
+    packed = torch.zeros(rows, 3 * d)
+    q, k, v = packed.split(d, dim=1)
+    for args in ((q, k, v), (packed[:, :d].contiguous(),) * 3, tuple(t.view(rows, 2, 64) for t in (packed[:, :d].contiguous(),) * 3)):
+        out = binding.op_attention(*args, 2, 3, 2, 64)
+        ld = calls[-1][9]
+        assert ld == args[0].stride(0) and calls[-1][4].value == out.data_ptr()
+        assert out.untyped_storage().nbytes() >= 4 * ((rows - 1) * ld + d) and out.shape == args[0].shape
+    dense = q.contiguous()
+    for args in ((q, dense, dense), (dense, k, dense), (dense, dense, v), (dense.t().contiguous().t(),) * 3):
+        with pytest.raises(ValueError):
+            binding.op_attention(*args, 2, 3, 2, 64)
+    assert len(calls) == 3
