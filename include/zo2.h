@@ -435,7 +435,7 @@ zo2_status zo2_op_set_gemm_wavefronts(int32_t waves);
 /* Causal multi-head self-attention.  q, k, v, out: [n_seq * seq, ld] of `dtype`, head h in
  * columns h*d_head .. (h+1)*d_head-1; q already carries the 1/sqrt(d_head) factor.
  * out[i] = softmax_{j <= i}(q_i . k_j) v_j within each sequence.  d_head in {8,16,32,64,80,128}.
- * bf16 / fp16 with d_head 64, 80 or 128 (ld < 2^25) and F32 with every d_head but 8 run on the matrix cores (operands aligned to 8
+ * bf16 / fp16 with d_head 64, 80 or 128 and F32 with every d_head but 8 run on the matrix cores (operands aligned to 8
  * elements) unless vector_kernel != 0; everything else runs on a float32 vector kernel. */
 zo2_status zo2_op_attention(int32_t dtype, const void* q, const void* k, const void* v, void* out,
                             int32_t n_seq, int32_t seq, int32_t n_heads, int32_t d_head, int64_t ld,

@@ -143,6 +143,9 @@ template <> struct AttMfma<f16_t> {
 __device__ __forceinline__ void att_load_to_lds(const void* sbase, uint32_t voff, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_base), "v"(voff), "s"(sbase) : "memory");
 }
+__device__ __forceinline__ void att_load_to_lds(const void* sbase, int64_t off, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"((const char*)sbase + off) : "memory");
+}
 
 // Maximum over a lane and its partner in the other half of the wavefront: the swap hands every lane the lower half's value in one
 // register and the upper half's in the other (a vector instruction; as an LDS permutation it cost a trip per tile).
@@ -180,7 +183,7 @@ __device__ __forceinline__ void att_place(int nqb, int n_pairs, int group, int& 
 // The order of every sum is that of one tile after the other.  2 x 8192 queries, 40 heads of 128: 1690 us one tile after the other
 // with banks met four times, 1380 now (1.0 PFLOP/s; matrix cores and vector ALU each busy half of the time); 32 heads of 64: 727 -> 670.
 // Above d_head 64 a wavefront in its second product goes before its neighbour's exponentials (2 %; at 64 that costs 2 %).
-template <typename T, int DH>
+template <typename T, int DH, bool FAR>      // FAR: rows lie too far apart for 32-bit offsets inside a tile
 __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v,
                                                                  T* __restrict__ out, int seq, int64_t ld, int n_heads, int n_pairs, int group) {
     constexpr int KS = DH / 16;          // contraction steps of the first product
@@ -233,7 +236,9 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const T* __restr
     const int g16 = lane >> 4, a16 = lane & 15;
 
     // loader plan: offsets inside a tile, the same for every tile that lies wholly inside the sequence
-    uint32_t ld_chunk[KINSTR], ld_off[KINSTR];
+    using Off = std::conditional_t<FAR, int64_t, uint32_t>;
+    Off ld_off[KINSTR];
+    uint32_t ld_chunk[KINSTR];
     int ld_row[KINSTR];
 #pragma unroll
     for (int x = 0; x < KINSTR; ++x) {                       // 1024 / (2 DHP) rows per instruction
@@ -241,7 +246,7 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const T* __restr
         int chunk = (lane % KCH) ^ swz(ld_row[x]);
         if (GCH < KCH && chunk >= GCH) chunk &= 7;           // padding positions of a row repeat a real chunk (finite, never used in a kept result)
         ld_chunk[x] = chunk * 16;
-        ld_off[x] = (uint32_t)ld_row[x] * (uint32_t)ld * 2u + ld_chunk[x];
+        ld_off[x] = (Off)ld_row[x] * (Off)ld * 2 + ld_chunk[x];
     }
     auto issue_tile = [&](int tile, int buf) {
         const int j0 = tile * 32;
@@ -250,7 +255,7 @@ __global__ __launch_bounds__(256, 2) void attention_mfma_kernel(const T* __restr
         const int last = seq - 1 - j0;                       // rows past the end repeat the last one (masked keys)
 #pragma unroll
         for (int x = 0; x < KINSTR; ++x) {
-            const uint32_t off = last >= 31 ? ld_off[x] : (uint32_t)min(ld_row[x], last) * (uint32_t)ld * 2u + ld_chunk[x];
+            const Off off = last >= 31 ? ld_off[x] : (Off)min(ld_row[x], last) * (Off)ld * 2 + ld_chunk[x];
             const uint32_t dst = lds0 + buf * BUF + (wave * KINSTR + x) * 1024;
             att_load_to_lds(kt, off, dst);
             att_load_to_lds(vt, off, dst + KTILE);
@@ -420,9 +425,14 @@ static zo2_status launch_mfma_att(const T* q, const T* k, const T* v, T* out, in
     const int n_pairs = n_heads * n_seq, nqb = (seq + 127) / 128;
     const int group = att_group(n_pairs, nqb);
     const dim3 grid((unsigned)(8 * nqb) * (unsigned)((n_pairs + 7) / 8)), block(256);
-    if (d_head == 64) hipLaunchKernelGGL((attention_mfma_kernel<T, 64>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs, group);
-    else if (d_head == 80) hipLaunchKernelGGL((attention_mfma_kernel<T, 80>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs, group);
-    else hipLaunchKernelGGL((attention_mfma_kernel<T, 128>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs, group);
+    const bool far = ld >= (int64_t)1 << 25;       // 31 rows of 2^25 elements are 2 GB behind the first
+#define ZO2_ATT16(DH)                                                                                                                       \
+    if (far) hipLaunchKernelGGL((attention_mfma_kernel<T, DH, true>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs, group); \
+    else hipLaunchKernelGGL((attention_mfma_kernel<T, DH, false>), grid, block, 0, st, q, k, v, out, seq, ld, n_heads, n_pairs, group)
+    if (d_head == 64) { ZO2_ATT16(64); }
+    else if (d_head == 80) { ZO2_ATT16(80); }
+    else { ZO2_ATT16(128); }
+#undef ZO2_ATT16
     ZO2_HIP_LAUNCH_CHECK();
     return ZO2_OK;
 }
@@ -606,8 +616,7 @@ zo2_status attention_launch(int dtype, const void* q, const void* k, const void*
         ZO2_OP_CHECK(align != 0 && ((uintptr_t)q % align) == 0 && ((uintptr_t)k % align) == 0 && ((uintptr_t)v % align) == 0 &&
                      ((uintptr_t)out % align) == 0, ZO2_EINVAL, "attention: unknown dtype, or operands not aligned to 8 elements");
     }
-    // (an offset inside a tile of 32 rows is 32 bits wide there)
-    if (!vector_kernel && dtype != ZO2_F32 && ld < (int64_t)1 << 25 && (d_head == 64 || d_head == 80 || d_head == 128)) {
+    if (!vector_kernel && dtype != ZO2_F32 && (d_head == 64 || d_head == 80 || d_head == 128)) {
         if (dtype == ZO2_BF16)
             return launch_mfma_att<bf16_t>((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)out, n_seq, seq, n_heads, d_head, ld, st);
         return launch_mfma_att<f16_t>((const f16_t*)q, (const f16_t*)k, (const f16_t*)v, (f16_t*)out, n_seq, seq, n_heads, d_head, ld, st);
