@@ -62,7 +62,8 @@ zo2_status gemm_launch_f32(const GemmArgs& a, int splits, int rows, hipStream_t 
 int gemm_f32_pick_splits(int M, int N, int K, int nprob, size_t workspace_bytes);
 // sum = false: the pieces stay in the workspace ([problem][piece][M][N]), the caller adds them and finishes the values.
 zo2_status gemm_launch_f32_splitk(const GemmArgs& a, int splits, void* workspace, size_t workspace_bytes, hipStream_t st, bool sum = true);
-// What a block projection runs on: rows 0 the large-tile kernel (gemm_launch / gemm_launch_splitk), 64 or 128 the 128 x 128
+// What a block projection runs on: rows 0 the large-tile kernel (gemm_launch / gemm_launch_splitk), 64 or 128 (256 in
+// gemm_launch_groups only) the 128 x 128
 // kernel with tiles of that height (gemm_launch_mid_splitk); splits: pieces along k that the workspace holds.
 struct GemmChoice { int rows, splits; };
 GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes);

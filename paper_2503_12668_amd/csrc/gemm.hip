@@ -371,6 +371,9 @@ zo2_status gemm_launch_f32_splitk(const GemmArgs& a, int splits, void* workspace
 // told apart with 4.5 us a round (3 with 64 rows) and correspondingly less a slab.  General -> this kernel (us): K 832, N 832: 512 rows 16.6 ->
 // 8.1, 4096 21.6 -> 15.2, 8192 25.9 against 27.8; K 704, N 2816: 1024 16.5 -> 11.8, 4096 36.6 against 38.0, 7504 57.9 against 70.7; K 1728, N
 // 6080: 512 29.7 -> 20.5, 2048 66.9 -> 61.7, 8192 225 against 247.  The choice is the faster one or within 4 % of it in 90 launches.
+// Tiles of 256 rows are for the launches of several directions at once (gemm_launch_groups), which have tiles for two rounds of 128 rows: the
+// wavefronts of a compute unit then ask for three quarters of the bytes per product.  Eight problems of 512 rows, d 2048, in a step: FC2
+// (K 8192) 161 -> 136 us, output 67 -> 54; a step of 4 x 128 tokens and four directions, 8 blocks, 7550 -> 7294.
 static double general_ns(double tiles, double slabs) {
     const double cu = (double)device_cu_count();
     return tiles <= cu ? 5600.0 + 900.0 * slabs : 3000.0 + ceil(tiles / (2.0 * cu)) * (3800.0 + 1250.0 * slabs);
@@ -378,6 +381,7 @@ static double general_ns(double tiles, double slabs) {
 static double mid_ns(int rows, double tiles, int kp, bool large) {
     const double cu = (double)device_cu_count(), rounds = ceil(tiles / cu), fill = tiles / (rounds * cu);
     if (!large && rounds > 1.0) return 3000.0 + rounds * (rows == 128 ? 4500.0 + (kp / 64) * (400.0 + 250.0 * fill) : 3000.0 + (kp / 64) * (240.0 + 120.0 * fill));
+    if (rows == 256) return 3500.0 + rounds * (kp / 64) * (780.0 + 260.0 * fill);
     return 3500.0 + rounds * (kp / 64) * (rows == 128 ? 440.0 + 180.0 * fill : 280.0 + 90.0 * fill);
 }
 GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes) {
@@ -493,7 +497,9 @@ zo2_status gemm_launch_groups(const GemmArgs& a, int dtype, GemmChoice k, int gr
         const int kp = k.splits > 1 ? ((a.K + k.splits - 1) / k.splits + 63) / 64 * 64 : a.K;
         const double n = (double)a.nprob * k.splits * (double)((a.N + 127) / 128);
         const bool large = gemm256_applicable(a, dtype);
-        const int rows = mid_ns(64, n * ((a.M + 63) / 64), kp, large) < mid_ns(128, n * ((a.M + 127) / 128), kp, large) ? 64 : 128;
+        int rows = 64;
+        for (int h = 128; h <= 256; h *= 2)
+            if (mid_ns(h, n * ((a.M + h - 1) / h), kp, large) <= mid_ns(rows, n * ((a.M + rows - 1) / rows), kp, large)) rows = h;
         return gemm_launch_mid_splitk(a, dtype, rows, k.splits, workspace, workspace_bytes, st);
     }
     if (k.splits <= 1) {

@@ -1,5 +1,5 @@
-// 16-bit projections with a few hundred rows per stream: 128 x 128 x 64 (or 64 x 128 x 64) block tiles, eight wavefronts,
-// a ring of LDS stages filled by direct-to-LDS loads.
+// 16-bit projections with a few hundred rows per stream: 128 x 128 x 64 (64 x 128 x 64, 256 x 128 x 64) block tiles, eight
+// wavefronts, a ring of LDS stages filled by direct-to-LDS loads.
 //
 // With so few rows a launch is a handful of k-slabs per compute unit, bound by the bytes a compute unit can have under way
 // (about 64 KB, whatever the ring's depth: weights from HBM and activations from L2 alike, 46 - 50 GB/s a unit) and by its
@@ -7,8 +7,11 @@
 // k whose partial sums are written and read back).  Here the tile is small enough that the launch fills the chip with little
 // or no splitting, and a ring of four slabs keeps three of them under way (five and six are no faster, three cost 10 % on
 // weights from HBM).  A wavefront owns
-// 64 x 64 of the tile (32 x 64 of the lower one) for one half of each slab's k - two wavefronts per SIMD, no more LDS reads
+// 64 x 64 of the tile (32 x 64 of the lower one, 128 x 64 of the higher) for one half of each slab's k - two wavefronts per SIMD, no more LDS reads
 // than four would make - and the two halves' sums meet in LDS at the end.
+//
+// Tiles of 256 rows (a ring of three slabs) are for launches with many of them: 1.04 us a slab with a tile on every compute unit where two
+// tiles of 128 rows take 1.24, by 48 KB of loads in place of 64.  A sum has the same order at every height.
 //
 // Slab layout: rows of 8 chunks of 16 bytes, chunk kc of row m at position kc ^ ((m >> 1) & 7); a direct-to-LDS load lands
 // lane i's 16 bytes at offset 16 i, so the permutation is applied to the address a lane fetches from.
@@ -38,9 +41,9 @@ template <> struct MidMfma<f16_t> {
 
 static constexpr int kMidBN = 128, kMidBK = 64;
 template <int BM> struct MidTile {
-    static constexpr int kStage = (BM + kMidBN) * kMidBK * 2;      // 32 KB / 24 KB
-    static constexpr int kStages = 4;
-    static constexpr int kLds = kStage * kStages;                  // 128 KB / 96 KB
+    static constexpr int kStage = (BM + kMidBN) * kMidBK * 2;      // 48 KB / 32 KB / 24 KB
+    static constexpr int kStages = BM == 256 ? 3 : 4;
+    static constexpr int kLds = kStage * kStages;                  // 144 KB / 128 KB / 96 KB
 };
 
 // source address = wave-uniform base + per-lane 32-bit byte offset
@@ -284,7 +287,7 @@ bool gemm_mid_applicable(const GemmArgs& a, int dtype) {
 
 // splits > 1: a.kpiece k per piece (a multiple of 64), p[i].Y = the problem's float32 partial sums, one [M][N] plane per piece
 zo2_status gemm_launch_mid(const GemmArgs& a, int dtype, int rows, int splits, hipStream_t st) {
-    ZO2_OP_CHECK(gemm_mid_applicable(a, dtype) && (rows == 64 || rows == 128) && splits >= 1 && a.kpiece > 0 && a.kpiece % kMidBK == 0 &&
+    ZO2_OP_CHECK(gemm_mid_applicable(a, dtype) && (rows == 64 || rows == 128 || rows == 256) && splits >= 1 && a.kpiece > 0 && a.kpiece % kMidBK == 0 &&
                  (int64_t)a.kpiece * (splits - 1) < a.K && (int64_t)a.kpiece * splits >= a.K && (splits == 1 || a.out_f32),
                  ZO2_EINVAL, "gemm: shape or alignment not supported by the 128 x 128 kernel");
     // rows of 8 MB and more: 64-row tiles with 64-bit addresses (the height does not show in a sum)
@@ -292,6 +295,7 @@ zo2_status gemm_launch_mid(const GemmArgs& a, int dtype, int rows, int splits, h
 #define ZO2_MID(T, OutT)                                                \
     if (far) return mid_launch_t<T, OutT, 64, true>(a, splits, st);     \
     if (rows == 64) return mid_launch_t<T, OutT, 64>(a, splits, st);    \
+    if (rows == 256) return mid_launch_t<T, OutT, 256>(a, splits, st);  \
     return mid_launch_t<T, OutT, 128>(a, splits, st)
     if (dtype == ZO2_BF16) {
         if (a.out_f32) { ZO2_MID(bf16_t, float); }

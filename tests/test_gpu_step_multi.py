@@ -194,3 +194,27 @@ def test_directions_that_share_their_launches(batch, seq, dirs, wire, sr):
         assert out == found[0][0]
         for n in params:
             assert np.array_equal(params[n], found[0][1][n]), n
+
+
+@pytest.mark.parametrize("batch,seq,d_ffn,dirs", [(1, 257, 320, 4), (2, 150, 2112, 4), (1, 290, 576, 3)])
+def test_directions_on_tiles_of_256_rows(batch, seq, d_ffn, dirs):
+    """At d_model 2048, six or eight problems of 257 - 300 rows: output projection and FC2 take tiles of 256 rows where one direction takes
+    lower ones.  One row and 44 rows in the second tile, 5 to 33 slabs (a ring of three, an odd last slab): the bits of single directions."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=1, d_model=2048, n_heads=32, d_ffn=d_ffn, vocab=260, max_pos=320, tied=True)
+    P = si.make_weights(cfg, seed=31, std=0.03, ln_jitter=True)
+    tok = si.make_tokens(cfg["vocab"], batch, seq, seed=32)
+    lab = si.next_token_labels(tok)
+    found = []
+    for rnd in (_multi_round, _sequential_round):
+        ctx = b.Zo2Context(cfg, P, wire="bf16", compute="bf16", arena_bytes=2 << 30)
+        ctx.set_loader_fusion(-1)
+        out = [rnd(ctx, tok, lab, [20 * k + j for j in range(dirs)], 1e-3, 1e-4) for k in (0, 1)]
+        if rnd is _multi_round:
+            assert ctx.pass_facts()[0] == dirs
+        ctx.flush(); ctx.sync_to_host()
+        found.append((out, ctx.parameters()))
+        ctx.close()
+    assert found[0][0] == found[1][0]
+    for n in found[0][1]:
+        assert np.array_equal(found[0][1][n], found[1][1][n]), n
