@@ -35,7 +35,7 @@ struct K1Args {
 };
 
 // The sweep of a round of several directions: any number of deferred updates, each stored before the next is applied, and the
-// perturbed copies of up to kMaxDirs directions, with theta read and written once.
+// perturbed copies of up to kMaxDirs directions (or of none), with theta read and written once.
 struct K1RoundArgs {
     static constexpr int kMaxUpdates = 16, kMaxDirs = 4;
     void* theta;

@@ -313,10 +313,10 @@ zo2_status k1_launch(K1Args& a, int wire_dtype, int compute_dtype, bool update, 
 
 zo2_status k1_round_launch(K1RoundArgs& a, int wire_dtype, int compute_dtype, hipStream_t st) {
     { const zo2_status s = plan_chunks(a.seg, a.nseg, a.first_chunk, a.total_chunks); if (s != ZO2_OK) return s; }
-    ZO2_OP_CHECK(a.n_upd >= 0 && a.n_upd <= K1RoundArgs::kMaxUpdates && a.n_dir >= 1 && a.n_dir <= K1RoundArgs::kMaxDirs && a.theta && (a.n_upd == 0 || a.c_ptr),
+    ZO2_OP_CHECK(a.n_upd >= 0 && a.n_upd <= K1RoundArgs::kMaxUpdates && a.n_dir >= 0 && a.n_dir <= K1RoundArgs::kMaxDirs && a.theta && (a.n_upd == 0 || a.c_ptr),
                  ZO2_EINVAL, "k1: a round of %d updates and %d directions", a.n_upd, a.n_dir);
     for (int j = 0; j < a.n_dir; ++j) ZO2_OP_CHECK(a.w_plus[j] && a.w_minus[j], ZO2_EINVAL, "k1: W+- of direction %d missing", j);
-    if (a.total_chunks == 0) return ZO2_OK;
+    if (a.total_chunks == 0 || a.n_upd + a.n_dir == 0) return ZO2_OK;
     ZO2_DISPATCH_WIRE(wire_dtype, W, {
         ZO2_DISPATCH_COMPUTE(compute_dtype, C, { return launch_round<W, C>(a, st); });
     });

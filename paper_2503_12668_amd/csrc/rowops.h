@@ -37,11 +37,13 @@ struct EmbedArgs {
     int32_t T, seq, d, pos_offset;
     float eps, scale_tok, scale_pos;
     int32_t single;          // 1: only the "+" rows are produced (single forward; eps is 0 then)
-    int32_t stochastic;      // 1: the pending update is stored with stochastic rounding, as K1 will do for the table
-    const float* c_ptr;      // device scalar eta_prev * g_prev
-    PhiloxKeys k_prev, k_cur;
+    int32_t stochastic;      // 1: a pending update is stored with stochastic rounding, as K1 will do for the table
+    static constexpr int kMaxUpdates = 16;
+    int32_t n_upd;           // pending updates that the tables do not have yet, each stored before the next
+    const float* c_ptr;      // their coefficients eta g, in order, on the device
+    PhiloxKeys k_upd[kMaxUpdates], k_cur;
 };
-zo2_status embed_gather(const EmbedArgs& a, int wire_dtype, int compute_dtype, bool update, hipStream_t st);
+zo2_status embed_gather(const EmbedArgs& a, int wire_dtype, int compute_dtype, hipStream_t st);
 
 // rows of logits -> row_loss[row0 + r]; the label of stacked row i is labels[i % label_period]
 zo2_status cross_entropy_rows(const float* logits, int64_t ld, const int32_t* labels, int rows, int row0, int label_period,

@@ -495,7 +495,9 @@ zo2_status reduce_layernorm(int dtype, const RowSum& a, float* h, const void* w,
 // h+[t] = W+tok[id_t] + W+pos[t + off], h-[t] likewise, with the pending update and the
 // perturbation evaluated only for the rows the batch touches.  The tables themselves are
 // brought up to date by K1 afterwards; both evaluate the same per-element expression.
-template <typename W, typename C, bool UPDATE>
+// UPDATES: 0, 1, or 2 for any number of them.  (One alone is not a loop: where float16 results are made, whether the compiler folds a rounding
+// into the multiply-add in front of it depends on such things, and a run is to keep its bits.)
+template <typename W, typename C, int UPDATES>
 __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a) {
     const int dv = a.d >> 2;
     const int64_t gi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -503,7 +505,6 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a) {
     const int t = (int)(gi / dv), j = (int)(gi % dv) * 4;
     const int id = a.tokens[t];
     const int pos = t % a.seq + a.pos_offset;
-    const float c = UPDATE ? *a.c_ptr : 0.f;
     constexpr bool kScaled = (Fmt<W>::kBytes == 1);
     float hp[4] = {0.f, 0.f, 0.f, 0.f}, hm[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -518,11 +519,12 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a) {
             th[i] = Fmt<W>::load(tv.v[i]);
             if (kScaled) th[i] *= inv_scale;
         }
-        if (UPDATE) {
-            gaussian4(a.k_prev, (uint32_t)which, e, z);
+        auto update = [&](int n) {
+            const float c = a.c_ptr[n];
+            gaussian4(a.k_upd[n], (uint32_t)which, e, z);
             uint32_t rw[4] = {0u, 0u, 0u, 0u};
             const bool sr = Fmt<W>::kBytes < 4 && a.stochastic != 0;
-            if (sr) rounding_words(a.k_prev, (uint32_t)which, e >> 3, rw);
+            if (sr) rounding_words(a.k_upd[n], (uint32_t)which, e >> 3, rw);
             // this group of 4 is the lower or the upper half of its Philox call: rounding words 0, 1 or 2, 3
             const uint32_t r2[2] = {(e & 4) ? rw[2] : rw[0], (e & 4) ? rw[3] : rw[1]};
 #pragma unroll
@@ -533,6 +535,11 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a) {
                 th[i] = Fmt<W>::load(sr ? store_stochastic<W>(us, r16) : Fmt<W>::store(us));
                 if (kScaled) th[i] *= inv_scale;
             }
+        };
+        if constexpr (UPDATES == 1) update(0);
+        if constexpr (UPDATES == 2) {
+#pragma unroll 1
+            for (int n = 0; n < a.n_upd; ++n) update(n);
         }
         if (a.single) {
 #pragma unroll
@@ -553,15 +560,17 @@ __global__ __launch_bounds__(256) void embed_kernel(EmbedArgs a) {
     *reinterpret_cast<float4*>(om) = make_float4(hm[0], hm[1], hm[2], hm[3]);
 }
 
-zo2_status embed_gather(const EmbedArgs& a, int wire_dtype, int compute_dtype, bool update, hipStream_t st) {
+zo2_status embed_gather(const EmbedArgs& a, int wire_dtype, int compute_dtype, hipStream_t st) {
     if (a.T == 0) return ZO2_OK;
+    ZO2_OP_CHECK(a.n_upd >= 0 && a.n_upd <= EmbedArgs::kMaxUpdates, ZO2_EINVAL, "embed: %d updates", a.n_upd);
     ZO2_OP_CHECK(a.d % 4 == 0, ZO2_EINVAL, "embed: d %d not a multiple of 4", a.d);
     const int64_t n = (int64_t)a.T * (a.d / 4);
     const dim3 grid((unsigned)((n + 255) / 256)), block(256);
     ZO2_DISPATCH_WIRE(wire_dtype, W, {
         ZO2_DISPATCH_COMPUTE(compute_dtype, C, {
-            if (update) hipLaunchKernelGGL((embed_kernel<W, C, true>), grid, block, 0, st, a);
-            else hipLaunchKernelGGL((embed_kernel<W, C, false>), grid, block, 0, st, a);
+            if (a.n_upd > 1) hipLaunchKernelGGL((embed_kernel<W, C, 2>), grid, block, 0, st, a);
+            else if (a.n_upd) hipLaunchKernelGGL((embed_kernel<W, C, 1>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((embed_kernel<W, C, 0>), grid, block, 0, st, a);
         });
     });
     ZO2_HIP_LAUNCH_CHECK();

@@ -165,6 +165,11 @@ struct zo2_ctx {
     char *wide_wp[kMaxWide], *wide_wm[kMaxWide];
     char *wide_x, *wide_q, *wide_k, *wide_v, *wide_ctx, *wide_mid, *wide_ws;      // [direction][stream][token][...]
     size_t wide_ws_bytes;
+    // The same for the head: up to `head_wide` directions, on their own copies of the vocabulary matrix, in the room that the blocks have left by then.
+    int head_wide;
+    char *head_wp[kMaxWide], *head_wm[kMaxWide];
+    char *head_fln, *head_x;             // [direction][stream] copies of the final LayerNorm's vectors; its output
+    float *head_pmax, *head_psum, *head_lab, *head_loss;
     bool overlap_k1;
     hipStream_t sk;                     // optional fourth stream for that overlap
     hipEvent_t ev_k1done[2], ev_fwd_done[2], ev_embed;
@@ -676,6 +681,21 @@ static zo2_status plan(zo2_ctx* c, int T, int batch, int seq) {
             for (int j = 0; j < w; ++j) { c->wide_wp[j] = wp[j]; c->wide_wm[j] = wm[j]; }
             c->wide_x = x; c->wide_q = q; c->wide_k = k; c->wide_v = v; c->wide_ctx = ctx; c->wide_mid = mid; c->wide_ws = ws;
             c->wide_ws_bytes = w * split_bytes;
+        }
+    }
+    c->head_wide = 1;
+    if (n_dirs > 1 && resident && fused_ce && !fuse && !two_sets && !c->sk && !forced && k1_round_applicable(g.wire_dtype, g.compute_dtype)) {
+        for (int w = std::min(n_dirs, (int)zo2_ctx::kMaxWide); w > 1 && c->head_wide == 1; --w) {
+            size_t at = align_up(off, 256);
+            auto take = [&](size_t bytes) { char* p = base + at; at += align_up(bytes, 256); return p; };
+            char *wp[zo2_ctx::kMaxWide] = {}, *wm[zo2_ctx::kMaxWide] = {};
+            for (int j = 0; j < w; ++j) { wp[j] = take((size_t)head_elems * c->csz); wm[j] = take((size_t)head_elems * c->csz); }
+            char *fln = take(2 * w * align_up((size_t)c->fln_elems * c->csz, 256)), *x = take(rows2 * w * d * c->csz), *pmax = take(rows2 * w * ce_parts * 4),
+                 *psum = take(rows2 * w * ce_parts * 4), *lab = take(rows2 * w * 4), *loss = take(rows2 * w * 4);
+            if (at > budget) continue;
+            c->head_wide = w;
+            for (int j = 0; j < w; ++j) { c->head_wp[j] = wp[j]; c->head_wm[j] = wm[j]; }
+            c->head_fln = fln; c->head_x = x; c->head_pmax = (float*)pmax; c->head_psum = (float*)psum; c->head_lab = (float*)lab; c->head_loss = (float*)loss;
         }
     }
     c->logit_rows = (int)lrows;
@@ -1285,6 +1305,55 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
     return ZO2_OK;
 }
 
+// A sweep of a round over one tensor or two: all deferred updates (updates = true), and the copies of directions j0 .. j0 + n - 1.
+static zo2_status k1_round_tables(zo2_ctx* c, void* theta, const K1Seg* seg, int nseg, bool updates, const uint64_t* seeds, int n, char* const* wp, char* const* wm, float eps) {
+    K1RoundArgs a;
+    memset(&a, 0, sizeof(a));
+    a.theta = theta; a.c_ptr = coef_slot(c, 0); a.n_upd = updates ? c->n_pend : 0; a.n_dir = n; a.nseg = nseg;
+    a.stochastic = c->stochastic ? 1 : 0; a.eps = eps;
+    for (int u = 0; u < a.n_upd; ++u) a.k_upd[u] = philox_keys(c->pend_seed[u]);
+    for (int j = 0; j < n; ++j) { a.w_plus[j] = wp[j]; a.w_minus[j] = wm[j]; a.k_dir[j] = philox_keys(seeds[j]); }
+    for (int k = 0; k < nseg; ++k) { a.seg[k] = seg[k]; a.seg[k].scale = c->scales[seg[k].tensor_id]; }
+    OPK(c, ZO2_KC_K1, k1_round_launch(a, c->cfg.wire_dtype, c->cfg.compute_dtype, c->sc));
+    return ZO2_OK;
+}
+static inline K1Seg whole_tensor(int64_t off, int64_t n, uint32_t tid) { return K1Seg{off, 0, (uint64_t)n, tid, 1.0f, 0}; }
+
+// The head under directions j0 .. j0 + n - 1 of a round: final LayerNorm, vocabulary matrix and row losses of all of them in one launch each.
+// Row losses of direction j0 + j: head_loss + 2 j T.  (Vocabulary 50272, d 2048, 4 x 128 tokens, four directions, in us, one after the
+// other -> together: sweeps of the matrix 579, three of them in front of the gather -> 367; logits 977, four launches of 3.1 rounds of tiles
+// each -> 755; a step of 8 blocks 7294 -> 6779.)
+static zo2_status head_round(zo2_ctx* c, int T, const uint64_t* seeds, int j0, int n, bool update, float eps) {
+    const zo2_config& g = c->cfg;
+    const int d = g.d_model, dt = g.compute_dtype;
+    const size_t cs = c->csz, half_d = (size_t)T * d * cs;
+    const int64_t set = (int64_t)align_up((size_t)c->fln_elems * cs, 256);      // from one copy of the final LayerNorm's vectors to the next
+    char *fp[zo2_ctx::kMaxWide], *fm[zo2_ctx::kMaxWide];
+    for (int j = 0; j < n; ++j) { fp[j] = c->head_fln + 2 * j * set; fm[j] = fp[j] + set; }
+    const K1Seg ln[2] = {whole_tensor(0, d, fln_tid(c)), whole_tensor(c->fln_off_b, d, fln_tid(c) + 1)};
+    { zo2_status s = k1_round_tables(c, c->d_fln, ln, 2, update, seeds + j0, n, fp, fm, eps); if (s != ZO2_OK) return s; }
+    const size_t b = (size_t)c->fln_off_b * cs;
+    if ((n == 1 || c->hs[j0 + 1] - c->hs[j0] == (int64_t)2 * T * d) && layernorm_sets_applicable(dt, d, c->head_x, fp[0], fp[0] + b, set)) {
+        OPK(c, ZO2_KC_LN, layernorm_sets(dt, c->hs[j0], fp[0], fp[0] + b, set, c->head_x, 2 * n * T, T, d, g.ln_eps, c->sc));
+    } else {
+        for (int j = 0; j < n; ++j)
+            OPK(c, ZO2_KC_LN, layernorm(dt, c->hs[j0 + j], fp[j], fp[j] + b, fm[j], fm[j] + b, c->head_x + 2 * j * half_d, 2 * T, T, d, g.ln_eps, c->sc));
+    }
+    const K1Seg table = whole_tensor(0, c->tok_elems, g.tied_lm_head ? 0u : lm_tid(c));
+    { zo2_status s = k1_round_tables(c, g.tied_lm_head ? c->d_tok : c->d_lm, &table, 1, update, seeds + j0, n, c->head_wp, c->head_wm, eps); if (s != ZO2_OK) return s; }
+    GemmArgs ga;
+    memset(&ga, 0, sizeof(ga));
+    ga.M = T; ga.N = g.vocab; ga.K = d; ga.ldx = d; ga.ldw = d; ga.ldy = g.vocab; ga.out_f32 = 1; ga.nprob = 2 * n; ga.ce_mode = 1; ga.part_ld = 2 * (int64_t)n * T;
+    for (int i = 0; i < 2 * n; ++i) {
+        GemmProblem& p = ga.p[i];
+        p.X = c->head_x + i * half_d; p.W = i & 1 ? c->head_wm[i / 2] : c->head_wp[i / 2]; p.out_scale = 1.0f; p.labels = c->d_labels;
+        p.part_max = c->head_pmax + (size_t)i * T; p.part_sum = c->head_psum + (size_t)i * T; p.label_logit = c->head_lab + (size_t)i * T;
+    }
+    OPK(c, ZO2_KC_GEMM, gemm_launch(ga, dt, c->sc));
+    OPK(c, ZO2_KC_CE, ce_combine(c->head_pmax, c->head_psum, c->head_lab, c->d_labels, 2 * n * T, c->ce_parts, 2 * (int64_t)n * T, 0, T, c->head_loss, c->sc, keep_order(c)));
+    return ZO2_OK;
+}
+
 // ---------------------------------------------------------------------------------- streaming (Alg. 3)
 // U(W_i): runs on the upload stream once the slot's previous occupant has left it.
 static zo2_status enqueue_upload(zo2_ctx* c, int l) {
@@ -1422,7 +1491,9 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
 
     TraceRange step_range(ns == 2 ? (extra ? "zo2_step_extra" : "zo2_step") : "zo2_eval");
     // DualForward(Embedding)
-    {   // earlier directions of the last round: the tables first, the gather then sees them
+    // (a head of several directions sweeps the tables once, with all deferred updates; the gather makes them for the rows it reads)
+    const bool round_head = ndirs > 1 && ns == 2 && c->head_wide > 1;
+    if (!round_head) {   // earlier directions of the last round: the tables first, the gather then sees them
         zo2_status s = earlier_updates_tensor(c, c->d_tok, c->tok_elems, 0);
         if (s == ZO2_OK) s = earlier_updates_tensor(c, c->d_pos, c->pos_elems, 1);
         if (s != ZO2_OK) return s;
@@ -1431,14 +1502,20 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
     memset(&ea, 0, sizeof(ea));
     ea.tok_emb = c->d_tok; ea.pos_emb = c->d_pos; ea.tokens = c->d_tokens; ea.h = c->h;
     ea.T = T; ea.seq = seq; ea.d = d; ea.pos_offset = g.pos_offset; ea.eps = eps; ea.single = ns == 1; ea.stochastic = c->stochastic ? 1 : 0;
-    ea.scale_tok = c->scales[0]; ea.scale_pos = c->scales[1]; ea.c_ptr = coef_slot(c, c->n_pend > 0 ? c->n_pend - 1 : 0);
-    ea.k_prev = philox_keys(c->n_pend > 0 ? c->pend_seed[c->n_pend - 1] : 0); ea.k_cur = philox_keys(seed);
+    ea.scale_tok = c->scales[0]; ea.scale_pos = c->scales[1]; ea.n_upd = !upd ? 0 : round_head ? c->n_pend : 1;
+    const int first_upd = c->n_pend - ea.n_upd;
+    ea.c_ptr = coef_slot(c, first_upd);
+    for (int u = 0; u < ea.n_upd; ++u) ea.k_upd[u] = philox_keys(c->pend_seed[first_upd + u]);
     for (int j = 0; j < ndirs; ++j) {      // every direction gathers before the tables are updated in place below
         ea.h = c->hs[j];
         ea.k_cur = philox_keys(seeds[j]);
-        OPK(c, ZO2_KC_EMBED, embed_gather(ea, g.wire_dtype, dt, upd, c->sc));
+        OPK(c, ZO2_KC_EMBED, embed_gather(ea, g.wire_dtype, dt, c->sc));
     }
-    if (upd) {
+    if (upd && round_head) {
+        const K1Seg pos = whole_tensor(0, c->pos_elems, 1), tok = whole_tensor(0, c->tok_elems, 0);
+        { zo2_status s = k1_round_tables(c, c->d_pos, &pos, 1, true, nullptr, 0, nullptr, nullptr, 0.f); if (s != ZO2_OK) return s; }
+        if (!g.tied_lm_head) { zo2_status s = k1_round_tables(c, c->d_tok, &tok, 1, true, nullptr, 0, nullptr, nullptr, 0.f); if (s != ZO2_OK) return s; }
+    } else if (upd) {
         { zo2_status s = k1_tensor(c, c->d_pos, c->pos_elems, 1, false, nullptr, nullptr, seed, eps); if (s != ZO2_OK) return s; }
         if (!g.tied_lm_head) { zo2_status s = k1_tensor(c, c->d_tok, c->tok_elems, 0, false, nullptr, nullptr, seed, eps); if (s != ZO2_OK) return s; }
     }
@@ -1514,6 +1591,13 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
     for (int j = 0; j < ndirs; ++j) {
         const uint64_t seed = seeds[j];
         set_dir(j);
+        if (round_head) {
+            const int in_group = j % c->head_wide;
+            if (in_group == 0) { zo2_status s = head_round(c, T, seeds, j, std::min(c->head_wide, ndirs - j), upd && j == 0, eps); if (s != ZO2_OK) { set_dir(0); return s; } }
+            OPK(c, ZO2_KC_CE, loss_epilogue(c->head_loss + (size_t)2 * in_group * T, c->d_labels, T, eps, lr, ns, c->d_state + 4, coef_slot(c, j), c->sc));
+            HIPCHK(c, hipMemcpyAsync(pass_result(c, j), c->d_state + 4, 4 * sizeof(float), hipMemcpyDeviceToHost, c->sc));
+            continue;
+        }
         if (c->apply_now)
             for (int k = 0; k + 1 < c->n_pend; ++k) { zo2_status s = k1_final_ln(c, false, 0, 0.f, k); if (s != ZO2_OK) return s; }
         { zo2_status s = k1_final_ln(c, true, seed, eps); if (s != ZO2_OK) return s; }

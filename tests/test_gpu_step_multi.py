@@ -218,3 +218,39 @@ def test_directions_on_tiles_of_256_rows(batch, seq, d_ffn, dirs):
     assert found[0][0] == found[1][0]
     for n in found[0][1]:
         assert np.array_equal(found[0][1][n], found[1][1][n]), n
+
+
+@pytest.mark.parametrize("wire,sr,tied,dirs", [("bf16", False, True, 4), ("bf16", False, False, 5), ("fp8_e4m3", True, True, 3), ("f32", False, False, 2), ("bf16", True, True, 7)])
+def test_head_of_several_directions(wire, sr, tied, dirs):
+    """The head takes a round's directions together too, and the tables all deferred updates in one sweep behind a gather that makes them
+    for the rows it reads: the bits of a budget that leaves no room for it, of one that leaves room for two directions, and of single directions.
+    Vocabulary with a last tile of 4 columns and a last chunk of the sweep that is not full; more directions than go together; a last
+    round of another size."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=1, d_model=128, n_heads=4, d_ffn=256, vocab=516, max_pos=160, tied=tied)
+    P = si.make_weights(cfg, seed=41, std=0.05, ln_jitter=True)
+    tok = si.make_tokens(cfg["vocab"], 2, 150, seed=42)
+    lab = si.next_token_labels(tok)
+    lab[1, 7] = -100
+    found = []
+    for how in ("room", "room for two", "no room", "one by one"):
+        scales = np.full(4 + 16 + (0 if tied else 1), 64.0, np.float32) if wire.startswith("fp8") else None
+        ctx = b.Zo2Context(cfg, P, wire=wire, compute="bf16", arena_bytes=256 << 20, scales=scales)
+        ctx.set_wire_rounding(sr)
+        rnd = _sequential_round if how == "one by one" else _multi_round
+        out = [rnd(ctx, tok, lab, [7 + j for j in range(dirs)], 1e-3, 1e-3)]
+        used = ctx.plan()["bytes_used"]
+        if how == "no room":
+            ctx.set_resident_budget(used)
+        elif how == "room for two":      # four copies of the vocabulary matrix, activations and the partials of two directions, and half a direction more
+            ctx.set_resident_budget(used + 5 * (516 * 128 * 2 + 300 * 128 * 2 + 300 * (2 * 12 + 2) * 4) + 8192)
+        out += [rnd(ctx, tok, lab, [20 * k + j for j in range(n)], 1e-3, 1e-3) for k, n in ((1, dirs), (2, 2))]
+        out.append(tuple(float(v) for v in ctx.step(tok, lab, 90, 1e-3, 1e-3)))
+        assert ctx.plan()["resident"]
+        ctx.flush(); ctx.sync_to_host()
+        found.append((out, ctx.parameters()))
+        ctx.close()
+    for out, params in found[1:]:
+        assert out == found[0][0]
+        for n in params:
+            assert np.array_equal(params[n], found[0][1][n]), n
