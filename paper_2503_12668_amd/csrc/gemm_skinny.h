@@ -9,7 +9,7 @@ namespace zo2 {
 struct SkinnyProblem {
     const void* Xp;         // [M, ldx] activations of the "+" stream (compute dtype)
     const void* Xm;         // [M, ldx] activations of the "-" stream
-    const void* theta;      // [N, K] the weight as stored (dense, row n = output feature n; its update already applied)
+    void* theta;            // [N, K] the weight as stored (dense, row n = output feature n); rewritten if an update is applied
     const void* bias_p;     // [N] perturbed bias of the "+" stream (compute dtype) or nullptr
     const void* bias_m;
     const float* res_p;     // [M, ldy] float32 residual or nullptr
@@ -22,13 +22,17 @@ struct SkinnyProblem {
 
 struct SkinnyArgs {
     static constexpr int kMaxProblems = 3;
-    int32_t M, N, K;        // M <= 256 rows per stream; K % 64 == 0; N % 4 == 0
+    int32_t M, N, K;        // M <= 256 rows per stream (float32: 96); K % 64 == 0; N % 4 == 0
     int64_t ldx, ldy;
     int32_t relu, out_f32, nprob;
     int32_t in_order;       // 1: one wavefront adds a slab's k in order, where two would share it (33 - 128 rows)
     int32_t splits, k_per_split;     // filled in by skinny_launch: the k range is cut into `splits` pieces of k_per_split
     float eps;
     PhiloxKeys key;         // of the step seed
+    // float32 only: the update that theta lacks, applied on the way (theta' = theta - c z_prev is written back and used); c_ptr, the device scalar
+    // eta g, is nullptr where theta is up to date
+    PhiloxKeys key_prev;
+    const float* c_ptr;
     float* partial;         // filled in by skinny_launch: [nprob][splits][2][M][N] float32 partial sums
     // cross-entropy mode (skinny_launch_ce, the LM head): per row and 64-column span max and sum(exp(y - max)) of the logits,
     // span-major, and the label's logit; the "-" stream's M rows behind the "+" stream's.  As in GemmProblem.
@@ -47,6 +51,10 @@ zo2_status skinny_launch(SkinnyArgs& a, int dtype, void* workspace, size_t works
 // The LM head on the same loader: one problem without bias, residual or output matrix; at most 128 rows.
 zo2_status skinny_launch_ce(SkinnyArgs& a, int dtype, hipStream_t st);
 size_t skinny_workspace_bytes(int M, int N, int K, int nprob);
+// float32: the sums as they are, into out[2][M][N] (one problem, k in one piece)
+zo2_status skinny_launch_sums(SkinnyArgs& a, float* out, hipStream_t st);
+bool skinny_f32_applicable(int M, int N, int K);
+zo2_status skinny_f32_launch(const SkinnyArgs& a, hipStream_t st);      // gemm_skinny_f32.hip; splits, k_per_split and partial are set
 bool skinny_applicable(int M, int N, int K, int dtype);
 // W+ and W- of rows [n0, n0 + rows) of a dense [N, K] tensor, chunk by chunk with the loader's arithmetic (a test hook)
 zo2_status skinny_perturbed_rows(int dtype, const void* theta, int64_t K, int64_t n0, int64_t rows, uint32_t tensor_id, uint64_t seed,

@@ -10,6 +10,8 @@
 // (deterministic, unlike atomics) and applies bias, scale, ReLU and residual.
 #include "gemm_skinny.h"
 
+#include <algorithm>
+
 namespace zo2 {
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
@@ -358,6 +360,7 @@ __global__ __launch_bounds__(256) void perturbed_rows_kernel(const T* theta, uin
 }
 
 bool skinny_applicable(int M, int N, int K, int dtype) {
+    if (dtype == ZO2_F32) return skinny_f32_applicable(M, N, K);
     return (dtype == ZO2_BF16 || dtype == ZO2_F16) && M >= 1 && M <= 256 && N >= 1 && N % 4 == 0 && K >= 64 && K % 64 == 0;
 }
 
@@ -370,6 +373,17 @@ static void pick_splits(int M, int N, int K, int nprob, int& splits, int& k_per_
     const int cap = K / M > 1 ? K / M : 1;
     want = want > cap ? cap : want;
     want = want < 1 ? 1 : (want > slabs ? slabs : want);
+    const int slabs_per = (slabs + want - 1) / want;
+    k_per_split = slabs_per * kSkBK;
+    splits = (slabs + slabs_per - 1) / slabs_per;
+}
+
+// float32: one workgroup per compute unit, of two slabs and more, as many pieces as the workspace holds
+static void pick_splits_f32(int M, int N, int K, int nprob, size_t workspace_bytes, int& splits, int& k_per_split) {
+    const int n_tiles = (N + kSkBN - 1) / kSkBN, slabs = K / kSkBK;
+    const size_t room = workspace_bytes / ((size_t)nprob * 2 * M * N * sizeof(float));
+    int want = std::min(std::max(1, 256 / (n_tiles * nprob)), slabs);
+    want = (int)std::max<size_t>(1, std::min<size_t>(want, room));
     const int slabs_per = (slabs + want - 1) / want;
     k_per_split = slabs_per * kSkBK;
     splits = (slabs + slabs_per - 1) / slabs_per;
@@ -402,28 +416,31 @@ static zo2_status skinny_launch_mt(const SkinnyArgs& a, hipStream_t st) {
 }
 
 template <typename T>
-static zo2_status skinny_launch_t(const SkinnyArgs& a, hipStream_t st, bool sum) {
-    const dim3 block(256);
-    zo2_status s = a.M <= 32 ? skinny_launch_mt<T, 1, false>(a, st)
-                 : a.in_order && a.M <= 64 ? skinny_launch_mt<T, 2, false, 4>(a, st) : a.in_order && a.M <= 128 ? skinny_launch_mt<T, 4, false, 4>(a, st)
-                 : a.M <= 64 ? skinny_launch_mt<T, 2, false>(a, st) : a.M <= 96 ? skinny_launch_mt<T, 3, false>(a, st) : a.M <= 128 ? skinny_launch_mt<T, 4, false>(a, st)
-                 : a.M <= 192 ? skinny_launch_mt<T, 6, false>(a, st) : skinny_launch_mt<T, 8, false>(a, st);
-    if (s != ZO2_OK || !sum) return s;
+static zo2_status launch_reduce(const SkinnyArgs& a, hipStream_t st) {
     const size_t work = 2 * (size_t)a.M * (a.N / 4);
-    const dim3 rgrid((unsigned)((work + 255) / 256), a.nprob);
+    const dim3 rgrid((unsigned)((work + 255) / 256), a.nprob), block(256);
     if (a.out_f32) hipLaunchKernelGGL((skinny_reduce_kernel<T, float>), rgrid, block, 0, st, a);
     else hipLaunchKernelGGL((skinny_reduce_kernel<T, T>), rgrid, block, 0, st, a);
     ZO2_HIP_LAUNCH_CHECK();
     return ZO2_OK;
 }
 
+template <typename T>
+static zo2_status skinny_launch_t(const SkinnyArgs& a, hipStream_t st, bool sum) {
+    zo2_status s = a.M <= 32 ? skinny_launch_mt<T, 1, false>(a, st)
+                 : a.in_order && a.M <= 64 ? skinny_launch_mt<T, 2, false, 4>(a, st) : a.in_order && a.M <= 128 ? skinny_launch_mt<T, 4, false, 4>(a, st)
+                 : a.M <= 64 ? skinny_launch_mt<T, 2, false>(a, st) : a.M <= 96 ? skinny_launch_mt<T, 3, false>(a, st) : a.M <= 128 ? skinny_launch_mt<T, 4, false>(a, st)
+                 : a.M <= 192 ? skinny_launch_mt<T, 6, false>(a, st) : skinny_launch_mt<T, 8, false>(a, st);
+    return s != ZO2_OK || !sum ? s : launch_reduce<T>(a, st);
+}
+
 zo2_status skinny_launch(SkinnyArgs& a, int dtype, void* workspace, size_t workspace_bytes, hipStream_t st, bool sum) {
     ZO2_OP_CHECK(skinny_applicable(a.M, a.N, a.K, dtype), ZO2_EINVAL,
-                 "skinny gemm: needs 16-bit dtype, 1 <= M <= 256, N %% 4 == 0, K %% 64 == 0 (got %d x %d x %d)", a.M, a.N, a.K);
+                 "skinny gemm: needs 1 <= M <= 256 (float32: 96), N %% 4 == 0, K %% 64 == 0 (got %d x %d x %d)", a.M, a.N, a.K);
     ZO2_OP_CHECK(a.nprob >= 1 && a.nprob <= SkinnyArgs::kMaxProblems, ZO2_EINVAL, "skinny gemm: %d problems", a.nprob);
     ZO2_OP_CHECK(a.ldx >= a.K && a.ldx % 8 == 0 && a.ldy >= a.N && a.ldy % 4 == 0, ZO2_EINVAL, "skinny gemm: bad leading dimension");
     ZO2_OP_CHECK((size_t)a.M * (size_t)a.ldx < 0xffffffffull, ZO2_EINVAL, "skinny gemm: activation panel too large");
-    const size_t osz = a.out_f32 ? 4 : 2;
+    const size_t osz = a.out_f32 || dtype == ZO2_F32 ? 4 : 2;
     for (int i = 0; i < a.nprob; ++i) {
         const SkinnyProblem& p = a.p[i];
         ZO2_OP_CHECK(p.Xp && p.Xm && p.theta && p.Yp && p.Ym, ZO2_EINVAL, "skinny gemm: NULL operand in problem %d", i);
@@ -433,13 +450,28 @@ zo2_status skinny_launch(SkinnyArgs& a, int dtype, void* workspace, size_t works
                      "skinny gemm: bias / residual must be given for both streams or neither");
         ZO2_OP_CHECK(!p.res_p || a.out_f32, ZO2_EINVAL, "skinny gemm: a residual needs float32 output");
     }
-    pick_splits(a.M, a.N, a.K, a.nprob, a.splits, a.k_per_split);
+    if (dtype == ZO2_F32) pick_splits_f32(a.M, a.N, a.K, a.nprob, workspace_bytes, a.splits, a.k_per_split);
+    else pick_splits(a.M, a.N, a.K, a.nprob, a.splits, a.k_per_split);
     const size_t need = (size_t)a.nprob * a.splits * 2 * (size_t)a.M * a.N * sizeof(float);
     ZO2_OP_CHECK(workspace && ((uintptr_t)workspace & 15) == 0 && workspace_bytes >= need, ZO2_EINVAL,
                  "skinny gemm: workspace of %zu bytes needed (16-byte aligned)", need);
     a.partial = reinterpret_cast<float*>(workspace);
+    if (dtype == ZO2_F32) {
+        const zo2_status s = skinny_f32_launch(a, st);
+        return s != ZO2_OK || !sum ? s : launch_reduce<float>(a, st);
+    }
     if (dtype == ZO2_BF16) return skinny_launch_t<bf16_t>(a, st, sum);
     return skinny_launch_t<f16_t>(a, st, sum);
+}
+
+zo2_status skinny_launch_sums(SkinnyArgs& a, float* out, hipStream_t st) {
+    ZO2_OP_CHECK(skinny_f32_applicable(a.M, a.N, a.K) && a.nprob == 1 && a.ldx >= a.K && a.ldx % 4 == 0, ZO2_EINVAL,
+                 "skinny gemm: %d x %d x %d in %d problems as sums", a.M, a.N, a.K, a.nprob);
+    const SkinnyProblem& p = a.p[0];
+    ZO2_OP_CHECK(p.Xp && p.Xm && p.theta && out && (((uintptr_t)p.Xp | (uintptr_t)p.Xm | (uintptr_t)p.theta | (uintptr_t)out) & 15) == 0, ZO2_EINVAL,
+                 "skinny gemm: NULL operand, or operands not aligned to 16 bytes");
+    a.splits = 1; a.k_per_split = a.K; a.partial = out;
+    return skinny_f32_launch(a, st);
 }
 
 template <typename T>
@@ -449,7 +481,7 @@ static zo2_status skinny_launch_ce_t(const SkinnyArgs& a, hipStream_t st) {
 }
 
 zo2_status skinny_launch_ce(SkinnyArgs& a, int dtype, hipStream_t st) {
-    ZO2_OP_CHECK(skinny_applicable(a.M, a.N, a.K, dtype) && a.M <= 128 && a.nprob == 1, ZO2_EINVAL,
+    ZO2_OP_CHECK(dtype != ZO2_F32 && skinny_applicable(a.M, a.N, a.K, dtype) && a.M <= 128 && a.nprob == 1, ZO2_EINVAL,
                  "skinny head: needs 16-bit dtype, 1 <= M <= 128, N %% 4 == 0, K %% 64 == 0 (got %d x %d x %d)", a.M, a.N, a.K);
     ZO2_OP_CHECK(a.ldx >= a.K && a.ldx % 8 == 0 && (size_t)a.M * (size_t)a.ldx < 0xffffffffull, ZO2_EINVAL, "skinny head: bad leading dimension");
     const SkinnyProblem& p = a.p[0];

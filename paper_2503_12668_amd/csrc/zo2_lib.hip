@@ -83,6 +83,7 @@ static constexpr int kDefaultSweeps = 1;       // update + perturb sweeps per bl
 // elements, which keeps its launches on the older kernels (gemm_choose), the line is 64: d 256 x 8, ffn 2048 64 641 -> 585, 100 660 ->
 // 736; d 512, ffn 2048 64 698 -> 674, 80 689 -> 717; d 640 64 747 -> 744; d 704 64 938 -> 762; d 1024, ffn 512 64 790 -> 726.
 static constexpr int kFuseAlways = 64;      // beyond this its workspace must fit into what the ordinary path needs; the line of contexts that keep_order()
+static constexpr int kFuseF32 = 96;         // float32 (why: gemm_skinny_f32.hip)
 static int fuse_max_tokens(int d, int f) {
     if ((int64_t)d * std::min(d, f) <= 1 << 19) return 64;
     return std::min(128, std::max(16, 16 + (d - 1536) * 11 / 128) + (d % 128 ? 16 : 0));
@@ -571,8 +572,11 @@ static zo2_status plan(zo2_ctx* c, int T, int batch, int seq) {
     if (lrows > (size_t)T) lrows = T;
     // few tokens per step: the block projections read the stored weights and perturb in their loader (16-bit storage
     // that is also the compute format, no wire scale)
-    const bool fuse_shapes = g.wire_dtype == g.compute_dtype && g.compute_dtype != ZO2_F32 && T <= 256 && d % 64 == 0 && f % 64 == 0 &&
-                             (size_t)T * f * 2 < 0xffffffffull;
+    const bool f32 = g.compute_dtype == ZO2_F32;
+    // (float32: the pieces go to the logits, which are idle until the head)
+    const bool fuse_f32 = f32 && T <= kFuseF32 && (size_t)T * V >= (size_t)T * std::max(3 * d, f);
+    const bool fuse_shapes = g.wire_dtype == g.compute_dtype && (f32 ? fuse_f32 : T <= 256) && d % 64 == 0 && f % 64 == 0 &&
+                             (size_t)T * f * 2 < 0xffffffffull && std::max(d, f) < (size_t)1 << 22;
     size_t split_bytes = 0, fuse_bytes = 0;
     if (c->split_k >= 0 && g.compute_dtype != ZO2_F32) {      // split-k partial sums of the block projections (steps and single forwards)
         for (int ns_ = 1; ns_ <= 2; ++ns_) {
@@ -581,17 +585,17 @@ static zo2_status plan(zo2_ctx* c, int T, int batch, int seq) {
                 split_bytes = std::max(split_bytes, gemm_splitk_workspace_bytes(T, sh[0], sh[2], gemm_pick_splits(T, sh[0], sh[1], sh[2], g.compute_dtype)));
         }
     }
-    if (fuse_shapes) {
+    if (fuse_shapes && !f32) {
         fuse_bytes = std::max(std::max(skinny_workspace_bytes(T, (int)d, (int)d, 3), skinny_workspace_bytes(T, (int)d, (int)d, 1)),
                               std::max(skinny_workspace_bytes(T, (int)f, (int)d, 1), skinny_workspace_bytes(T, (int)d, (int)f, 1)));
     }
     // above 64 tokens only where the slices' partial sums take no more than the logits that the head's partials replace, so
     // that no budget that holds the ordinary path is too small for this one
     const size_t freed = fused_ce && T < 256 ? 2 * std::min<size_t>(T, 128) * V * 4 - rows2 * (2 * ce_parts + 1) * 4 : 0;
-    const bool few_tokens = keep_order(c) ? T <= kFuseAlways
+    const bool few_tokens = f32 ? T <= kFuseF32 : keep_order(c) ? T <= kFuseAlways
                                           : T <= fuse_max_tokens((int)d, (int)f) && (T <= kFuseAlways || fuse_bytes <= split_bytes + freed);
-    const bool fuse = fuse_shapes && c->loader_fusion >= 0 && (c->loader_fusion == 1 || few_tokens) && !c->sk;
-    const size_t sk_ws_bytes = std::max(split_bytes, fuse ? fuse_bytes : 0);
+    const bool fuse = fuse_shapes && c->loader_fusion >= 0 && (c->loader_fusion == 1 || few_tokens) && (f32 || !c->sk);
+    const size_t sk_ws_bytes = std::max(split_bytes, fuse ? fuse_bytes : 0);      // (float32: none)
     size_t act = 0;
     auto sz = [&](size_t bytes) { size_t o = act; act = align_up(act + bytes, 256); return o; };
     const int n_dirs = std::max(1, c->want_dirs);
@@ -618,7 +622,8 @@ static zo2_status plan(zo2_ctx* c, int T, int batch, int seq) {
     // it was given, then the default organisation, then ever smaller scratch sets until 3 block slots fit
     const int forced = c->scratch_plan_forced;
     const int first = forced ? forced : kDefaultSweeps;
-    for (int attempt = (c->sk && !forced ? 0 : 1); attempt < 4; ++attempt) {
+    // (in float32 steps on the loader path have no sweep that a stream of its own could take)
+    for (int attempt = (c->sk && !forced && !fuse ? 0 : 1); attempt < 4; ++attempt) {
         two_sets = attempt == 0;
         sweeps = attempt == 0 ? 1 : attempt == 1 ? first : attempt == 2 ? std::max(first, 2) : 4;
         scratch = scratch_for(sweeps);
@@ -1220,11 +1225,20 @@ static zo2_status block_forward_round(zo2_ctx* c, int l, char* bucket, int batch
 // perturb in their weight loader, both streams per pass over the weights (gemm_skinny.hip).
 static const int kVecTensors[10] = {0, 1, 3, 5, 7, 9, 10, 11, 13, 15};      // ln1.w ln1.b q.b k.b v.b o.b ln2.w ln2.b fc1.b fc2.b
 
+// float32: the same loader applies the last deferred update, so that a matrix is read and written once.  (In 16 bits a sweep does: with two draws an
+// element the loader is bound by the vector ALU, and the sweep leaves the block in the memory-side cache; d 2048, 12 blocks, 1 x 16 tokens 1583 us, with
+// the update in the loader 1596; d 4096, 4 blocks, 1 x 20 1532 against 1481.)
+static void loader_applies(const zo2_ctx* c, SkinnyArgs& sa) {
+    sa.key_prev = philox_keys(c->pend_seed[c->n_pend - 1]);
+    sa.c_ptr = coef_slot(c, c->n_pend - 1);
+}
+
 static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch, int seq, uint64_t seed, float eps, hipEvent_t k1_done) {
     const zo2_config& g = c->cfg;
     const int T = batch * seq, d = g.d_model, f = g.d_ffn, dh = d / g.n_heads;
     const int dt = g.compute_dtype;
     const size_t cs = c->csz;
+    const bool f32 = dt == ZO2_F32;
     const size_t half_d = (size_t)T * d * cs, half_f = (size_t)T * f * cs;
     { zo2_status s = earlier_updates_block(c, l, bucket); if (s != ZO2_OK) return s; }
     int64_t voff[ZO2_BLOCK_TENSORS] = {0}, vec_elems = 0;
@@ -1237,27 +1251,32 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
             o += (c->tn[k] + kTensorAlign - 1) / kTensorAlign * kTensorAlign;
         }
         auto is_vec = [](int k) { for (const int v : kVecTensors) if (v == k) return true; return false; };
-        const bool update = fused_update(c);       // without an update the matrices have no part in the sweep
+        // the matrices have no part in the sweep where no update is pending, or where the loader applies it
+        const bool update = fused_update(c), sweep_matrices = update && !f32;
         K1Args a;
         k1_common(c, a, seed, eps);
-        a.theta = bucket; a.w_plus = c->wp; a.w_minus = c->wm; a.packed_w = 1; a.mixed = update ? 1 : 0; a.nseg = 0;
+        a.theta = bucket; a.w_plus = c->wp; a.w_minus = c->wm; a.packed_w = 1; a.mixed = sweep_matrices ? 1 : 0; a.nseg = 0;
         for (int k = 0; k < ZO2_BLOCK_TENSORS; ++k) {
-            if (!update && !is_vec(k)) continue;
+            if (!sweep_matrices && !is_vec(k)) continue;
             K1Seg& sg = a.seg[a.nseg++];
             sg.off = c->offs[k]; sg.e0 = 0; sg.n = (uint64_t)c->tn[k]; sg.tensor_id = block_tid(l, k); sg.scale = 1.0f;
             sg.woff = is_vec(k) ? voff[k] : -1;
         }
         OPK(c, ZO2_KC_K1, k1_launch(a, g.wire_dtype, g.compute_dtype, update, true, c->sc));
     }
-    if (k1_done) HIPCHK(c, hipEventRecord(k1_done, c->sc));      // the block's parameters are final: the offload may start
+    const bool loader_updates = f32 && fused_update(c);
+    if (k1_done && !loader_updates) HIPCHK(c, hipEventRecord(k1_done, c->sc));      // the block's parameters are final: the offload may start
     auto VP = [&](int k) { return (const void*)(c->wp + (size_t)voff[k] * cs); };
     auto VM = [&](int k) { return (const void*)(c->wm + (size_t)voff[k] * cs); };
-    auto TH = [&](int k) { return (const void*)(bucket + (size_t)c->offs[k] * cs); };
+    auto TH = [&](int k) { return (void*)(bucket + (size_t)c->offs[k] * cs); };
+    void* ws = f32 ? (void*)c->logits : c->sk_ws;
+    const size_t ws_bytes = f32 ? f32_split_workspace(c, T) : c->sk_ws_bytes;
     SkinnyArgs sa;
     auto common = [&](int N, int K, int ldx, int ldy, int relu, int out_f32, int nprob) {
         memset(&sa, 0, sizeof(sa));
         sa.M = T; sa.N = N; sa.K = K; sa.ldx = ldx; sa.ldy = ldy; sa.relu = relu; sa.out_f32 = out_f32; sa.nprob = nprob; sa.eps = eps;
         sa.key = philox_keys(seed); sa.in_order = keep_order(c);
+        if (loader_updates) loader_applies(c, sa);
     };
 
     // ---- attention half: h += O(Attn(LN1(h)))
@@ -1269,7 +1288,7 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
         p.Xp = c->x; p.Xm = c->x + half_d; p.theta = TH(2 + 2 * t); p.bias_p = VP(3 + 2 * t); p.bias_m = VM(3 + 2 * t);
         p.Yp = outs[t]; p.Ym = outs[t] + half_d; p.out_scale = t == 0 ? 1.0f / sqrtf((float)dh) : 1.0f; p.tensor_id = block_tid(l, 2 + 2 * t);
     }
-    OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, c->sk_ws, c->sk_ws_bytes, c->sc));
+    OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, ws, ws_bytes, c->sc));
     OPK(c, ZO2_KC_ATTN, attention_launch(dt, c->qb, c->kb, c->vb, c->ctxb, 2 * batch, seq, g.n_heads, dh, d, 0, c->sc));
     common(d, d, d, d, 0, 1, 1);
     {
@@ -1279,7 +1298,7 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
     }
     // the output projection's slices are summed by the pass that makes FFN half's LayerNorm: h += FC2(ReLU(FC1(LN2(h))))
     const bool sum_with_ln = reduce_layernorm_applicable(d);
-    OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, c->sk_ws, c->sk_ws_bytes, c->sc, !sum_with_ln));
+    OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, ws, ws_bytes, c->sc, !sum_with_ln));
     if (sum_with_ln) {
         const RowSum rs = {sa.partial, sa.splits, 2 * (int64_t)T * d, (int64_t)T * d, VP(9), VM(9)};
         ++c->sums_left;
@@ -1293,15 +1312,16 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
         p.Xp = c->x; p.Xm = c->x + half_d; p.theta = TH(12); p.bias_p = VP(13); p.bias_m = VM(13);
         p.Yp = c->mid; p.Ym = c->mid + half_f; p.out_scale = 1.0f; p.tensor_id = block_tid(l, 12);
     }
-    OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, c->sk_ws, c->sk_ws_bytes, c->sc));
+    OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, ws, ws_bytes, c->sc));
     common(d, f, f, d, 0, 1, 1);
     {
         SkinnyProblem& p = sa.p[0];
         p.Xp = c->mid; p.Xm = c->mid + half_f; p.theta = TH(14); p.bias_p = VP(15); p.bias_m = VM(15);
         p.res_p = c->h; p.res_m = c->h + (size_t)T * d; p.Yp = c->h; p.Ym = c->h + (size_t)T * d; p.out_scale = 1.0f; p.tensor_id = block_tid(l, 14);
     }
-    OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, c->sk_ws, c->sk_ws_bytes, c->sc, !leave_fc2));
+    OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, ws, ws_bytes, c->sc, !leave_fc2));
     if (leave_fc2) c->left = RowSum{sa.partial, sa.splits, 2 * (int64_t)T * d, (int64_t)T * d, VP(15), VM(15)};
+    if (k1_done && loader_updates) HIPCHK(c, hipEventRecord(k1_done, c->sc));
     return ZO2_OK;
 }
 
@@ -1606,7 +1626,20 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
         // few tokens: the sweep only updates the vocabulary matrix, the head perturbs it in its loader (c->fuse rules overlap_k1 out)
         const char *head_wp = nullptr, *head_wm = nullptr;      // the vocabulary matrix of the ordinary head
         const bool loader_head = c->fuse && ns == 2 && c->fused_ce && T <= 128;
-        if (loader_head) {
+        const bool loader_logits = c->fuse && ns == 2 && dt == ZO2_F32 && c->logit_rows >= T && skinny_f32_applicable(T, g.vocab, d);      // float32: written
+        if (loader_logits) {
+            char* table = g.tied_lm_head ? c->d_tok : c->d_lm;
+            const uint32_t tid = g.tied_lm_head ? 0u : lm_tid(c);
+            if (!g.tied_lm_head) { zo2_status es = earlier_updates_tensor(c, c->d_lm, c->tok_elems, tid); if (es != ZO2_OK) return es; }
+            SkinnyArgs sa;
+            memset(&sa, 0, sizeof(sa));
+            sa.M = T; sa.N = g.vocab; sa.K = d; sa.ldx = d; sa.nprob = 1; sa.eps = eps; sa.key = philox_keys(seed);
+            sa.p[0].Xp = c->x; sa.p[0].Xm = c->x + (size_t)T * d * c->csz; sa.p[0].theta = table; sa.p[0].tensor_id = tid;
+            if (fused_update(c)) loader_applies(c, sa);
+            OPK(c, ZO2_KC_GEMM, skinny_launch_sums(sa, c->logits, c->sc));
+            for (int s = 0; s < 2; ++s)
+                OPK(c, ZO2_KC_CE, cross_entropy_rows(c->logits + (size_t)s * T * g.vocab, g.vocab, c->d_labels, T, s * T, T, g.vocab, c->row_loss, c->sc));
+        } else if (loader_head) {
             char* table = g.tied_lm_head ? c->d_tok : c->d_lm;
             const uint32_t tid = g.tied_lm_head ? 0u : lm_tid(c);
             if (!g.tied_lm_head) { zo2_status es = earlier_updates_tensor(c, c->d_lm, c->tok_elems, tid); if (es != ZO2_OK) return es; }
@@ -1643,7 +1676,7 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
                 HIPCHK(c, hipStreamWaitEvent(c->sc, c->ev_k1done[sb], 0));
             }
         }
-        if (loader_head) {
+        if (loader_head || loader_logits) {
         } else if (c->fused_ce) {
             // logits are never written: the GEMM epilogue reduces each 64-column span to (max, sum exp) and picks the label's logit
             GemmArgs ga;
@@ -2061,13 +2094,14 @@ extern "C" zo2_status zo2_op_gemm_perturbed(int32_t dtype, int32_t M, int32_t N,
                                             void* Y_minus, int32_t out_dtype, int64_t ldy, float out_scale, int32_t relu, void* workspace,
                                             size_t workspace_bytes, void* stream) {
     if (M == 0 || N == 0) return ZO2_OK;
+    ZO2_OP_CHECK(dtype == ZO2_BF16 || dtype == ZO2_F16, ZO2_EINVAL, "skinny gemm: needs 16-bit dtype");
     ZO2_OP_CHECK(out_dtype == ZO2_F32 || out_dtype == dtype, ZO2_EINVAL, "gemm_perturbed: output dtype must be F32 or the input dtype");
     SkinnyArgs a;
     memset(&a, 0, sizeof(a));
     a.M = M; a.N = N; a.K = K; a.ldx = ldx; a.ldy = ldy; a.relu = relu; a.out_f32 = out_dtype == ZO2_F32; a.nprob = 1; a.eps = eps;
     a.key = philox_keys(seed);
     SkinnyProblem& p = a.p[0];
-    p.Xp = X_plus; p.Xm = X_minus; p.theta = theta; p.bias_p = bias_plus; p.bias_m = bias_minus; p.res_p = residual_plus; p.res_m = residual_minus;
+    p.Xp = X_plus; p.Xm = X_minus; p.theta = const_cast<void*>(theta); p.bias_p = bias_plus; p.bias_m = bias_minus; p.res_p = residual_plus; p.res_m = residual_minus;
     p.Yp = Y_plus; p.Ym = Y_minus; p.out_scale = out_scale; p.tensor_id = tensor_id;
     return skinny_launch(a, dtype, workspace, workspace_bytes, as_stream(stream));
 }

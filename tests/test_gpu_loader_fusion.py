@@ -192,3 +192,64 @@ def test_default_line_of_the_loader_path_by_width(d, f, vocab, line):
             ctx.step(t, si.next_token_labels(t), 9, 1e-3, 0.0)
             assert ctx.plan()["loader_fusion"] == (seq == at), (stochastic, seq)
     ctx.close()
+
+
+@pytest.mark.parametrize("d,f,vocab,batch,seq,tied", [(64, 128, 212, 1, 2, True), (192, 320, 1092, 1, 31, False), (192, 64, 1091, 3, 11, True), (256, 1088, 2052, 1, 64, True),
+                                                        (128, 192, 516, 5, 13, False), (448, 576, 1352, 2, 48, True)])
+def test_float32_loader_updates_as_the_sweep_does(d, f, vocab, batch, seq, tied):
+    """float32: the projections' loader applies the pending update too.  2 - 96 rows (edges of its three heights), features that end inside a
+    workgroup's 128, one slab and several, a vocabulary that the head's loader takes or leaves: the stored parameters are the sweep's bit for bit, the
+    losses those of the ordinary path and of the oracle to the float32 bar, and a second direction at the same parameters agrees as well."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=2, d_model=d, n_heads=d // 64, d_ffn=f, vocab=vocab, max_pos=80, tied=tied)
+    P = si.make_weights(cfg, seed=11, std=0.05, ln_jitter=True)
+    tok = si.make_tokens(vocab, batch, seq, seed=12)
+    lab = si.next_token_labels(tok)
+    oz = zo_step.Zo2Blockwise(opt_model.OptShape(**cfg), copy.deepcopy(P))
+    want = [oz.step(tok, lab, 42, 1e-3, 1e-4), oz.step(tok, lab, 43, 1e-3, 1e-4), oz.step_extra(tok, lab, 44, 1e-3, 1e-4)]
+    got = {}
+    for mode in (1, -1):
+        ctx = b.Zo2Context(cfg, P, arena_bytes=512 << 20)
+        ctx.set_loader_fusion(mode)
+        r = [ctx.step(tok, lab, 42, 1e-3, 1e-4), ctx.step(tok, lab, 43, 1e-3, 1e-4), ctx.step_extra(tok, lab, 44, 1e-3, 1e-4)]
+        assert ctx.plan()["loader_fusion"] == (mode == 1)
+        for a, w in zip(r, want):
+            for k in (0, 1):
+                assert abs(float(a[k]) - float(w[k])) <= 1e-5 * abs(float(w[k])), (mode, a, w)
+        ctx.close()
+        # one update of the same coefficient on either path
+        ctx = b.Zo2Context(cfg, P, arena_bytes=512 << 20)
+        ctx.set_loader_fusion(mode)
+        ctx.set_pending(True, 7, 3e-3)
+        ctx.step(tok, lab, 42, 1e-3, 0.0)
+        ctx.sync_to_host()
+        got[mode] = ctx.parameters()
+        ctx.close()
+    for n in P:
+        assert np.array_equal(got[1][n], got[-1][n]), n
+        assert not np.array_equal(got[1][n], P[n]), n
+
+
+def test_float32_loader_computes_sums_of_tiny_operands_with_float32_products():
+    """Activations of 2^-100 behind the second LayerNorm: FC1's sums are below what three bfloat16 parts hold, FC2's weights of 2^100 bring them
+    back to the residual stream's size.  (eps as small, so that the perturbation leaves them there.)"""
+    b = _b()
+    cfg = si.tiny_config(n_layers=2, d_model=128, n_heads=2, d_ffn=192, vocab=516, max_pos=40)
+    P = si.make_weights(cfg, seed=11, std=0.05, ln_jitter=False)
+    for l in range(2):
+        P[f"blocks.{l}.ln2.w"] = np.full_like(P[f"blocks.{l}.ln2.w"], 2.0 ** -100)
+        P[f"blocks.{l}.fc1.b"] = np.zeros_like(P[f"blocks.{l}.fc1.b"])
+        P[f"blocks.{l}.fc2.w"] = P[f"blocks.{l}.fc2.w"] * np.float32(2.0 ** 100)
+    tok = si.make_tokens(cfg["vocab"], 1, 35, seed=12)
+    lab = si.next_token_labels(tok)
+    want = zo_step.Zo2Blockwise(opt_model.OptShape(**cfg), copy.deepcopy(P)).step(tok, lab, 42, 1e-33, 0.0)
+    plain = {n: (a * 0 if ".fc2.w" in n else a) for n, a in P.items()}
+    without = zo_step.Zo2Blockwise(opt_model.OptShape(**cfg), plain).step(tok, lab, 42, 1e-33, 0.0)
+    assert abs(float(want[0]) - float(without[0])) > 1e-3 * abs(float(want[0]))       # FC2 matters to the loss
+    ctx = b.Zo2Context(cfg, P, arena_bytes=128 << 20)
+    ctx.set_loader_fusion(1)
+    got = ctx.step(tok, lab, 42, 1e-33, 0.0)
+    assert ctx.plan()["loader_fusion"]
+    for k in (0, 1):
+        assert abs(float(got[k]) - float(want[k])) <= 1e-5 * abs(float(want[k])), (got, want)
+    ctx.close()
