@@ -29,7 +29,7 @@ struct SkinnyArgs {
     int32_t splits, k_per_split;     // filled in by skinny_launch: the k range is cut into `splits` pieces of k_per_split
     float eps;
     PhiloxKeys key;         // of the step seed
-    // float32 only: the update that theta lacks, applied on the way (theta' = theta - c z_prev is written back and used); c_ptr, the device scalar
+    // float32, and bfloat16 up to 96 rows: an update that theta lacks, applied on the way (theta' = theta - c z_prev is written back and used); c_ptr, the device scalar
     // eta g, is nullptr where theta is up to date
     PhiloxKeys key_prev;
     const float* c_ptr;
@@ -54,7 +54,8 @@ size_t skinny_workspace_bytes(int M, int N, int K, int nprob);
 // float32: the sums as they are, into out[2][M][N] (one problem, k in one piece)
 zo2_status skinny_launch_sums(SkinnyArgs& a, float* out, hipStream_t st);
 bool skinny_f32_applicable(int M, int N, int K);
-zo2_status skinny_f32_launch(const SkinnyArgs& a, hipStream_t st);      // gemm_skinny_f32.hip; splits, k_per_split and partial are set
+// gemm_skinny_rows.hip: up to 96 rows; splits, k_per_split and partial are set.  ce: the LM head's partials
+zo2_status skinny_rows_launch(const SkinnyArgs& a, int dtype, bool ce, hipStream_t st);
 bool skinny_applicable(int M, int N, int K, int dtype);
 // W+ and W- of rows [n0, n0 + rows) of a dense [N, K] tensor, chunk by chunk with the loader's arithmetic (a test hook)
 zo2_status skinny_perturbed_rows(int dtype, const void* theta, int64_t K, int64_t n0, int64_t rows, uint32_t tensor_id, uint64_t seed,

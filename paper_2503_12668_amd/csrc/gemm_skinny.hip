@@ -78,6 +78,7 @@ __device__ __forceinline__ void mix_from() {
     if constexpr (J + 1 < N) mix_from<N, J + 1>();
 }
 
+static constexpr int kSkRows = 96;          // rows of skinny_rows_kernel
 static constexpr int kSkBN = 128, kSkBK = 64, kSkKC = 8;      // weight rows per workgroup, k per slab, 16-byte chunks per slab row
 
 // MT: 32-row MFMA tiles per stream (the workgroup covers 32 MT rows of each stream, every wavefront all of them).
@@ -88,11 +89,12 @@ static constexpr int kSkBN = 128, kSkBK = 64, kSkKC = 8;      // weight rows per
 // weights never pass through LDS and no wavefront waits for another's generation.  Only the activations are shared:
 // their slab (2 streams x 32 MT rows x 64 k) is staged in LDS, double-buffered, one barrier per slab.
 //
-// What bounds it is the generator: 19 wide multiplies and 16 transcendental operations, 16 cycles each, and about 100
-// ordinary instructions per chunk.  One wavefront alone leaves a good part of that time unused on dependences, so a slab's
+// What bounds it is the generator: about 130 instructions per chunk, 16 of them transcendental, which take twice an ordinary
+// one's time.  One wavefront alone leaves a good part of that time unused on dependences, so a slab's
 // two pairs of chunks go to two wavefronts (NW = 8; their sums meet in LDS at the end, a pair's MFMAs run under the
 // generation of the wavefront's next) where two wavefronts per SIMD fit the registers: up to 128 rows per stream.  Beyond,
 // one wavefront takes both pairs (NW = 4).
+// Up to 96 rows skinny_rows_kernel (gemm_skinny_rows.hip) has taken its place, but for contexts that keep the order of their sums.
 template <typename T, int MT, int NW, bool CE>
 __global__ __launch_bounds__(64 * NW, (MT <= 4 ? 2 : 1)) void skinny_dual_kernel(const SkinnyArgs a) {
     constexpr int MP = 32 * MT, NT = 64 * NW, CX = (MP * kSkKC + NT - 1) / NT;      // rows per stream; X chunks each thread stages per stream and slab
@@ -396,7 +398,7 @@ size_t skinny_workspace_bytes(int M, int N, int K, int nprob) {
     return (size_t)nprob * splits * 2 * (size_t)M * N * sizeof(float);
 }
 
-template <typename T, int MT, bool CE, int NW = (MT >= 2 && MT <= 4 ? 8 : 4)>
+template <typename T, int MT, bool CE, int NW>
 static zo2_status skinny_launch_mt(const SkinnyArgs& a, hipStream_t st) {
     const dim3 grid((a.N + kSkBN - 1) / kSkBN, a.splits, a.nprob), block(64 * NW);
     constexpr int lds = 2 * 2 * 32 * MT * kSkKC * 16;
@@ -427,10 +429,10 @@ static zo2_status launch_reduce(const SkinnyArgs& a, hipStream_t st) {
 
 template <typename T>
 static zo2_status skinny_launch_t(const SkinnyArgs& a, hipStream_t st, bool sum) {
-    zo2_status s = a.M <= 32 ? skinny_launch_mt<T, 1, false>(a, st)
-                 : a.in_order && a.M <= 64 ? skinny_launch_mt<T, 2, false, 4>(a, st) : a.in_order && a.M <= 128 ? skinny_launch_mt<T, 4, false, 4>(a, st)
-                 : a.M <= 64 ? skinny_launch_mt<T, 2, false>(a, st) : a.M <= 96 ? skinny_launch_mt<T, 3, false>(a, st) : a.M <= 128 ? skinny_launch_mt<T, 4, false>(a, st)
-                 : a.M <= 192 ? skinny_launch_mt<T, 6, false>(a, st) : skinny_launch_mt<T, 8, false>(a, st);
+    const zo2_status s = !a.in_order && a.M <= kSkRows && a.K < 1 << 22 ? skinny_rows_launch(a, __is_same(T, bf16_t) ? ZO2_BF16 : ZO2_F16, false, st)
+                       : a.M <= 32 ? skinny_launch_mt<T, 1, false, 4>(a, st) : a.M <= 64 ? skinny_launch_mt<T, 2, false, 4>(a, st)
+                       : a.M <= 128 ? (a.in_order ? skinny_launch_mt<T, 4, false, 4>(a, st) : skinny_launch_mt<T, 4, false, 8>(a, st))
+                       : a.M <= 192 ? skinny_launch_mt<T, 6, false, 4>(a, st) : skinny_launch_mt<T, 8, false, 4>(a, st);
     return s != ZO2_OK || !sum ? s : launch_reduce<T>(a, st);
 }
 
@@ -457,7 +459,7 @@ zo2_status skinny_launch(SkinnyArgs& a, int dtype, void* workspace, size_t works
                  "skinny gemm: workspace of %zu bytes needed (16-byte aligned)", need);
     a.partial = reinterpret_cast<float*>(workspace);
     if (dtype == ZO2_F32) {
-        const zo2_status s = skinny_f32_launch(a, st);
+        const zo2_status s = skinny_rows_launch(a, ZO2_F32, false, st);
         return s != ZO2_OK || !sum ? s : launch_reduce<float>(a, st);
     }
     if (dtype == ZO2_BF16) return skinny_launch_t<bf16_t>(a, st, sum);
@@ -471,13 +473,7 @@ zo2_status skinny_launch_sums(SkinnyArgs& a, float* out, hipStream_t st) {
     ZO2_OP_CHECK(p.Xp && p.Xm && p.theta && out && (((uintptr_t)p.Xp | (uintptr_t)p.Xm | (uintptr_t)p.theta | (uintptr_t)out) & 15) == 0, ZO2_EINVAL,
                  "skinny gemm: NULL operand, or operands not aligned to 16 bytes");
     a.splits = 1; a.k_per_split = a.K; a.partial = out;
-    return skinny_f32_launch(a, st);
-}
-
-template <typename T>
-static zo2_status skinny_launch_ce_t(const SkinnyArgs& a, hipStream_t st) {
-    return a.M <= 32 ? skinny_launch_mt<T, 1, true>(a, st) : a.M <= 64 ? skinny_launch_mt<T, 2, true>(a, st)
-         : a.M <= 96 ? skinny_launch_mt<T, 3, true>(a, st) : skinny_launch_mt<T, 4, true>(a, st);
+    return skinny_rows_launch(a, ZO2_F32, false, st);
 }
 
 zo2_status skinny_launch_ce(SkinnyArgs& a, int dtype, hipStream_t st) {
@@ -489,7 +485,8 @@ zo2_status skinny_launch_ce(SkinnyArgs& a, int dtype, hipStream_t st) {
                  "skinny head: NULL operand or short partial arrays");
     ZO2_OP_CHECK((((uintptr_t)p.Xp | (uintptr_t)p.Xm | (uintptr_t)p.theta) & 15) == 0, ZO2_EINVAL, "skinny head: operands must be 16-byte aligned");
     a.splits = 1; a.k_per_split = a.K; a.partial = nullptr;      // a vocabulary has tiles for every compute unit
-    return dtype == ZO2_BF16 ? skinny_launch_ce_t<bf16_t>(a, st) : skinny_launch_ce_t<f16_t>(a, st);
+    if (a.M <= kSkRows && a.K < 1 << 22) return skinny_rows_launch(a, dtype, true, st);
+    return dtype == ZO2_BF16 ? skinny_launch_mt<bf16_t, 4, true, 8>(a, st) : skinny_launch_mt<f16_t, 4, true, 8>(a, st);
 }
 
 zo2_status skinny_perturbed_rows(int dtype, const void* theta, int64_t K, int64_t n0, int64_t rows, uint32_t tensor_id, uint64_t seed,

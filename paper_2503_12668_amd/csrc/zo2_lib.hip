@@ -83,7 +83,7 @@ static constexpr int kDefaultSweeps = 1;       // update + perturb sweeps per bl
 // elements, which keeps its launches on the older kernels (gemm_choose), the line is 64: d 256 x 8, ffn 2048 64 641 -> 585, 100 660 ->
 // 736; d 512, ffn 2048 64 698 -> 674, 80 689 -> 717; d 640 64 747 -> 744; d 704 64 938 -> 762; d 1024, ffn 512 64 790 -> 726.
 static constexpr int kFuseAlways = 64;      // beyond this its workspace must fit into what the ordinary path needs; the line of contexts that keep_order()
-static constexpr int kFuseF32 = 96;         // float32 (why: gemm_skinny_f32.hip)
+static constexpr int kFuseF32 = 96;         // float32 (why: gemm_skinny_rows.hip)
 static int fuse_max_tokens(int d, int f) {
     if ((int64_t)d * std::min(d, f) <= 1 << 19) return 64;
     return std::min(128, std::max(16, 16 + (d - 1536) * 11 / 128) + (d % 128 ? 16 : 0));

@@ -253,3 +253,26 @@ def test_float32_loader_computes_sums_of_tiny_operands_with_float32_products():
     for k in (0, 1):
         assert abs(float(got[k]) - float(want[k])) <= 1e-5 * abs(float(want[k])), (got, want)
     ctx.close()
+
+
+@pytest.mark.parametrize("dt,rows,vocab,tied", [("bf16", 2, 212, True), ("f16", 32, 1092, False), ("bf16", 33, 1028, False), ("f16", 64, 260, True), ("bf16", 65, 2052, True),
+                                                ("bf16", 96, 516, False), ("f16", 96, 132, True), ("bf16", 97, 516, True)])
+def test_head_in_the_loader_by_rows_and_ragged_vocabularies(dt, rows, vocab, tied):
+    """16-bit head whose logits stay in the kernel: 2 - 97 rows (edges of its three heights and the kernel beyond them), vocabularies that end inside
+    a workgroup's 128 columns and inside a half's 64.  The losses are the ordinary path's but for the order of the float32 sums."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=1, d_model=128, n_heads=2, d_ffn=192, vocab=vocab, max_pos=100, tied=tied)
+    P = si.make_weights(cfg, seed=11, std=0.05, ln_jitter=True)
+    tok = si.make_tokens(vocab, 1, rows, seed=12)
+    lab = si.next_token_labels(tok)
+    lab[0, rows // 3] = -100
+    lab[0, rows // 2] = vocab - 1
+    got = {}
+    for mode in (1, -1):
+        ctx = b.Zo2Context(cfg, P, wire=dt, compute=dt, arena_bytes=256 << 20)
+        ctx.set_loader_fusion(mode)
+        got[mode] = ctx.step(tok, lab, 42, 1e-3, 0.0)
+        assert ctx.plan()["loader_fusion"] == (mode == 1)
+        ctx.close()
+    for k in (0, 1):
+        assert abs(float(got[1][k]) - float(got[-1][k])) <= 2e-3 * abs(float(got[-1][k]))
