@@ -1225,9 +1225,15 @@ static zo2_status block_forward_round(zo2_ctx* c, int l, char* bucket, int batch
 // perturb in their weight loader, both streams per pass over the weights (gemm_skinny.hip).
 static const int kVecTensors[10] = {0, 1, 3, 5, 7, 9, 10, 11, 13, 15};      // ln1.w ln1.b q.b k.b v.b o.b ln2.w ln2.b fc1.b fc2.b
 
-// float32: the same loader applies the last deferred update, so that a matrix is read and written once.  (In 16 bits a sweep does: with two draws an
-// element the loader is bound by the vector ALU, and the sweep leaves the block in the memory-side cache; d 2048, 12 blocks, 1 x 16 tokens 1583 us, with
-// the update in the loader 1596; d 4096, 4 blocks, 1 x 20 1532 against 1481.)
+// The last deferred update can be applied by the same loader, so that a matrix is read and written once: always in float32, in bfloat16 up to 32
+// tokens.  With more the loader, bound by the vector ALU, takes longer for the second draw than a sweep of its own, which leaves the block in the
+// memory-side cache (sweep -> loader, us: d 2048, 12 blocks, 16 tokens 1526 -> 1485, 48 1702 -> 1686; d 4096, 4 blocks, 20 1499 -> 1365, 64 1717 -> 1748;
+// d 5120, 3 blocks, 90 2159 -> 2252; d 768 766 -> 767).  float16 stays with the sweep, whose compiled roundings every update has to share (embed_kernel),
+// and so does stochastic rounding, a third draw.
+static inline bool updates_in_loader(const zo2_ctx* c, int T) {
+    const int dt = c->cfg.compute_dtype;
+    return fused_update(c) && (dt == ZO2_F32 || (dt == ZO2_BF16 && T <= 32 && !c->stochastic));
+}
 static void loader_applies(const zo2_ctx* c, SkinnyArgs& sa) {
     sa.key_prev = philox_keys(c->pend_seed[c->n_pend - 1]);
     sa.c_ptr = coef_slot(c, c->n_pend - 1);
@@ -1238,7 +1244,7 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
     const int T = batch * seq, d = g.d_model, f = g.d_ffn, dh = d / g.n_heads;
     const int dt = g.compute_dtype;
     const size_t cs = c->csz;
-    const bool f32 = dt == ZO2_F32;
+    const bool f32 = dt == ZO2_F32, loader_updates = updates_in_loader(c, T);
     const size_t half_d = (size_t)T * d * cs, half_f = (size_t)T * f * cs;
     { zo2_status s = earlier_updates_block(c, l, bucket); if (s != ZO2_OK) return s; }
     int64_t voff[ZO2_BLOCK_TENSORS] = {0}, vec_elems = 0;
@@ -1252,7 +1258,7 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
         }
         auto is_vec = [](int k) { for (const int v : kVecTensors) if (v == k) return true; return false; };
         // the matrices have no part in the sweep where no update is pending, or where the loader applies it
-        const bool update = fused_update(c), sweep_matrices = update && !f32;
+        const bool update = fused_update(c), sweep_matrices = update && !loader_updates;
         K1Args a;
         k1_common(c, a, seed, eps);
         a.theta = bucket; a.w_plus = c->wp; a.w_minus = c->wm; a.packed_w = 1; a.mixed = sweep_matrices ? 1 : 0; a.nseg = 0;
@@ -1264,7 +1270,6 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
         }
         OPK(c, ZO2_KC_K1, k1_launch(a, g.wire_dtype, g.compute_dtype, update, true, c->sc));
     }
-    const bool loader_updates = f32 && fused_update(c);
     if (k1_done && !loader_updates) HIPCHK(c, hipEventRecord(k1_done, c->sc));      // the block's parameters are final: the offload may start
     auto VP = [&](int k) { return (const void*)(c->wp + (size_t)voff[k] * cs); };
     auto VM = [&](int k) { return (const void*)(c->wm + (size_t)voff[k] * cs); };
@@ -1635,7 +1640,7 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
             memset(&sa, 0, sizeof(sa));
             sa.M = T; sa.N = g.vocab; sa.K = d; sa.ldx = d; sa.nprob = 1; sa.eps = eps; sa.key = philox_keys(seed);
             sa.p[0].Xp = c->x; sa.p[0].Xm = c->x + (size_t)T * d * c->csz; sa.p[0].theta = table; sa.p[0].tensor_id = tid;
-            if (fused_update(c)) loader_applies(c, sa);
+            if (updates_in_loader(c, T)) loader_applies(c, sa);
             OPK(c, ZO2_KC_GEMM, skinny_launch_sums(sa, c->logits, c->sc));
             for (int s = 0; s < 2; ++s)
                 OPK(c, ZO2_KC_CE, cross_entropy_rows(c->logits + (size_t)s * T * g.vocab, g.vocab, c->d_labels, T, s * T, T, g.vocab, c->row_loss, c->sc));
@@ -1643,9 +1648,10 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
             char* table = g.tied_lm_head ? c->d_tok : c->d_lm;
             const uint32_t tid = g.tied_lm_head ? 0u : lm_tid(c);
             if (!g.tied_lm_head) { zo2_status es = earlier_updates_tensor(c, c->d_lm, c->tok_elems, tid); if (es != ZO2_OK) return es; }
-            { zo2_status s = k1_tensor(c, table, c->tok_elems, tid, false, nullptr, nullptr, seed, eps); if (s != ZO2_OK) return s; }
             SkinnyArgs sa;
             memset(&sa, 0, sizeof(sa));
+            if (updates_in_loader(c, T)) loader_applies(c, sa);
+            else { zo2_status s = k1_tensor(c, table, c->tok_elems, tid, false, nullptr, nullptr, seed, eps); if (s != ZO2_OK) return s; }
             sa.M = T; sa.N = g.vocab; sa.K = d; sa.ldx = d; sa.nprob = 1; sa.eps = eps; sa.key = philox_keys(seed);
             sa.p[0].Xp = c->x; sa.p[0].Xm = c->x + (size_t)T * d * c->csz; sa.p[0].theta = table; sa.p[0].tensor_id = tid;
             sa.labels = c->d_labels; sa.part_max = c->ce_pmax; sa.part_sum = c->ce_psum; sa.label_logit = c->ce_lab; sa.part_ld = 2 * (int64_t)T;

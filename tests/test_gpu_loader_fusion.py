@@ -276,3 +276,35 @@ def test_head_in_the_loader_by_rows_and_ragged_vocabularies(dt, rows, vocab, tie
         ctx.close()
     for k in (0, 1):
         assert abs(float(got[1][k]) - float(got[-1][k])) <= 2e-3 * abs(float(got[-1][k]))
+
+
+@pytest.mark.parametrize("d,f,vocab,rows,tied", [(64, 128, 212, 2, True), (192, 320, 1092, 17, False), (256, 1088, 2052, 32, True), (448, 576, 1091, 32, False), (192, 320, 260, 33, True)])
+def test_bf16_loader_updates_as_the_sweep_does(d, f, vocab, rows, tied):
+    """bfloat16: the projections' loader applies the pending update too up to 32 tokens, the sweep from 33 on.  The stored parameters are the sweep's
+    bit for bit (features that end inside a workgroup's 128, one slab and several, heads that the loader takes or leaves), resident and
+    streamed, over a pending update and a round of two directions; the losses are the ordinary path's but for the order of the float32 sums."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=5, d_model=d, n_heads=d // 64, d_ffn=f, vocab=vocab, max_pos=80, tied=tied)
+    P = si.make_weights(cfg, seed=11, std=0.05, ln_jitter=True)
+    tok = si.make_tokens(vocab, 1, rows, seed=12)
+    lab = si.next_token_labels(tok)
+    got = {}
+    for mode, streamed in ((1, 0), (-1, 0), (1, 1)):
+        ctx = b.Zo2Context(cfg, P, wire="bf16", compute="bf16", arena_bytes=512 << 20)
+        ctx.set_loader_fusion(mode)
+        r = [ctx.step(tok, lab, 41, 1e-3, 0.0)]
+        if streamed:
+            ctx.set_resident_budget(ctx.plan()["bytes_used"] - 2 * ctx.offs[16] * 2)        # 3 slots for 5 blocks
+            ctx.debug_set_slot_poison(True)
+        ctx.set_pending(True, 7, 3e-3)
+        r += [ctx.step(tok, lab, 42, 1e-3, 0.0), ctx.step(tok, lab, 43, 1e-3, 0.0), ctx.step_extra(tok, lab, 44, 1e-3, 0.0)]
+        assert ctx.plan()["loader_fusion"] == (mode == 1) and ctx.plan()["resident"] == (not streamed)
+        ctx.sync_to_host()
+        got[mode, streamed] = ([float(x) for a in r for x in a[:2]], ctx.parameters())
+        ctx.close()
+    for x, y in zip(got[1, 0][0], got[-1, 0][0]):
+        assert abs(x - y) <= 2e-3 * abs(y)
+    assert got[1, 0][0] == got[1, 1][0]
+    for n in P:
+        assert np.array_equal(got[1, 0][1][n], got[-1, 0][1][n]) and np.array_equal(got[1, 0][1][n], got[1, 1][1][n]), n
+    assert any(not np.array_equal(got[1, 0][1][n], codec.round_to(P[n], "bf16")) for n in P)
