@@ -53,6 +53,25 @@ struct K1RoundArgs {
 bool k1_round_applicable(int wire_dtype, int compute_dtype);
 zo2_status k1_round_launch(K1RoundArgs& a, int wire_dtype, int compute_dtype, hipStream_t st);
 
+// The perturbed (and updated) vectors of all blocks of a step in one launch, and with them those of the final LayerNorm: the same segments
+// of every block, `theta_stride` elements and `tid_stride` tensors apart.  float32 and bfloat16, stored in the compute format; lengths in whole
+// groups of eight.
+struct K1VectorsArgs {
+    struct List {
+        void *theta, *w_plus, *w_minus;      // (copies packed: a segment's start at woff)
+        int32_t nseg;
+        uint32_t total_chunks;
+        uint32_t first_chunk[K1Args::kMaxSeg];
+        K1Seg seg[K1Args::kMaxSeg];
+    } block, last;                           // of block 0; of the final LayerNorm
+    int64_t theta_stride, w_stride;
+    int32_t n_blocks, tid_stride;
+    float eps;
+    const float* c_ptr;
+    PhiloxKeys k_prev, k_cur;
+};
+zo2_status k1_vectors_launch(K1VectorsArgs& a, int dtype, bool update, hipStream_t st);
+
 // Enqueue K1 over the segments.  update: apply theta' = theta - c z_prev; perturb: write W+, W-.
 zo2_status k1_launch(K1Args& a, int wire_dtype, int compute_dtype, bool update, bool perturb, hipStream_t st);
 uint32_t k1_chunks(uint64_t n);

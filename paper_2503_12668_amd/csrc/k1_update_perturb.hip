@@ -12,6 +12,8 @@
 // a contiguous chunk of one tensor, the grid covers up to 16 tensors of a bucket.
 #include <math.h>
 
+#include <algorithm>
+
 #include "k1.h"
 #include "philox.h"
 
@@ -182,6 +184,29 @@ __global__ __launch_bounds__(kThreads) void k1_kernel(const K1Args a) {
     }
 }
 
+// Where the loader applies the update, or there is none, the vectors are all that a step's blocks need swept: 13 workgroups a block at d 2048, a
+// launch of 4.7 us that is start and end.  With resident blocks one launch does them for all, and for the final LayerNorm.
+template <typename T, bool UPDATE>
+__global__ __launch_bounds__(kThreads) void k1_vectors_kernel(const K1VectorsArgs a) {
+    const bool last = blockIdx.y == (uint32_t)a.n_blocks;
+    const K1VectorsArgs::List& li = last ? a.last : a.block;
+    if (blockIdx.x >= li.total_chunks) return;
+    int s = 0;
+#pragma unroll
+    for (int i = 1; i < K1Args::kMaxSeg; ++i) s += (blockIdx.x >= li.first_chunk[i]) ? 1 : 0;
+    const K1Seg& sg = li.seg[s];
+    const uint64_t i = (uint64_t)(blockIdx.x - li.first_chunk[s]) * kChunk + (uint64_t)threadIdx.x * kPerLane;
+    if (i >= sg.n) return;
+    const int64_t b = last ? 0 : (int64_t)blockIdx.y, w = sg.woff + b * a.w_stride + (int64_t)i;
+    T* theta = reinterpret_cast<T*>(li.theta) + sg.off + b * a.theta_stride + (int64_t)i;
+    const float c = UPDATE ? *a.c_ptr : 0.f;
+    Vec<T, kPerLane> tv = load_vec<T, kPerLane>(theta), p, m;
+    k1_group<T, T, UPDATE, true, false, true>(a.k_prev, a.k_cur, sg.tensor_id + (uint32_t)(b * a.tid_stride), i >> 3, c, a.eps, 1.f, 1.f, tv, p, m);
+    if (UPDATE) store_vec<T, kPerLane>(theta, tv);
+    store_vec<T, kPerLane>(reinterpret_cast<T*>(li.w_plus) + w, p);
+    store_vec<T, kPerLane>(reinterpret_cast<T*>(li.w_minus) + w, m);
+}
+
 // A round of directions in one sweep (zo2_step_multi).  Bound by the vector ALU, which draws n_upd + n_dir Gaussians an element
 // (busy 99 % of the cycles; at four and four the bytes alone would take about as long);
 // sweep by sweep the same draws each wait for theta and its write: a block of 50 M bf16 elements, four updates and four directions
@@ -308,6 +333,28 @@ zo2_status k1_launch(K1Args& a, int wire_dtype, int compute_dtype, bool update, 
     ZO2_DISPATCH_WIRE(wire_dtype, W, {
         ZO2_DISPATCH_COMPUTE(compute_dtype, C, { return launch_wc<W, C>(a, update, perturb, st); });
     });
+    return ZO2_OK;
+}
+
+zo2_status k1_vectors_launch(K1VectorsArgs& a, int dtype, bool update, hipStream_t st) {
+    for (K1VectorsArgs::List* li : {&a.block, &a.last}) {
+        const zo2_status s = plan_chunks(li->seg, li->nseg, li->first_chunk, li->total_chunks);
+        if (s != ZO2_OK) return s;
+        ZO2_OP_CHECK(li->theta && li->w_plus && li->w_minus, ZO2_EINVAL, "k1: NULL buffer");
+        for (int i = 0; i < li->nseg; ++i)
+            ZO2_OP_CHECK(li->seg[i].n % kPerLane == 0 && li->seg[i].woff >= 0 && li->seg[i].woff % kPerLane == 0 && li->seg[i].e0 == 0, ZO2_EINVAL, "k1: vectors in whole groups of eight");
+    }
+    ZO2_OP_CHECK(a.n_blocks >= 0 && a.n_blocks < 65535 && a.theta_stride % kPerLane == 0 && a.w_stride % kPerLane == 0 && (!update || a.c_ptr) &&
+                 (dtype == ZO2_F32 || dtype == ZO2_BF16), ZO2_EINVAL, "k1: vectors of %d blocks", a.n_blocks);
+    const dim3 grid(std::max(a.block.total_chunks, a.last.total_chunks), a.n_blocks + 1), block(kThreads);
+    if (dtype == ZO2_F32) {
+        if (update) hipLaunchKernelGGL((k1_vectors_kernel<float, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((k1_vectors_kernel<float, false>), grid, block, 0, st, a);
+    } else {
+        if (update) hipLaunchKernelGGL((k1_vectors_kernel<bf16_t, true>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((k1_vectors_kernel<bf16_t, false>), grid, block, 0, st, a);
+    }
+    ZO2_HIP_LAUNCH_CHECK();
     return ZO2_OK;
 }
 

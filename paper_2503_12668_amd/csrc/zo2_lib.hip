@@ -185,6 +185,7 @@ struct zo2_ctx {
     bool serial_streams;                 // ablation: upload, compute and offload of a block run one after the other
     int ns;                              // perturbation streams of the pass in progress: 2 (step) or 1 (evaluation)
     bool one_dir;                        // the pass in progress evaluates one direction
+    bool vectors_at_once;                // the pass in progress has swept the vectors of all blocks ahead of them (sweep_vectors)
     int together, sums_left;             // facts about the last pass: directions that went through a block at once; sums that a LayerNorm's pass made
     RowSum left;                         // FC2's pieces that the next LayerNorm adds up (pieces 0: none)
     float *ce_pmax, *ce_psum, *ce_lab;  // [4 ceil(V/256), 2T] x 2 and [2T]
@@ -1239,6 +1240,41 @@ static void loader_applies(const zo2_ctx* c, SkinnyArgs& sa) {
     sa.c_ptr = coef_slot(c, c->n_pend - 1);
 }
 
+static int64_t place_vectors(const zo2_ctx* c, int64_t* voff) {      // where a block's copies of its vectors stand; returns their elements
+    int64_t o = 0;
+    for (const int k : kVecTensors) {
+        voff[k] = o;
+        o += (c->tn[k] + kTensorAlign - 1) / kTensorAlign * kTensorAlign;
+    }
+    return o;
+}
+// The vectors of resident blocks have no reason to wait for their block: one launch ahead of the first sweeps those of all and the final
+// LayerNorm's, where no sweep of the matrices would take them along and the scratch holds them (12 blocks: 4.7 -> 0.5 us a
+// block; steps, us: d 2048, 16 tokens, bf16 1497 -> 1464; d 768, 64 tokens, float32 1290 -> 1252).  (float16: embed_kernel says why its
+// roundings stay in the instance they are in.)
+static bool vectors_at_once(const zo2_ctx* c, int T) {
+    int64_t voff[ZO2_BLOCK_TENSORS];
+    return c->fuse && c->ns == 2 && c->resident && c->one_dir && !c->overlap_k1 && c->cfg.compute_dtype != ZO2_F16 && c->cfg.n_layers >= 2 && c->cfg.n_layers < 65535 &&
+           (!fused_update(c) || updates_in_loader(c, T)) && (int64_t)c->cfg.n_layers * place_vectors(c, voff) <= c->scratch_elems;
+}
+static zo2_status sweep_vectors(zo2_ctx* c, uint64_t seed, float eps) {
+    for (int l = 0; l < c->cfg.n_layers; ++l) { zo2_status s = earlier_updates_block(c, l, c->slots + (size_t)l * c->bucket_bytes); if (s != ZO2_OK) return s; }
+    for (int k = 0; c->apply_now && k + 1 < c->n_pend; ++k) { zo2_status s = k1_final_ln(c, false, 0, 0.f, k); if (s != ZO2_OK) return s; }
+    K1Args common;
+    k1_common(c, common, seed, eps);
+    K1VectorsArgs a;
+    memset(&a, 0, sizeof(a));
+    int64_t voff[ZO2_BLOCK_TENSORS];
+    a.w_stride = place_vectors(c, voff);
+    a.theta_stride = c->offs[ZO2_BLOCK_TENSORS]; a.n_blocks = c->cfg.n_layers; a.tid_stride = (int32_t)(block_tid(1, 0) - block_tid(0, 0));
+    a.eps = eps; a.c_ptr = common.c_ptr; a.k_prev = common.k_prev; a.k_cur = common.k_cur;
+    a.block.theta = c->slots; a.block.w_plus = c->wps[0]; a.block.w_minus = c->wms[0];
+    for (const int k : kVecTensors) a.block.seg[a.block.nseg++] = K1Seg{c->offs[k], 0, (uint64_t)c->tn[k], block_tid(0, k), 1.0f, voff[k]};
+    a.last.theta = c->d_fln; a.last.w_plus = c->fln_wp; a.last.w_minus = c->fln_wm; a.last.nseg = 2;
+    for (int k = 0; k < 2; ++k) a.last.seg[k] = K1Seg{k * c->fln_off_b, 0, (uint64_t)c->cfg.d_model, fln_tid(c) + k, 1.0f, k * c->fln_off_b};
+    OPK(c, ZO2_KC_K1, k1_vectors_launch(a, c->cfg.compute_dtype, fused_update(c), c->sc));
+    return ZO2_OK;
+}
 static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch, int seq, uint64_t seed, float eps, hipEvent_t k1_done) {
     const zo2_config& g = c->cfg;
     const int T = batch * seq, d = g.d_model, f = g.d_ffn, dh = d / g.n_heads;
@@ -1246,16 +1282,15 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
     const size_t cs = c->csz;
     const bool f32 = dt == ZO2_F32, loader_updates = updates_in_loader(c, T);
     const size_t half_d = (size_t)T * d * cs, half_f = (size_t)T * f * cs;
-    { zo2_status s = earlier_updates_block(c, l, bucket); if (s != ZO2_OK) return s; }
-    int64_t voff[ZO2_BLOCK_TENSORS] = {0}, vec_elems = 0;
-    for (const int k : kVecTensors) vec_elems += (c->tn[k] + kTensorAlign - 1) / kTensorAlign * kTensorAlign;
+    int64_t voff[ZO2_BLOCK_TENSORS] = {0};
+    const int64_t vec_elems = place_vectors(c, voff);
     const bool leave_fc2 = may_leave_fc2(c, T, vec_elems, vec_elems);
     {
-        int64_t o = leave_fc2 && (l & 1) ? vec_elems : 0;
-        for (const int k : kVecTensors) {
-            voff[k] = o;
-            o += (c->tn[k] + kTensorAlign - 1) / kTensorAlign * kTensorAlign;
-        }
+        const int64_t base = c->vectors_at_once ? l * vec_elems : leave_fc2 && (l & 1) ? vec_elems : 0;
+        for (const int k : kVecTensors) voff[k] += base;
+    }
+    if (!c->vectors_at_once) {
+        { zo2_status s = earlier_updates_block(c, l, bucket); if (s != ZO2_OK) return s; }
         auto is_vec = [](int k) { for (const int v : kVecTensors) if (v == k) return true; return false; };
         // the matrices have no part in the sweep where no update is pending, or where the loader applies it
         const bool update = fused_update(c), sweep_matrices = update && !loader_updates;
@@ -1549,6 +1584,8 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
     // stream as soon as the forwards of block l-2 have released its scratch set, i.e. under the
     // forwards of block l-1 (K1 is bound by the vector ALU and HBM, the forwards by the matrix cores).
     if (c->overlap_k1) HIPCHK(c, hipEventRecord(c->ev_embed, c->sc));
+    c->vectors_at_once = vectors_at_once(c, T);
+    if (c->vectors_at_once) { zo2_status s = sweep_vectors(c, seed, eps); if (s != ZO2_OK) return s; }
     for (int l = 0; l < g.n_layers; ++l) {
         TraceRange block_range("block %d", l);
         const int sl = c->resident ? l : l % c->n_slots;
@@ -1623,9 +1660,8 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
             HIPCHK(c, hipMemcpyAsync(pass_result(c, j), c->d_state + 4, 4 * sizeof(float), hipMemcpyDeviceToHost, c->sc));
             continue;
         }
-        if (c->apply_now)
-            for (int k = 0; k + 1 < c->n_pend; ++k) { zo2_status s = k1_final_ln(c, false, 0, 0.f, k); if (s != ZO2_OK) return s; }
-        { zo2_status s = k1_final_ln(c, true, seed, eps); if (s != ZO2_OK) return s; }
+        for (int k = 0; !c->vectors_at_once && c->apply_now && k + 1 < c->n_pend; ++k) { zo2_status s = k1_final_ln(c, false, 0, 0.f, k); if (s != ZO2_OK) return s; }
+        if (!c->vectors_at_once) { zo2_status s = k1_final_ln(c, true, seed, eps); if (s != ZO2_OK) return s; }
         const size_t boff = (size_t)c->fln_off_b * c->csz;
         { zo2_status s = sum_and_norm(c, c->fln_wp, c->fln_wp + boff, c->fln_wm, c->fln_wm + boff, T); if (s != ZO2_OK) return s; }
         // few tokens: the sweep only updates the vocabulary matrix, the head perturbs it in its loader (c->fuse rules overlap_k1 out)

@@ -308,3 +308,31 @@ def test_bf16_loader_updates_as_the_sweep_does(d, f, vocab, rows, tied):
     for n in P:
         assert np.array_equal(got[1, 0][1][n], got[-1, 0][1][n]) and np.array_equal(got[1, 0][1][n], got[1, 1][1][n]), n
     assert any(not np.array_equal(got[1, 0][1][n], codec.round_to(P[n], "bf16")) for n in P)
+
+
+@pytest.mark.parametrize("dt,d,f,rows", [("f32", 64, 128, 2), ("bf16", 192, 320, 32), ("f32", 448, 1856, 33), ("bf16", 2112, 64, 9)])
+def test_vectors_of_resident_blocks_in_one_launch(dt, d, f, rows):
+    """Resident blocks have their vectors swept by one launch ahead of the first block, streamed ones block by block: the same losses and parameters
+    bit for bit, with no update pending, with one, with the several of a round, and in a further direction at the same parameters; vectors
+    that are a fraction of a workgroup's 2048 elements, and more."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=6, d_model=d, n_heads=d // 64, d_ffn=f, vocab=2052, max_pos=80)
+    P = si.make_weights(cfg, seed=11, std=0.05, ln_jitter=True)
+    tok = si.make_tokens(2052, 1, rows, seed=12)
+    lab = si.next_token_labels(tok)
+    got = []
+    for streamed in (False, True):
+        ctx = b.Zo2Context(cfg, P, wire=dt, compute=dt, arena_bytes=2 << 30)
+        ctx.set_loader_fusion(1)
+        r = [ctx.step(tok, lab, 41, 1e-3, 1e-4)]
+        if streamed:
+            ctx.set_resident_budget(ctx.plan()["bytes_used"] - 3 * ctx.offs[16] * (4 if dt == "f32" else 2))        # 3 slots for 6 blocks
+            ctx.debug_set_slot_poison(True)
+        r += [ctx.step(tok, lab, 42, 1e-3, 1e-4), ctx.step_extra(tok, lab, 43, 1e-3, 1e-4), ctx.step_extra(tok, lab, 44, 1e-3, 1e-4), ctx.step(tok, lab, 45, 1e-3, 1e-4)]
+        assert ctx.plan()["loader_fusion"] and ctx.plan()["resident"] == (not streamed)
+        ctx.flush(); ctx.sync_to_host()
+        got.append(([float(x) for a in r for x in a], ctx.parameters()))
+        ctx.close()
+    assert got[0][0] == got[1][0] and all(np.isfinite(got[0][0]))
+    for n in P:
+        assert np.array_equal(got[0][1][n], got[1][1][n]), n
