@@ -629,17 +629,84 @@ zo2_status cross_entropy_rows(const float* logits, int64_t ld, const int32_t* la
 // ------------------------------------------------------------------ combine the LM-head kernel's cross-entropy partials
 // Row r has n_parts pairs (m_i, s_i), span-major ([i * part_ld + r]), with s_i = sum over a 64-column span of
 // exp(y - m_i); then logsumexp = M + log(sum_i s_i exp(m_i - M)), M = max_i m_i.
-template <int kGroups>
-__global__ __launch_bounds__(32 * kGroups) void ce_combine_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum,
+// Eight rows per workgroup and 128 lanes to a row, so that a row's 788 spans of a 50272-word vocabulary are seven loads a lane, all under way
+// at once, and few rows still are several workgroups: bound by the latency of one such load and of the launch.  (32 rows per workgroup walked
+// 25 spans a lane, twice: 15, 17, 22 and 23 us at 32, 370, 1026 and 8192 rows; this 7, 8, 9.5 and 24.6.)  The four workgroups that share a 128-byte line of
+// partials have indexes 8 apart, which the hardware deals to one XCD and so to one L2.
+__global__ __launch_bounds__(1024) void ce_combine_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum,
+                                                          const float* __restrict__ label_logit, const int32_t* __restrict__ labels,
+                                                          int rows, int n_parts, int64_t part_ld, int row0, int label_period,
+                                                          float* __restrict__ row_loss) {
+    constexpr int kRows = 8, kLanes = 128, kLoads = 8;
+    __shared__ float sh_m[16][kRows];
+    __shared__ double sh_s[16][kRows];
+    const int lr = threadIdx.x & (kRows - 1), grp = threadIdx.x / kRows, wave = threadIdx.x >> 6;
+    const int line = (blockIdx.x >> 5) * 8 + (blockIdx.x & 7);
+    const int first = (line * 4 + ((blockIdx.x >> 3) & 3)) * kRows, r = first + lr;
+    if (first >= rows) return;
+    const int rc = r < rows ? r : rows - 1;
+    const float* pm = part_max + rc;
+    const float* ps = part_sum + rc;
+    float m = -INFINITY;
+    double s = 0.0;
+    for (int i0 = grp; i0 < n_parts; i0 += kLanes * kLoads) {
+        float mi[kLoads], si[kLoads];
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) {
+            const int i = i0 + kLanes * j;
+            mi[j] = i < n_parts ? pm[(size_t)i * part_ld] : -INFINITY;
+            si[j] = i < n_parts ? ps[(size_t)i * part_ld] : 0.f;
+        }
+        float mx = m;
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) mx = fmaxf(mx, mi[j]);
+        if (mx == -INFINITY) continue;
+        if (mx > m) {
+            s *= (double)expf(m - mx);
+            m = mx;
+        }
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) s += (double)(si[j] * expf(mi[j] - m));       // a span past the last column has sum 0 and exp(-inf) = 0
+    }
+    // the row's lanes of this wavefront (8 apart), then the wavefronts
+    auto merge = [](float& m0, double& s0, float m1, double s1) {
+        const float mm = fmaxf(m0, m1);
+        const double a = m0 == -INFINITY ? 0.0 : s0 * (double)expf(m0 - mm), b = m1 == -INFINITY ? 0.0 : s1 * (double)expf(m1 - mm);
+        m0 = mm;
+        s0 = a + b;
+    };
+#pragma unroll
+    for (int d = kRows; d < 64; d <<= 1) merge(m, s, __shfl_xor(m, d, 64), __shfl_xor(s, d, 64));
+    if ((threadIdx.x & 63) < kRows) {
+        sh_m[wave][lr] = m;
+        sh_s[wave][lr] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x >= kRows || r >= rows) return;
+    const int lab = labels[(row0 + r) % label_period];
+    if (lab < 0) {
+        row_loss[row0 + r] = 0.f;
+        return;
+    }
+    float mm = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) mm = fmaxf(mm, sh_m[k][lr]);
+    double ss = 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+        if (sh_m[k][lr] != -INFINITY) ss += sh_s[k][lr] * (double)expf(sh_m[k][lr] - mm);
+    row_loss[row0 + r] = (float)(log(ss) + (double)mm - (double)label_logit[r]);
+}
+
+// Contexts that keep the order of their sums: 32 rows per block; 8 groups of lanes split the spans, so every load is 32 consecutive floats and a
+// thread walks 99 of the 788 spans of a 50272-word vocabulary.  Two sweeps (max, then sum) keep the loads
+// independent of each other.
+// (eight loads under way: 55 us at 4096 rows instead of 32)
+__global__ __launch_bounds__(256) void ce_combine_in_order_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum,
                                                          const float* __restrict__ label_logit, const int32_t* __restrict__ labels,
                                                          int rows, int n_parts, int64_t part_ld, int row0, int label_period,
                                                          float* __restrict__ row_loss) {
-    // 32 rows per block; 32 groups of lanes split the spans, so every load is 32 consecutive floats and a thread walks 25 of
-    // the 788 spans of a 50272-word vocabulary (a block is bound by the latency of that walk: with 8 groups, which stay where
-    // the order of the sums is kept, 31 us at 8192 rows and as much at 1026).  Two sweeps (max, then sum) keep the loads
-    // independent of each other.
-    // (eight loads under way at 8 groups: 55 us at 4096 rows instead of 32)
-    constexpr int kRows = 32, kUnroll = kGroups == 8 ? 4 : 8;
+    constexpr int kRows = 32, kGroups = 8, kUnroll = 4;
     __shared__ float sh_m[kGroups][kRows];
     __shared__ double sh_s[kGroups][kRows];
     const int lr = threadIdx.x & (kRows - 1), grp = threadIdx.x / kRows;
@@ -682,9 +749,8 @@ zo2_status ce_combine(const float* part_max, const float* part_sum, const float*
     if (rows == 0) return ZO2_OK;
     ZO2_OP_CHECK(part_max && part_sum && label_logit && labels && row_loss && n_parts > 0 && label_period > 0 && part_ld >= rows,
                  ZO2_EINVAL, "ce_combine: bad argument");
-    const dim3 grid((rows + 31) / 32);
-    if (keep_order) hipLaunchKernelGGL(ce_combine_kernel<8>, grid, dim3(256), 0, st, part_max, part_sum, label_logit, labels, rows, n_parts, part_ld, row0, label_period, row_loss);
-    else hipLaunchKernelGGL(ce_combine_kernel<32>, grid, dim3(1024), 0, st, part_max, part_sum, label_logit, labels, rows, n_parts, part_ld, row0, label_period, row_loss);
+    if (keep_order) hipLaunchKernelGGL(ce_combine_in_order_kernel, dim3((rows + 31) / 32), dim3(256), 0, st, part_max, part_sum, label_logit, labels, rows, n_parts, part_ld, row0, label_period, row_loss);
+    else hipLaunchKernelGGL(ce_combine_kernel, dim3((rows + 255) / 256 * 32), dim3(1024), 0, st, part_max, part_sum, label_logit, labels, rows, n_parts, part_ld, row0, label_period, row_loss);
     ZO2_HIP_LAUNCH_CHECK();
     return ZO2_OK;
 }
