@@ -1678,6 +1678,7 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
             sa.p[0].Xp = c->x; sa.p[0].Xm = c->x + (size_t)T * d * c->csz; sa.p[0].theta = table; sa.p[0].tensor_id = tid;
             if (updates_in_loader(c, T)) loader_applies(c, sa);
             OPK(c, ZO2_KC_GEMM, skinny_launch_sums(sa, c->logits, c->sc));
+            // (both streams' rows lie together: 64 each, 50272 logits, 12.3 + 12.3 -> 13.2 us)
             OPK(c, ZO2_KC_CE, cross_entropy_rows(c->logits, g.vocab, c->d_labels, 2 * T, 0, T, g.vocab, c->row_loss, c->sc));
         } else if (loader_head) {
             char* table = g.tied_lm_head ? c->d_tok : c->d_lm;
@@ -1747,9 +1748,8 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
                 }
                 // (the kernel of all T rows: R is the budget's, and the budget is not to show in a loss)
                 OPK(c, ZO2_KC_GEMM, gemm_launch(ga, dt, c->sc, T));
-                const int both = rows == T && R == T ? ns : 1;      // streams per launch (50272 logits, 768 rows each: 41 + 41 us -> 71; 64 each, 12.3 + 12.3 -> 13.2)
-                for (int s = 0; s < ns; s += both)
-                    OPK(c, ZO2_KC_CE, cross_entropy_rows(c->logits + (size_t)s * R * g.vocab, g.vocab, c->d_labels, both * rows, s * T + r0, T, g.vocab, c->row_loss, c->sc, keep_order(c)));
+                for (int s = 0; s < ns; ++s)
+                    OPK(c, ZO2_KC_CE, cross_entropy_rows(c->logits + (size_t)s * R * g.vocab, g.vocab, c->d_labels, rows, s * T + r0, T, g.vocab, c->row_loss, c->sc, keep_order(c)));
             }
         }
         // eta g of this pass: deferred update 0 of a new round (every older one has been applied on the way), or one more of
