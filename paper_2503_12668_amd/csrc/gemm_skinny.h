@@ -33,6 +33,7 @@ struct SkinnyArgs {
     // eta g, is nullptr where theta is up to date
     PhiloxKeys key_prev;
     const float* c_ptr;
+    int32_t direct;         // filled in by skinny_launch: 1: the kernel finishes the outputs, nothing goes to partial
     float* partial;         // filled in by skinny_launch: [nprob][splits][2][M][N] float32 partial sums
     // cross-entropy mode (skinny_launch_ce, the LM head): per row and 64-column span max and sum(exp(y - max)) of the logits,
     // span-major, and the label's logit; the "-" stream's M rows behind the "+" stream's.  As in GemmProblem.
@@ -56,6 +57,10 @@ zo2_status skinny_launch_sums(SkinnyArgs& a, float* out, hipStream_t st);
 bool skinny_f32_applicable(int M, int N, int K);
 // gemm_skinny_rows.hip: up to 96 rows; splits, k_per_split and partial are set.  ce: the LM head's partials
 zo2_status skinny_rows_launch(const SkinnyArgs& a, int dtype, bool ce, hipStream_t st);
+// gemm_skinny_few.hip: 16 bits, up to 32 rows; splits, k_per_split, direct (one piece) and partial are set
+bool skinny_few_pays(const SkinnyArgs& a, bool own_sum);
+void skinny_few_splits(int N, int K, int nprob, bool own_sum, int max_splits, int& splits, int& k_per_split);
+zo2_status skinny_few_launch(const SkinnyArgs& a, int dtype, hipStream_t st);
 bool skinny_applicable(int M, int N, int K, int dtype);
 // W+ and W- of rows [n0, n0 + rows) of a dense [N, K] tensor, chunk by chunk with the loader's arithmetic (a test hook)
 zo2_status skinny_perturbed_rows(int dtype, const void* theta, int64_t K, int64_t n0, int64_t rows, uint32_t tensor_id, uint64_t seed,

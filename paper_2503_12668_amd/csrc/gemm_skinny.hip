@@ -436,6 +436,24 @@ static zo2_status skinny_launch_t(const SkinnyArgs& a, hipStream_t st, bool sum)
     return s != ZO2_OK || !sum ? s : launch_reduce<T>(a, st);
 }
 
+// does an output lie where some workgroup still reads?  (The sums of all go to the workspace then, and the outputs are made from them.)
+static bool writes_its_inputs(const SkinnyArgs& a, int dtype) {
+    const size_t osz = a.out_f32 ? 4 : zo2_dtype_size(dtype), y_bytes = ((size_t)(a.M - 1) * a.ldy + a.N) * osz, x_bytes = ((size_t)(a.M - 1) * a.ldx + a.K) * zo2_dtype_size(dtype);
+    auto meet = [](const void* y, size_t ny, const void* x, size_t nx) { return x && (uintptr_t)y < (uintptr_t)x + nx && (uintptr_t)x < (uintptr_t)y + ny; };
+    for (int i = 0; i < a.nprob; ++i)
+        for (const void* y : {(const void*)a.p[i].Yp, (const void*)a.p[i].Ym})
+            for (int j = 0; j < a.nprob; ++j) {
+                const SkinnyProblem& q = a.p[j];
+                const size_t b = (size_t)a.N * zo2_dtype_size(dtype), r_bytes = ((size_t)(a.M - 1) * a.ldy + a.N) * 4;
+                if (meet(y, y_bytes, q.Xp, x_bytes) || meet(y, y_bytes, q.Xm, x_bytes) || meet(y, y_bytes, q.bias_p, b) || meet(y, y_bytes, q.bias_m, b) ||
+                    meet(y, y_bytes, q.theta, (size_t)a.N * a.K * zo2_dtype_size(dtype)))
+                    return true;
+                for (const void* res : {(const void*)q.res_p, (const void*)q.res_m})
+                    if (res != y && meet(y, y_bytes, res, r_bytes)) return true;
+            }
+    return false;
+}
+
 zo2_status skinny_launch(SkinnyArgs& a, int dtype, void* workspace, size_t workspace_bytes, hipStream_t st, bool sum) {
     ZO2_OP_CHECK(skinny_applicable(a.M, a.N, a.K, dtype), ZO2_EINVAL,
                  "skinny gemm: needs 1 <= M <= 256 (float32: 96), N %% 4 == 0, K %% 64 == 0 (got %d x %d x %d)", a.M, a.N, a.K);
@@ -458,6 +476,13 @@ zo2_status skinny_launch(SkinnyArgs& a, int dtype, void* workspace, size_t works
     ZO2_OP_CHECK(workspace && ((uintptr_t)workspace & 15) == 0 && workspace_bytes >= need, ZO2_EINVAL,
                  "skinny gemm: workspace of %zu bytes needed (16-byte aligned)", need);
     a.partial = reinterpret_cast<float*>(workspace);
+    a.direct = 0;
+    if (dtype != ZO2_F32 && !a.in_order && skinny_few_pays(a, sum)) {
+        skinny_few_splits(a.N, a.K, a.nprob, sum, a.splits, a.splits, a.k_per_split);
+        a.direct = sum && a.splits == 1 && !writes_its_inputs(a, dtype);
+        const zo2_status s = skinny_few_launch(a, dtype, st);
+        return s != ZO2_OK || !sum || a.direct ? s : dtype == ZO2_BF16 ? launch_reduce<bf16_t>(a, st) : launch_reduce<f16_t>(a, st);
+    }
     if (dtype == ZO2_F32) {
         const zo2_status s = skinny_rows_launch(a, ZO2_F32, false, st);
         return s != ZO2_OK || !sum ? s : launch_reduce<float>(a, st);

@@ -21,7 +21,7 @@
 #include <algorithm>
 
 #include "f32_parts.h"
-#include "gemm_skinny.h"
+#include "skinny_weights.h"
 
 namespace zo2 {
 
@@ -31,21 +31,6 @@ static constexpr int kSfBN = 128, kSfBK = 64;      // weight rows per workgroup,
 // + 15 of the workgroup's 128 over the whole slice, so nothing has to meet at the end; the lanes of a row read and write whole lines of theta.
 // With the weights as the first operand a lane ends with row r of the activations and features 4 g .. + 3.
 // MT: 32 rows of each stream.
-__device__ __forceinline__ v4f_t mfma16_bf16(v4u_t w, v4u_t x, v4f_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, x), c, 0, 0, 0);
-}
-// The matrix instruction's operands of 8 k: float32 as three bfloat16 parts, 16-bit formats as they are.
-template <typename T> struct RowsMfma {
-    static constexpr int kParts = 1;
-    static __device__ __forceinline__ v4f_t run(v4u_t w, v4u_t x, v4f_t c);
-};
-template <> __device__ __forceinline__ v4f_t RowsMfma<f16_t>::run(v4u_t w, v4u_t x, v4f_t c) {
-    typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, w), __builtin_bit_cast(f16x8_t, x), c, 0, 0, 0);
-}
-template <> __device__ __forceinline__ v4f_t RowsMfma<bf16_t>::run(v4u_t w, v4u_t x, v4f_t c) { return mfma16_bf16(w, x, c); }
-template <> struct RowsMfma<float> { static constexpr int kParts = 3; };
-
 template <typename T, int MT, bool UPDATE, bool CE>
 __global__ __launch_bounds__(512, MT == 1 && sizeof(T) == 2 ? 4 : 2) void skinny_rows_kernel(const SkinnyArgs a) {
     constexpr bool F32 = sizeof(T) == 4;
@@ -63,66 +48,18 @@ __global__ __launch_bounds__(512, MT == 1 && sizeof(T) == 2 ? 4 : 2) void skinny
     const T* __restrict__ Xm = reinterpret_cast<const T*>(p.Xm);
     const float c = UPDATE ? *a.c_ptr : 0.f;
 
-    // this lane's weight row; its chunks' place in the tensor (the random stream's counter) and in the workgroup's rows as a buffer: rows
-    // past N are outside it, are read as zeros and not written
-    const int row = wave * 16 + r;
-    const uint64_t we = (uint64_t)(n0 + row) * (uint64_t)a.K + (uint64_t)(8 * g);
-    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<T*>(p.theta) + (size_t)n0 * a.K, 0,
-                                                                          (int)((uint32_t)min(kSfBN, a.N - n0) * a.K * (uint32_t)sizeof(T)), 0x00020000);
-    const int row_at = (row * a.K + 8 * g) * (int)sizeof(T);
-
-    struct Theta { v4u_t v[2][Q]; };                           // two chunks of eight, 32 apart
-    auto load_theta = [&](Theta& t, int k0) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int e = 0; e < Q; ++e) t.v[h][e] = __builtin_amdgcn_raw_buffer_load_b128(rows, row_at + 32 * (int)sizeof(T) * h + 16 * e, k0 * (int)sizeof(T), 0);
-    };
-    // theta' of both chunks, stored if this is where the update is applied.  (k0 in the lanes' offsets: with a scalar offset in a register the
-    // compiler lets the very next instruction write the store's data registers, here theta' - eps z over theta', and what arrives in
-    // memory is now and then the new value.)
-    auto updated = [&](const Theta& t, int k0, bool apply, float (&th)[2][8]) {
-        Vec<T, 8> s[2];
-        __builtin_memcpy(s, &t, sizeof(s));
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) th[h][j] = Fmt<T>::load(s[h].v[j]);
-        if (!apply) return;
-        uint32_t w[2][4];
-        const uint64_t e = we + (uint64_t)k0;
-        philox4x32_10_x2(e >> 3, (e >> 3) + 4, p.tensor_id, a.key_prev, w);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            float z[8];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) box_muller(w[h][i], z[2 * i], z[2 * i + 1]);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                s[h].v[j] = Fmt<T>::store(__builtin_fmaf(-c, z[j], th[h][j]));
-                th[h][j] = Fmt<T>::load(s[h].v[j]);
-            }
-            v4u_t u[Q];
-            __builtin_memcpy(u, &s[h], sizeof(u));
-#pragma unroll
-            for (int q = 0; q < Q; ++q) __builtin_amdgcn_raw_buffer_store_b128(u[q], rows, row_at + 32 * (int)sizeof(T) * h + 16 * q + k0 * (int)sizeof(T), 0, 0);
-        }
-    };
-    auto draw = [&](int k0, float (&z)[2][8]) {
-        uint32_t w[2][4];
-        const uint64_t e = we + (uint64_t)k0;
-        philox4x32_10_x2(e >> 3, (e >> 3) + 4, p.tensor_id, a.key, w);
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) box_muller(w[h][i], z[h][2 * i], z[h][2 * i + 1]);
-    };
+    const WeightLane<T> lane_w(a, p, n0, kSfBN, wave * 16 + r, 8 * g);
+    using Theta = typename WeightLane<T>::Theta;
     // the parts of a chunk's W+ and W-: [stream][part]
     struct Parts { v4u_t w[2][P]; } part[2];
     auto perturb = [&](const Theta& t, int k0) {
         float th[2][8], z[2][8];
-        updated(t, k0, UPDATE, th);
-        draw(k0, z);
+        lane_w.values(t, th);
+        if constexpr (UPDATE) {
+            lane_w.draw(k0, a.key_prev, z);
+            lane_w.update(k0, c, z, th);
+        }
+        lane_w.draw(k0, a.key, z);
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -217,7 +154,7 @@ __global__ __launch_bounds__(512, MT == 1 && sizeof(T) == 2 ? 4 : 2) void skinny
         }
     };
     Theta t;
-    load_theta(t, k_begin);
+    lane_w.load(t, k_begin);
     load_x(k_begin);
     perturb(t, k_begin);
     store_x(0);
@@ -225,7 +162,7 @@ __global__ __launch_bounds__(512, MT == 1 && sizeof(T) == 2 ? 4 : 2) void skinny
     for (int k0 = k_begin;; k0 += kSfBK) {
         const bool more = k0 + kSfBK < k_end;
         if (more) {
-            load_theta(t, k0 + kSfBK);
+            lane_w.load(t, k0 + kSfBK);
             load_x(k0 + kSfBK);
         }
         __syncthreads();                   // this slab's activations are there, and nobody reads those of the one before any more
@@ -251,9 +188,9 @@ __global__ __launch_bounds__(512, MT == 1 && sizeof(T) == 2 ? 4 : 2) void skinny
 #pragma unroll 1
             for (int k0 = k_begin; k0 < k_end; k0 += kSfBK) {
                 float th[2][8], z[2][8];
-                load_theta(t, k0);
-                updated(t, k0, false, th);
-                draw(k0, z);
+                lane_w.load(t, k0);
+                lane_w.values(t, th);
+                lane_w.draw(k0, a.key, z);
 #pragma unroll
                 for (int i = 0; i < NI; ++i) {
                     const bool s = i >= NI / 2;

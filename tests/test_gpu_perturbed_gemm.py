@@ -180,3 +180,43 @@ def test_loader_kernel_itself_forms_the_bits_of_the_sweep_kernel(dt, M):
         X[:m] = eye[k0:k0 + m]
         for Y, w in zip(b.op_gemm_perturbed(X, X, theta, tid, seed, eps, out_dtype=b.F32), want):
             assert torch.equal(Y[:m].T, w.reshape(N, K)[:, k0:k0 + m].float()), k0
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("M,N,K", [(1, 4, 64), (15, 20, 576), (16, 36, 512), (17, 52, 1088), (31, 1028, 128), (32, 16, 4160), (16, 4096, 8192), (17, 2048, 8192)])
+def test_few_rows_finished_in_the_kernel_or_summed_behind_it(dt, M, N, K):
+    """Up to 32 rows: 16 features a workgroup, of which the last has 4 or 12 here, slabs that its eight wavefronts share unevenly or not at all, pieces of
+    k, both heights, and the shapes on the other side of its line: against the sweep kernel's W+- in float64, with bias, ReLU and a residual."""
+    b = _b()
+    tid, seed, eps = 40, 9, 1e-3
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    Xp, Xm = (torch.randn(M, K, device="cuda", generator=g).to(TD[dt]) for _ in range(2))
+    theta = (torch.randn(N, K, device="cuda", generator=g) * 0.05).to(TD[dt])
+    bp, bm = ((torch.randn(N, device="cuda", generator=g) * 0.1).to(TD[dt]) for _ in range(2))
+    R = torch.randn(M, N, device="cuda", generator=g)
+    t = theta.clone().reshape(-1)
+    wp, wm = torch.empty_like(t), torch.empty_like(t)
+    b.op_update_perturb(t, wp, wm, tid, 0, False, 0, 0.0, seed, eps)
+    F = b.op_gemm_perturbed(Xp, Xm, theta, tid, seed, eps, bp, bm, R, R, out_dtype=b.F32, out_scale=0.25, relu=True)
+    H = b.op_gemm_perturbed(Xp, Xm, theta, tid, seed, eps, bp, bm)
+    for Y, y16, X, w, bias in ((F[0], H[0], Xp, wp, bp), (F[1], H[1], Xm, wm, bm)):
+        Z = X.double() @ w.reshape(N, K).double().T + bias.double()
+        tol = 2e-5 * max(1.0, float(Z.abs().max()))
+        assert ((Y.double() - torch.relu(Z * 0.25) - R.double()).abs().max()) <= tol
+        assert bool(((y16.double() - Z).abs() <= tol + (2.0 ** -8 if dt == "bf16" else 2.0 ** -11) * Z.abs()).all())
+
+
+def test_few_rows_into_the_activations_buffer():
+    """Outputs that overwrite the activations, which other workgroups still read: the sums go through the workspace."""
+    b = _b()
+    M, N, tid, seed, eps = 16, 512, 40, 9, 1e-3
+    g = torch.Generator(device="cuda").manual_seed(3)
+    Xp, Xm = (torch.randn(M, N, device="cuda", generator=g).bfloat16() for _ in range(2))
+    theta = (torch.randn(N, N, device="cuda", generator=g) * 0.05).bfloat16()
+    Yp, Ym = b.op_gemm_perturbed(Xp, Xm, theta, tid, seed, eps)
+    nb = b.lib().zo2_op_gemm_perturbed_workspace_bytes(M, N, N)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    rc = b.lib().zo2_op_gemm_perturbed(b._dt(Xp), M, N, N, b._ptr(Xp), b._ptr(Xm), N, b._ptr(theta), tid, seed, eps, None, None, None, None,
+                                       b._ptr(Xp), b._ptr(Xm), b._dt(Xp), N, 1.0, 0, b._ptr(ws), nb, b._stream_ptr(None))
+    torch.cuda.synchronize()
+    assert rc == 0 and torch.equal(Xp, Yp) and torch.equal(Xm, Ym)
