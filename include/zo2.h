@@ -223,7 +223,8 @@ zo2_status zo2_set_scratch_plan(zo2_ctx* ctx, int32_t sweeps);
  * workspace; 64 where a matrix of the block has at most 2^19 elements, and under stochastic rounding
  * (zo2_set_wire_rounding) - where the projections are bound by reading the weights, lets the projections read the stored
  * weights and form W+ / W- in their loader (zo2_op_gemm_perturbed), the sweep kernel then only applies the pending
- * update and perturbs the block's one-dimensional tensors (the LM head does the same with the vocabulary matrix up to 128 tokens); larger steps write the perturbed copies with the sweep kernel,
+ * update and perturbs the block's one-dimensional tensors - bfloat16 up to 32 tokens, rounded to
+ * nearest: the loader applies the update too - (the LM head does the same with the vocabulary matrix up to 128 tokens); larger steps write the perturbed copies with the sweep kernel,
  * because a weight tile would otherwise be regenerated once per 256-row tile of activations.  mode 1: in the loader
  * whenever the shapes allow (16-bit storage equal to the compute format, d_model and d_ffn multiples of 64, at most
  * 256 tokens per stream); mode -1: never.  float32 throughout: modes 0 and 1 alike up to 96 tokens (d_model and d_ffn multiples of 64, a
