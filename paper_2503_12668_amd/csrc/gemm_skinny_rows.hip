@@ -280,17 +280,17 @@ template <bool UPDATE>
 static zo2_status launch_f32(const SkinnyArgs& a, hipStream_t st) {
     return a.M <= 32 ? launch_as<float, 1, UPDATE, false>(a, st) : a.M <= 64 ? launch_as<float, 2, UPDATE, false>(a, st) : launch_as<float, 3, UPDATE, false>(a, st);
 }
-template <typename T, bool UPDATE, bool CE>
+template <typename T, bool CE>
 static zo2_status launch_16(const SkinnyArgs& a, hipStream_t st) {
-    return a.M <= 32 ? launch_as<T, 1, UPDATE, CE>(a, st) : a.M <= 64 ? launch_as<T, 2, UPDATE, CE>(a, st)
-         : launch_as<T, 3, UPDATE, CE>(a, st);
+    return a.M <= 32 ? launch_as<T, 1, false, CE>(a, st) : a.M <= 64 ? launch_as<T, 2, false, CE>(a, st) : launch_as<T, 3, false, CE>(a, st);
 }
 
 zo2_status skinny_rows_launch(const SkinnyArgs& a, int dtype, bool ce, hipStream_t st) {
     if (dtype == ZO2_F32) return a.c_ptr ? launch_f32<true>(a, st) : launch_f32<false>(a, st);
-    if (dtype == ZO2_F16) return ce ? launch_16<f16_t, false, true>(a, st) : launch_16<f16_t, false, false>(a, st);
-    if (a.c_ptr) return ce ? launch_16<bf16_t, true, true>(a, st) : launch_16<bf16_t, true, false>(a, st);
-    return ce ? launch_16<bf16_t, false, true>(a, st) : launch_16<bf16_t, false, false>(a, st);
+    if (dtype == ZO2_F16) return ce ? launch_16<f16_t, true>(a, st) : launch_16<f16_t, false>(a, st);
+    if (!a.c_ptr) return ce ? launch_16<bf16_t, true>(a, st) : launch_16<bf16_t, false>(a, st);
+    ZO2_OP_CHECK(a.M <= 32, ZO2_EINVAL, "skinny gemm: an update in the loader of bfloat16 takes at most 32 rows, not %d", a.M);
+    return ce ? launch_as<bf16_t, 1, true, true>(a, st) : launch_as<bf16_t, 1, true, false>(a, st);
 }
 
 }  // namespace zo2

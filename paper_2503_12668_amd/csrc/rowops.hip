@@ -568,8 +568,15 @@ zo2_status embed_gather(const EmbedArgs& a, int wire_dtype, int compute_dtype, h
     const dim3 grid((unsigned)((n + 255) / 256)), block(256);
     ZO2_DISPATCH_WIRE(wire_dtype, W, {
         ZO2_DISPATCH_COMPUTE(compute_dtype, C, {
-            if (a.n_upd > 1) hipLaunchKernelGGL((embed_kernel<W, C, 2>), grid, block, 0, st, a);
-            else if (a.n_upd) hipLaunchKernelGGL((embed_kernel<W, C, 1>), grid, block, 0, st, a);
+            if constexpr (__is_same(C, bf16_t) && !__is_same(W, f16_t)) {      // the formats of a round in one sweep (k1_round_applicable)
+                if (a.n_upd > 1) {
+                    hipLaunchKernelGGL((embed_kernel<W, C, 2>), grid, block, 0, st, a);
+                    ZO2_HIP_LAUNCH_CHECK();
+                    return ZO2_OK;
+                }
+            }
+            ZO2_OP_CHECK(a.n_upd <= 1, ZO2_EINVAL, "embed: %d updates in these formats", a.n_upd);
+            if (a.n_upd) hipLaunchKernelGGL((embed_kernel<W, C, 1>), grid, block, 0, st, a);
             else hipLaunchKernelGGL((embed_kernel<W, C, 0>), grid, block, 0, st, a);
         });
     });
