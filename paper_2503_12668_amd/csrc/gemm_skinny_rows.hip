@@ -1,4 +1,4 @@
-// The projections of up to 96 tokens: gemm_skinny.hip's layout - a workgroup owns 128 output features and a slice of k, reads the stored
+// The projections of up to 96 tokens (16 bits: those that gemm_skinny_few.hip does not take): gemm_skinny.hip's layout - a workgroup owns 128 output features and a slice of k, reads the stored
 // weights once for both perturbation streams and forms W+- in registers - with wavefronts of 16 features over the whole slice on 16-row matrix
 // instructions: nothing meets at the end, the four lanes of a row read (and write) its whole 128 bytes, and a lane ends with four
 // neighbouring columns of a row.  The pending update can be applied in the same place: a lane writes theta' = theta - c z_prev back and multiplies with

@@ -1228,7 +1228,7 @@ static const int kVecTensors[10] = {0, 1, 3, 5, 7, 9, 10, 11, 13, 15};      // l
 
 // The last deferred update can be applied by the same loader, so that a matrix is read and written once: always in float32, in bfloat16 up to 32
 // tokens.  With more the loader, bound by the vector ALU, takes longer for the second draw than a sweep of its own, which leaves the block in the
-// memory-side cache (sweep -> loader, us: d 2048, 12 blocks, 16 tokens 1526 -> 1485, 48 1702 -> 1686; d 4096, 4 blocks, 20 1499 -> 1365, 64 1717 -> 1748;
+// memory-side cache (sweep -> loader, both with skinny_rows_kernel, us: d 2048, 12 blocks, 16 tokens 1526 -> 1485, 48 1702 -> 1686; d 4096, 4 blocks, 20 1499 -> 1365, 64 1717 -> 1748;
 // d 5120, 3 blocks, 90 2159 -> 2252; d 768 766 -> 767).  float16 stays with the sweep, whose compiled roundings every update has to share (embed_kernel),
 // and so does stochastic rounding, a third draw.
 static inline bool updates_in_loader(const zo2_ctx* c, int T) {
