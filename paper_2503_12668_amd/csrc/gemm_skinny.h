@@ -58,7 +58,7 @@ bool skinny_f32_applicable(int M, int N, int K);
 // gemm_skinny_rows.hip: up to 96 rows; splits, k_per_split and partial are set.  ce: the LM head's partials
 zo2_status skinny_rows_launch(const SkinnyArgs& a, int dtype, bool ce, hipStream_t st);
 // gemm_skinny_few.hip: 16 bits, up to 32 rows; splits, k_per_split, direct (one piece) and partial are set
-bool skinny_few_pays(const SkinnyArgs& a, bool own_sum);
+bool skinny_few_pays(const SkinnyArgs& a, int dtype, bool own_sum);
 void skinny_few_splits(int N, int K, int nprob, bool own_sum, int max_splits, int& splits, int& k_per_split);
 zo2_status skinny_few_launch(const SkinnyArgs& a, int dtype, hipStream_t st);
 bool skinny_applicable(int M, int N, int K, int dtype);

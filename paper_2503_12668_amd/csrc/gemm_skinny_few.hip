@@ -6,8 +6,8 @@
 // and FC1 each, and 8 MB of sums that a LayerNorm pass has to read.)  An activation is read once for 16 features instead of once for 128: from
 // L2, 2 M bytes a weight, which is why the line is 32 rows.
 // What bounds it is the generator, as there.  d 2048, 16 rows, update and perturbation, us: QKV 21.8 + 4.7 -> 21.7, FC1 22.5 + 4.9 -> 23.3, output 10.2 -> 8.4, the
-// LayerNorm behind it 5.8 -> 4.8.  Steps, us: d 2048, 12 blocks, 16 tokens 1437 -> 1282, 32 1573 -> 1470, float16 16 1503 -> 1378; d 768, 12 blocks, 14
-// 724 -> 537; d 512, 6 blocks, 24 391 -> 297; d 5120, 3 blocks, 10 1507 -> 1490.
+// LayerNorm behind it 5.8 -> 4.8.  Steps, us: d 2048, 12 blocks, 16 tokens 1457 -> 1306, 32 1573 -> 1470, float16 16 1503 -> 1378; d 768, 12 blocks, 14
+// 724 -> 537; d 512, 6 blocks, 24 391 -> 297.
 #include <algorithm>
 
 #include "skinny_weights.h"
@@ -131,11 +131,13 @@ __global__ __launch_bounds__(64 * kFewWaves, 4) void skinny_few_kernel(const Ski
 
 // Up to 32 rows, while the activations that its workgroups read - once for 16 features, 16-row tiles of both streams - take less time than it saves: a
 // launch where the sum is one of its own, a part of the LayerNorm behind it otherwise.  MB of them at which both sides meet, from the launches at d 2048
-// and the steps at 2560 and 4096: what is left of them behind a generator that draws twice costs 0.03 us a MB, behind one draw 0.07.
-bool skinny_few_pays(const SkinnyArgs& a, bool own_sum) {
+// and the steps at 2560 and 4096: what is left of them behind a generator that draws twice costs 0.03 us a MB (200 and 80 MB), behind one draw
+// 0.07 (86 and 34).  float16 draws once here; bfloat16 once or twice, but an order of sums that depended on whether an update
+// is pending would show in the losses of a step behind a flush: one line for both.
+bool skinny_few_pays(const SkinnyArgs& a, int dtype, bool own_sum) {
     if (a.M > 32 || a.K >= 1 << 22) return false;
     const double mb = 4e-6 * (a.M <= 16 ? 1 : 2) * a.N * (double)a.K * a.nprob;
-    return mb <= (own_sum ? (a.c_ptr ? 200. : 86.) : (a.c_ptr ? 80. : 34.));
+    return mb <= (dtype == ZO2_BF16 ? (own_sum ? 150. : 60.) : (own_sum ? 86. : 34.));
 }
 
 // Pieces of k, at most max_splits of them.  The time is that of the slabs that one wavefront walks, while two workgroups a compute unit are resident (512 on

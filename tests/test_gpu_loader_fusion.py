@@ -336,3 +336,26 @@ def test_vectors_of_resident_blocks_in_one_launch(dt, d, f, rows):
     assert got[0][0] == got[1][0] and all(np.isfinite(got[0][0]))
     for n in P:
         assert np.array_equal(got[0][1][n], got[1][1][n]), n
+
+
+@pytest.mark.parametrize("dt,d,f,rows", [("bf16", 2048, 8192, 16), ("bf16", 2048, 6144, 30), ("bf16", 1536, 6144, 9), ("f16", 2048, 8192, 16), ("f32", 512, 2048, 40)])
+def test_a_flush_does_not_show_in_the_losses_behind_it(dt, d, f, rows):
+    """An update that the loader applies and one that a flush has applied before leave the same parameters, and the step behind them adds
+    its products in the same order: the losses are the same bits."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=2, d_model=d, n_heads=d // 64, d_ffn=f, vocab=8196, max_pos=40)
+    P = si.make_weights(cfg, seed=11, std=0.02, ln_jitter=True)
+    tok = si.make_tokens(8196, 1, rows, seed=12)
+    lab = si.next_token_labels(tok)
+    got = []
+    for flush in (False, True):
+        ctx = b.Zo2Context(cfg, P, wire=dt, compute=dt, arena_bytes=2 << 30)
+        ctx.set_loader_fusion(1)
+        r = [ctx.step(tok, lab, 41, 1e-3, 1e-4)]
+        if flush:
+            ctx.flush()
+        r.append(ctx.step(tok, lab, 42, 1e-3, 1e-4))
+        assert ctx.plan()["loader_fusion"]
+        got.append([float(x) for a in r for x in a])
+        ctx.close()
+    assert got[0] == got[1] and all(np.isfinite(got[0]))
