@@ -26,6 +26,7 @@ struct SkinnyArgs {
     int64_t ldx, ldy;
     int32_t relu, out_f32, nprob;
     int32_t in_order;       // 1: one wavefront adds a slab's k in order, where two would share it (33 - 128 rows)
+    int32_t onto_residual;  // 1: a projection whose pieces a LayerNorm's pass adds where it can: kernel and pieces are those that pay then, whoever adds them
     int32_t splits, k_per_split;     // filled in by skinny_launch: the k range is cut into `splits` pieces of k_per_split
     float eps;
     PhiloxKeys key;         // of the step seed
@@ -58,8 +59,8 @@ bool skinny_f32_applicable(int M, int N, int K);
 // gemm_skinny_rows.hip: up to 96 rows; splits, k_per_split and partial are set.  ce: the LM head's partials
 zo2_status skinny_rows_launch(const SkinnyArgs& a, int dtype, bool ce, hipStream_t st);
 // gemm_skinny_few.hip: 16 bits, up to 32 rows; splits, k_per_split, direct (one piece) and partial are set
-bool skinny_few_pays(const SkinnyArgs& a, int dtype, bool own_sum);
-void skinny_few_splits(int N, int K, int nprob, bool own_sum, int max_splits, int& splits, int& k_per_split);
+bool skinny_few_pays(const SkinnyArgs& a, int dtype);
+void skinny_few_splits(const SkinnyArgs& a, int max_splits, int& splits, int& k_per_split);
 zo2_status skinny_few_launch(const SkinnyArgs& a, int dtype, hipStream_t st);
 bool skinny_applicable(int M, int N, int K, int dtype);
 // W+ and W- of rows [n0, n0 + rows) of a dense [N, K] tensor, chunk by chunk with the loader's arithmetic (a test hook)

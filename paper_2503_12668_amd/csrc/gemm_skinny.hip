@@ -477,8 +477,9 @@ zo2_status skinny_launch(SkinnyArgs& a, int dtype, void* workspace, size_t works
                  "skinny gemm: workspace of %zu bytes needed (16-byte aligned)", need);
     a.partial = reinterpret_cast<float*>(workspace);
     a.direct = 0;
-    if (dtype != ZO2_F32 && !a.in_order && skinny_few_pays(a, dtype, sum)) {
-        skinny_few_splits(a.N, a.K, a.nprob, sum, a.splits, a.splits, a.k_per_split);
+    // (not by `sum`: who adds the pieces is a matter of the scratch's organisation and of how many directions a round has, and is not to show in a sum)
+    if (dtype != ZO2_F32 && !a.in_order && skinny_few_pays(a, dtype)) {
+        skinny_few_splits(a, a.splits, a.splits, a.k_per_split);
         a.direct = sum && a.splits == 1 && !writes_its_inputs(a, dtype);
         const zo2_status s = skinny_few_launch(a, dtype, st);
         return s != ZO2_OK || !sum || a.direct ? s : dtype == ZO2_BF16 ? launch_reduce<bf16_t>(a, st) : launch_reduce<f16_t>(a, st);

@@ -133,22 +133,23 @@ __global__ __launch_bounds__(64 * kFewWaves, 4) void skinny_few_kernel(const Ski
 // launch where the sum is one of its own, a part of the LayerNorm behind it otherwise.  MB of them at which both sides meet, from the launches at d 2048
 // and the steps at 2560 and 4096: what is left of them behind a generator that draws twice costs 0.03 us a MB (200 and 80 MB), behind one draw
 // 0.07 (86 and 34).  float16 draws once here; bfloat16 once or twice, but an order of sums that depended on whether an update
-// is pending would show in the losses of a step behind a flush: one line for both.
-bool skinny_few_pays(const SkinnyArgs& a, int dtype, bool own_sum) {
+// is pending would show in the losses of a step behind a flush: one line for both.  Nor does it ask who adds the pieces this time (a LayerNorm's pass does
+// not in a round that goes through the blocks together, or under a smaller scratch set): a projection onto the residual stream has the second line always.
+bool skinny_few_pays(const SkinnyArgs& a, int dtype) {
     if (a.M > 32 || a.K >= 1 << 22) return false;
     const double mb = 4e-6 * (a.M <= 16 ? 1 : 2) * a.N * (double)a.K * a.nprob;
-    return mb <= (dtype == ZO2_BF16 ? (own_sum ? 150. : 60.) : (own_sum ? 86. : 34.));
+    return mb <= (dtype == ZO2_BF16 ? (a.onto_residual ? 60. : 150.) : (a.onto_residual ? 34. : 86.));
 }
 
 // Pieces of k, at most max_splits of them.  The time is that of the slabs that one wavefront walks, while two workgroups a compute unit are resident (512 on
 // the chip); a sum in a launch of its own costs as much as two slabs, one that a LayerNorm pass makes next to nothing a piece.
-void skinny_few_splits(int N, int K, int nprob, bool own_sum, int max_splits, int& splits, int& k_per_split) {
-    const int slabs = K / kFewBK, tiles = (N + kFewBN - 1) / kFewBN * nprob;
+void skinny_few_splits(const SkinnyArgs& a, int max_splits, int& splits, int& k_per_split) {
+    const int slabs = a.K / kFewBK, tiles = (a.N + kFewBN - 1) / kFewBN * a.nprob;
     float best = 0.f;
     splits = 0;
     for (int s = 1; s <= std::min(max_splits, slabs); ++s) {
         const int each = (slabs + s - 1) / s, n = (slabs + each - 1) / each;
-        const float cost = (float)((each + kFewWaves - 1) / kFewWaves) * std::max(1.f, (float)tiles * (float)n / 512.f) + (own_sum ? (n > 1 ? 2.f : 0.f) : 0.05f * (float)n);
+        const float cost = (float)((each + kFewWaves - 1) / kFewWaves) * std::max(1.f, (float)tiles * (float)n / 512.f) + (a.onto_residual ? 0.05f * (float)n : n > 1 ? 2.f : 0.f);
         if (splits == 0 || cost < best) {
             best = cost;
             splits = n;

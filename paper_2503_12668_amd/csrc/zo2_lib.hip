@@ -1331,6 +1331,7 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
     OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, ws, ws_bytes, c->sc));
     OPK(c, ZO2_KC_ATTN, attention_launch(dt, c->qb, c->kb, c->vb, c->ctxb, 2 * batch, seq, g.n_heads, dh, d, 0, c->sc));
     common(d, d, d, d, 0, 1, 1);
+    sa.onto_residual = 1;
     {
         SkinnyProblem& p = sa.p[0];
         p.Xp = c->ctxb; p.Xm = c->ctxb + half_d; p.theta = TH(8); p.bias_p = VP(9); p.bias_m = VM(9);
@@ -1354,6 +1355,7 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
     }
     OPK(c, ZO2_KC_GEMM, skinny_launch(sa, dt, ws, ws_bytes, c->sc));
     common(d, f, f, d, 0, 1, 1);
+    sa.onto_residual = 1;
     {
         SkinnyProblem& p = sa.p[0];
         p.Xp = c->mid; p.Xm = c->mid + half_f; p.theta = TH(14); p.bias_p = VP(15); p.bias_m = VM(15);

@@ -359,3 +359,35 @@ def test_a_flush_does_not_show_in_the_losses_behind_it(dt, d, f, rows):
         got.append([float(x) for a in r for x in a])
         ctx.close()
     assert got[0] == got[1] and all(np.isfinite(got[0]))
+
+
+@pytest.mark.parametrize("dt,d,f,rows", [("bf16", 2048, 8192, 16), ("bf16", 2048, 8192, 30), ("bf16", 2560, 10240, 16), ("bf16", 1536, 6144, 20), ("f16", 2048, 8192, 16),
+                                         ("f16", 1536, 6144, 9), ("bf16", 192, 320, 9), ("f32", 512, 2048, 40)])
+def test_who_adds_a_projection_s_pieces_does_not_show(dt, d, f, rows):
+    """The second FFN projection's pieces are added by the next LayerNorm or, in a round that goes through the blocks together and under smaller
+    scratch sets, by a pass of their own.  Kernel and pieces are the shape's: the same losses and parameters bit for bit."""
+    b = _b()
+    vocab = max(3 * d, f) + 4 if dt == "f32" else 260
+    cfg = si.tiny_config(n_layers=2, d_model=d, n_heads=d // 64, d_ffn=f, vocab=vocab, max_pos=40)
+    P = si.make_weights(cfg, seed=11, std=0.03, ln_jitter=True)
+    tok = si.make_tokens(vocab, 1, rows, seed=12)
+    lab = si.next_token_labels(tok)
+    got = {}
+    for how in ("1", "2", "4", "multi"):
+        ctx = b.Zo2Context(cfg, P, wire=dt, compute=dt, arena_bytes=2 << 30)
+        ctx.set_loader_fusion(1)
+        ctx.set_scratch_plan(0 if how == "multi" else int(how))
+        r = []
+        for seeds in ([41, 42], [51, 52, 53]):
+            r += ctx.step_multi(tok, lab, seeds, 1e-3, 1e-4) if how == "multi" else [ctx.step(tok, lab, seeds[0], 1e-3, 1e-4)] + [ctx.step_extra(tok, lab, s, 1e-3, 1e-4) for s in seeds[1:]]
+            waiting = ctx.pass_facts()[1]
+        assert ctx.plan()["loader_fusion"] and waiting % 2 == 0
+        ctx.flush(); ctx.sync_to_host()
+        got[how] = ([float(x) for a in r for x in a], ctx.parameters(), waiting)
+        ctx.close()
+    assert got["1"][2] > got["2"][2]               # FC2's pieces waited here, and not there
+    for how in ("2", "4", "multi"):
+        assert got[how][0] == got["1"][0], how
+        for n in P:
+            assert np.array_equal(got[how][1][n], got["1"][1][n]), (how, n)
+    assert all(np.isfinite(got["1"][0]))
