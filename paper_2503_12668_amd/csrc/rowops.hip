@@ -636,6 +636,9 @@ zo2_status cross_entropy_rows(const float* logits, int64_t ld, const int32_t* la
 // ------------------------------------------------------------------ combine the LM-head kernel's cross-entropy partials
 // Row r has n_parts pairs (m_i, s_i), span-major ([i * part_ld + r]), with s_i = sum over a 64-column span of
 // exp(y - m_i); then logsumexp = M + log(sum_i s_i exp(m_i - M)), M = max_i m_i.
+// The maximum of spans whose logits are all NaN is -inf (fmaxf passes them over), like that of spans that add nothing: exponents are taken against 0
+// then, so that what is added is the spans' sums times exp(-inf) = 0, which is 0, or the NaN that is to reach the row's loss.
+__device__ __forceinline__ float ce_base(float m) { return m == -INFINITY ? 0.f : m; }
 // Eight rows per workgroup and 128 lanes to a row, so that a row's 788 spans of a 50272-word vocabulary are seven loads a lane, all under way
 // at once, and few rows still are several workgroups: bound by the latency of one such load and of the launch.  (32 rows per workgroup walked
 // 25 spans a lane, twice: 15, 17, 22 and 23 us at 32, 370, 1026 and 8192 rows; this 7, 8, 9.5 and 24.6.)  The four workgroups that share a 128-byte line of
@@ -667,18 +670,18 @@ __global__ __launch_bounds__(1024) void ce_combine_kernel(const float* __restric
         float mx = m;
 #pragma unroll
         for (int j = 0; j < kLoads; ++j) mx = fmaxf(mx, mi[j]);
-        if (mx == -INFINITY) continue;
         if (mx > m) {
             s *= (double)expf(m - mx);
             m = mx;
         }
+        const float base = ce_base(m);
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) s += (double)(si[j] * expf(mi[j] - m));       // a span past the last column has sum 0 and exp(-inf) = 0
+        for (int j = 0; j < kLoads; ++j) s += (double)(si[j] * expf(mi[j] - base));       // a span past the last column has sum 0 and exp(-inf) = 0
     }
     // the row's lanes of this wavefront (8 apart), then the wavefronts
     auto merge = [](float& m0, double& s0, float m1, double s1) {
         const float mm = fmaxf(m0, m1);
-        const double a = m0 == -INFINITY ? 0.0 : s0 * (double)expf(m0 - mm), b = m1 == -INFINITY ? 0.0 : s1 * (double)expf(m1 - mm);
+        const double a = m0 == -INFINITY ? s0 : s0 * (double)expf(m0 - mm), b = m1 == -INFINITY ? s1 : s1 * (double)expf(m1 - mm);
         m0 = mm;
         s0 = a + b;
     };
@@ -699,9 +702,9 @@ __global__ __launch_bounds__(1024) void ce_combine_kernel(const float* __restric
 #pragma unroll
     for (int k = 0; k < 16; ++k) mm = fmaxf(mm, sh_m[k][lr]);
     double ss = 0.0;
+    const float base = ce_base(mm);
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
-        if (sh_m[k][lr] != -INFINITY) ss += sh_s[k][lr] * (double)expf(sh_m[k][lr] - mm);
+    for (int k = 0; k < 16; ++k) ss += sh_s[k][lr] * (double)expf(sh_m[k][lr] - base);
     row_loss[row0 + r] = (float)(log(ss) + (double)mm - (double)label_logit[r]);
 }
 
@@ -725,12 +728,11 @@ __global__ __launch_bounds__(256) void ce_combine_in_order_kernel(const float* _
 #pragma unroll kUnroll
     for (int i = grp; i < n_parts; i += kGroups) m = fmaxf(m, pm[(size_t)i * part_ld]);
     double s = 0.0;
-    if (m != -INFINITY) {
+    const float base = ce_base(m);
 #pragma unroll kUnroll
-        for (int i = grp; i < n_parts; i += kGroups) {
-            const float mi = pm[(size_t)i * part_ld];
-            s += (double)(ps[(size_t)i * part_ld] * expf(mi - m));     // a span past the last column has sum 0 and exp(-inf) = 0
-        }
+    for (int i = grp; i < n_parts; i += kGroups) {
+        const float mi = pm[(size_t)i * part_ld];
+        s += (double)(ps[(size_t)i * part_ld] * expf(mi - base));     // a span past the last column has sum 0 and exp(-inf) = 0
     }
     sh_m[grp][lr] = m;
     sh_s[grp][lr] = s;
@@ -745,9 +747,9 @@ __global__ __launch_bounds__(256) void ce_combine_in_order_kernel(const float* _
 #pragma unroll
     for (int k = 0; k < kGroups; ++k) mm = fmaxf(mm, sh_m[k][lr]);
     double ss = 0.0;
+    const float base_all = ce_base(mm);
 #pragma unroll
-    for (int k = 0; k < kGroups; ++k)
-        if (sh_m[k][lr] != -INFINITY) ss += sh_s[k][lr] * (double)expf(sh_m[k][lr] - mm);
+    for (int k = 0; k < kGroups; ++k) ss += sh_s[k][lr] * (double)expf(sh_m[k][lr] - base_all);
     row_loss[row0 + r] = (float)(log(ss) + (double)mm - (double)label_logit[r]);
 }
 

@@ -457,3 +457,26 @@ def test_bf16_master_with_stochastic_rounding_tracks_oracle(compute):
     if compute == "f32":
         assert same / tot > 0.98
     ctx.close(); ctx_s.close()
+
+
+# few tokens (the head's loader), many, the head that keeps the order of its sums, a head of several directions, written logits
+@pytest.mark.parametrize("wire,vocab,batch,seq,sr,dirs", [("bf16", 4100, 1, 16, False, 1), ("bf16", 4100, 2, 150, False, 1), ("bf16", 512, 2, 150, True, 1),
+                                                          ("bf16", 4100, 2, 150, False, 3), ("f32", 4100, 1, 16, False, 1), ("f32", 516, 2, 150, False, 1)])
+def test_nan_weights_of_a_few_words_end_a_step(wire, vocab, batch, seq, sr, dirs):
+    """The vocabulary matrix ends in a span of 64 columns that are NaN, all of them, for words that are no label: the loss is not finite, and
+    nothing is left to apply."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=1, d_model=128, n_heads=4, d_ffn=256, vocab=vocab, max_pos=160, tied=False)
+    P = si.make_weights(cfg, seed=11, std=0.05)
+    P["lm_head.w"][(vocab - 1) // 64 * 64:] = np.nan
+    tok = si.make_tokens(vocab - 64, batch, seq, seed=12)
+    lab = si.next_token_labels(tok)
+    ctx = b.Zo2Context(cfg, P, wire=wire, compute=wire, arena_bytes=256 << 20)
+    ctx.set_wire_rounding(sr)
+    with pytest.raises(b.Zo2Error, match="ENONFINITE"):
+        if dirs > 1:
+            ctx.step_multi(tok, lab, list(range(dirs)), 1e-3, 1e-3)
+        else:
+            ctx.step(tok, lab, 7, 1e-3, 1e-3)
+    assert ctx.pending_list() == []
+    ctx.close()
