@@ -30,6 +30,7 @@ struct GemmArgs {
     int32_t relu;
     int32_t out_f32;        // Y is float32 instead of the compute dtype
     int32_t ce_mode;        // 1: LM-head + cross-entropy partials instead of an output matrix (256 x 256 kernel only)
+    int32_t like_nprob;     // ce_mode: spans are added up as in a launch of this many problems (0: no matter)
     int32_t kpiece;         // float32 and 128 x 128 kernels: k per piece (K when the launch is not split), a multiple of 32 or 64 if there are several
     int32_t large_only;     // 1: not on the 128 x 128 kernel, whose wavefronts add a slab's k in two halves
     int32_t nprob;          // problems of identical shape, one per grid.z (the +/- streams, q/k/v)

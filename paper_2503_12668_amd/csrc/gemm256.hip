@@ -4,7 +4,7 @@
 //     wavefront of a SIMD issues LDS reads, loads or waits, the other one's MFMAs keep the matrix pipeline busy.
 //   256-row tiles, four wavefronts (2 x 2) of 128 x 128: the deeper prefetch below; taken for long k (pick_waves).
 //   192- and 128-row tiles: four wavefronts (2 x 2) of 96 x 128 or 64 x 128, for launches that 256-row tiles would spread
-//     badly over the compute units or whose last tile row they would leave mostly empty (pick_tile_rows).
+//     badly over the compute units or whose last tile row they would leave mostly empty (pick_height).
 // (Under this kernel's full load - MFMA, LDS reads, 64 KB per k-slab streaming from L2 - the chip sustains a
 // higher clock with the 16 x 16 x 32 shape than with 32 x 32 x 16, although the latter is faster in an MFMA-only loop.)
 //
@@ -694,19 +694,26 @@ static int g_forced_tile_rows = 0;      // 0: per launch; 128 / 256: every launc
 void gemm256_force_tile_rows(int rows) { g_forced_tile_rows = rows; }
 // A launch of `cols` tile columns (of all problems together): the best height, and its time in 256-row tiles of four wavefronts
 struct HeightCost { int rows; double cost; };
-static HeightCost best_height(const GemmArgs& a, long cols) {
+static HeightCost best_height(const GemmArgs& a, long cols, int waves) {
     const long cu = device_cu_count();
     HeightCost best = {256, 0.0};
     for (int rows = 256; rows >= 128; rows -= 64) {
         const long t = ((a.M + rows - 1) / rows) * cols, rounds = (t + cu - 1) / cu;
-        const double cost = (double)rounds * gemm256_tile_cost(rows) * (rows == 256 && pick_waves(a) == 8 ? 0.96 : 1.0);
+        const double cost = (double)rounds * gemm256_tile_cost(rows) * (rows == 256 && waves == 8 ? 0.96 : 1.0);
         if (rows == 256 || cost < best.cost) best = {rows, cost};
     }
     return best;
 }
-static int pick_tile_rows(const GemmArgs& a) {
-    if (g_forced_tile_rows == 128 || g_forced_tile_rows == 256) return g_forced_tile_rows;
-    return best_height(a, (long)((a.N + kBN - 1) / kBN) * a.nprob).rows;
+// Eight wavefronts add a span of the cross-entropy's partials in two halves, four do not, and which of them a launch has depends on its count
+// of tiles: the head of several directions takes the side that the head of one (like_nprob) takes, and the best height there.
+struct Height { int rows; bool eight; };
+static Height pick_height(const GemmArgs& a) {
+    const int waves = pick_waves(a);
+    if (g_forced_tile_rows == 128 || g_forced_tile_rows == 256) return {g_forced_tile_rows, g_forced_tile_rows == 256 && waves == 8};
+    const long tn = (a.N + kBN - 1) / kBN;
+    const int rows = best_height(a, tn * (a.like_nprob ? a.like_nprob : a.nprob), waves).rows;
+    const bool eight = rows == 256 && waves == 8;
+    return {a.like_nprob && !eight ? best_height(a, tn * a.nprob, 4).rows : rows, eight};
 }
 
 // Two launches of different heights where one leaves its last round mostly empty: 1.5 rounds of 256-row tiles run as one such round and
@@ -721,9 +728,10 @@ static LaunchCut pick_cut(const GemmArgs& a) {
     LaunchCut best = {0, 0};
     if (a.ce_mode || a.stamps || g_forced_tile_rows || g_forced_waves || (long)((a.M + 255) / 256) * tn * a.nprob <= device_cu_count()) return best;
     const double second = 4500.0 / (25.5 * a.K + 4000.0);
-    double best_cost = 0.95 * best_height(a, (long)tn * a.nprob).cost;
+    const int waves = pick_waves(a);
+    double best_cost = 0.95 * best_height(a, (long)tn * a.nprob, waves).cost;
     auto consider = [&](long first, long rest, LaunchCut cut) {
-        const double cost = best_height(a, first).cost + best_height(a, rest).cost + second;
+        const double cost = best_height(a, first, waves).cost + best_height(a, rest, waves).cost + second;
         if (cost < best_cost) { best = cut; best_cost = cost; }
     };
     for (int p = 1; p < a.nprob; ++p) consider((long)p * tn, (long)(a.nprob - p) * tn, {p, 0});
@@ -760,8 +768,7 @@ bool gemm256_applicable(const GemmArgs& a, int dtype) {
 }
 
 static zo2_status launch_one_height(const GemmArgs& a, int dtype, hipStream_t st) {
-    const int rows = pick_tile_rows(a);
-    const bool eight = rows == 256 && pick_waves(a) == 8;
+    const auto [rows, eight] = pick_height(a);
 #define ZO2_G256(T, MI, NW) return a.out_f32 ? launch256_t<T, float, MI, NW>(a, st) : launch256_t<T, T, MI, NW>(a, st)
 #define ZO2_G256_DTYPE(T)               \
     if (rows == 128) ZO2_G256(T, 4, 4); \
@@ -799,10 +806,10 @@ static void cut_launch(const GemmArgs& a, LaunchCut cut, GemmArgs& first, GemmAr
 
 GemmTiles gemm256_tiles(const GemmArgs& a) {
     const LaunchCut cut = pick_cut(a);
-    if (!cut.probs && !cut.cols) return {{pick_tile_rows(a), 0}, 0, 0};
+    if (!cut.probs && !cut.cols) return {{pick_height(a).rows, 0}, 0, 0};
     GemmArgs first, rest;
     cut_launch(a, cut, first, rest);
-    return {{pick_tile_rows(first), pick_tile_rows(rest)}, cut.probs, cut.cols};
+    return {{pick_height(first).rows, pick_height(rest).rows}, cut.probs, cut.cols};
 }
 
 zo2_status gemm_launch_256(const GemmArgs& a, int dtype, hipStream_t st) {

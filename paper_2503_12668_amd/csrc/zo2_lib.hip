@@ -1405,7 +1405,7 @@ static zo2_status head_round(zo2_ctx* c, int T, const uint64_t* seeds, int j0, i
     { zo2_status s = k1_round_tables(c, g.tied_lm_head ? c->d_tok : c->d_lm, &table, 1, update, seeds + j0, n, c->head_wp, c->head_wm, eps); if (s != ZO2_OK) return s; }
     GemmArgs ga;
     memset(&ga, 0, sizeof(ga));
-    ga.M = T; ga.N = g.vocab; ga.K = d; ga.ldx = d; ga.ldw = d; ga.ldy = g.vocab; ga.out_f32 = 1; ga.nprob = 2 * n; ga.ce_mode = 1; ga.part_ld = 2 * (int64_t)n * T;
+    ga.M = T; ga.N = g.vocab; ga.K = d; ga.ldx = d; ga.ldw = d; ga.ldy = g.vocab; ga.out_f32 = 1; ga.nprob = 2 * n; ga.ce_mode = 1; ga.like_nprob = 2; ga.part_ld = 2 * (int64_t)n * T;
     for (int i = 0; i < 2 * n; ++i) {
         GemmProblem& p = ga.p[i];
         p.X = c->head_x + i * half_d; p.W = i & 1 ? c->head_wm[i / 2] : c->head_wp[i / 2]; p.out_scale = 1.0f; p.labels = c->d_labels;

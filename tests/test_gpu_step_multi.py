@@ -254,3 +254,29 @@ def test_head_of_several_directions(wire, sr, tied, dirs):
         assert out == found[0][0]
         for n in params:
             assert np.array_equal(params[n], found[0][1][n]), n
+
+
+@pytest.mark.parametrize("batch,seq,vocab,dirs", [(10, 205, 8196, 4), (9, 257, 8196, 2), (13, 250, 4100, 3)])
+def test_head_of_several_directions_adds_a_span_as_one_direction_does(batch, seq, vocab, dirs):
+    """More than 2048 rows, where a launch of 256-row tiles has eight wavefronts, which add a span of 64 columns in halves: by the count of tiles alone the
+    head of several directions would take other tiles than that of one (two problems), in one sense or the other.  (Two labels, of
+    losses near 0, the words that stand there: the mean over all rows, or a loss of 9, would hide the last digit.)"""
+    b = _b()
+    cfg = si.tiny_config(n_layers=1, d_model=128, n_heads=4, d_ffn=256, vocab=vocab, max_pos=270)
+    P = si.make_weights(cfg, seed=41, std=0.2, ln_jitter=True)
+    for n in ("blocks.0.o.w", "blocks.0.fc2.w"):
+        P[n] = P[n] * np.float32(0.02)
+    tok = si.make_tokens(vocab, batch, seq, seed=42)
+    lab = np.full_like(tok, -100)
+    lab[0, 3], lab[batch - 1, seq - 1] = tok[0, 3], tok[batch - 1, seq - 1]
+    found = []
+    for rnd in (_multi_round, _sequential_round):
+        ctx = b.Zo2Context(cfg, P, wire="bf16", compute="bf16", arena_bytes=1 << 30)
+        out = [rnd(ctx, tok, lab, [20 * k + j for j in range(dirs)], 1e-3, 1e-4) for k in range(12)]
+        ctx.flush(); ctx.sync_to_host()
+        found.append((out, ctx.parameters()))
+        ctx.close()
+    assert max(float(r[0]) for r in found[1][0][0]) < 2.0
+    assert found[0][0] == found[1][0]
+    for n in found[0][1]:
+        assert np.array_equal(found[0][1][n], found[1][1][n]), n
