@@ -376,6 +376,9 @@ int32_t zo2_op_gemm_split_k_pieces(int32_t dtype, int32_t M, int32_t N, int32_t 
  * take, the general kernel), cut into *pieces along k; 64 or 128: 128-wide tiles of that height, *pieces along k.
  * workspace_bytes: what is there for partial sums (zo2_op_gemm calls have 0). */
 zo2_status zo2_op_gemm_choice(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t nprob, size_t workspace_bytes, int32_t* rows, int32_t* pieces);
+/* The same for a launch of `groups` times as many (the directions of a round together), on the kernel that `nprob` problems choose: *rows = the height of its
+ * 128-wide tiles, 64, 128 or 256, or 0 where it is not on these.  For tests. */
+zo2_status zo2_op_gemm_group_rows(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t nprob, int32_t groups, size_t workspace_bytes, int32_t* rows);
 /* How a launch of `nprob` problems of this shape, whole along k, is tiled: float32 in tiles of rows[0] rows; 16-bit dtypes, on the large
  * tiles, in tiles of rows[0] rows and, where rows[1] is not 0, in a second launch of tiles of rows[1] rows, which has the problems from
  * *problems on, or of every problem the columns from *columns on (the other of the two is 0).  For tests. */

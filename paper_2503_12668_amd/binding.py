@@ -104,6 +104,7 @@ def lib():
         "zo2_op_set_gemm_tile_rows": (i32, [i32]),
         "zo2_op_set_gemm_wavefronts": (i32, [i32]),
         "zo2_op_gemm_choice": (i32, [i32, i32, i32, i32, i32, C.c_size_t, C.POINTER(i32), C.POINTER(i32)]),
+        "zo2_op_gemm_group_rows": (i32, [i32, i32, i32, i32, i32, i32, C.c_size_t, C.POINTER(i32)]),
         "zo2_op_gemm_tiles": (i32, [i32, i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]),
         "zo2_op_gemm_wide128": (i32, [i32, i32, i32, i32, vp, i64, vp, i64, vp, vp, vp, i32, i64, f32, i32, i32, i32, vp, C.c_size_t, vp]),
         "zo2_op_gemm_phases": (i32, [i32, i32, i32, i32, vp, i64, vp, i64, vp, vp, i32, i64, vp, vp]),
@@ -128,7 +129,7 @@ def lib():
 EXPORTED = ["zo2_block_tensor_offsets", "zo2_dtype_size", "zo2_init", "zo2_set_resident_budget", "zo2_step", "zo2_step_extra", "zo2_step_multi", "zo2_flush", "zo2_eval", "zo2_get_pending", "zo2_set_pending",
             "zo2_pending_count", "zo2_get_pending_at", "zo2_add_pending",
             "zo2_sync_to_host", "zo2_get_plan", "zo2_get_scratch_plan", "zo2_get_pass_facts", "zo2_set_scratch_plan", "zo2_set_loader_fusion", "zo2_get_loader_fusion", "zo2_set_split_k", "zo2_set_writeback_interval", "zo2_get_writeback_state", "zo2_get_step_stats", "zo2_set_profiling", "zo2_set_stream_overlap", "zo2_set_wire_rounding", "zo2_get_kernel_times", "zo2_debug_set_stream_delay", "zo2_debug_set_slot_poison", "zo2_last_error", "zo2_destroy", "zo2_op_last_error",
-            "zo2_op_philox_words", "zo2_op_gaussian", "zo2_op_update_perturb", "zo2_op_update_perturb_block", "zo2_op_convert", "zo2_op_gemm", "zo2_op_gemm_split_k", "zo2_op_gemm_split_k_workspace_bytes", "zo2_op_gemm_split_k_pieces", "zo2_op_gemm_choice", "zo2_op_gemm_tiles", "zo2_op_gemm_wide128", "zo2_op_set_gemm_tile_rows", "zo2_op_set_gemm_wavefronts", "zo2_op_gemm_phases", "zo2_op_gemm_perturbed", "zo2_op_gemm_perturbed_workspace_bytes", "zo2_op_perturbed_rows",
+            "zo2_op_philox_words", "zo2_op_gaussian", "zo2_op_update_perturb", "zo2_op_update_perturb_block", "zo2_op_convert", "zo2_op_gemm", "zo2_op_gemm_split_k", "zo2_op_gemm_split_k_workspace_bytes", "zo2_op_gemm_split_k_pieces", "zo2_op_gemm_choice", "zo2_op_gemm_group_rows", "zo2_op_gemm_tiles", "zo2_op_gemm_wide128", "zo2_op_set_gemm_tile_rows", "zo2_op_set_gemm_wavefronts", "zo2_op_gemm_phases", "zo2_op_gemm_perturbed", "zo2_op_gemm_perturbed_workspace_bytes", "zo2_op_perturbed_rows",
             "zo2_op_attention", "zo2_op_layernorm", "zo2_op_cross_entropy_rows", "zo2_op_lm_head_ce",
             "zo2_op_lm_head_ce_workspace_bytes", "zo2_op_lm_head_ce_static"]
 
@@ -245,6 +246,13 @@ def op_gemm_choice(dtype_id, M, N, K, nprob, workspace_bytes=0):
     rows, pieces = C.c_int32(), C.c_int32()
     _op_check(lib().zo2_op_gemm_choice(dtype_id, M, N, K, nprob, workspace_bytes, C.byref(rows), C.byref(pieces)))
     return rows.value, pieces.value
+
+
+def op_gemm_group_rows(dtype_id, M, N, K, nprob, groups, workspace_bytes=0):
+    """Height of the 128-wide tiles of a launch of `groups` directions together, 0 where it is not on these."""
+    rows = C.c_int32()
+    _op_check(lib().zo2_op_gemm_group_rows(dtype_id, M, N, K, nprob, groups, workspace_bytes, C.byref(rows)))
+    return rows.value
 
 
 def op_gemm_tiles(dtype_id, M, N, K, nprob=1):

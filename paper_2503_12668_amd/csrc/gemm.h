@@ -70,6 +70,7 @@ struct GemmChoice { int rows, splits; };
 GemmChoice gemm_choose(const GemmArgs& a, int dtype, size_t workspace_bytes);
 // The launch that choice `k`, made for a.nprob / groups problems, stands for: the same sums for `groups` times as many problems at once
 // (tile heights, which do not change a sum's order, are chosen anew).  Workspace: the pieces of all of them.
+int gemm_groups_rows(const GemmArgs& a, int dtype, GemmChoice k);      // (k.rows not 0) that height
 zo2_status gemm_launch_groups(const GemmArgs& a, int dtype, GemmChoice k, int groups, void* workspace, size_t workspace_bytes, hipStream_t st);
 bool gemm256_is_forced();                 // a tile height or wavefront count is forced: the large-tile kernel is meant
 zo2_status gemm_launch_mid_splitk(const GemmArgs& a, int dtype, int rows, int splits, void* workspace, size_t workspace_bytes, hipStream_t st, bool sum = true);

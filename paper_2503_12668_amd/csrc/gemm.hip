@@ -373,14 +373,17 @@ zo2_status gemm_launch_f32_splitk(const GemmArgs& a, int splits, void* workspace
 // 6080: 512 29.7 -> 20.5, 2048 66.9 -> 61.7, 8192 225 against 247.  The choice is the faster one or within 4 % of it in 90 launches.
 // Tiles of 256 rows are for the launches of several directions at once (gemm_launch_groups), which have tiles for two rounds of 128 rows: the
 // wavefronts of a compute unit then ask for three quarters of the bytes per product.  Eight problems of 512 rows, d 2048, in a step: FC2
-// (K 8192) 161 -> 136 us, output 67 -> 54; a step of 4 x 128 tokens and four directions, 8 blocks, 7550 -> 7294.
+// (K 8192) 161 -> 136 us, output 67 -> 54; a step of 4 x 128 tokens and four directions, 8 blocks, 7550 -> 7294.  Where k is no multiple of 128 a
+// round has its fixed 4.5 us there too; rounds of four directions, tiles of up to 128 rows -> of up to 256, us: d 1728, 4 blocks, 2 x 128 tokens 3435 -> 3273, d 1088,
+// 2 x 250 2976 -> 2805, d 832, 6 blocks, 200 1693 -> 1631; with up to 128 tokens they stay on the lower ones (d 1344, 64 tokens 1797, on 256 rows 1902).
 static double general_ns(double tiles, double slabs) {
     const double cu = (double)device_cu_count();
     return tiles <= cu ? 5600.0 + 900.0 * slabs : 3000.0 + ceil(tiles / (2.0 * cu)) * (3800.0 + 1250.0 * slabs);
 }
 static double mid_ns(int rows, double tiles, int kp, bool large) {
     const double cu = (double)device_cu_count(), rounds = ceil(tiles / cu), fill = tiles / (rounds * cu);
-    if (!large && rounds > 1.0) return 3000.0 + rounds * (rows == 128 ? 4500.0 + (kp / 64) * (400.0 + 250.0 * fill) : 3000.0 + (kp / 64) * (240.0 + 120.0 * fill));
+    if (!large && rounds > 1.0)
+        return 3000.0 + rounds * (rows == 256 ? 4500.0 + (kp / 64) * (780.0 + 260.0 * fill) : rows == 128 ? 4500.0 + (kp / 64) * (400.0 + 250.0 * fill) : 3000.0 + (kp / 64) * (240.0 + 120.0 * fill));
     if (rows == 256) return 3500.0 + rounds * (kp / 64) * (780.0 + 260.0 * fill);
     return 3500.0 + rounds * (kp / 64) * (rows == 128 ? 440.0 + 180.0 * fill : 280.0 + 90.0 * fill);
 }
@@ -491,17 +494,18 @@ zo2_status gemm_launch_splitk(const GemmArgs& a, int dtype, int splits, void* wo
     return ZO2_OK;
 }
 
+int gemm_groups_rows(const GemmArgs& a, int dtype, GemmChoice k) {
+    const int kp = k.splits > 1 ? ((a.K + k.splits - 1) / k.splits + 63) / 64 * 64 : a.K;
+    const double n = (double)a.nprob * k.splits * (double)((a.N + 127) / 128);
+    const bool large = gemm256_applicable(a, dtype);
+    int rows = 64;
+    for (int h = 128; h <= 256; h *= 2)
+        if (mid_ns(h, n * ((a.M + h - 1) / h), kp, large) <= mid_ns(rows, n * ((a.M + rows - 1) / rows), kp, large)) rows = h;
+    return rows;
+}
 zo2_status gemm_launch_groups(const GemmArgs& a, int dtype, GemmChoice k, int groups, void* workspace, size_t workspace_bytes, hipStream_t st) {
     ZO2_OP_CHECK(groups >= 1 && a.nprob >= groups && a.nprob % groups == 0 && a.nprob <= GemmArgs::kMaxProblems, ZO2_EINVAL, "gemm: %d problems in %d groups", a.nprob, groups);
-    if (k.rows) {
-        const int kp = k.splits > 1 ? ((a.K + k.splits - 1) / k.splits + 63) / 64 * 64 : a.K;
-        const double n = (double)a.nprob * k.splits * (double)((a.N + 127) / 128);
-        const bool large = gemm256_applicable(a, dtype);
-        int rows = 64;
-        for (int h = 128; h <= 256; h *= 2)
-            if (mid_ns(h, n * ((a.M + h - 1) / h), kp, large) <= mid_ns(rows, n * ((a.M + rows - 1) / rows), kp, large)) rows = h;
-        return gemm_launch_mid_splitk(a, dtype, rows, k.splits, workspace, workspace_bytes, st);
-    }
+    if (k.rows) return gemm_launch_mid_splitk(a, dtype, gemm_groups_rows(a, dtype, k), k.splits, workspace, workspace_bytes, st);
     if (k.splits <= 1) {
         { const zo2_status s = check_operands(a); if (s != ZO2_OK) return s; }
         return launch_large(a, dtype, st);

@@ -2104,6 +2104,18 @@ extern "C" zo2_status zo2_op_gemm_choice(int32_t dtype, int32_t M, int32_t N, in
     return ZO2_OK;
 }
 
+extern "C" zo2_status zo2_op_gemm_group_rows(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t nprob, int32_t groups, size_t workspace_bytes, int32_t* rows) {
+    ZO2_OP_CHECK((dtype == ZO2_BF16 || dtype == ZO2_F16) && M > 0 && N > 0 && K > 0 && nprob >= 1 && groups >= 1 && (int64_t)nprob * groups <= GemmArgs::kMaxProblems && rows,
+                 ZO2_EINVAL, "gemm_group_rows: 16-bit dtypes and positive sizes");
+    GemmArgs a;
+    memset(&a, 0, sizeof(a));
+    a.M = M; a.N = N; a.K = K; a.ldx = K; a.ldw = K; a.ldy = N; a.nprob = nprob;
+    const GemmChoice k = gemm_choose(a, dtype, workspace_bytes);
+    a.nprob = nprob * groups;
+    *rows = k.rows ? gemm_groups_rows(a, dtype, k) : 0;
+    return ZO2_OK;
+}
+
 extern "C" zo2_status zo2_op_gemm_tiles(int32_t dtype, int32_t M, int32_t N, int32_t K, int32_t nprob, int32_t rows[2], int32_t* problems, int32_t* columns) {
     ZO2_OP_CHECK((dtype == ZO2_F32 || dtype == ZO2_BF16 || dtype == ZO2_F16) && M > 0 && N > 0 && K > 0 && nprob >= 1 && nprob <= GemmArgs::kMaxProblems && rows && problems &&
                  columns, ZO2_EINVAL, "gemm_tiles: compute dtypes and positive sizes");
