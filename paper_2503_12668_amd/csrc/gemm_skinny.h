@@ -30,8 +30,8 @@ struct SkinnyArgs {
     int32_t splits, k_per_split;     // filled in by skinny_launch: the k range is cut into `splits` pieces of k_per_split
     float eps;
     PhiloxKeys key;         // of the step seed
-    // float32, and bfloat16 up to 96 rows: an update that theta lacks, applied on the way (theta' = theta - c z_prev is written back and used); c_ptr, the device scalar
-    // eta g, is nullptr where theta is up to date
+    // float32, and bfloat16 up to 32 rows (not in_order; refused elsewhere): an update that theta lacks, applied on the way (theta' = theta - c z_prev is
+    // written back and used); c_ptr, the device scalar eta g, is nullptr where theta is up to date
     PhiloxKeys key_prev;
     const float* c_ptr;
     int32_t direct;         // filled in by skinny_launch: 1: the kernel finishes the outputs, nothing goes to partial

@@ -454,9 +454,15 @@ static bool writes_its_inputs(const SkinnyArgs& a, int dtype) {
     return false;
 }
 
+// the launches whose kernels apply a pending update; the others would pass it by
+static bool update_fits(const SkinnyArgs& a, int dtype) {
+    return !a.c_ptr || dtype == ZO2_F32 || (dtype == ZO2_BF16 && a.M <= 32 && !a.in_order && a.K < 1 << 22);
+}
+
 zo2_status skinny_launch(SkinnyArgs& a, int dtype, void* workspace, size_t workspace_bytes, hipStream_t st, bool sum) {
     ZO2_OP_CHECK(skinny_applicable(a.M, a.N, a.K, dtype), ZO2_EINVAL,
                  "skinny gemm: needs 1 <= M <= 256 (float32: 96), N %% 4 == 0, K %% 64 == 0 (got %d x %d x %d)", a.M, a.N, a.K);
+    ZO2_OP_CHECK(update_fits(a, dtype), ZO2_EINVAL, "skinny gemm: no update in the loader of this format, %d rows of %d (in order: %d)", a.M, a.K, a.in_order);
     ZO2_OP_CHECK(a.nprob >= 1 && a.nprob <= SkinnyArgs::kMaxProblems, ZO2_EINVAL, "skinny gemm: %d problems", a.nprob);
     ZO2_OP_CHECK(a.ldx >= a.K && a.ldx % 8 == 0 && a.ldy >= a.N && a.ldy % 4 == 0, ZO2_EINVAL, "skinny gemm: bad leading dimension");
     ZO2_OP_CHECK((size_t)a.M * (size_t)a.ldx < 0xffffffffull, ZO2_EINVAL, "skinny gemm: activation panel too large");
@@ -505,6 +511,7 @@ zo2_status skinny_launch_sums(SkinnyArgs& a, float* out, hipStream_t st) {
 zo2_status skinny_launch_ce(SkinnyArgs& a, int dtype, hipStream_t st) {
     ZO2_OP_CHECK(dtype != ZO2_F32 && skinny_applicable(a.M, a.N, a.K, dtype) && a.M <= 128 && a.nprob == 1, ZO2_EINVAL,
                  "skinny head: needs 16-bit dtype, 1 <= M <= 128, N %% 4 == 0, K %% 64 == 0 (got %d x %d x %d)", a.M, a.N, a.K);
+    ZO2_OP_CHECK(update_fits(a, dtype), ZO2_EINVAL, "skinny head: no update in the loader of this format, %d rows of %d (in order: %d)", a.M, a.K, a.in_order);
     ZO2_OP_CHECK(a.ldx >= a.K && a.ldx % 8 == 0 && (size_t)a.M * (size_t)a.ldx < 0xffffffffull, ZO2_EINVAL, "skinny head: bad leading dimension");
     const SkinnyProblem& p = a.p[0];
     ZO2_OP_CHECK(p.Xp && p.Xm && p.theta && a.labels && a.part_max && a.part_sum && a.label_logit && a.part_ld >= 2 * (int64_t)a.M, ZO2_EINVAL,
