@@ -159,7 +159,8 @@ zo2_status zo2_step_extra(zo2_ctx* ctx, const int32_t* tokens, const int32_t* la
  * more residual stream (2 tokens x d_model floats) of arena per further direction; the plan is redone when n_dirs
  * exceeds what it holds.  Where blocks are resident and the budget has room for it - two sets of a block's perturbed copies and the
  * activations of two streams per direction - up to four directions go through a block together (bfloat16 compute), faster.  1 <= n_dirs <= 16 (ZO2_EINVAL beyond); ZO2_ENONFINITE if any direction's loss is not finite:
- * then the whole round is dropped (results still filled in). */
+ * then the whole round is dropped (results still filled in).  ZO2_ESTATE for more than one direction while zo2_device.stream_k1 is in use
+ * (two scratch sets, see zo2_get_scratch_plan). */
 zo2_status zo2_step_multi(zo2_ctx* ctx, const int32_t* tokens, const int32_t* labels, int32_t batch, int32_t seq,
                           int32_t n_dirs, const uint64_t* seeds, float eps, float lr, float* results);
 

@@ -1512,10 +1512,18 @@ static zo2_status model_pass(zo2_ctx* c, const char* who, const int32_t* tokens,
         if (tokens[i] < 0 || tokens[i] >= g.vocab) return fail(c, ZO2_EINVAL, "%s: token %d at %d outside [0, %d)", who, tokens[i], i, g.vocab);
         if (labels[i] != -100 && (labels[i] < 0 || labels[i] >= g.vocab)) return fail(c, ZO2_EINVAL, "%s: label %d at %d invalid", who, labels[i], i);
     }
+    const int held = c->want_dirs;
+    const bool stands = c->planned && !c->need_plan && c->plan_T == T && c->plan_seq == seq;
     c->want_dirs = std::max(c->want_dirs, ndirs);
-    if (!c->planned || c->need_plan || c->plan_T != T || c->plan_seq != seq || c->plan_dirs < ndirs) {
+    if (!stands || (c->plan_dirs < ndirs && !c->overlap_k1)) {
         zo2_status s = plan(c, T, batch, seq);
         if (s != ZO2_OK) return s;
+    }
+    // (asked of this call's plan: the one before it may have been for a step without a sweep, or there was none)
+    if (c->overlap_k1 && ndirs > 1) {
+        c->want_dirs = held;
+        c->need_plan = !stands;
+        return fail(c, ZO2_ESTATE, "%s: not available with the sweep kernel on a stream of its own", who);
     }
     const int d = g.d_model, dt = g.compute_dtype;
     c->apply_now = !extra;
@@ -1860,7 +1868,6 @@ extern "C" zo2_status zo2_step_multi(zo2_ctx* c, const int32_t* tokens, const in
     if (!tokens || !labels || !seeds || !results) return fail(c, ZO2_EINVAL, "zo2_step_multi: NULL argument");
     if (n_dirs < 1 || n_dirs > zo2_ctx::kMaxPending) return fail(c, ZO2_EINVAL, "zo2_step_multi: %d directions (1 .. %d)", n_dirs, zo2_ctx::kMaxPending);
     if (!(eps != 0.f) || !isfinite(eps) || !isfinite(lr)) return fail(c, ZO2_EINVAL, "zo2_step_multi: eps must be non-zero and finite, lr finite");
-    if (c->overlap_k1 && n_dirs > 1) return fail(c, ZO2_ESTATE, "zo2_step_multi: not available with the sweep kernel on a stream of its own");
     const zo2_status s = model_pass(c, "zo2_step_multi", tokens, labels, batch, seq, seeds, n_dirs, eps, lr, 2);
     if (s == ZO2_OK || s == ZO2_ENONFINITE)
         for (int j = 0; j < n_dirs; ++j) {

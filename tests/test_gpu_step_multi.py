@@ -280,3 +280,42 @@ def test_head_of_several_directions_adds_a_span_as_one_direction_does(batch, seq
     assert found[0][0] == found[1][0]
     for n in found[0][1]:
         assert np.array_equal(found[0][1][n], found[1][1][n]), n
+
+
+@pytest.mark.parametrize("wire,first", [("f32", "small step"), ("f32", "nothing"), ("bf16", "nothing"), ("bf16", "evaluation")])
+def test_rounds_are_refused_where_the_sweep_has_a_stream_of_its_own(wire, first):
+    """With a stream for the sweep a block runs one direction.  The plan that gives it one may be that of the very call: the first of a context, or one
+    behind a step of few tokens, which in float32 has no sweep.  Refused, and the context goes on as if it had not been asked."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=2, d_model=64, n_heads=2, d_ffn=128, vocab=260, max_pos=80)
+    P = si.make_weights(cfg, seed=11, std=0.08, ln_jitter=True)
+    small, large = (si.make_tokens(260, n, 50, seed=n) for n in (1, 4))
+    got = []
+    for overlap in (True, False):
+        ctx = b.Zo2Context(cfg, P, wire=wire, compute=wire, arena_bytes=64 << 20, overlap_k1=overlap)
+        ctx.set_loader_fusion(0 if wire == "f32" else -1)
+        out = []
+        if first == "small step":
+            out += [ctx.step(small, si.next_token_labels(small), 3, 1e-3, 1e-3)]
+            assert ctx.plan()["loader_fusion"] and ctx.plan()["scratch_sets"] == 1
+        elif first == "evaluation":
+            out += [(ctx.eval(small, si.next_token_labels(small)),)]
+        lab = si.next_token_labels(large)
+        if overlap:
+            with pytest.raises(b.Zo2Error, match="ESTATE"):
+                ctx.step_multi(large, lab, [7, 8, 9], 1e-3, 1e-3)
+        out += [ctx.step(large, lab, 5 + j, 1e-3, 1e-3) for j in range(2)]
+        assert ctx.plan()["scratch_sets"] == 1 + overlap
+        used = ctx.plan()["bytes_used"]
+        ctx.flush(); ctx.sync_to_host()
+        got.append(([float(x) for a in out for x in a], ctx.parameters(), used))
+        if overlap:      # no residual streams are held for the directions that were refused
+            other = b.Zo2Context(cfg, P, wire=wire, compute=wire, arena_bytes=64 << 20, overlap_k1=True)
+            other.set_loader_fusion(-1)
+            other.step(large, lab, 5, 1e-3, 1e-3)
+            assert other.plan()["bytes_used"] == used
+            other.close()
+        ctx.close()
+    assert got[0][0] == got[1][0]
+    for n in P:
+        assert np.array_equal(got[0][1][n], got[1][1][n]), n
