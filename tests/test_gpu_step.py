@@ -480,3 +480,29 @@ def test_nan_weights_of_a_few_words_end_a_step(wire, vocab, batch, seq, sr, dirs
             ctx.step(tok, lab, 7, 1e-3, 1e-3)
     assert ctx.pending_list() == []
     ctx.close()
+
+
+@pytest.mark.parametrize("wire", ["f32", "bf16"])
+def test_sweeps_on_their_own_stream_change_nothing(wire):
+    """As above with the loader path off, so that there is a sweep to overlap, and the two scratch sets that it needs."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=5, d_model=64, n_heads=4, d_ffn=128, vocab=211, max_pos=40)
+    P = si.make_weights(cfg, seed=11, std=0.08, ln_jitter=True)
+    tok = si.make_tokens(cfg["vocab"], 2, 17, seed=12)
+    lab = si.next_token_labels(tok)
+    runs = {}
+    for name, overlap, streamed in (("plain", False, False), ("overlap", True, False), ("overlap_streamed", True, True)):
+        ctx = b.Zo2Context(cfg, P, wire=wire, compute=wire, arena_bytes=64 << 20, overlap_k1=overlap)
+        ctx.set_loader_fusion(-1)
+        r = [ctx.step(tok, lab, 5, 1e-3, 1e-3)]
+        if streamed:
+            ctx.set_resident_budget(ctx.plan()["bytes_used"] - 2 * ctx.offs[16] * (4 if wire == "f32" else 2))
+        r += [ctx.step(tok, lab, 6 + j, 1e-3, 1e-3) for j in range(3)]
+        assert ctx.plan()["scratch_sets"] == 1 + overlap and ctx.plan()["resident"] == (not streamed)
+        ctx.flush(); ctx.sync_to_host()
+        runs[name] = ([tuple(map(float, x)) for x in r], ctx.parameters())
+        ctx.close()
+    for name in ("overlap", "overlap_streamed"):
+        assert runs[name][0] == runs["plain"][0], name
+        for n in runs["plain"][1]:
+            assert np.array_equal(runs[name][1][n], runs["plain"][1][n]), (name, n)
