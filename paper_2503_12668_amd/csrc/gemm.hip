@@ -499,7 +499,7 @@ int gemm_groups_rows(const GemmArgs& a, int dtype, GemmChoice k) {
     const double n = (double)a.nprob * k.splits * (double)((a.N + 127) / 128);
     const bool large = gemm256_applicable(a, dtype);
     int rows = 64;
-    for (int h = 128; h <= 256; h *= 2)
+    for (int h = 128; h <= (dtype == ZO2_BF16 ? 256 : 128); h *= 2)      // (directions go together in bfloat16)
         if (mid_ns(h, n * ((a.M + h - 1) / h), kp, large) <= mid_ns(rows, n * ((a.M + rows - 1) / rows), kp, large)) rows = h;
     return rows;
 }

@@ -10,7 +10,7 @@
 // 64 x 64 of the tile (32 x 64 of the lower one, 128 x 64 of the higher) for one half of each slab's k - two wavefronts per SIMD, no more LDS reads
 // than four would make - and the two halves' sums meet in LDS at the end.
 //
-// Tiles of 256 rows (a ring of three slabs) are for launches with many of them: 1.04 us a slab with a tile on every compute unit where two
+// Tiles of 256 rows (bfloat16, a ring of three slabs) are for launches with many of them: 1.04 us a slab with a tile on every compute unit where two
 // tiles of 128 rows take 1.24, by 48 KB of loads in place of 64.  A sum has the same order at every height.
 //
 // Slab layout: rows of 8 chunks of 16 bytes, chunk kc of row m at position kc ^ ((m >> 1) & 7); a direct-to-LDS load lands
@@ -287,7 +287,7 @@ bool gemm_mid_applicable(const GemmArgs& a, int dtype) {
 
 // splits > 1: a.kpiece k per piece (a multiple of 64), p[i].Y = the problem's float32 partial sums, one [M][N] plane per piece
 zo2_status gemm_launch_mid(const GemmArgs& a, int dtype, int rows, int splits, hipStream_t st) {
-    ZO2_OP_CHECK(gemm_mid_applicable(a, dtype) && (rows == 64 || rows == 128 || rows == 256) && splits >= 1 && a.kpiece > 0 && a.kpiece % kMidBK == 0 &&
+    ZO2_OP_CHECK(gemm_mid_applicable(a, dtype) && (rows == 64 || rows == 128 || (rows == 256 && dtype == ZO2_BF16)) && splits >= 1 && a.kpiece > 0 && a.kpiece % kMidBK == 0 &&
                  (int64_t)a.kpiece * (splits - 1) < a.K && (int64_t)a.kpiece * splits >= a.K && (splits == 1 || a.out_f32),
                  ZO2_EINVAL, "gemm: shape or alignment not supported by the 128 x 128 kernel");
     // rows of 8 MB and more: 64-row tiles with 64-bit addresses (the height does not show in a sum)
@@ -295,7 +295,8 @@ zo2_status gemm_launch_mid(const GemmArgs& a, int dtype, int rows, int splits, h
 #define ZO2_MID(T, OutT)                                                \
     if (far) return mid_launch_t<T, OutT, 64, true>(a, splits, st);     \
     if (rows == 64) return mid_launch_t<T, OutT, 64>(a, splits, st);    \
-    if (rows == 256) return mid_launch_t<T, OutT, 256>(a, splits, st);  \
+    if constexpr (std::is_same_v<T, bf16_t>)                            \
+        if (rows == 256) return mid_launch_t<T, OutT, 256>(a, splits, st); \
     return mid_launch_t<T, OutT, 128>(a, splits, st)
     if (dtype == ZO2_BF16) {
         if (a.out_f32) { ZO2_MID(bf16_t, float); }
