@@ -1235,6 +1235,10 @@ static inline bool updates_in_loader(const zo2_ctx* c, int T) {
     const int dt = c->cfg.compute_dtype;
     return fused_update(c) && (dt == ZO2_F32 || (dt == ZO2_BF16 && T <= 32 && !c->stochastic));
 }
+// A streamed block that goes back to its host buffer is swept all the same: it is final, and its offload starts, a sweep behind its upload and not behind its
+// FC2, and the link, not the kernels, is what such a step waits for (3 slots, us a step, swept -> updated in the loader: bfloat16, 16 tokens, d 768,
+// 8 blocks 2760 -> 2800, d 2048 18270 -> 18326; float32, 64 tokens, d 768, 10 blocks 6515 -> 6597).  The tables and the head never leave.
+static inline bool block_updates_in_loader(const zo2_ctx* c, int T) { return updates_in_loader(c, T) && (c->resident || !c->pass_writes_back); }
 static void loader_applies(const zo2_ctx* c, SkinnyArgs& sa) {
     sa.key_prev = philox_keys(c->pend_seed[c->n_pend - 1]);
     sa.c_ptr = coef_slot(c, c->n_pend - 1);
@@ -1280,7 +1284,7 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
     const int T = batch * seq, d = g.d_model, f = g.d_ffn, dh = d / g.n_heads;
     const int dt = g.compute_dtype;
     const size_t cs = c->csz;
-    const bool f32 = dt == ZO2_F32, loader_updates = updates_in_loader(c, T);
+    const bool f32 = dt == ZO2_F32, loader_updates = block_updates_in_loader(c, T);
     const size_t half_d = (size_t)T * d * cs, half_f = (size_t)T * f * cs;
     int64_t voff[ZO2_BLOCK_TENSORS] = {0};
     const int64_t vec_elems = place_vectors(c, voff);
@@ -1294,16 +1298,19 @@ static zo2_status block_forward_fused(zo2_ctx* c, int l, char* bucket, int batch
         auto is_vec = [](int k) { for (const int v : kVecTensors) if (v == k) return true; return false; };
         // the matrices have no part in the sweep where no update is pending, or where the loader applies it
         const bool update = fused_update(c), sweep_matrices = update && !loader_updates;
-        K1Args a;
+        K1Args a, m;                               // (float32: the matrices in a launch of their own, which only updates)
         k1_common(c, a, seed, eps);
-        a.theta = bucket; a.w_plus = c->wp; a.w_minus = c->wm; a.packed_w = 1; a.mixed = sweep_matrices ? 1 : 0; a.nseg = 0;
+        a.theta = bucket; a.w_plus = c->wp; a.w_minus = c->wm; a.packed_w = 1; a.mixed = sweep_matrices && !f32; a.nseg = 0;
+        m = a;
         for (int k = 0; k < ZO2_BLOCK_TENSORS; ++k) {
             if (!sweep_matrices && !is_vec(k)) continue;
-            K1Seg& sg = a.seg[a.nseg++];
+            K1Args& to = f32 && !is_vec(k) ? m : a;
+            K1Seg& sg = to.seg[to.nseg++];
             sg.off = c->offs[k]; sg.e0 = 0; sg.n = (uint64_t)c->tn[k]; sg.tensor_id = block_tid(l, k); sg.scale = 1.0f;
             sg.woff = is_vec(k) ? voff[k] : -1;
         }
         OPK(c, ZO2_KC_K1, k1_launch(a, g.wire_dtype, g.compute_dtype, update, true, c->sc));
+        if (m.nseg) OPK(c, ZO2_KC_K1, k1_launch(m, g.wire_dtype, g.compute_dtype, true, false, c->sc));
     }
     if (k1_done && !loader_updates) HIPCHK(c, hipEventRecord(k1_done, c->sc));      // the block's parameters are final: the offload may start
     auto VP = [&](int k) { return (const void*)(c->wp + (size_t)voff[k] * cs); };

@@ -391,3 +391,39 @@ def test_who_adds_a_projection_s_pieces_does_not_show(dt, d, f, rows):
         for n in P:
             assert np.array_equal(got[how][1][n], got["1"][1][n]), (how, n)
     assert all(np.isfinite(got["1"][0]))
+
+
+@pytest.mark.parametrize("dt,rows", [("bf16", 16), ("f32", 40)])
+def test_blocks_that_go_back_to_the_host_are_swept(dt, rows):
+    """A streamed block's offload waits for its parameters: where the pass writes it back the sweep has updated it before its projections run, where
+    the write-back interval lets it stay the loader does it (the projections' time says which: one draw a weight, 0.8 - 0.85 of that of two).  The losses and parameters of resident blocks, bit for bit."""
+    b = _b()
+    d, f, layers = 1536, 6144, 4
+    cfg = si.tiny_config(n_layers=layers, d_model=d, n_heads=24, d_ffn=f, vocab=f + 4, max_pos=40)
+    P = si.make_weights(cfg, seed=11, std=0.02, ln_jitter=True)
+    tok = si.make_tokens(f, 1, rows, seed=12)
+    lab = si.next_token_labels(tok)
+    got, ms = {}, {}
+    for interval in (0, 1, 8):                     # 0: resident
+        ctx = b.Zo2Context(cfg, P, wire=dt, compute=dt, arena_bytes=4 << 30)
+        ctx.set_loader_fusion(1)
+        r = [ctx.step(tok, lab, 41, 1e-3, 1e-4)]
+        if interval:
+            ctx.set_resident_budget(ctx.plan()["bytes_used"] - ctx.offs[16] * (4 if dt == "f32" else 2))        # 3 slots for 4 blocks
+            ctx.debug_set_slot_poison(True)
+            ctx.set_writeback_interval(interval)
+        r += [ctx.step(tok, lab, 42, 1e-3, 1e-4), ctx.step_extra(tok, lab, 43, 1e-3, 1e-4), ctx.step(tok, lab, 44, 1e-3, 1e-4)]
+        ctx.set_profiling(["gemm"])
+        r.append(ctx.step(tok, lab, 45, 1e-3, 1e-4))
+        ms[interval] = ctx.kernel_times()["gemm"][0]
+        wrote = ctx.step_stats()["bytes_down"]
+        assert ctx.plan()["loader_fusion"] and ctx.plan()["resident"] == (not interval) and (wrote > 0) == (interval == 1)
+        ctx.set_profiling([])
+        ctx.flush(); ctx.sync_to_host()
+        got[interval] = ([float(x) for a in r for x in a], ctx.parameters())
+        ctx.close()
+    for interval in (1, 8):
+        assert got[interval][0] == got[0][0]
+        for n in P:
+            assert np.array_equal(got[interval][1][n], got[0][1][n]), (interval, n)
+    assert ms[1] < 0.93 * ms[8], ms
