@@ -83,7 +83,10 @@ static constexpr int kDefaultSweeps = 1;       // update + perturb sweeps per bl
 // elements, which keeps its launches on the older kernels (gemm_choose), the line is 64: d 256 x 8, ffn 2048 64 641 -> 585, 100 660 ->
 // 736; d 512, ffn 2048 64 698 -> 674, 80 689 -> 717; d 640 64 747 -> 744; d 704 64 938 -> 762; d 1024, ffn 512 64 790 -> 726.
 static constexpr int kFuseAlways = 64;      // beyond this its workspace must fit into what the ordinary path needs; the line of contexts that keep_order()
-static constexpr int kFuseF32 = 96;         // float32 (why: gemm_skinny_rows.hip); by default 64 where a block's matrices are small (d 512, ffn 2048, 8 blocks: 64 779 -> 732, 96 845 -> 859)
+// float32 (why: gemm_skinny_rows.hip).  By default 64 where a block's matrices are small (d 512, ffn 2048, 8 blocks: 64 tokens 779 -> 732, 96 845 -> 859), 32 where
+// a launch has a workgroup or two (d 128, ffn 512: 16 468 -> 455, 48 471 -> 515, 64 497 -> 519; d 64: 16 443 -> 392, 64 438 -> 475; d 192, ffn 768: 64 558 -> 538).
+static constexpr int kFuseF32 = 96;
+static int fuse_f32_tokens(int64_t d, int64_t f) { return d * f <= 1 << 16 ? 32 : d * f <= 1 << 20 ? 64 : kFuseF32; }
 static int fuse_max_tokens(int d, int f) {
     if ((int64_t)d * std::min(d, f) <= 1 << 19) return 64;
     return std::min(128, std::max(16, 16 + (d - 1536) * 11 / 128) + (d % 128 ? 16 : 0));
@@ -593,7 +596,7 @@ static zo2_status plan(zo2_ctx* c, int T, int batch, int seq) {
     // above 64 tokens only where the slices' partial sums take no more than the logits that the head's partials replace, so
     // that no budget that holds the ordinary path is too small for this one
     const size_t freed = fused_ce && T < 256 ? 2 * std::min<size_t>(T, 128) * V * 4 - rows2 * (2 * ce_parts + 1) * 4 : 0;
-    const bool few_tokens = f32 ? T <= ((int64_t)d * f <= 1 << 20 ? 64 : kFuseF32) : keep_order(c) ? T <= kFuseAlways
+    const bool few_tokens = f32 ? T <= fuse_f32_tokens((int64_t)d, (int64_t)f) : keep_order(c) ? T <= kFuseAlways
                                           : T <= fuse_max_tokens((int)d, (int)f) && (T <= kFuseAlways || fuse_bytes <= split_bytes + freed);
     const bool fuse = fuse_shapes && c->loader_fusion >= 0 && (c->loader_fusion == 1 || few_tokens) && (f32 || !c->sk);
     const size_t sk_ws_bytes = std::max(split_bytes, fuse ? fuse_bytes : 0);      // (float32: none)

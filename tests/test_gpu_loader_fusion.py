@@ -194,6 +194,21 @@ def test_default_line_of_the_loader_path_by_width(d, f, vocab, line):
     ctx.close()
 
 
+@pytest.mark.parametrize("d,f,line", [(64, 256, 32), (128, 512, 32), (128, 576, 64), (192, 768, 64), (512, 2048, 64), (576, 2048, 96)])
+def test_default_line_of_the_float32_loader_path_by_width(d, f, line):
+    """32 tokens where d_model d_ffn is at most 2^16, 64 where it is at most 2^20, 96 beyond; a forced loader path goes to 96 everywhere."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=1, d_model=d, n_heads=d // 64, d_ffn=f, vocab=max(3 * d, f), max_pos=130)
+    ctx = b.Zo2Context(cfg, si.make_weights(cfg, seed=1), arena_bytes=256 << 20)
+    for mode, at in ((0, line), (1, 96)):
+        ctx.set_loader_fusion(mode)
+        for seq in (at, at + 1):
+            t = si.make_tokens(cfg["vocab"], 1, seq, seed=3)
+            ctx.step(t, si.next_token_labels(t), 9, 1e-3, 0.0)
+            assert ctx.plan()["loader_fusion"] == (seq == at), (mode, seq)
+    ctx.close()
+
+
 @pytest.mark.parametrize("d,f,vocab,batch,seq,tied", [(64, 128, 212, 1, 2, True), (192, 320, 1092, 1, 31, False), (192, 64, 1091, 3, 11, True), (256, 1088, 2052, 1, 64, True),
                                                         (128, 192, 516, 5, 13, False), (448, 576, 1352, 2, 48, True)])
 def test_float32_loader_updates_as_the_sweep_does(d, f, vocab, batch, seq, tied):

@@ -289,7 +289,7 @@ def test_rounds_are_refused_where_the_sweep_has_a_stream_of_its_own(wire, first)
     b = _b()
     cfg = si.tiny_config(n_layers=2, d_model=64, n_heads=2, d_ffn=128, vocab=260, max_pos=80)
     P = si.make_weights(cfg, seed=11, std=0.08, ln_jitter=True)
-    small, large = (si.make_tokens(260, n, 50, seed=n) for n in (1, 4))
+    small, large = si.make_tokens(260, 1, 30, seed=1), si.make_tokens(260, 4, 50, seed=4)
     got = []
     for overlap in (True, False):
         ctx = b.Zo2Context(cfg, P, wire=wire, compute=wire, arena_bytes=64 << 20, overlap_k1=overlap)
