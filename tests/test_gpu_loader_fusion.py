@@ -442,3 +442,96 @@ def test_blocks_that_go_back_to_the_host_are_swept(dt, rows):
         for n in P:
             assert np.array_equal(got[interval][1][n], got[0][1][n]), (interval, n)
     assert ms[1] < 0.93 * ms[8], ms
+
+
+# bfloat16: skinny_few_kernel and, in FC2 of d 2048, all of d 4096 but FC1 and the head, skinny_rows_kernel, as in float32; 1 to 64 slabs a wavefront
+@pytest.mark.parametrize("dt,d,f,vocab,rows", [("bf16", 2048, 8192, 4100, 16), ("bf16", 2048, 8192, 260, 31), ("bf16", 4096, 4096, 1028, 20), ("bf16", 768, 3072, 8196, 9),
+                                               ("f32", 2048, 8192, 8196, 40), ("f32", 1024, 4096, 4100, 96)])
+def test_updates_of_wide_blocks_reach_memory_as_the_sweep_s_do(dt, d, f, vocab, rows):
+    """The loader stores theta' and forms theta' +- eps z in the registers behind it: over several updates of blocks whose wavefronts walk many slabs, every
+    stored parameter is the sweep's, bit for bit."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=2, d_model=d, n_heads=d // 64, d_ffn=f, vocab=vocab, max_pos=100, tied=False)
+    P = si.make_weights(cfg, seed=11, std=0.05, ln_jitter=True)
+    tok = si.make_tokens(vocab, 1, rows, seed=12)
+    lab = si.next_token_labels(tok)
+    got = {}
+    for mode in (1, -1):
+        ctx = b.Zo2Context(cfg, P, wire=dt, compute=dt, arena_bytes=4 << 30)
+        ctx.set_loader_fusion(mode)
+        for k in range(6):
+            ctx.set_pending(True, 100 + k, 1e-3 * (k + 1))
+            ctx.step(tok, lab, 42 + k, 1e-3, 0.0)
+        assert ctx.plan()["loader_fusion"] == (mode == 1)
+        ctx.sync_to_host()
+        got[mode] = ctx.parameters()
+        ctx.close()
+    for n in P:
+        assert np.array_equal(got[1][n], got[-1][n]), n
+        assert not np.array_equal(got[1][n], P[n]), n
+
+
+def test_float32_products_of_tiny_weights_see_the_pending_update():
+    """FC1's weights of 2^-100, updated by as much on the way: its sums are computed once more with float32 products, from theta' as the loader has
+    stored it.  FC2's weights of 2^100 bring them back to the residual stream's size; an update of that coefficient is nothing to the other tensors."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=2, d_model=128, n_heads=2, d_ffn=192, vocab=516, max_pos=40)
+    P = si.make_weights(cfg, seed=11, std=0.05, ln_jitter=False)
+    for l in range(2):
+        P[f"blocks.{l}.fc1.w"] = P[f"blocks.{l}.fc1.w"] * np.float32(2.0 ** -100)
+        P[f"blocks.{l}.fc1.b"] = np.zeros_like(P[f"blocks.{l}.fc1.b"])
+        P[f"blocks.{l}.fc2.w"] = P[f"blocks.{l}.fc2.w"] * np.float32(2.0 ** 100)
+    tok = si.make_tokens(cfg["vocab"], 1, 35, seed=12)
+    lab = si.next_token_labels(tok)
+    c = np.float32(2.0 ** -105)
+    want = []
+    for pending in ((c, 7, 1.0), None):
+        oz = zo_step.Zo2Blockwise(opt_model.OptShape(**cfg), copy.deepcopy(P))
+        oz.pending = pending
+        want.append(oz.step(tok, lab, 42, 1e-33, 0.0))
+    assert abs(float(want[0][0]) - float(want[1][0])) > 1e-3 * abs(float(want[0][0]))       # the update matters to the loss
+    for update, w in zip((True, False), want):
+        ctx = b.Zo2Context(cfg, P, arena_bytes=128 << 20)
+        ctx.set_loader_fusion(1)
+        if update:
+            ctx.set_pending(True, 7, float(c))
+        got = ctx.step(tok, lab, 42, 1e-33, 0.0)
+        assert ctx.plan()["loader_fusion"]
+        for k in (0, 1):
+            assert abs(float(got[k]) - float(w[k])) <= 1e-5 * abs(float(w[k])), (got, w)
+        ctx.close()
+
+
+@pytest.mark.parametrize("dt,rows,interval,sweeps", [("bf16", 16, 1, 0), ("bf16", 16, 4, 0), ("bf16", 32, 3, 4), ("f32", 40, 1, 0), ("f32", 40, 4, 2)])
+def test_streamed_rounds_of_few_tokens_equal_resident_steps(dt, rows, interval, sweeps):
+    """Streamed blocks, written back on every update or on every third or fourth, rounds in one pass and in several, whatever the scratch: the losses
+    and parameters of resident blocks bit for bit, with the update in the loader where it may be there."""
+    b = _b()
+    cfg = si.tiny_config(n_layers=5, d_model=192, n_heads=3, d_ffn=320, vocab=580, max_pos=80)
+    P = si.make_weights(cfg, seed=11, std=0.05, ln_jitter=True)
+    tok = si.make_tokens(580, 1, rows, seed=12)
+    lab = si.next_token_labels(tok)
+    got = {}
+    for streamed in (0, 1, 2):                     # 2: rounds in one pass
+        ctx = b.Zo2Context(cfg, P, wire=dt, compute=dt, arena_bytes=128 << 20)
+        ctx.set_loader_fusion(1)
+        if streamed and sweeps:
+            ctx.set_scratch_plan(sweeps)
+        r = [ctx.step(tok, lab, 41, 1e-3, 1e-4)]
+        if streamed:
+            ctx.set_resident_budget(ctx.plan()["bytes_used"] - 2 * ctx.offs[16] * (4 if dt == "f32" else 2) + 2 * (2 * rows * 192 * 4) + 4096)      # and two more residual streams
+            ctx.debug_set_slot_poison(True)
+            ctx.set_writeback_interval(interval)
+        for k in range(4):
+            seeds = [50 + 4 * k + j for j in range(1 + k % 3)]
+            r += ctx.step_multi(tok, lab, seeds, 1e-3, 1e-4) if streamed == 2 else [ctx.step(tok, lab, seeds[0], 1e-3, 1e-4)] + [ctx.step_extra(tok, lab, s, 1e-3, 1e-4) for s in seeds[1:]]
+        r.append(ctx.step(tok, lab, 90, 1e-3, 1e-4))
+        assert ctx.plan()["loader_fusion"] and ctx.plan()["resident"] == (not streamed)
+        ctx.flush(); ctx.sync_to_host()
+        got[streamed] = ([float(x) for a in r for x in a], ctx.parameters())
+        ctx.close()
+    for streamed in (1, 2):
+        assert got[streamed][0] == got[0][0]
+        for n in P:
+            assert np.array_equal(got[streamed][1][n], got[0][1][n]), (streamed, n)
+    assert all(np.isfinite(got[0][0]))
