@@ -411,7 +411,8 @@ def test_who_adds_a_projection_s_pieces_does_not_show(dt, d, f, rows):
 @pytest.mark.parametrize("dt,rows", [("bf16", 16), ("f32", 40)])
 def test_blocks_that_go_back_to_the_host_are_swept(dt, rows):
     """A streamed block's offload waits for its parameters: where the pass writes it back the sweep has updated it before its projections run, where
-    the write-back interval lets it stay the loader does it (the projections' time says which: one draw a weight, 0.8 - 0.85 of that of two).  The losses and parameters of resident blocks, bit for bit."""
+    the write-back interval lets it stay the loader does it (the projections' time says which: one draw a weight, 0.80 - 0.86 of that of two, and no less than that where the
+    loader updates in both).  The losses and parameters of resident blocks, bit for bit."""
     b = _b()
     d, f, layers = 1536, 6144, 4
     cfg = si.tiny_config(n_layers=layers, d_model=d, n_heads=24, d_ffn=f, vocab=f + 4, max_pos=40)
@@ -419,7 +420,7 @@ def test_blocks_that_go_back_to_the_host_are_swept(dt, rows):
     tok = si.make_tokens(f, 1, rows, seed=12)
     lab = si.next_token_labels(tok)
     got, ms = {}, {}
-    for interval in (0, 1, 8):                     # 0: resident
+    for interval in (0, 1, 16):                     # 0: resident
         ctx = b.Zo2Context(cfg, P, wire=dt, compute=dt, arena_bytes=4 << 30)
         ctx.set_loader_fusion(1)
         r = [ctx.step(tok, lab, 41, 1e-3, 1e-4)]
@@ -429,19 +430,23 @@ def test_blocks_that_go_back_to_the_host_are_swept(dt, rows):
             ctx.set_writeback_interval(interval)
         r += [ctx.step(tok, lab, 42, 1e-3, 1e-4), ctx.step_extra(tok, lab, 43, 1e-3, 1e-4), ctx.step(tok, lab, 44, 1e-3, 1e-4)]
         ctx.set_profiling(["gemm"])
-        r.append(ctx.step(tok, lab, 45, 1e-3, 1e-4))
-        ms[interval] = ctx.kernel_times()["gemm"][0]
-        wrote = ctx.step_stats()["bytes_down"]
-        assert ctx.plan()["loader_fusion"] and ctx.plan()["resident"] == (not interval) and (wrote > 0) == (interval == 1)
+        times = []
+        for k in range(8):
+            r.append(ctx.step(tok, lab, 45 + k, 1e-3, 1e-4))
+            times.append(ctx.kernel_times()["gemm"][0])
+            assert (ctx.step_stats()["bytes_down"] > 0) == (interval == 1)
+        ms[interval] = min(times)
+        assert ctx.plan()["loader_fusion"] and ctx.plan()["resident"] == (not interval)
         ctx.set_profiling([])
         ctx.flush(); ctx.sync_to_host()
         got[interval] = ([float(x) for a in r for x in a], ctx.parameters())
         ctx.close()
-    for interval in (1, 8):
+    for interval in (1, 16):
         assert got[interval][0] == got[0][0]
         for n in P:
             assert np.array_equal(got[interval][1][n], got[0][1][n]), (interval, n)
-    assert ms[1] < 0.93 * ms[8], ms
+    # (the least of eight passes: beside copies under way a single one takes up to a sixth longer)
+    assert ms[1] < 0.93 * ms[16], ms
 
 
 # bfloat16: skinny_few_kernel and, in FC2 of d 2048, all of d 4096 but FC1 and the head, skinny_rows_kernel, as in float32; 1 to 64 slabs a wavefront
