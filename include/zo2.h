@@ -225,11 +225,11 @@ zo2_status zo2_set_scratch_plan(zo2_ctx* ctx, int32_t sweeps);
  * (zo2_set_wire_rounding) - where the projections are bound by reading the weights, lets the projections read the stored
  * weights and form W+ / W- in their loader (zo2_op_gemm_perturbed), the sweep kernel then only applies the pending
  * update and perturbs the block's one-dimensional tensors - bfloat16 up to 32 tokens, rounded to
- * nearest: the loader applies the update too - (the LM head does the same with the vocabulary matrix up to 128 tokens); larger steps write the perturbed copies with the sweep kernel,
+ * nearest: the loader applies the update too, but for streamed blocks in a pass that writes them back - (the LM head does the same with the vocabulary matrix up to 128 tokens); larger steps write the perturbed copies with the sweep kernel,
  * because a weight tile would otherwise be regenerated once per 256-row tile of activations.  mode 1: in the loader
  * whenever the shapes allow (16-bit storage equal to the compute format, d_model and d_ffn multiples of 64, at most
  * 256 tokens per stream); mode -1: never.  float32 throughout: modes 0 and 1 alike up to 96 tokens, mode 0 up to 64 where d_model d_ffn is at most 2^20, 32 where it is at most 2^16 (d_model and d_ffn multiples of 64, a
- * vocabulary of at least 3 d_model and d_ffn, whose logits take the partial sums), the loader applies the pending update too, and a stream
+ * vocabulary of at least 3 d_model and d_ffn, whose logits take the partial sums), the loader applies the pending update too, as in bfloat16, and a stream
  * for K1 (zo2_device.stream_k1) has nothing to do.  The two paths give the same W+- bit for bit; their projections add the
  * same products in a different order (results agree to float32 rounding, each path is deterministic by itself).
  * Evaluation passes (zo2_eval) have nothing to perturb: they read the weights in place, or a sweep's converted copies.  Takes effect at the next step. */

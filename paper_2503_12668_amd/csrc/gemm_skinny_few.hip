@@ -1,7 +1,7 @@
 // The projections of up to 32 tokens in 16 bits.  A workgroup owns 16 output features; its eight wavefronts take the slabs of its k in turn, each with
 // its own activations straight from memory into the matrix instruction's registers, and meet once, at the end.  No barrier and no LDS until then,
 // and k as long as a workgroup can make it: QKV and FC1 are finished here, with bias, ReLU and rounding, and the output projection and FC2 leave
-// the LayerNorm behind them a few sums to add, not 32.
+// the LayerNorm behind them a few sums to add, not 32 (where skinny_few_pays takes them: FC2 of d 2048, ffn 8192 is beyond its line and leaves 32).
 // (gemm_skinny_rows.hip's 128 features a workgroup need 8 - 32 pieces of k to fill the chip: a launch of 4.7 us for their sum behind QKV
 // and FC1 each, and 8 MB of sums that a LayerNorm pass has to read.)  An activation is read once for 16 features instead of once for 128: from
 // L2, 2 M bytes a weight, which is why the line is 32 rows.

@@ -1224,9 +1224,9 @@ static zo2_status block_forward_round(zo2_ctx* c, int l, char* bucket, int batch
     return ZO2_OK;
 }
 
-// The same block for a step of few tokens: K1 only applies the pending update (theta' is final after it) and perturbs
-// the block's ten one-dimensional tensors into a densely packed scratch; the six projections read theta' itself and
-// perturb in their weight loader, both streams per pass over the weights (gemm_skinny.hip).
+// The same block for a step of few tokens: K1 applies the pending update (theta' is final after it), or leaves that of the matrices to the projections
+// (block_updates_in_loader: final behind FC2), and perturbs the block's ten one-dimensional tensors into a densely packed scratch; the six projections
+// read theta' itself and perturb in their weight loader, both streams per pass over the weights (gemm_skinny.hip).
 static const int kVecTensors[10] = {0, 1, 3, 5, 7, 9, 10, 11, 13, 15};      // ln1.w ln1.b q.b k.b v.b o.b ln2.w ln2.b fc1.b fc2.b
 
 // The last deferred update can be applied by the same loader, so that a matrix is read and written once: always in float32, in bfloat16 up to 32
@@ -1446,8 +1446,8 @@ static zo2_status enqueue_upload(zo2_ctx* c, int l) {
     return ZO2_OK;
 }
 
-// O(W_i): the updated block goes back as soon as its K1 pass is done (the forwards read
-// only the scratch copies, never the slot); without a pending update nothing changed.
+// O(W_i): the updated block goes back as soon as its K1 pass is done (the forwards behind it write only
+// scratch; those that read the slot itself keep its next occupant waiting, ev_read); without a pending update nothing changed.
 static zo2_status enqueue_offload(zo2_ctx* c, int l, bool changed) {
     const int s = l % c->n_slots;
     if (changed) {
