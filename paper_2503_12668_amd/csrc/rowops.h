@@ -49,9 +49,10 @@ zo2_status embed_gather(const EmbedArgs& a, int wire_dtype, int compute_dtype, h
 zo2_status cross_entropy_rows(const float* logits, int64_t ld, const int32_t* labels, int rows, int row0, int label_period,
                               int vocab, float* row_loss, hipStream_t st, bool keep_order = false);
 // (keep_order: the exponentials are added up as by 256 threads; see keep_order() in zo2_lib.hip)
-// span-major (max, sum exp) partials written by the LM-head kernel's cross-entropy mode -> row_loss[row0 + r]
+// span-major (max, sum exp) partials written by the LM-head kernel's cross-entropy mode -> row_loss[row0 + r].  like_rows: added up as in a launch
+// of that many rows (0: its own)
 zo2_status ce_combine(const float* part_max, const float* part_sum, const float* label_logit, const int32_t* labels, int rows,
-                      int n_parts, int64_t part_ld, int row0, int label_period, float* row_loss, hipStream_t st, bool keep_order = false);
+                      int n_parts, int64_t part_ld, int row0, int label_period, float* row_loss, hipStream_t st, bool keep_order = false, int like_rows = 0);
 // result[0..3] = l+, l-, g, number of counted labels; *c_pending = lr * g.  ns = 1 (single forward): only rows 0..T-1
 // exist, result = (l, l, 0, count) and c_pending is left alone
 zo2_status loss_epilogue(const float* row_loss, const int32_t* labels, int T, float eps, float lr, int ns, float* result,

@@ -708,15 +708,16 @@ __global__ __launch_bounds__(1024) void ce_combine_kernel(const float* __restric
     row_loss[row0 + r] = (float)(log(ss) + (double)mm - (double)label_logit[r]);
 }
 
-// Contexts that keep the order of their sums: 32 rows per block; 8 groups of lanes split the spans, so every load is 32 consecutive floats and a
-// thread walks 99 of the 788 spans of a 50272-word vocabulary.  Two sweeps (max, then sum) keep the loads
-// independent of each other.
-// (eight loads under way: 55 us at 4096 rows instead of 32)
-__global__ __launch_bounds__(256) void ce_combine_in_order_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum,
+// 32 rows per block; kGroups groups of lanes split the spans, so every load is 32 consecutive floats.  Two sweeps (max, then sum) keep the loads
+// independent of each other.  Eight groups, a thread walking 99 of the 788 spans of a 50272-word vocabulary, for contexts that keep the order of their
+// sums (with eight loads under way: 55 us at 4096 rows instead of 32).  32 groups for more than 8192 rows, where whole 128-byte lines are
+// worth more than short walks (beside loss_epilogue_kernel, eight rows a workgroup -> this, us: 8192 rows 33 and 34, 16384 55 -> 50, 32768 110 -> 91).
+template <int kGroups>
+__global__ __launch_bounds__(32 * kGroups) void ce_combine_rows_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum,
                                                          const float* __restrict__ label_logit, const int32_t* __restrict__ labels,
                                                          int rows, int n_parts, int64_t part_ld, int row0, int label_period,
                                                          float* __restrict__ row_loss) {
-    constexpr int kRows = 32, kGroups = 8, kUnroll = 4;
+    constexpr int kRows = 32, kUnroll = kGroups == 8 ? 4 : 8;
     __shared__ float sh_m[kGroups][kRows];
     __shared__ double sh_s[kGroups][kRows];
     const int lr = threadIdx.x & (kRows - 1), grp = threadIdx.x / kRows;
@@ -754,11 +755,13 @@ __global__ __launch_bounds__(256) void ce_combine_in_order_kernel(const float* _
 }
 
 zo2_status ce_combine(const float* part_max, const float* part_sum, const float* label_logit, const int32_t* labels, int rows,
-                      int n_parts, int64_t part_ld, int row0, int label_period, float* row_loss, hipStream_t st, bool keep_order) {
+                      int n_parts, int64_t part_ld, int row0, int label_period, float* row_loss, hipStream_t st, bool keep_order, int like_rows) {
     if (rows == 0) return ZO2_OK;
     ZO2_OP_CHECK(part_max && part_sum && label_logit && labels && row_loss && n_parts > 0 && label_period > 0 && part_ld >= rows,
                  ZO2_EINVAL, "ce_combine: bad argument");
-    if (keep_order) hipLaunchKernelGGL(ce_combine_in_order_kernel, dim3((rows + 31) / 32), dim3(256), 0, st, part_max, part_sum, label_logit, labels, rows, n_parts, part_ld, row0, label_period, row_loss);
+    const dim3 by32((rows + 31) / 32);
+    if (keep_order) hipLaunchKernelGGL(ce_combine_rows_kernel<8>, by32, dim3(256), 0, st, part_max, part_sum, label_logit, labels, rows, n_parts, part_ld, row0, label_period, row_loss);
+    else if ((like_rows ? like_rows : rows) > 8192) hipLaunchKernelGGL(ce_combine_rows_kernel<32>, by32, dim3(1024), 0, st, part_max, part_sum, label_logit, labels, rows, n_parts, part_ld, row0, label_period, row_loss);
     else hipLaunchKernelGGL(ce_combine_kernel, dim3((rows + 255) / 256 * 32), dim3(1024), 0, st, part_max, part_sum, label_logit, labels, rows, n_parts, part_ld, row0, label_period, row_loss);
     ZO2_HIP_LAUNCH_CHECK();
     return ZO2_OK;

@@ -1422,7 +1422,7 @@ static zo2_status head_round(zo2_ctx* c, int T, const uint64_t* seeds, int j0, i
         p.part_max = c->head_pmax + (size_t)i * T; p.part_sum = c->head_psum + (size_t)i * T; p.label_logit = c->head_lab + (size_t)i * T;
     }
     OPK(c, ZO2_KC_GEMM, gemm_launch(ga, dt, c->sc));
-    OPK(c, ZO2_KC_CE, ce_combine(c->head_pmax, c->head_psum, c->head_lab, c->d_labels, 2 * n * T, c->ce_parts, 2 * (int64_t)n * T, 0, T, c->head_loss, c->sc, keep_order(c)));
+    OPK(c, ZO2_KC_CE, ce_combine(c->head_pmax, c->head_psum, c->head_lab, c->d_labels, 2 * n * T, c->ce_parts, 2 * (int64_t)n * T, 0, T, c->head_loss, c->sc, keep_order(c), 2 * T));
     return ZO2_OK;
 }
 

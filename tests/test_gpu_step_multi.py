@@ -256,7 +256,7 @@ def test_head_of_several_directions(wire, sr, tied, dirs):
             assert np.array_equal(params[n], found[0][1][n]), n
 
 
-@pytest.mark.parametrize("batch,seq,vocab,dirs", [(10, 205, 8196, 4), (9, 257, 8196, 2), (13, 250, 4100, 3)])
+@pytest.mark.parametrize("batch,seq,vocab,dirs", [(10, 205, 8196, 4), (9, 257, 8196, 2), (13, 250, 4100, 3), (17, 250, 4100, 2)])
 def test_head_of_several_directions_adds_a_span_as_one_direction_does(batch, seq, vocab, dirs):
     """More than 2048 rows, where a launch of 256-row tiles has eight wavefronts, which add a span of 64 columns in halves: by the count of tiles alone the
     head of several directions would take other tiles than that of one (two problems), in one sense or the other.  (Two labels, of
